@@ -541,8 +541,20 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         a.win_waves = lc.win_waves;
         a.waves_per_group = lc.waves_per_group;
         a.dense_cache = lc.dense_cache ? 1 : 0;
+        // the sweeps after the replicas have settled go to the settled kernel
+        sa_plan::Sched *one = nullptr;
+        rc = get_schedule(plan, 1, &one);
+        if (rc != SA_OK) {
+            if (tmp) (void)hipFree(tmp);
+            return rc;
+        }
+        a.order = one->dev;
+        a.n_order = one->n_win;
+        const sa::SettledChoice set =
+            sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
         std::string err;
-        rc = sa::launch_anneal(plan->rule, a, lc, stream, err);
+        rc = sa::launch_windows(plan->rule, a, lc, set, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
+                                stream, err);
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);

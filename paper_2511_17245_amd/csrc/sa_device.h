@@ -1022,8 +1022,11 @@ struct ReplicaCtx {
     int32_t n_win;
     bool shared;            // the replica's waves cooperate (barrier after each window)
     bool active;            // false: an idle team that only keeps the workgroup's barriers
-    uint64_t *trace;        // this read's per-sweep hash words (s_end - s_begin), or nullptr
+    uint64_t *trace;        // this read's hash word of sweep 0 (indexed by the sweep), or nullptr
     int64_t *c1;            // dense form: this replica's coefficient cache in LDS, or nullptr
+    int32_t stop;           // 0, or: end after a sweep with at most n_order / stop changes (the settled
+    int32_t n_order;        // kernel takes the rest); the variables of a sweep
+    uint32_t *ctr;          // shared replicas that may end so: three change counters (LDS)
 };
 
 // Initial state (given, or uniform on each box, Sec. 3.1) written by threads tid, tid+nthr, ...
@@ -1075,10 +1078,72 @@ __device__ __forceinline__ int64_t energy_part(const DevProblem &P, const ZT *z,
     return (int64_t)wave_sum_u64(eacc);
 }
 
+// One update's rule (Sec. 3.3) for variable k: the new (or proposed) value v and its energy change d;
+// returns whether it is taken.  crec / ccoef / cd: the variable's first records (or coupling row),
+// loaded ahead; next() is called where the rule has finished with them.
+template <int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT, typename Next>
+__device__ __forceinline__ bool update_rule(const ReplicaCtx &R, const ZT *z, int32_t k, int64_t lo, int64_t W,
+                                            uint32_t em, int32_t row, int32_t deg, uint32_t r0, uint32_t r1,
+                                            double U, int64_t zk, double beta, double r_opt, int lane,
+                                            const IncRec &crec, uint64_t ccoef, int64_t cd, ScanCarry &cy,
+                                            Next &&next, int64_t &v, int64_t &d) {
+    const DevProblem &P = R.P;
+    if (kRule == SA_METROPOLIS) {
+        v = lo + (int64_t)(((uint64_t)r1 * (uint64_t)(W - 1)) >> 32);
+        if (v >= zk) v += 1;
+        // (Metropolis kernels are built with kMaxE = 1 for any problem: the
+        // variable's own exponents decide)
+        if (R.c1) {
+            // dense form with the coefficient cache: dE in O(1)
+            const Acc a1 = (Acc)(uint64_t)R.c1[k];
+            const Acc dd = kRegChunk == 1 ? (Acc)cd : (Acc)P.d[k];
+            d = to_i64<Acc>(a1 * (Acc)(v - zk) + dd * ((Acc)v * (Acc)v - (Acc)zk * (Acc)zk));
+        } else {
+            d = direct_delta<Acc, ZT, kRegChunk == 1>(P, z, k, row, deg, zk, v, lane, crec, ccoef, cd,
+                                                      (em & ~2u) == 0);
+        }
+        return metropolis_accept(d, beta, U);
+    } else if (kRule == SA_HEAT_BATH || kRule == SA_HEAT_BATH_CLOSED) {
+        Coeffs<kMaxE, Acc> C;
+        row_coeffs<kMaxE, Acc, ZT>(P, z, k, row, deg, em, lane, crec, ccoef, C, R.c1);
+        next();
+        // closed form where dE is linear in the new value (no exponent above one)
+        const bool linear = kMaxE == 1 || (em & ~2u) == 0;
+        if (kRule == SA_HEAT_BATH_CLOSED && linear)
+            v = heat_bath_closed(to_i64<Acc>(C.a[1]), lo, W, beta, U, r1);
+        else
+            v = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, lo, W, zk, beta, U, lane, linear, cy);
+        d = poly_delta(C, zk, v);
+        return true;
+    } else {
+        if ((double)r0 * 0x1p-32 < r_opt) {
+            Coeffs<kMaxE, Acc> C;
+            row_coeffs<kMaxE, Acc, ZT>(P, z, k, row, deg, em, lane, crec, ccoef, C, R.c1);
+            if (kMaxE == 1 || (em & ~2u) == 0) {
+                // dE = a1 (v - z_k): the lowest value for a1 >= 0 (every value ties
+                // when a1 = 0), the highest for a1 < 0
+                const int64_t a1 = to_i64<Acc>(C.a[1]);
+                v = a1 >= 0 ? lo : lo + W - 1;
+                d = to_i64<Acc>(C.a[1] * (Acc)(v - zk));
+            } else if (kRegChunk == 1 && W > R.otm_enum_max && W > kWave)
+                v = argmin_wide<kMaxE, Acc>(C, lo, W, zk, lane, d);
+            else
+                v = argmin_range<kMaxE, Acc>(C, lo, W, zk, lane, d);
+        } else {
+            v = lo + (int64_t)(((uint64_t)r1 * (uint64_t)(W - 1)) >> 32);
+            if (v >= zk) v += 1;
+            d = direct_delta<Acc, ZT, false>(P, z, k, row, deg, zk, v, lane, crec, ccoef, cd,
+                                      (em & ~2u) == 0);
+        }
+        return metropolis_accept(d, beta, U);
+    }
+}
+
 // Sweeps [s_begin, s_end) of one replica (index order, Sec. 3.1): this wave's slots of the
-// schedule.  Returns the sum of the energy changes this wave applied.
+// schedule.  Returns the sum of the energy changes this wave applied, and in s_next the first sweep
+// not made.
 template <int kRule, bool kStateInLds, int kRegChunk, int kMaxE, typename Acc, typename ZT>
-__device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int lane) {
+__device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int lane, int32_t &s_next) {
     const DevProblem &P = R.P;
     const int32_t n_win = R.n_win;
     const SchedRec *mine = R.sched;
@@ -1091,7 +1156,10 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
                 for (int32_t w = 0; w < n_win; ++w) window_barrier();
         return 0;
     }
-    for (int32_t s = R.s_begin; s < R.s_end; ++s) {
+    s_next = R.s_end;
+    uint32_t sweep_no = 0;
+    for (int32_t s = R.s_begin; s < R.s_end; ++s, ++sweep_no) {
+        uint32_t moves = 0;   // changes by this wave
         const double beta = R.beta[s];
         const double r_opt =
             R.otm_r >= 0.0 ? R.otm_r : (R.n_sweeps > 1 ? (double)s / (double)(R.n_sweeps - 1) : 0.0);
@@ -1151,58 +1219,11 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
                     const int64_t zk = (int64_t)(int32_t)uni32((uint32_t)z[k]);
                     int64_t v, d;
                     bool accept;
-                    if (kRule == SA_METROPOLIS) {
-                        v = lo + (int64_t)(((uint64_t)r1 * (uint64_t)(W - 1)) >> 32);
-                        if (v >= zk) v += 1;
-                        // (Metropolis kernels are built with kMaxE = 1 for any problem: the
-                        // variable's own exponents decide)
-                        if (R.c1) {
-                            // dense form with the coefficient cache: dE in O(1)
-                            const Acc a1 = (Acc)(uint64_t)R.c1[k];
-                            const Acc dd = kRegChunk == 1 ? (Acc)cd : (Acc)P.d[k];
-                            d = to_i64<Acc>(a1 * (Acc)(v - zk) + dd * ((Acc)v * (Acc)v - (Acc)zk * (Acc)zk));
-                        } else {
-                            d = direct_delta<Acc, ZT, kRegChunk == 1>(P, z, k, row, deg, zk, v, lane, crec, ccoef, cd,
-                                                                      (lane_read32(sl.emask, j) & ~2u) == 0);
-                        }
-                        accept = metropolis_accept(d, beta, U);
-                    } else if (kRule == SA_HEAT_BATH || kRule == SA_HEAT_BATH_CLOSED) {
-                        Coeffs<kMaxE, Acc> C;
-                        const uint32_t em = lane_read32(sl.emask, j);
-                        row_coeffs<kMaxE, Acc, ZT>(P, z, k, row, deg, em, lane, crec, ccoef, C, R.c1);
-                        next();
-                        // closed form where dE is linear in the new value (no exponent above one)
-                        const bool linear = kMaxE == 1 || (em & ~2u) == 0;
-                        if (kRule == SA_HEAT_BATH_CLOSED && linear)
-                            v = heat_bath_closed(to_i64<Acc>(C.a[1]), lo, W, beta, U, r1);
-                        else
-                            v = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, lo, W, zk, beta, U, lane, linear, cy);
-                        d = poly_delta(C, zk, v);
-                        accept = true;
-                    } else {
-                        if ((double)r0 * 0x1p-32 < r_opt) {
-                            Coeffs<kMaxE, Acc> C;
-                            const uint32_t em = lane_read32(sl.emask, j);
-                            row_coeffs<kMaxE, Acc, ZT>(P, z, k, row, deg, em, lane, crec, ccoef, C, R.c1);
-                            if (kMaxE == 1 || (em & ~2u) == 0) {
-                                // dE = a1 (v - z_k): the lowest value for a1 >= 0 (every value ties
-                                // when a1 = 0), the highest for a1 < 0
-                                const int64_t a1 = to_i64<Acc>(C.a[1]);
-                                v = a1 >= 0 ? lo : lo + W - 1;
-                                d = to_i64<Acc>(C.a[1] * (Acc)(v - zk));
-                            } else if (kRegChunk == 1 && W > R.otm_enum_max && W > kWave)
-                                v = argmin_wide<kMaxE, Acc>(C, lo, W, zk, lane, d);
-                            else
-                                v = argmin_range<kMaxE, Acc>(C, lo, W, zk, lane, d);
-                        } else {
-                            v = lo + (int64_t)(((uint64_t)r1 * (uint64_t)(W - 1)) >> 32);
-                            if (v >= zk) v += 1;
-                            d = direct_delta<Acc, ZT, false>(P, z, k, row, deg, zk, v, lane, crec, ccoef, cd,
-                                                      (lane_read32(sl.emask, j) & ~2u) == 0);
-                        }
-                        accept = metropolis_accept(d, beta, U);
-                    }
+                    accept = update_rule<kRule, kRegChunk, kMaxE, Acc, ZT>(R, z, k, lo, W, lane_read32(sl.emask, j), row,
+                                                                           deg, r0, r1, U, zk, beta, r_opt, lane, crec,
+                                                                           ccoef, cd, cy, next, v, d);
                     if (accept && v != zk) {
+                        moves += 1;
                         z[k] = (ZT)v;  // every lane stores the same value
                         E += d;
                         if (R.trace) H += hash_word(k, v) - hash_word(k, zk);
@@ -1235,8 +1256,22 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
             }
         }
         if (R.trace) {
-            if (lane == 0) atomicAdd((unsigned long long *)&R.trace[s - R.s_begin], (unsigned long long)H);
+            if (lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
             H = 0;
+        }
+        if (R.stop != 0) {
+            if (R.shared) {
+                // the waves decide together, from their sum; the next sweep's counter is cleared before
+                // this barrier, a sweep after its last reads
+                if (lane == 0 && moves != 0) atomicAdd(&R.ctr[sweep_no % 3], moves);
+                if (threadIdx.x == 0) R.ctr[(sweep_no + 1) % 3] = 0;
+                window_barrier();
+                moves = uni32(R.ctr[sweep_no % 3]);
+            }
+            if (moves * (uint32_t)R.stop <= (uint32_t)R.n_order) {   // uniform over the replica's waves
+                s_next = s + 1;
+                break;
+            }
         }
     }
     return E;
@@ -1267,6 +1302,8 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     int32_t *z = kStateInLds ? lds_state + (shared ? 0 : (size_t)wave * n) : A.z_out + (size_t)read * n;
     const int tid = g * kWave + lane, nthr = G * kWave;  // threads of this replica
 
+    // the last of a run's three launches starts where the others ended (e_out holds the next sweep)
+    const int32_t s_begin = A.phase == kPhaseLast ? (int32_t)A.e_out[read] : A.s_begin;
     init_state(P, z, A.z_init ? A.z_init + (size_t)read * n : nullptr, (uint32_t)read, A.instance_id,
                A.key0, A.key1, tid, nthr);
     if (shared) window_barrier();
@@ -1280,7 +1317,7 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
         state_write_fence<kStateInLds>();
     }
     uint64_t *trace = A.trace ? A.trace + (size_t)read * (size_t)(A.s_end - A.s_begin) : nullptr;
-    if (trace && A.s_end > A.s_begin) {
+    if (trace && A.s_end > A.s_begin && A.phase != kPhaseLast) {
         // the initial state's hash goes into the first sweep's word
         uint64_t h0 = 0;
         for (int32_t k = tid; k < n; k += nthr) h0 += hash_word(k, z[k]);
@@ -1292,7 +1329,7 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     R.P = P;
     R.beta = A.beta;
     R.n_sweeps = A.n_sweeps;
-    R.s_begin = A.s_begin;
+    R.s_begin = s_begin;
     R.s_end = A.s_end;
     R.key0 = A.key0;
     R.key1 = A.key1;
@@ -1304,13 +1341,23 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     R.n_win = A.n_win;
     R.shared = shared;
     R.active = true;
-    R.trace = trace;
+    R.trace = trace ? trace - A.s_begin : nullptr;
     R.c1 = c1;
-    E += sweep_replica<kRule, kStateInLds, kRegChunk, kMaxE, Acc, int32_t>(R, z, lane);
+    R.stop = A.phase == kPhaseFirst ? settled_share(G) : 0;
+    R.n_order = A.n_order;
+    // the waves' energy parts follow the state (shared replicas); the change counters use their place
+    int64_t *parts = (int64_t *)(lds_state + (((size_t)n + 1) & ~(size_t)1));
+    R.ctr = (uint32_t *)parts;
+    if (shared && R.stop != 0) {
+        if (tid < 3) R.ctr[tid] = 0;   // (a sweep's barriers come before their first use)
+        if (A.n_win == 0) window_barrier();
+    }
+    int32_t s_next;
+    E += sweep_replica<kRule, kStateInLds, kRegChunk, kMaxE, Acc, int32_t>(R, z, lane, s_next);
+    if (shared && R.stop != 0) window_barrier();   // the counters' last reads
 
     if (shared) {
-        // combine the waves' energy parts; LDS slots follow the state
-        int64_t *parts = (int64_t *)(lds_state + (((size_t)n + 1) & ~(size_t)1));
+        // combine the waves' energy parts
         if (lane == 0) parts[g] = E;
         window_barrier();
         if (g == 0) {
@@ -1322,7 +1369,7 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
         int32_t *zo = A.z_out + (size_t)read * n;
         for (int32_t k = tid; k < n; k += nthr) zo[k] = z[k];
     }
-    if (g == 0 && lane == 0) A.e_out[read] = E;
+    if (g == 0 && lane == 0) A.e_out[read] = A.phase == kPhaseFirst ? (int64_t)s_next : E;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1382,24 +1429,26 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         R.active = active;
         R.trace = nullptr;
         R.c1 = nullptr;
+        R.stop = 0;
+        int32_t s_next;
         if (D.rule == SA_METROPOLIS) {
-            E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane);
+            E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane, s_next);
         } else if (D.rule == SA_HEAT_BATH) {
             switch (D.chunk) {
-                case 1: E += sweep_replica<SA_HEAT_BATH, true, 1, kMaxE, Acc, ZT>(R, z, lane); break;
-                case 2: E += sweep_replica<SA_HEAT_BATH, true, 2, kMaxE, Acc, ZT>(R, z, lane); break;
-                case 8: E += sweep_replica<SA_HEAT_BATH, true, 8, kMaxE, Acc, ZT>(R, z, lane); break;
-                default: E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane); break;
+                case 1: E += sweep_replica<SA_HEAT_BATH, true, 1, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                case 2: E += sweep_replica<SA_HEAT_BATH, true, 2, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                case 8: E += sweep_replica<SA_HEAT_BATH, true, 8, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                default: E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
             }
         } else if (D.rule == SA_HEAT_BATH_CLOSED) {
             switch (D.chunk) {
-                case 1: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 1, kMaxE, Acc, ZT>(R, z, lane); break;
-                case 2: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 2, kMaxE, Acc, ZT>(R, z, lane); break;
-                case 8: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 8, kMaxE, Acc, ZT>(R, z, lane); break;
-                default: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane); break;
+                case 1: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 1, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                case 2: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 2, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                case 8: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 8, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
+                default: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
             }
         } else {
-            E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane);
+            E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane, s_next);
         }
         if (lane == 0) parts[wave] = E;
         window_barrier();

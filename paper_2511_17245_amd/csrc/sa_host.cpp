@@ -417,6 +417,13 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
             f = g;
         }
     }
+    p.cached.assign(n, 1);
+    for (int32_t k = 0; k < n; ++k) {
+        const VarRec &vr = p.var[k];
+        for (int32_t q = vr.row; q < vr.row + vr.deg; ++q)
+            if ((p.inc[q].meta & 0xFFu) != 1 || (p.inc[q].meta >> 8) > 3) p.cached[k] = 0;
+        if (vr.width > 1) (p.cached[k] ? p.any_cached : p.any_margin) = true;
+    }
     p.t_off.resize((size_t)nt + 1);
     for (int64_t t = 0; t <= nt; ++t) p.t_off[t] = (int32_t)c.t_off[t];
     p.t_var = c.t_var;
@@ -491,7 +498,8 @@ int32_t build_schedule(const Packed &p, int G, std::vector<SchedRec> &out) {
             const int g = i - starts[w];
             const int32_t k = members[i];
             const VarRec &vr = p.var[k];
-            out[(size_t)g * n_win + w] = SchedRec{k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k], {0, 0}};
+            out[(size_t)g * n_win + w] = SchedRec{k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k],
+                                                   {0, p.cached.empty() ? 1 : p.cached[k]}};
         }
     }
     return n_win;

@@ -97,6 +97,10 @@ struct Packed {
     // {0, 0} up to a multiple of kPairBlock) and its linear coefficient
     std::vector<PairRec> pair;
     std::vector<int32_t> pair_row, pair_deg, pair_h;
+    // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficient cached (every term
+    // holds it to the first power with at most three other factors), 0 for one that keeps a margin
+    std::vector<uint8_t> cached;
+    bool any_cached = false, any_margin = false;   // among the variables that are not fixed
 };
 int pack(const Canonical &c, Packed &out, std::string &err);
 int maxe_class_of(int32_t max_exp);
@@ -109,7 +113,7 @@ struct SchedRec {
     int32_t k;
     int32_t lo, width, row, deg;
     uint32_t emask;
-    int32_t pad[2];
+    int32_t pad[2];   // pad[1]: 1 for a variable whose coefficient settled sweeps keep cached
 };
 // Greedy windows of at most G mutually non-interacting variables, stored wave-major
 // (slot g * n_win + w).  Returns the number of windows.
@@ -174,6 +178,18 @@ struct DevProblem {
     const PairRec *pair;     // compact pair records (nullptr when the problem has none)
 };
 
+// A run is one launch, or three: the first ends each replica at its first sweep that changes few
+// variables (at most 1 / settled_share of them) and leaves the next sweep's
+// index in e_out; the settled kernel (sa_settled.h) takes it from there, and the last finishes the
+// replicas that came unsettled (a schedule that warms up) and writes every energy.  States pass
+// through z_out.
+constexpr int32_t kPhaseWhole = 0, kPhaseFirst = 1, kPhaseLast = 2;
+// A settled sweep serves its changes and visits one after another by one wave, where the ordinary
+// kernel's G waves share them: a quarter of the variables for G = 1 (a visit costs about the same in
+// both), and for G > 1 the share at which the serial visits (about 1 us each) cost less than the
+// sweep they replace.
+constexpr int32_t settled_share(int32_t G) { return G == 1 ? 4 : 8 * G; }
+
 // Kernel arguments of one annealing launch.
 struct AnnealArgs {
     DevProblem P;
@@ -198,6 +214,12 @@ struct AnnealArgs {
                              // wave adds its share of the state hash's change per sweep (and of the
                              // initial state's hash into the first sweep); a prefix pass then turns
                              // them into the hash after every sweep
+    int32_t phase;           // kPhaseWhole, kPhaseFirst or kPhaseLast
+    // the settled kernel (order also where phase is kPhaseFirst)
+    const SchedRec *order;   // the variables in index order
+    int32_t n_order;
+    int32_t off_c, off_m;    // LDS byte offsets of the coefficients (dense: c1, else ca) and margins; -1: none
+    int32_t leave;           // changes per sweep past which a replica leaves
 };
 
 // Kernel arguments of one launch of the quad kernel (one update per four lanes, dependency levels).
@@ -221,6 +243,8 @@ struct QuadArgs {
     int32_t *z_out;
     int64_t *e_out;
     uint64_t *trace;             // as AnnealArgs::trace
+    int32_t phase;               // as AnnealArgs::phase
+    int32_t n_order;
 };
 // Waves of the quad kernel's workgroup (one replica): heat bath, 8 or 16 (below), and Metropolis /
 // optimal transition, one (a HUIO level holds about 16 variables, and a single wave needs no
@@ -278,6 +302,19 @@ struct LaunchChoice {
     bool dense_cache = false;  // dense form: coefficient cache in LDS (one wave per replica)
     int variant = 0;
 };
+
+// The settled kernel's launch for a problem and a run, or none (lds_bytes = 0).
+struct SettledChoice {
+    int lds_bytes = 0;     // state and caches of one replica
+    int off_c = -1, off_m = -1;
+};
+SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int32_t n_order, int32_t n_sweeps, int device);
+// Launches it: `a` as for launch_anneal, with order, n_order and leave set.
+int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp, bool narrow,
+                   void *stream, std::string &err);
+// A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order and n_order set).
+int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t max_width,
+                   int32_t max_exp, bool narrow, void *stream, std::string &err);
 
 // Byte layout of a packed instance in one device area, each part 256-byte aligned (the records
 // and their coefficients are followed by one zero record).

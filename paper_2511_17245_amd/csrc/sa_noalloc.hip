@@ -135,6 +135,13 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
                                                   sa::dE_fits_32(canon), enum_max, pk.dense);
     std::vector<sa::SchedRec> sch;
     const int32_t n_win = lanes == 64 ? sa::build_schedule(pk, lc.win_waves, sch) : 0;
+    // the settled kernel's order: the schedule itself for one wave per replica, else a second list
+    sa::SettledChoice set;
+    std::vector<sa::SchedRec> order;
+    if (lanes == 64) {
+        set = sa::choose_settled(pk, sa::coefs_fit_32(canon), n_reads, active, s1 - s0, device);
+        if (set.lds_bytes && lc.win_waves > 1) (void)sa::build_schedule(pk, 1, order);
+    }
 
     // one image: packed instance | inverse temperatures | schedule (windows, or level offsets then
     // level slots)
@@ -144,9 +151,15 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     const size_t off_slots = off_sched + sa::align256(lv_start.size() * sizeof(int32_t));
     const size_t off_mrec = off_slots + sa::align256(std::max<size_t>(lv_slots.size(), 1) * sizeof(sa::SchedRec));
     const size_t off_mcoef = off_mrec + sa::align256(mrec.size() * sizeof(sa::MoRec));
-    const size_t total = lanes == 64
-                             ? off_sched + sa::align256(std::max<size_t>(sch.size(), 1) * sizeof(sa::SchedRec))
-                             : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
+    const size_t off_order = off_sched + sa::align256(std::max<size_t>(sch.size(), 1) * sizeof(sa::SchedRec));
+    size_t total = lanes == 64 ? off_order + sa::align256(order.size() * sizeof(sa::SchedRec))
+                               : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
+    if (lanes == 64 && !order.empty() && total > kScratchBytes) {
+        // no room for the second list: every sweep in the ordinary kernel (the same results)
+        set = sa::SettledChoice();
+        order.clear();
+        total = off_order;
+    }
     if (total > kScratchBytes)
         return sa::fail(SA_ENOMEM, "sa_anneal_noalloc: the problem needs " + std::to_string(total) +
                                        " bytes of staging; the static area holds " +
@@ -158,6 +171,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     // eligible, also when the choice falls on the windows, and share their offset
     if (lanes == 64) {
         if (!sch.empty()) std::memcpy(image.data() + off_sched, sch.data(), sch.size() * sizeof(sa::SchedRec));
+        if (!order.empty()) std::memcpy(image.data() + off_order, order.data(), order.size() * sizeof(sa::SchedRec));
     } else {
         if (!lv_start.empty())
             std::memcpy(image.data() + off_sched, lv_start.data(), lv_start.size() * sizeof(int32_t));
@@ -223,7 +237,9 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
         rc = (mo ? sa::launch_quad_mo : sa::launch_quad)(rule, q, pk.max_width, pk.max_exp, sa::dE_fits_32(canon),
                                                          stream, err);
     } else {
-        rc = sa::launch_anneal(rule, a, lc, stream, err);
+        a.order = order.empty() ? a.sched : (const sa::SchedRec *)((char *)area + off_order);
+        a.n_order = active;
+        rc = sa::launch_windows(rule, a, lc, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
     }
     if (rc == SA_OK && a.trace) rc = sa::launch_trace_prefix(a.trace, n_reads, s1 - s0, stream, err);
     if (rc != SA_OK) return sa::fail(rc, err);
