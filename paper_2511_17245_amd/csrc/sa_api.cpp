@@ -508,8 +508,24 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         q.trace = t_dev;
         std::string err;
         const bool mo = plan->rule == SA_METROPOLIS || plan->rule == SA_OPT_METROPOLIS;
-        rc = (mo ? sa::launch_quad_mo : sa::launch_quad)(plan->rule, q, plan->info.max_width,
-                                                          plan->info.max_exponent, plan->narrow_ok, stream, err);
+        if (mo) {
+            // the sweeps after the replicas have settled go to the settled kernel
+            sa_plan::Sched *one = nullptr;
+            rc = get_schedule(plan, 1, &one);
+            if (rc != SA_OK) {
+                if (tmp) (void)hipFree(tmp);
+                return rc;
+            }
+            a.order = one->dev;
+            a.n_order = one->n_win;
+            const sa::SettledChoice set =
+                sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
+            rc = sa::launch_rounds(plan->rule, q, a, set, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
+                                   stream, err);
+        } else {
+            rc = sa::launch_quad(plan->rule, q, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok, stream,
+                                 err);
+        }
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);

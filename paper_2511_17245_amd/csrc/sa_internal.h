@@ -189,6 +189,9 @@ constexpr int32_t kPhaseWhole = 0, kPhaseFirst = 1, kPhaseLast = 2;
 // both), and for G > 1 the share at which the serial visits (about 1 us each) cost less than the
 // sweep they replace.
 constexpr int32_t settled_share(int32_t G) { return G == 1 ? 4 : 8 * G; }
+// The same for the Metropolis / OTM quad kernel, whose ordinary update costs about 170 cycles (16 per
+// round): a settled sweep's change costs some ten times that.
+constexpr int32_t kSettledShareQuad = 16;
 
 // Kernel arguments of one annealing launch.
 struct AnnealArgs {
@@ -315,6 +318,10 @@ int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_
 // A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order and n_order set).
 int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err);
+
+// The same for the Metropolis / OTM quad kernel: q as for launch_quad_mo, a as for launch_settled.
+int launch_rounds(int rule, QuadArgs q, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp,
+                  bool narrow, void *stream, std::string &err);
 
 // Byte layout of a packed instance in one device area, each part 256-byte aligned (the records
 // and their coefficients are followed by one zero record).

@@ -108,4 +108,19 @@ int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const Settled
     return launch_anneal(rule, a, lc, stream, err);
 }
 
+int launch_rounds(int rule, QuadArgs q, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp,
+                  bool narrow, void *stream, std::string &err) {
+    q.phase = kPhaseWhole;
+    if (sc.lds_bytes == 0) return launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
+    q.phase = kPhaseFirst;
+    q.n_order = a.n_order;
+    a.leave = std::max<int32_t>(1, (int32_t)(3 * (int64_t)a.n_order / kSettledShareQuad));
+    int rc = launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
+    if (rc == SA_OK) rc = launch_settled(rule, a, sc, max_width, max_exp, narrow, stream, err);
+    if (rc != SA_OK) return rc;
+    q.phase = kPhaseLast;
+    q.z_init = q.z_out;
+    return launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
+}
+
 }  // namespace sa

@@ -138,9 +138,9 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     // the settled kernel's order: the schedule itself for one wave per replica, else a second list
     sa::SettledChoice set;
     std::vector<sa::SchedRec> order;
-    if (lanes == 64) {
+    if (lanes == 64 || mo) {
         set = sa::choose_settled(pk, sa::coefs_fit_32(canon), n_reads, active, s1 - s0, device);
-        if (set.lds_bytes && lc.win_waves > 1) (void)sa::build_schedule(pk, 1, order);
+        if (set.lds_bytes && (lanes == 4 || lc.win_waves > 1)) (void)sa::build_schedule(pk, 1, order);
     }
 
     // one image: packed instance | inverse temperatures | schedule (windows, or level offsets then
@@ -151,10 +151,11 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     const size_t off_slots = off_sched + sa::align256(lv_start.size() * sizeof(int32_t));
     const size_t off_mrec = off_slots + sa::align256(std::max<size_t>(lv_slots.size(), 1) * sizeof(sa::SchedRec));
     const size_t off_mcoef = off_mrec + sa::align256(mrec.size() * sizeof(sa::MoRec));
-    const size_t off_order = off_sched + sa::align256(std::max<size_t>(sch.size(), 1) * sizeof(sa::SchedRec));
-    size_t total = lanes == 64 ? off_order + sa::align256(order.size() * sizeof(sa::SchedRec))
-                               : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
-    if (lanes == 64 && !order.empty() && total > kScratchBytes) {
+    const size_t off_order =
+        lanes == 64 ? off_sched + sa::align256(std::max<size_t>(sch.size(), 1) * sizeof(sa::SchedRec))
+                    : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
+    size_t total = off_order + sa::align256(order.size() * sizeof(sa::SchedRec));
+    if (!order.empty() && total > kScratchBytes) {
         // no room for the second list: every sweep in the ordinary kernel (the same results)
         set = sa::SettledChoice();
         order.clear();
@@ -171,7 +172,6 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     // eligible, also when the choice falls on the windows, and share their offset
     if (lanes == 64) {
         if (!sch.empty()) std::memcpy(image.data() + off_sched, sch.data(), sch.size() * sizeof(sa::SchedRec));
-        if (!order.empty()) std::memcpy(image.data() + off_order, order.data(), order.size() * sizeof(sa::SchedRec));
     } else {
         if (!lv_start.empty())
             std::memcpy(image.data() + off_sched, lv_start.data(), lv_start.size() * sizeof(int32_t));
@@ -180,6 +180,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
         if (!mrec.empty()) std::memcpy(image.data() + off_mrec, mrec.data(), mrec.size() * sizeof(sa::MoRec));
         if (!mcoef.empty()) std::memcpy(image.data() + off_mcoef, mcoef.data(), mcoef.size());
     }
+    if (!order.empty()) std::memcpy(image.data() + off_order, order.data(), order.size() * sizeof(sa::SchedRec));
     hipStream_t stream = (hipStream_t)opts.hip_stream;
     e = hipMemcpyAsync(area, image.data(), total, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);   // the host image is freed on return
@@ -207,6 +208,8 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     a.win_waves = lc.win_waves;
     a.waves_per_group = lc.waves_per_group;
     a.dense_cache = lc.dense_cache ? 1 : 0;
+    a.order = order.empty() ? a.sched : (const sa::SchedRec *)((char *)area + off_order);
+    a.n_order = active;
     if (a.trace) {
         rc = sa::launch_zero_u64(a.trace, (int64_t)n_reads * (s1 - s0), stream, err);
         if (rc != SA_OK) return sa::fail(rc, err);
@@ -234,11 +237,9 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
         q.z_out = a.z_out;
         q.e_out = a.e_out;
         q.trace = a.trace;
-        rc = (mo ? sa::launch_quad_mo : sa::launch_quad)(rule, q, pk.max_width, pk.max_exp, sa::dE_fits_32(canon),
-                                                         stream, err);
+        rc = mo ? sa::launch_rounds(rule, q, a, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err)
+                : sa::launch_quad(rule, q, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
     } else {
-        a.order = order.empty() ? a.sched : (const sa::SchedRec *)((char *)area + off_order);
-        a.n_order = active;
         rc = sa::launch_windows(rule, a, lc, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
     }
     if (rc == SA_OK && a.trace) rc = sa::launch_trace_prefix(a.trace, n_reads, s1 - s0, stream, err);

@@ -128,13 +128,16 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
     int32_t *z = lds_state;
     using Part = std::conditional_t<kNarrow, uint32_t, uint64_t>;
 
+    // the last of a run's three launches starts where the others ended (e_out holds the next sweep)
+    const int32_t s_begin = A.phase == kPhaseLast ? (int32_t)A.e_out[read] : A.s_begin;
+    int32_t s_next = A.s_end;
     init_state(P, z, A.z_init ? A.z_init + (size_t)read * n : nullptr, (uint32_t)read, A.instance_id, A.key0,
                A.key1, lane, kWave);
     if (lane == 0) z[n] = 1;   // the value of an unused factor place in the records' copy
     window_barrier();
     int64_t E = energy_part(P, z, lane, kWave);
     uint64_t *trace = A.trace ? A.trace + (size_t)read * (size_t)(A.s_end - A.s_begin) : nullptr;
-    if (trace && A.s_end > A.s_begin) {
+    if (trace && A.s_end > A.s_begin && A.phase != kPhaseLast) {
         uint64_t h0 = 0;
         for (int32_t k = lane; k < n; k += kWave) h0 += hash_word(k, z[k]);
         h0 = wave_sum_u64(h0);
@@ -153,7 +156,8 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
         load_round<kNarrow>(A, 0, lane, RA);
         uint32_t y0 = 0, y1 = 0, y2 = 0, y3 = 0;
 
-        for (int32_t s = A.s_begin; s < A.s_end; ++s) {
+        for (int32_t s = s_begin; s < A.s_end; ++s) {
+            uint32_t moves = 0;   // the sweep's changes
             const double beta = __ldg(&A.beta[s]);
             const double r_opt =
                 A.otm_r >= 0.0 ? A.otm_r : (A.n_sweeps > 1 ? (double)s / (double)(A.n_sweeps - 1) : 0.0);
@@ -219,11 +223,13 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
                     // a linear variable's a_k^(m), m >= 2, are zero: dE = a1 (v - z_k), the same ring value
                     d = all_linear ? to_i64<Acc>(C.a[1] * (Acc)(v - zk)) : poly_delta(C, zk, v);
                 }
-                if (valid && v != zk && metropolis_accept(d, beta, U)) {
+                const bool taken = valid && v != zk && metropolis_accept(d, beta, U);
+                if (taken) {
                     z[k] = (int32_t)v;   // the quad's four lanes store the same value
                     dE += d;
                     if (trace) H += hash_word(k, v) - hash_word(k, zk);
                 }
+                moves += (uint32_t)__popcll(__ballot(taken)) / 4u;
             };
 
             for (int32_t t = 0; t < R; t += 2) {
@@ -252,10 +258,14 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
                 if (lane == 0) atomicAdd((unsigned long long *)&trace[s - A.s_begin], (unsigned long long)hw);
                 H = 0;
             }
+            if (A.phase == kPhaseFirst && moves * (uint32_t)kSettledShareQuad <= (uint32_t)A.n_order) {
+                s_next = s + 1;
+                break;
+            }
         }
     }
     E += (int64_t)wave_sum_u64(ql == 0 ? (uint64_t)dE : 0ull);
-    if (lane == 0) A.e_out[read] = E;
+    if (lane == 0) A.e_out[read] = A.phase == kPhaseFirst ? (int64_t)s_next : E;
     int32_t *zo = A.z_out + (size_t)read * n;
     for (int32_t k = lane; k < n; k += kWave) zo[k] = z[k];
 }
