@@ -268,6 +268,27 @@ int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out) {
     return SA_OK;
 }
 
+int get_order(sa_plan *plan, sa_plan::Sched **out) {
+    std::lock_guard<std::mutex> lk(plan->sched_mu);
+    sa_plan::Sched &sc = plan->order;
+    if (!sc.dev) {
+        std::vector<sa::SchedRec> host;
+        sc.n_active = sa::build_order(plan->packed, host);
+        sc.n_win = (int32_t)host.size();
+        void *dev = nullptr;
+        hipError_t e = hipMalloc(&dev, host.size() * sizeof(sa::SchedRec));
+        if (e != hipSuccess) return fail(SA_ENOMEM, std::string("hipMalloc(order): ") + hipGetErrorString(e));
+        e = hipMemcpy(dev, host.data(), host.size() * sizeof(sa::SchedRec), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(dev);
+            return hip_fail(e, "hipMemcpy(order)");
+        }
+        sc.dev = (sa::SchedRec *)dev;
+    }
+    *out = &sc;
+    return SA_OK;
+}
+
 int get_levels(sa_plan *plan, sa_plan::Levels **out) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Levels &lv = plan->levels;
@@ -511,13 +532,14 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         if (mo) {
             // the sweeps after the replicas have settled go to the settled kernel
             sa_plan::Sched *one = nullptr;
-            rc = get_schedule(plan, 1, &one);
+            rc = sa::get_order(plan, &one);
             if (rc != SA_OK) {
                 if (tmp) (void)hipFree(tmp);
                 return rc;
             }
             a.order = one->dev;
-            a.n_order = one->n_win;
+            a.n_order = one->n_active;
+            a.z30 = plan->packed.z30 ? 1 : 0;
             const sa::SettledChoice set =
                 sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
             rc = sa::launch_rounds(plan->rule, q, a, set, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
@@ -559,13 +581,14 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         a.dense_cache = lc.dense_cache ? 1 : 0;
         // the sweeps after the replicas have settled go to the settled kernel
         sa_plan::Sched *one = nullptr;
-        rc = get_schedule(plan, 1, &one);
+        rc = sa::get_order(plan, &one);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);
             return rc;
         }
         a.order = one->dev;
-        a.n_order = one->n_win;
+        a.n_order = one->n_active;
+        a.z30 = plan->packed.z30 ? 1 : 0;
         const sa::SettledChoice set =
             sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
         std::string err;

@@ -343,6 +343,8 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
     p.n_terms = (int32_t)nt;
     p.var.resize(n);
     p.emask.assign(n, 0u);
+    p.z30 = true;
+    for (int32_t k = 0; k < n; ++k) p.z30 = p.z30 && c.lo[k] > -(1 << 30) && c.hi[k] < (1 << 30);
     if (pack_dense(c, p)) {
         for (int32_t k = 0; k < n; ++k) {
             const int64_t w = (int64_t)c.hi[k] - c.lo[k] + 1;
@@ -421,8 +423,11 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
     for (int32_t k = 0; k < n; ++k) {
         const VarRec &vr = p.var[k];
         for (int32_t q = vr.row; q < vr.row + vr.deg; ++q)
-            if ((p.inc[q].meta & 0xFFu) != 1 || (p.inc[q].meta >> 8) > 3) p.cached[k] = 0;
-        if (vr.width > 1) (p.cached[k] ? p.any_cached : p.any_margin) = true;
+            if ((p.inc[q].meta & 0xFFu) > 2 || (p.inc[q].meta >> 8) > 3) p.cached[k] = 0;
+        if (vr.width > 1 && p.cached[k]) {
+            p.any_cached = true;
+            p.any_square = p.any_square || (p.emask[k] & 4u) != 0;
+        }
     }
     p.t_off.resize((size_t)nt + 1);
     for (int64_t t = 0; t <= nt; ++t) p.t_off[t] = (int32_t)c.t_off[t];
@@ -498,11 +503,23 @@ int32_t build_schedule(const Packed &p, int G, std::vector<SchedRec> &out) {
             const int g = i - starts[w];
             const int32_t k = members[i];
             const VarRec &vr = p.var[k];
-            out[(size_t)g * n_win + w] = SchedRec{k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k],
-                                                   {0, p.cached.empty() ? 1 : p.cached[k]}};
+            out[(size_t)g * n_win + w] = SchedRec{k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k], {0, 0}};
         }
     }
     return n_win;
+}
+
+int32_t build_order(const Packed &p, std::vector<SchedRec> &out) {
+    int32_t n_order = 0;
+    out.resize((size_t)p.n);
+    for (int32_t k = 0; k < p.n; ++k) {
+        const VarRec &vr = p.var[k];
+        const bool fixed = vr.width == 1;
+        n_order += fixed ? 0 : 1;
+        out[(size_t)k] = SchedRec{fixed ? -1 : k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k],
+                                  {0, p.cached.empty() ? 1 : p.cached[k]}};
+    }
+    return n_order;
 }
 
 }  // namespace sa

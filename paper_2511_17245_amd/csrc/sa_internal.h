@@ -97,10 +97,11 @@ struct Packed {
     // {0, 0} up to a multiple of kPairBlock) and its linear coefficient
     std::vector<PairRec> pair;
     std::vector<int32_t> pair_row, pair_deg, pair_h;
-    // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficient cached (every term
-    // holds it to the first power with at most three other factors), 0 for one that keeps a margin
+    // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficients cached (every term
+    // holds it to the first or second power with at most three other factors)
     std::vector<uint8_t> cached;
-    bool any_cached = false, any_margin = false;   // among the variables that are not fixed
+    bool any_cached = false, any_square = false;   // of one that is not fixed / and has a square
+    bool z30 = false;               // every bound below 2^30 in magnitude
 };
 int pack(const Canonical &c, Packed &out, std::string &err);
 int maxe_class_of(int32_t max_exp);
@@ -113,11 +114,14 @@ struct SchedRec {
     int32_t k;
     int32_t lo, width, row, deg;
     uint32_t emask;
-    int32_t pad[2];   // pad[1]: 1 for a variable whose coefficient settled sweeps keep cached
+    int32_t pad[2];   // pad[1]: 1 for a variable whose coefficients settled sweeps keep cached
 };
 // Greedy windows of at most G mutually non-interacting variables, stored wave-major
 // (slot g * n_win + w).  Returns the number of windows.
 int32_t build_schedule(const Packed &p, int G, std::vector<SchedRec> &out);
+
+// Every variable in index order, k = -1 for a fixed one; returns the number that are not fixed.
+int32_t build_order(const Packed &p, std::vector<SchedRec> &out);
 
 // Dependency levels of one sweep: a level holds, in index order, variables (not fixed) none of
 // which shares a term with another, each placed after all of its lower-index neighbours' levels.
@@ -219,9 +223,10 @@ struct AnnealArgs {
                              // them into the hash after every sweep
     int32_t phase;           // kPhaseWhole, kPhaseFirst or kPhaseLast
     // the settled kernel (order also where phase is kPhaseFirst)
-    const SchedRec *order;   // the variables in index order
-    int32_t n_order;
-    int32_t off_c, off_m;    // LDS byte offsets of the coefficients (dense: c1, else ca) and margins; -1: none
+    const SchedRec *order;   // every variable in index order (build_order)
+    int32_t n_order;         // those that are not fixed
+    int32_t off_c, off_c2, off_m;   // LDS byte offsets of the caches (dense: c1, else ca; cb; margins); -1: none
+    int32_t z30;             // every bound of the problem is below 2^30 in magnitude
     int32_t leave;           // changes per sweep past which a replica leaves
 };
 
@@ -309,7 +314,7 @@ struct LaunchChoice {
 // The settled kernel's launch for a problem and a run, or none (lds_bytes = 0).
 struct SettledChoice {
     int lds_bytes = 0;     // state and caches of one replica
-    int off_c = -1, off_m = -1;
+    int off_c = -1, off_c2 = -1, off_m = -1;
 };
 SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int32_t n_order, int32_t n_sweeps, int device);
 // Launches it: `a` as for launch_anneal, with order, n_order and leave set.

@@ -42,20 +42,22 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
     // the dense form changes every cached sum with each move: no gain beyond the sizes that keep the
     // cache in the ordinary kernel too
     if (p.dense && n > 1024) return sc;
-    const int64_t c = p.dense ? 8 * n : coef32 && p.any_cached ? state : 0;
-    const int64_t m = !p.dense && (!coef32 || p.any_margin) ? 2 * n : 0;
-    const int64_t bytes = state + c + m;
+    const bool sparse_cache = !p.dense && coef32 && p.any_cached;
+    const int64_t c = p.dense ? 8 * n : sparse_cache ? state : 0, c2 = sparse_cache && p.any_square ? state : 0;
+    const int64_t bytes = state + c + c2 + 2 * ((n + 3) & ~(int64_t)3);
     // every replica at once, or in two goes
     if (bytes > max_lds || (max_lds / bytes) * cus * 2 < n_reads) return sc;
     sc.lds_bytes = (int)bytes;
     sc.off_c = c ? (int)state : -1;
-    sc.off_m = m ? (int)(state + c) : -1;
+    sc.off_c2 = c2 ? (int)(state + c) : -1;
+    sc.off_m = (int)(state + c + c2);
     return sc;
 }
 
 int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp, bool narrow,
                    void *stream, std::string &err) {
     a.off_c = sc.off_c;
+    a.off_c2 = sc.off_c2;
     a.off_m = sc.off_m;
     const int cls = maxe_class_of(max_exp);
     if (rule == SA_OPT_METROPOLIS && max_width > a.otm_enum_max) narrow = false;   // as launch_anneal

@@ -135,12 +135,12 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
                                                   sa::dE_fits_32(canon), enum_max, pk.dense);
     std::vector<sa::SchedRec> sch;
     const int32_t n_win = lanes == 64 ? sa::build_schedule(pk, lc.win_waves, sch) : 0;
-    // the settled kernel's order: the schedule itself for one wave per replica, else a second list
+    // the settled kernel's list of the variables
     sa::SettledChoice set;
     std::vector<sa::SchedRec> order;
     if (lanes == 64 || mo) {
         set = sa::choose_settled(pk, sa::coefs_fit_32(canon), n_reads, active, s1 - s0, device);
-        if (set.lds_bytes && (lanes == 4 || lc.win_waves > 1)) (void)sa::build_schedule(pk, 1, order);
+        if (set.lds_bytes) (void)sa::build_order(pk, order);
     }
 
     // one image: packed instance | inverse temperatures | schedule (windows, or level offsets then
@@ -156,7 +156,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
                     : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
     size_t total = off_order + sa::align256(order.size() * sizeof(sa::SchedRec));
     if (!order.empty() && total > kScratchBytes) {
-        // no room for the second list: every sweep in the ordinary kernel (the same results)
+        // no room for the list: every sweep in the ordinary kernel (the same results)
         set = sa::SettledChoice();
         order.clear();
         total = off_order;
@@ -208,8 +208,9 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     a.win_waves = lc.win_waves;
     a.waves_per_group = lc.waves_per_group;
     a.dense_cache = lc.dense_cache ? 1 : 0;
-    a.order = order.empty() ? a.sched : (const sa::SchedRec *)((char *)area + off_order);
+    a.order = order.empty() ? nullptr : (const sa::SchedRec *)((char *)area + off_order);
     a.n_order = active;
+    a.z30 = pk.z30 ? 1 : 0;
     if (a.trace) {
         rc = sa::launch_zero_u64(a.trace, (int64_t)n_reads * (s1 - s0), stream, err);
         if (rc != SA_OK) return sa::fail(rc, err);

@@ -65,11 +65,13 @@ struct sa_plan {
         int32_t uniform_width = 0;    // common width of every slot, 0 when they differ
     };
     Levels levels;
+    Sched order;                      // every variable in index order (the settled kernel), on first use
     std::mutex sched_mu;  // guards the lazy building of sched and levels (a server's preparers share plans)
     ~sa_plan() {
         if (beta_dev) (void)hipFree(beta_dev);
         for (auto &sc : sched)
             if (sc.dev) (void)hipFree(sc.dev);
+        if (order.dev) (void)hipFree(order.dev);
         if (levels.dev) (void)hipFree(levels.dev);
     }
 };
@@ -88,6 +90,8 @@ int build_plan(const sa_instance *inst, const sa_bounds *bounds, int32_t rule, s
 int resolve_schedule(sa_plan *plan, const sa_schedule *sched, std::vector<double> &beta);
 // The plan's sweep schedule for G waves per replica (built on first use, kept on the device).
 int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out);
+// The plan's variables in index order (build_order; n_active of them not fixed).
+int get_order(sa_plan *plan, sa_plan::Sched **out);
 // Uploads the inverse temperatures unless the device already holds the same array.
 int stage_beta(sa_plan *plan, const std::vector<double> &beta, hipStream_t stream);
 // Heat-bath register chunk class of a plan's widest range (1, 2, 8, 32, or 0 = recompute).

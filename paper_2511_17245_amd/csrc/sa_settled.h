@@ -27,12 +27,15 @@
 // sweeps registers: 460 spilled scalars instead of 114 in the wide heat-bath variant, whose ordinary
 // sweeps became 1.4 times slower.
 //
-// A variable whose dE is linear and whose terms hold at most three other factors (SchedRec::pad[1],
-// "cached") keeps a_k^(1) modulo 2^32 in ca (its true value fits: DevProblem::coef32); a change of
-// another variable adds the change of each shared term's product.  Any other variable keeps in cm
-// the smallest energy rise M of a move away from z_k, rounded down to the upper half of a float; 0
-// when it is not known, or not positive.  A change of a variable sharing a term sets it to 0.  The
-// dense form keeps c1 (int64) for every variable instead.
+// A variable whose terms hold it to the first or second power with at most three other factors
+// (SchedRec::pad[1], "cached") keeps a_k^(1) modulo 2^32 in ca, and a_k^(2) in cb when some term holds
+// its square (the true values fit: DevProblem::coef32); a change of another variable adds the change of
+// each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
+// also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
+// the upper half of a float; 0 when it is not known, or not positive.  A change of a variable sharing a
+// term sets it to 0, the next decision of a cached variable and the next visit of another finds it
+// again.  A sweep first reads cm alone, four variables per lane, and skips the blocks of 64 whose
+// variables are all frozen: beta M >= 746, where every other value's acceptance or weight is exactly 0.
 #pragma once
 
 #include "sa_device.h"
@@ -40,18 +43,19 @@
 namespace sa {
 namespace {
 
-// cm of a linear variable known to have a_k^(1) = 0: every value has the same energy
-constexpr uint16_t kFlat = 0x8000;
+// cm of a variable without a cached coefficient known to be linear with a_k^(1) = 0: every value has
+// the same energy.  And of a fixed variable: frozen at every temperature.
+constexpr uint16_t kFlat = 0x8000, kFixed = 0x7FFF;
 // e^(-beta M) = 0 in the device's exponential (exp_nonpos clamps there)
 constexpr double kSettledArg = 746.0;
 
 // The replica as the sweep's functions take it, with its caches in LDS.
 struct SettleView {
     ReplicaCtx R;
-    const SchedRec *order;
-    int32_t n_order;
-    uint32_t *ca;
-    uint16_t *cm;
+    const SchedRec *order;   // every variable in index order (k = -1 for a fixed one)
+    bool small;          // cached coefficients fit 32 bits, and every value 30
+    uint32_t *ca, *cb;   // nullptr where no variable is cached / cached with its square
+    uint16_t *cm;        // whole groups of four
 };
 
 __device__ __forceinline__ uint16_t margin_bits(int64_t M) {
@@ -62,20 +66,26 @@ __device__ __forceinline__ uint16_t margin_bits(int64_t M) {
 }
 __device__ __forceinline__ double margin_value(uint16_t b) { return (double)__uint_as_float((uint32_t)b << 16); }
 
-// ca of every cached variable from the state, and no margins known: one variable per lane.
+// The coefficients of every cached variable from the state, and no margins known: one variable per lane.
 template <typename ZT>
 __device__ __forceinline__ void settled_init(const SettleView &S, const ZT *z, int lane) {
     const DevProblem &P = S.R.P;
-    for (int32_t i = lane; i < S.n_order; i += kWave) {
-        const SchedRec sl = S.order[i];
-        if (S.cm) S.cm[sl.k] = 0;
-        if (S.ca && (sl.pad[1] & 1)) {
-            uint32_t acc = 0;
+    for (int32_t i = lane; i < ((P.n + 3) & ~3); i += kWave) {
+        SchedRec sl;
+        sl.k = -1;
+        if (i < P.n) sl = S.order[i];
+        S.cm[i] = sl.k >= 0 ? 0 : kFixed;
+        if (sl.k >= 0 && S.ca && sl.pad[1]) {
+            uint32_t a1 = 0, a2 = 0;
             for (int32_t q = 0; q < sl.deg; ++q) {
                 int e;
-                acc += record_product<uint32_t, ZT>(P, z, P.inc[sl.row + q], (uint64_t)P.inc_coef[sl.row + q], e);
+                const uint32_t p =
+                    record_product<uint32_t, ZT>(P, z, P.inc[sl.row + q], (uint64_t)P.inc_coef[sl.row + q], e);
+                a1 += e == 1 ? p : 0u;
+                a2 += e == 2 ? p : 0u;
             }
-            S.ca[sl.k] = acc;
+            S.ca[i] = a1;
+            if (S.cb) S.cb[i] = a2;
         }
     }
 }
@@ -87,7 +97,7 @@ __device__ __forceinline__ void settled_scatter(const SettleView &S, const ZT *z
                                                 int64_t zk, int64_t v, int lane) {
     const DevProblem &P = S.R.P;
     // (a flat variable's own value does not enter its coefficient: it stays flat)
-    if (S.cm && S.cm[k] != kFlat) S.cm[k] = 0;
+    if (S.cm[k] != kFlat) S.cm[k] = 0;
     for (int32_t c0 = 0; c0 < deg; c0 += kWave) {
         IncRec r;
         uint64_t coef;
@@ -97,20 +107,30 @@ __device__ __forceinline__ void settled_scatter(const SettleView &S, const ZT *z
         if (no > 3) {
             for (int32_t f = 0; f < no; ++f) S.cm[P.overflow[r.o[0] + f]] = 0;
         } else if (no > 0) {
+            const int32_t i0 = r.o[0], i1 = no > 1 ? r.o[1] : -1, i2 = no > 2 ? r.o[2] : -1;
             if (S.ca) {
                 const uint32_t g = (uint32_t)coef * (upow<uint32_t>((uint32_t)v, e) - upow<uint32_t>((uint32_t)zk, e));
-                const uint32_t z0 = (uint32_t)(int32_t)z[r.o[0]];
-                const uint32_t z1 = no > 1 ? (uint32_t)(int32_t)z[r.o[1]] : 1u;
-                const uint32_t z2 = no > 2 ? (uint32_t)(int32_t)z[r.o[2]] : 1u;
-                atomicAdd(&S.ca[r.o[0]], g * z1 * z2);
-                if (no > 1) atomicAdd(&S.ca[r.o[1]], g * z0 * z2);
-                if (no > 2) atomicAdd(&S.ca[r.o[2]], g * z0 * z1);
+                const uint32_t z0 = (uint32_t)(int32_t)z[i0];
+                const uint32_t z1 = no > 1 ? (uint32_t)(int32_t)z[i1] : 1u;
+                const uint32_t z2 = no > 2 ? (uint32_t)(int32_t)z[i2] : 1u;
+                // the others are sorted, so equal ones are neighbours: a factor that occurs once moves
+                // its variable's a^(1), one that occurs twice its a^(2) (three times: no cached variable)
+                if (i0 != i1) {
+                    atomicAdd(&S.ca[i0], g * z1 * z2);
+                    if (no > 1 && i1 != i2) {
+                        atomicAdd(&S.ca[i1], g * z0 * z2);
+                        if (no > 2) atomicAdd(&S.ca[i2], g * z0 * z1);
+                    } else if (no > 2 && S.cb) {
+                        atomicAdd(&S.cb[i1], g * z0);
+                    }
+                } else if (i1 != i2) {
+                    if (S.cb) atomicAdd(&S.cb[i0], g * z2);
+                    if (no > 2) atomicAdd(&S.ca[i2], g * z0 * z1);
+                }
             }
-            if (S.cm) {
-                S.cm[r.o[0]] = 0;
-                if (no > 1) S.cm[r.o[1]] = 0;
-                if (no > 2) S.cm[r.o[2]] = 0;
-            }
+            S.cm[i0] = 0;
+            if (no > 1) S.cm[i1] = 0;
+            if (no > 2) S.cm[i2] = 0;
         }
     }
 }
@@ -196,7 +216,7 @@ __device__ __forceinline__ bool settled_visit(const SettleView &S, const ZT *z, 
     }
     if (!taken || v == zk) {
         const uint16_t m = settled_margin(C, em, lo, W, zk, lane);
-        if (lane == 0) S.cm[k] = m;
+        if (lane == 0) S.cm[k] = m;   // (k: its place in index order)
     }
     return taken;
 }
@@ -212,22 +232,210 @@ __device__ __forceinline__ bool heat_bath_stays(double rho, double U) {
 // sum over d >= 1 of e^(-c d), from e1 = e^(-c); no bound above e1 = 1/2
 __device__ __forceinline__ double geometric_tail(double e1) { return e1 < 0.5 ? e1 / (1.0 - e1) : 1e300; }
 
-// One settled sweep of one replica (one wave).  kDense: the dense form with its coefficient cache
-// (c1; the changes keep it exact), else the incidence form with ca and cm.  Adds to H
-// the changes of the state hash (tracing) and to `moves` their number; the energy is
-// formed from the state at the end of the run.
+// Optimal transition of a variable with exponents one and two (quad_argmin_quadratic's candidates, all
+// in one lane): the value of smallest dE over the range, z_k included, ties to the lowest.
+__device__ __forceinline__ int64_t lane_argmin_quadratic(int64_t a1, int64_t a2, int64_t lo, int64_t hi, int64_t zk) {
+    int64_t f = lo;
+    if (a2 > 0) {
+        const double t = -(double)a1 / (2.0 * (double)a2);
+        f = t < (double)lo ? lo : t > (double)hi ? hi : (int64_t)__builtin_floor(t);
+    }
+    int64_t best = INT64_MAX, bv = INT64_MAX;
+    for (int i = 0; i < 7; ++i) {
+        int64_t v = i == 0 ? lo : i == 1 ? hi : i == 2 ? zk : f + (int64_t)(i - 4);
+        v = v < lo ? lo : v > hi ? hi : v;
+        const int64_t d = (v - zk) * (a1 + a2 * (v + zk));
+        if (d < best || (d == best && v < bv)) {
+            best = d;
+            bv = v;
+        }
+    }
+    return bv;
+}
+
+// One block of 64 variables (slots sl, one per lane) of a settled sweep.  Returns the number of changes.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT>
-__device__ __forceinline__ void settled_sweep(const SettleView &S, ZT *z, int lane, int32_t s, double beta, double r_opt,
-                                              ScanCarry &cy, uint64_t &H, uint32_t &moves) {
+__device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, int lane, int32_t b, const SchedRec &sl,
+                                                  int32_t s, double beta, double r_opt, ScanCarry &cy, uint64_t &H) {
     const ReplicaCtx &R = S.R;
     const DevProblem &P = R.P;
     constexpr bool kEnumerated = kRule == SA_HEAT_BATH;
     constexpr bool kClosed = kRule == SA_HEAT_BATH_CLOSED;
     constexpr bool kHeatBath = kEnumerated || kClosed;
-    auto slot = [&](int32_t i) {
+    uint32_t moves = 0;
+    const bool valid = sl.k >= 0;
+    const int32_t kk = valid ? sl.k : 0;
+    const int64_t lo = sl.lo, hi = lo + (int64_t)(uint32_t)sl.width - 1;
+    const uint32_t W32 = (uint32_t)sl.width;
+    const int64_t zk = (int64_t)z[kk];
+    const bool linear = (sl.emask & ~2u) == 0;
+    const bool has = kDense || (S.ca && sl.pad[1]);
+    bool cached = has;         // a1 and a2 are known (also of a flat variable without cached ones)
+    int64_t a1 = 0, a2 = 0;
+    double M = 0.0;            // smallest rise of a move away from z_k; <= 0: not known, or there is none
+    uint16_t mbits = 0;        // as cm keeps it
+    if (kDense && valid) a2 = P.d[kk];
+    // no variable of the block has a square; dE from 32-bit factors where coefficients and values allow
+    const bool all_linear = __ballot(valid && !linear) == 0;
+    auto de = [&](int64_t v) -> int64_t {
+        if (S.small) {
+            const int32_t dv = (int32_t)v - (int32_t)zk, sv = (int32_t)v + (int32_t)zk;
+            if (all_linear) return (int64_t)(int32_t)a1 * (int64_t)dv;
+            return ((int64_t)(int32_t)a1 + (int64_t)(int32_t)a2 * (int64_t)sv) * (int64_t)dv;
+        }
+        return (v - zk) * (a1 + a2 * (v + zk));
+    };
+    // The smallest dE(v), v != z_k, of a polynomial of degree at most two: on either side of z_k it lies
+    // next to z_k or at the range's end (a concave dE's minimum over a range is at an end of it, a
+    // convex one that rises on both sides of z_k keeps rising, and one that does not gives a value <= 0).
+    auto find_margin = [&] {
+        int64_t m = zk == lo ? a1 : zk == hi ? -a1 : 0;
+        if (!all_linear && !linear) {
+            m = INT64_MAX;
+            if (zk < hi) {
+                const int64_t p = de(zk + 1), q = de(hi);
+                m = p < q ? p : q;
+            }
+            if (zk > lo) {
+                const int64_t p = de(zk - 1), q = de(lo);
+                m = p < m ? p : m;
+                m = q < m ? q : m;
+            }
+        }
+        M = (double)m;
+        // (the closed-form draw at the top of the range depends on U = 0: never frozen)
+        mbits = kClosed && linear && zk != lo ? 0 : margin_bits(m);
+    };
+    // decisions that read M find it each time; the others only now and then, for cm (below)
+    constexpr bool kUsesMargin = kEnumerated || kRule == SA_OPT_METROPOLIS;
+    auto read_caches = [&] {
+        if (has) {
+            a1 = kDense ? R.c1[kk] : (int64_t)(int32_t)S.ca[kk];
+            if (!kDense && !linear) a2 = (int64_t)(int32_t)S.cb[kk];
+            if (kUsesMargin || (kClosed && !all_linear)) find_margin();
+        } else {
+            mbits = S.cm[kk];
+            M = margin_value(mbits);   // (-0.0 for a flat one)
+            cached = mbits == kFlat;
+        }
+    };
+    read_caches();
+    uint32_t x0 = (uint32_t)sl.k, x1 = (uint32_t)s, x2 = R.read, x3 = R.instance_id;
+    philox4x32_10(x0, x1, x2, x3, R.key0, R.key1);
+    const double U = (double)((((uint64_t)x2 << 32) | x3) >> 11) * 0x1p-53;
+    const bool optimal = kRule == SA_OPT_METROPOLIS && (double)x0 * 0x1p-32 < r_opt;
+    uint64_t todo = ~0ull;
+    for (;;) {
+        // want: 0 stays, 1 changes to v (energy change d), 2 needs a visit
+        int want = 0;
+        int64_t v = zk;
+        if (kHeatBath) {
+            if (kClosed && cached && linear) {
+                v = heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1);
+                want = v != zk ? 1 : 0;
+            } else {
+                want = 2;
+                if (M > 0.0) {
+                    const double ex = exp_nonpos(-(beta * M));
+                    // linear: the values at distance d weigh ex^d on one side; convex: at most that on
+                    // either side; else at most ex each
+                    const double rho = !cached || (!linear && a2 < 0) ? (double)(W32 - 1u) * ex
+                                       : linear                        ? geometric_tail(ex)
+                                                                       : 2.0 * geometric_tail(ex);
+                    want = heat_bath_stays(rho, U) ? 0 : 2;
+                }
+            }
+        } else if (cached) {
+            if (optimal) {
+                v = linear ? (a1 >= 0 ? lo : hi) : M > 0.0 ? zk : lane_argmin_quadratic(a1, a2, lo, hi, zk);
+            } else {
+                v = lo + (int64_t)(((uint64_t)x1 * (uint64_t)(W32 - 1u)) >> 32);
+                if (v >= zk) v += 1;
+            }
+            want = v != zk && metropolis_accept(de(v), beta, U) ? 1 : 0;
+        } else {
+            // a positive margin: z_k is the optimal value, and a proposal's rise is at least M
+            want = M > 0.0 && U > exp_nonpos(-(beta * M)) * (1.0 + 1e-9) ? 0 : 2;
+        }
+        uint64_t mask = __ballot(valid && want != 0) & todo;
+        bool changed = false;
+        while (mask != 0 && !changed) {   // uniform
+            const int j = __ffsll((unsigned long long)mask) - 1;
+            todo = j == kWave - 1 ? 0ull : ~0ull << (j + 1);
+            mask &= todo;
+            const int32_t kj = (int32_t)lane_read32((uint32_t)sl.k, j);
+            const int32_t row = (int32_t)lane_read32((uint32_t)sl.row, j);
+            const int32_t deg = (int32_t)lane_read32((uint32_t)sl.deg, j);
+            const int64_t zj = (int64_t)(int32_t)lane_read32((uint32_t)(int32_t)zk, j);
+            int64_t vj, dj;
+            if (lane_read32((uint32_t)want, j) == 1u) {
+                vj = (int64_t)(int32_t)lane_read32((uint32_t)(int32_t)v, j);
+                changed = true;
+            } else {
+                const int64_t loj = (int32_t)lane_read32((uint32_t)sl.lo, j);
+                const int64_t Wj = (int64_t)lane_read32((uint32_t)sl.width, j);
+                const uint32_t em = lane_read32(sl.emask, j);
+                const uint32_t r0 = lane_read32(x0, j), r1 = lane_read32(x1, j);
+                const double Uj = __longlong_as_double((long long)lane_read64((uint64_t)__double_as_longlong(U), j));
+                const bool cj = kDense || lane_read32(cached ? 1u : 0u, j) != 0;
+                bool taken = true;
+                if (kHeatBath && cj) {   // an enumerated draw from the cached coefficients
+                    Coeffs<kMaxE, Acc> C;
+#pragma unroll
+                    for (int m = 0; m <= kMaxE; ++m) C.a[m] = 0;
+                    C.a[1] = (Acc)lane_read64((uint64_t)a1, j);
+                    if (kMaxE >= 2) C.a[kMaxE >= 2 ? 2 : 1] = (Acc)lane_read64((uint64_t)a2, j);
+                    vj = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, loj, Wj, zj, beta, Uj, lane, (em & ~2u) == 0, cy);
+                } else if constexpr (!kDense) {
+                    taken = settled_visit<kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, kj, loj, Wj, em, row, deg, r0, r1, Uj, zj,
+                                                                            beta, r_opt, lane, cy, vj, dj);
+                } else {
+                    vj = zj;   // (not reached: the dense form's other rules decide in the lane)
+                }
+                changed = taken && vj != zj;
+            }
+            if (changed) {
+                moves += 1;
+                z[kj] = (ZT)vj;   // every lane stores the same value
+                if (R.trace) H += hash_word(kj, vj) - hash_word(kj, zj);
+                if (kDense) {
+                    dense_cache_update(P, R.c1, kj, vj - zj, lane, nullptr);
+                    for (int32_t i = 4 * lane; i < P.n; i += 4 * kWave) *(uint64_t *)&S.cm[i] = 0;
+                } else {
+                    settled_scatter(S, z, kj, row, deg, zj, vj, lane);
+                }
+            }
+            state_write_fence<true>();
+        }
+        if (!changed) break;
+        read_caches();
+    }
+    // the margins found; a variable that changed here (its z_k no longer the lane's) has none.  (Where no
+    // decision reads them they are found every fourth sweep.)
+    constexpr bool kAlways = kUsesMargin || kClosed;
+    if (kAlways || (s & 3) == 0) {
+        if (!kUsesMargin && has) find_margin();
+        if (valid ? has : b + lane < P.n) S.cm[b + lane] = !valid ? kFixed : (int64_t)z[kk] == zk ? mbits : 0;
+        state_write_fence<true>();
+    }
+    return moves;
+}
+
+// One settled sweep of one replica (one wave).  kDense: the dense form with its coefficient cache
+// (c1; the changes keep it exact), else the incidence form.  Adds to H the changes of the state hash
+// (tracing); the energy is formed from the state at the end of the run.  Returns the number of changes.
+template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT>
+__device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, int lane, int32_t s, double beta, double r_opt,
+                                                  ScanCarry &cy, uint64_t &H) {
+    const int32_t n = S.R.P.n;
+    // the least margin bits with beta M >= 746: above 746 / beta rounded up
+    const float t = (float)(kSettledArg / beta) * 1.000001f;
+    const uint32_t tb = (__float_as_uint(t) >> 16) + 1u;
+    const int16_t thr = (int16_t)(tb < (uint32_t)kFixed ? tb : (uint32_t)kFixed);
+    auto load = [&](int32_t b) {
         SchedRec m;
-        if (i < S.n_order) {
-            m = S.order[i];
+        if (b + lane < n) {
+            m = S.order[b + lane];
         } else {
             m.k = -1;
             m.lo = 0;
@@ -235,135 +443,48 @@ __device__ __forceinline__ void settled_sweep(const SettleView &S, ZT *z, int la
             m.row = 0;
             m.deg = 0;
             m.emask = 0;
-            m.pad[1] = 1;   // (an idle lane reads ca where there is one, as a cached variable does)
+            m.pad[1] = 1;
         }
         return m;
     };
-    SchedRec nx = slot(lane);
-    for (int32_t b = 0; b < S.n_order; b += kWave) {
-        const SchedRec sl = nx;
-        nx = slot(b + kWave + lane);   // loaded under this block's work
-        const bool valid = sl.k >= 0;
-        const int32_t kk = valid ? sl.k : 0;
-        const int64_t lo = sl.lo, hi = lo + (int64_t)(uint32_t)sl.width - 1;
-        const uint32_t W32 = (uint32_t)sl.width;
-        const int64_t zk = (int64_t)z[kk];
-        const bool linear = (sl.emask & ~2u) == 0;
-        const bool has_ca = kDense || (S.ca && (sl.pad[1] & 1));
-        bool cached = has_ca;   // a1 is known (also of a flat variable without a cached coefficient)
-        const int64_t a2 = kDense && valid ? P.d[kk] : 0;
-        int64_t a1 = 0;    // cached: a_k^(1)
-        double M = 0.0;    // smallest rise of a move away from z_k; <= 0: not known, or there is none
-        auto read_caches = [&] {
-            if (has_ca) {
-                a1 = kDense ? R.c1[kk] : (int64_t)(int32_t)S.ca[kk];
-                if (kDense && !linear) M = (double)quadratic_margin(a1, a2, lo, hi, zk);
-                else M = zk == lo ? (double)a1 : zk == hi ? -(double)a1 : 0.0;
-            } else {
-                const uint16_t m = S.cm[kk];
-                M = margin_value(m);   // (-0.0 for a flat one)
-                cached = m == kFlat;
+    uint32_t moves = 0;
+    for (int32_t base = 0; base < n; base += 4 * kWave) {
+        // lane l: variables base + 4 l .. + 3; block q of 64 is lanes 16 q .. 16 q + 15
+        auto active = [&]() -> uint64_t {
+            bool any = false;
+            if (base + 4 * lane < n) {
+                const uint64_t m = *(const uint64_t *)&S.cm[base + 4 * lane];
+                any = (int16_t)m < thr || (int16_t)(m >> 16) < thr || (int16_t)(m >> 32) < thr || (int16_t)(m >> 48) < thr;
             }
+            return __ballot(any);
         };
-        read_caches();
-        // Settled whatever the random words: every other value's acceptance or weight is exactly 0.
-        // (The closed-form draw at the top of the range depends on U = 0, so it reads its words.)
-        const bool frozen = beta * M >= kSettledArg && !(kClosed && linear && zk != lo);
-        if (__ballot(valid && !frozen) == 0) continue;
-        uint32_t x0 = (uint32_t)sl.k, x1 = (uint32_t)s, x2 = R.read, x3 = R.instance_id;
-        philox4x32_10(x0, x1, x2, x3, R.key0, R.key1);
-        const double U = (double)((((uint64_t)x2 << 32) | x3) >> 11) * 0x1p-53;
-        uint64_t todo = ~0ull;
-        for (;;) {
-            // want: 0 stays, 1 changes to v (energy change d), 2 needs a visit
-            int want = 0;
-            int64_t v = zk, d = 0;
-            if (kHeatBath) {
-                if (kClosed && cached && linear) {
-                    v = heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1);
-                    d = a1 * (v - zk);
-                    want = v != zk ? 1 : 0;
-                } else {
-                    want = 2;
-                    if (M > 0.0) {
-                        const double ex = exp_nonpos(-(beta * M));
-                        // linear: the values at distance d weigh ex^d on one side; convex: at most
-                        // that on either side; else at most ex each
-                        const double rho = cached ? (linear ? geometric_tail(ex)
-                                                            : a2 >= 0 ? 2.0 * geometric_tail(ex) : (double)(W32 - 1u) * ex)
-                                                  : (double)(W32 - 1u) * ex;
-                        want = heat_bath_stays(rho, U) ? 0 : 2;
-                    }
-                }
-            } else if (cached && (kRule == SA_METROPOLIS || linear || !((double)x0 * 0x1p-32 < r_opt))) {
-                if (kRule == SA_OPT_METROPOLIS && (double)x0 * 0x1p-32 < r_opt) {
-                    v = a1 >= 0 ? lo : hi;
-                } else {
-                    v = lo + (int64_t)(((uint64_t)x1 * (uint64_t)(W32 - 1u)) >> 32);
-                    if (v >= zk) v += 1;
-                }
-                d = kDense ? (v - zk) * (a1 + a2 * (v + zk)) : a1 * (v - zk);
-                want = v != zk && metropolis_accept(d, beta, U) ? 1 : 0;
-            } else {
-                // a positive margin: z_k is the optimal value, and a proposal's rise is at least M
-                want = M > 0.0 && U > exp_nonpos(-(beta * M)) * (1.0 + 1e-9) ? 0 : 2;
+        uint64_t am = active();
+        int q = 0;
+        auto next = [&](int from) {   // the first block from `from` on with an active variable, or 4
+            while (from < 4 && ((am >> (16 * from)) & 0xFFFFull) == 0) ++from;
+            return from;
+        };
+        q = next(0);
+        SchedRec sl;
+        if (q < 4) sl = load(base + kWave * q);
+        while (q < 4) {   // uniform
+            int qn = next(q + 1);
+            SchedRec sn = sl;
+            if (qn < 4) sn = load(base + kWave * qn);   // under this block's work
+            const uint32_t c = settled_block<kDense, kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, lane, base + kWave * q, sl, s, beta,
+                                                                                       r_opt, cy, H);
+            moves += c;
+            if (c != 0) {
+                am = active();
+                const int qc = next(q + 1);
+                if (qc != qn && qc < 4) sn = load(base + kWave * qc);
+                qn = qc;
             }
-            uint64_t mask = __ballot(valid && want != 0) & todo;
-            bool changed = false;
-            while (mask != 0 && !changed) {   // uniform
-                const int j = __ffsll((unsigned long long)mask) - 1;
-                todo = j == kWave - 1 ? 0ull : ~0ull << (j + 1);
-                mask &= todo;
-                const int32_t kj = (int32_t)lane_read32((uint32_t)sl.k, j);
-                const int32_t row = (int32_t)lane_read32((uint32_t)sl.row, j);
-                const int32_t deg = (int32_t)lane_read32((uint32_t)sl.deg, j);
-                const int64_t zj = (int64_t)(int32_t)lane_read32((uint32_t)(int32_t)zk, j);
-                int64_t vj, dj;
-                if (lane_read32((uint32_t)want, j) == 1u) {
-                    vj = (int64_t)(int32_t)lane_read32((uint32_t)(int32_t)v, j);
-                    dj = (int64_t)lane_read64((uint64_t)d, j);
-                    changed = true;
-                } else {
-                    const int64_t loj = (int32_t)lane_read32((uint32_t)sl.lo, j);
-                    const int64_t Wj = (int64_t)lane_read32((uint32_t)sl.width, j);
-                    const uint32_t em = lane_read32(sl.emask, j);
-                    const uint32_t r0 = lane_read32(x0, j), r1 = lane_read32(x1, j);
-                    const double Uj = __longlong_as_double((long long)lane_read64((uint64_t)__double_as_longlong(U), j));
-                    const bool cj = kDense || lane_read32(cached ? 1u : 0u, j) != 0;
-                    bool taken = true;
-                    if (kEnumerated && !kDense && cj) {
-                        Coeffs<kMaxE, Acc> C;
-#pragma unroll
-                        for (int m = 0; m <= kMaxE; ++m) C.a[m] = 0;
-                        C.a[1] = (Acc)lane_read64((uint64_t)a1, j);
-                        vj = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, loj, Wj, zj, beta, Uj, lane, true, cy);
-                        dj = to_i64<Acc>(C.a[1] * (Acc)(vj - zj));
-                    } else if constexpr (kDense) {
-                        IncRec none;
-                        none.meta = 0;
-                        none.o[0] = none.o[1] = none.o[2] = 0;
-                        taken = update_rule<kRule, kRegChunk, kMaxE, Acc, ZT>(R, z, kj, loj, Wj, em, row, deg, r0, r1, Uj,
-                                                                              zj, beta, r_opt, lane, none, 0, P.d[kj], cy,
-                                                                              [] {}, vj, dj);
-                    } else {
-                        taken = settled_visit<kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, kj, loj, Wj, em, row, deg, r0, r1, Uj,
-                                                                                zj, beta, r_opt, lane, cy, vj, dj);
-                    }
-                    changed = taken && vj != zj;
-                }
-                if (changed) {
-                    moves += 1;
-                    z[kj] = (ZT)vj;   // every lane stores the same value
-                    if (R.trace) H += hash_word(kj, vj) - hash_word(kj, zj);
-                    if (kDense) dense_cache_update(P, R.c1, kj, vj - zj, lane, nullptr);
-                    else settled_scatter(S, z, kj, row, deg, zj, vj, lane);
-                }
-                state_write_fence<true>();
-            }
-            if (!changed) break;
-            read_caches();
+            sl = sn;
+            q = qn;
         }
     }
+    return moves;
 }
 
 // The settled part of a run: read blockIdx.x from the state in z_out and the sweep in e_out to the end of
@@ -394,23 +515,24 @@ __global__ void __launch_bounds__(kWave) settled_kernel(AnnealArgs A) {
     R.otm_enum_max = A.otm_enum_max;
     R.trace = A.trace ? A.trace + (size_t)read * (size_t)(A.s_end - A.s_begin) - A.s_begin : nullptr;
     S.order = A.order;
-    S.n_order = A.n_order;
+    S.small = A.P.coef32 && A.z30;
     R.c1 = kDense ? (int64_t *)((char *)lds_state + A.off_c) : nullptr;
     S.ca = !kDense && A.off_c >= 0 ? (uint32_t *)((char *)lds_state + A.off_c) : nullptr;
-    S.cm = !kDense && A.off_m >= 0 ? (uint16_t *)((char *)lds_state + A.off_m) : nullptr;
+    S.cb = !kDense && A.off_c2 >= 0 ? (uint32_t *)((char *)lds_state + A.off_c2) : nullptr;
+    S.cm = (uint16_t *)((char *)lds_state + A.off_m);
     state_write_fence<true>();
+    settled_init(S, z, lane);
     if (kDense) dense_cache_init(A.P, z, R.c1, lane, kWave);
-    else settled_init(S, z, lane);
     state_write_fence<true>();
     ScanCarry cy;
     int busy = 0;   // sweeps on end past A.leave
     for (; s < A.s_end; ++s) {
         uint64_t H = 0;
-        uint32_t moves = 0;
         const double beta = A.beta[s];
         const double r_opt =
             A.otm_r >= 0.0 ? A.otm_r : (A.n_sweeps > 1 ? (double)s / (double)(A.n_sweeps - 1) : 0.0);
-        settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H, moves);
+        const uint32_t moves =
+            settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H);
         if (R.trace && H != 0 && lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
         busy = moves > (uint32_t)A.leave ? busy + 1 : 0;
         if (busy == 3) {
