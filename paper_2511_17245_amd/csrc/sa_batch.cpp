@@ -43,7 +43,8 @@ struct sa_batch {
     int cus = 256, max_lds = 65536;
     bool z16 = false;
     char *base = nullptr;
-    size_t o_inst = 0, o_task = 0;
+    size_t o_inst = 0, o_task = 0, o_settled = 0;
+    std::vector<int> settled_lds;      // LDS bytes of a settled replica of each problem (0: none)
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
     ~sa_batch() {
@@ -114,6 +115,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
         b.insts[i].sched = sc->dev;
         b.insts[i].n_win = sc->n_win;
         b.insts[i].slot_stride = (int32_t)stride;
+        b.insts[i].leave = std::max<int32_t>(1, 3 * b.insts[i].n_order / sa::settled_share(G));
         lds_elems_max = std::max<int64_t>(lds_elems_max, (int64_t)(sa::kBatchWaves / G) * stride);
     }
     // tasks: problems by decreasing cost of one replica, kBatchWaves / G_p reads per task
@@ -127,7 +129,12 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
         for (int32_t r = 0; r < b.n_reads[i]; r += per) tasks.push_back(sa::BatchTask{i, r});
     }
     b.n_tasks = (int64_t)tasks.size();
+    std::vector<sa::BatchTask> settled;
+    sa::settle_batch(b.insts, b.settled_lds, b.replica_cost, settled, b.launch.settled);
+    b.launch.settled_tasks = (const sa::BatchTask *)(b.base + b.o_settled);
     hipError_t e = hipMemcpy(b.base + b.o_inst, b.insts.data(), sizeof(sa::BatchInst) * n, hipMemcpyHostToDevice);
+    if (e == hipSuccess && !settled.empty())
+        e = hipMemcpy(b.base + b.o_settled, settled.data(), sizeof(sa::BatchTask) * settled.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(b.base + b.o_task, tasks.data(), sizeof(sa::BatchTask) * tasks.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(batch tasks)");
@@ -237,11 +244,13 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
     if (b->max_tasks > INT32_MAX) return fail(SA_EINVAL, "too many replicas in one batch");
     b->o_inst = 0;
     b->o_task = b->o_inst + align256(sizeof(sa::BatchInst) * n);
-    const size_t o_ctr = b->o_task + align256(sizeof(sa::BatchTask) * (size_t)b->max_tasks);
+    b->o_settled = b->o_task + align256(sizeof(sa::BatchTask) * (size_t)b->max_tasks);
+    const size_t o_ctr = b->o_settled + align256(sizeof(sa::BatchTask) * (size_t)b->max_tasks);
     const size_t o_beta = o_ctr + 256;
     const size_t o_z = o_beta + align256(sizeof(double) * beta_total);
     const size_t o_e = o_z + align256(sizeof(int32_t) * z_total);
-    const size_t total = o_e + align256(sizeof(int64_t) * e_total);
+    const size_t o_next = o_e + align256(sizeof(int64_t) * e_total);
+    const size_t total = o_next + align256(sizeof(int32_t) * e_total);
     hipError_t e = hipMalloc(&b->arena.base, total);
     if (e != hipSuccess) {
         b->arena.base = nullptr;
@@ -275,6 +284,12 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         d.instance_id = problems[i].instance_id;
         d.z_out = b->z_dev + b->z_off[i];
         d.e_out = b->e_dev + b->e_off[i];
+        sa_plan::Sched *all = nullptr;
+        int rc = sa::get_order(&p, &all);
+        if (rc != SA_OK) return rc;
+        b->settled_lds.push_back(
+            sa::settle_inst(p.packed, p.dp.coef32 != 0, all->dev, all->n_active, d.n_sweeps, b->device, d));
+        if (b->settled_lds.back()) d.next = (int32_t *)(b->base + o_next) + b->e_off[i];
     }
     b->args.insts = (const sa::BatchInst *)(b->base + b->o_inst);
     b->args.tasks = (const sa::BatchTask *)(b->base + b->o_task);

@@ -1010,6 +1010,9 @@ __device__ __forceinline__ void window_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// A word of device memory, the same for the whole wave.
+__device__ __forceinline__ int32_t uni_load(const int32_t *p) { return (int32_t)uni32((uint32_t)*p); }
+
 // What one replica's sweeps need (shared by the plain and the batched kernels).
 struct ReplicaCtx {
     DevProblem P;
@@ -1025,7 +1028,9 @@ struct ReplicaCtx {
     uint64_t *trace;        // this read's hash word of sweep 0 (indexed by the sweep), or nullptr
     int64_t *c1;            // dense form: this replica's coefficient cache in LDS, or nullptr
     int32_t stop;           // 0, or: end after a sweep with at most n_order / stop changes (the settled
-    int32_t n_order;        // kernel takes the rest); the variables of a sweep
+    int32_t n_order;        // kernel takes the rest); the variables of a sweep, over the replicas that share
+                            // the workgroup's barriers
+    int32_t s_first;        // this replica's first sweep (s_begin: the workgroup's)
     uint32_t *ctr;          // shared replicas that may end so: three change counters (LDS)
 };
 
@@ -1150,15 +1155,27 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
     int64_t E = 0;
     uint64_t H = 0;   // change of the state hash in this sweep by this wave's moves (tracing)
     ScanCarry cy;
-    if (!R.active) {
-        if (R.shared)
-            for (int32_t s = R.s_begin; s < R.s_end; ++s)
-                for (int32_t w = 0; w < n_win; ++w) window_barrier();
-        return 0;
-    }
     s_next = R.s_end;
+    if (!R.active && !R.shared) return 0;
     uint32_t sweep_no = 0;
+    // after a sweep with `moves` changes by this wave: whether the run ends here (uniform over the waves
+    // that share barriers; they decide together, from their sum)
+    auto settled = [&](uint32_t moves) -> bool {
+        if (R.shared) {
+            // the next sweep's counter is cleared before this barrier, a sweep after its last reads
+            if (lane == 0 && moves != 0) atomicAdd(&R.ctr[sweep_no % 3], moves);
+            if (threadIdx.x == 0) R.ctr[(sweep_no + 1) % 3] = 0;
+            window_barrier();
+            moves = uni32(R.ctr[sweep_no % 3]);
+        }
+        return moves * (uint32_t)R.stop <= (uint32_t)R.n_order;
+    };
     for (int32_t s = R.s_begin; s < R.s_end; ++s, ++sweep_no) {
+        if (!R.active || s < R.s_first) {   // an idle team only keeps the workgroup's barriers
+            for (int32_t w = 0; w < n_win; ++w) window_barrier();
+            if (R.stop != 0 && settled(0)) return 0;
+            continue;
+        }
         uint32_t moves = 0;   // changes by this wave
         const double beta = R.beta[s];
         const double r_opt =
@@ -1259,19 +1276,9 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
             if (lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
             H = 0;
         }
-        if (R.stop != 0) {
-            if (R.shared) {
-                // the waves decide together, from their sum; the next sweep's counter is cleared before
-                // this barrier, a sweep after its last reads
-                if (lane == 0 && moves != 0) atomicAdd(&R.ctr[sweep_no % 3], moves);
-                if (threadIdx.x == 0) R.ctr[(sweep_no + 1) % 3] = 0;
-                window_barrier();
-                moves = uni32(R.ctr[sweep_no % 3]);
-            }
-            if (moves * (uint32_t)R.stop <= (uint32_t)R.n_order) {   // uniform over the replica's waves
-                s_next = s + 1;
-                break;
-            }
+        if (R.stop != 0 && settled(moves)) {
+            s_next = s + 1;
+            break;
         }
     }
     return E;
@@ -1330,6 +1337,7 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     R.beta = A.beta;
     R.n_sweeps = A.n_sweeps;
     R.s_begin = s_begin;
+    R.s_first = s_begin;
     R.s_end = A.s_end;
     R.key0 = A.key0;
     R.key1 = A.key1;
@@ -1399,23 +1407,52 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         const DevProblem P = D.P;
         const int G = D.team;
         const int team = wave / G, g = wave % G;
+        const int teams = kBatchWaves / G;
         const int32_t read_i = task.read + team;
-        const bool active = read_i < D.n_reads;
         const uint32_t read = (uint32_t)read_i;
+        // Three launches per run where the problem takes part in settled sweeps (D.next: per read, the
+        // next sweep s, or ~s once the replica has settled): the first ends a replica where it settles
+        // (and leaves alone one that an earlier chunk left settled), the last takes up those that came
+        // unsettled.  Every wave looks at all the task's reads, so that the choice is uniform.
+        const bool chain = B.phase != kPhaseWhole && D.next != nullptr;
+        bool active = read_i < D.n_reads;
+        int32_t s_first = D.s_begin, s_from = D.s_begin, n_active = 0;
+        if (chain) {
+            s_from = D.s_end;
+            for (int q = 0; q < teams; ++q) {
+                if (task.read + q >= D.n_reads) break;
+                const int32_t nx = B.phase == kPhaseLast || D.resume ? uni_load(&D.next[task.read + q]) : D.s_begin;
+                const bool runs = nx >= 0 && nx < D.s_end;
+                n_active += runs ? 1 : 0;
+                if (runs && nx < s_from) s_from = nx;
+                if (q == team) {
+                    active = runs;
+                    s_first = nx;
+                }
+            }
+            if (n_active == 0) continue;   // uniform over the workgroup
+        } else if (B.phase == kPhaseLast) {
+            continue;   // the first launch ran it whole
+        }
+        // a replica that is taken up again starts from its state and energy in device memory
+        const bool resume = D.resume || B.phase == kPhaseLast;
         ZT *z = (ZT *)lds_state + (size_t)team * D.slot_stride;
         const int tid = g * kWave + lane, nthr = G * kWave;
         int32_t *zo = D.z_out + (size_t)read * P.n;
-        if (active) init_state(P, z, D.resume ? zo : nullptr, read, D.instance_id, D.key0, D.key1, tid, nthr);
+        if (active) init_state(P, z, resume ? zo : nullptr, read, D.instance_id, D.key0, D.key1, tid, nthr);
+        const bool may_stop = chain && B.phase == kPhaseFirst;
+        if (threadIdx.x < 3) ((uint32_t *)parts)[threadIdx.x] = 0;   // change counters, until the energies
         window_barrier();
         // a resumed replica continues from the exact energy its previous chunk wrote (the team's
         // first wave carries it); a new one sums its terms
         int64_t E = 0;
-        if (active) E = D.resume ? (g == 0 ? D.e_out[read] : 0) : energy_part(P, z, tid, nthr);
+        if (active) E = resume ? (g == 0 ? D.e_out[read] : 0) : energy_part(P, z, tid, nthr);
         ReplicaCtx R;
         R.P = P;
         R.beta = D.beta;
         R.n_sweeps = D.n_sweeps;
-        R.s_begin = D.s_begin;
+        R.s_begin = G > 1 ? s_from : s_first;
+        R.s_first = s_first;
         R.s_end = B.sweep_limit > 0 && B.sweep_limit < D.s_end ? B.sweep_limit : D.s_end;
         R.key0 = D.key0;
         R.key1 = D.key1;
@@ -1429,7 +1466,9 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         R.active = active;
         R.trace = nullptr;
         R.c1 = nullptr;
-        R.stop = 0;
+        R.stop = may_stop ? settled_share(G) : 0;
+        R.n_order = G > 1 ? D.n_order * n_active : D.n_order;
+        R.ctr = (uint32_t *)parts;
         int32_t s_next;
         if (D.rule == SA_METROPOLIS) {
             E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane, s_next);
@@ -1450,6 +1489,7 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         } else {
             E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane, s_next);
         }
+        if (may_stop && G > 1) window_barrier();   // the counters' last reads
         if (lane == 0) parts[wave] = E;
         window_barrier();
         if (active) {
@@ -1457,6 +1497,7 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
                 int64_t tot = 0;
                 for (int q = 0; q < G; ++q) tot += parts[team * G + q];
                 D.e_out[read] = tot;
+                if (chain) D.next[read] = may_stop && s_next < R.s_end ? ~s_next : s_next;
             }
             for (int32_t k = tid; k < P.n; k += nthr) zo[k] = (int32_t)z[k];
         }

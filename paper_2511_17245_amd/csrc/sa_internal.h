@@ -226,6 +226,7 @@ struct AnnealArgs {
     const SchedRec *order;   // every variable in index order (build_order)
     int32_t n_order;         // those that are not fixed
     int32_t off_c, off_c2, off_m;   // LDS byte offsets of the caches (dense: c1, else ca; cb; margins); -1: none
+    int32_t closed;          // heat bath: closed-form draws
     int32_t z30;             // every bound of the problem is below 2^30 in magnitude
     int32_t leave;           // changes per sweep past which a replica leaves
 };
@@ -369,6 +370,10 @@ struct BatchInst {
     uint32_t key0, key1, instance_id;
     int32_t *z_out;          // n_reads x n (device)
     int64_t *e_out;          // n_reads (device)
+    // settled sweeps (as AnnealArgs); next == nullptr: none
+    int32_t *next;           // n_reads: the next sweep s, or ~s of a settled replica (device)
+    const SchedRec *order;
+    int32_t n_order, off_c, off_c2, off_m, z30, leave;
 };
 struct BatchTask {
     int32_t inst;
@@ -381,16 +386,36 @@ struct BatchArgs {
     uint32_t *counter;       // next task (device)
     int32_t lds_words;       // dynamic LDS of a workgroup, 32-bit words
     int32_t parts_words;     // offset of the waves' energy parts (kBatchWaves int64)
+    int32_t phase;           // as AnnealArgs::phase; a problem with next == nullptr is run whole by the first
     int32_t sweep_limit;     // > 0: only the first sweep_limit sweeps (autotuning trials)
 };
+// One launch of the settled kernel over tasks first .. first + n - 1 of a list, each with lds_bytes of
+// LDS: the replicas of a batch in three groups by what their caches take (up to 10, 40 and 160 KB, that
+// is 16, 4 and 1 replicas per compute unit), the widest first, each longest first.
+struct SettledGroup {
+    int32_t first = 0, n = 0;
+    int lds_bytes = 0;
+};
+constexpr int kSettledGroups = 3;
+// The groups and their task list, for problems whose replicas take lds[i] bytes (0: not settled) and cost[i].
+void settle_batch(const std::vector<BatchInst> &insts, const std::vector<int> &lds, const std::vector<double> &cost,
+                  std::vector<BatchTask> &tasks, SettledGroup (&groups)[kSettledGroups]);
+int launch_settled_batch(const BatchInst *insts, const BatchTask *tasks, int32_t n_tasks, int lds_bytes, int maxe_class,
+                         void *stream, std::string &err);
+// Fills a problem's settled fields (next is the caller's) for teams of `team` waves; returns its LDS bytes, or 0.
+int settle_inst(const Packed &p, bool coef32, const SchedRec *order, int32_t n_order, int32_t n_sweeps, int device,
+                BatchInst &d);
 struct BatchLaunch {
+    SettledGroup settled[kSettledGroups];
+    const BatchTask *settled_tasks = nullptr;   // device
     int waves_per_group = kBatchWaves;
     int groups = 1;
     int maxe_class = 1;
     bool narrow = false;
     bool z16 = false;        // states held as int16 in LDS (every bound within int16)
 };
-// Queues the counter reset and the persistent kernel (both plain kernel launches).
+// Queues the counter reset and the persistent kernel, and with settled groups their kernels and the
+// persistent kernel again (all plain kernel launches).
 int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::string &err);
 
 // Zeroes n words of device memory with a kernel (no memset node, so the work may be captured).

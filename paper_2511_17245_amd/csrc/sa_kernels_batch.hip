@@ -33,9 +33,26 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
             return SA_EDEVICE;
         }
     }
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, b.counter);
-    hipLaunchKernelGGL(fn, dim3((unsigned)bl.groups), dim3((unsigned)(kBatchWaves * kWave)), (size_t)lds,
-                       (hipStream_t)stream, b);
+    int32_t n_settled = 0;
+    for (const SettledGroup &g : bl.settled) n_settled += g.n;
+    BatchArgs a = b;
+    auto persistent = [&](int32_t phase) {
+        a.phase = phase;
+        hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, a.counter);
+        hipLaunchKernelGGL(fn, dim3((unsigned)bl.groups), dim3((unsigned)(kBatchWaves * kWave)), (size_t)lds,
+                           (hipStream_t)stream, a);
+    };
+    if (n_settled == 0 || b.sweep_limit > 0) {
+        persistent(kPhaseWhole);
+    } else {
+        persistent(kPhaseFirst);
+        for (const SettledGroup &g : bl.settled) {
+            if (g.n == 0) continue;
+            int rc = launch_settled_batch(b.insts, bl.settled_tasks + g.first, g.n, g.lds_bytes, bl.maxe_class, stream, err);
+            if (rc != SA_OK) return rc;
+        }
+        persistent(kPhaseLast);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         err = std::string("batch launch: ") + hipGetErrorString(e);

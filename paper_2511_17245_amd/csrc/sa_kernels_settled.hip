@@ -11,7 +11,7 @@ using SettledFn = void (*)(AnnealArgs);
 // Heat-bath visits: weights per lane in registers up to 8 (kRegChunk), recomputed above.
 template <bool kDense, int kRule, int kMaxE, typename Acc>
 SettledFn pick_chunk(int32_t max_width) {
-    if (max_width <= kWave) return settled_kernel<kDense, kRule, 1, kMaxE, Acc>;
+    if (max_width <= 2 * kWave) return settled_kernel<kDense, kRule, 2, kMaxE, Acc>;
     if (max_width <= 8 * kWave) return settled_kernel<kDense, kRule, 8, kMaxE, Acc>;
     return settled_kernel<kDense, kRule, 0, kMaxE, Acc>;
 }
@@ -20,8 +20,8 @@ template <bool kDense, int kMaxE, typename Acc>
 SettledFn pick_rule(int rule, int32_t max_width, int32_t otm_enum_max) {
     switch (rule) {
         case SA_METROPOLIS: return settled_kernel<kDense, SA_METROPOLIS, 0, 1, Acc>;
-        case SA_HEAT_BATH: return pick_chunk<kDense, SA_HEAT_BATH, kMaxE, Acc>(max_width);
-        case SA_HEAT_BATH_CLOSED: return pick_chunk<kDense, SA_HEAT_BATH_CLOSED, kMaxE, Acc>(max_width);
+        case SA_HEAT_BATH:
+        case SA_HEAT_BATH_CLOSED: return pick_chunk<kDense, SA_HEAT_BATH, kMaxE, Acc>(max_width);
         default:
             return max_width > otm_enum_max ? settled_kernel<kDense, SA_OPT_METROPOLIS, 1, kMaxE < 4 ? kMaxE : 4, Acc>
                                             : settled_kernel<kDense, SA_OPT_METROPOLIS, 0, kMaxE < 4 ? kMaxE : 4, Acc>;
@@ -42,8 +42,9 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
     // the dense form changes every cached sum with each move: no gain beyond the sizes that keep the
     // cache in the ordinary kernel too
     if (p.dense && n > 1024) return sc;
-    const bool sparse_cache = !p.dense && coef32 && p.any_cached;
-    const int64_t c = p.dense ? 8 * n : sparse_cache ? state : 0, c2 = sparse_cache && p.any_square ? state : 0;
+    const bool sparse_cache = !p.dense && p.any_cached;
+    const int64_t words = coef32 ? state : 8 * n;
+    const int64_t c = p.dense ? 8 * n : sparse_cache ? words : 0, c2 = sparse_cache && p.any_square ? words : 0;
     const int64_t bytes = state + c + c2 + 2 * ((n + 3) & ~(int64_t)3);
     // every replica at once, or in two goes
     if (bytes > max_lds || (max_lds / bytes) * cus * 2 < n_reads) return sc;
@@ -56,6 +57,7 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
 
 int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp, bool narrow,
                    void *stream, std::string &err) {
+    a.closed = rule == SA_HEAT_BATH_CLOSED ? 1 : 0;
     a.off_c = sc.off_c;
     a.off_c2 = sc.off_c2;
     a.off_m = sc.off_m;
@@ -123,6 +125,63 @@ int launch_rounds(int rule, QuadArgs q, AnnealArgs a, const SettledChoice &sc, i
     q.phase = kPhaseLast;
     q.z_init = q.z_out;
     return launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
+}
+
+int launch_settled_batch(const BatchInst *insts, const BatchTask *tasks, int32_t n_tasks, int lds_bytes, int maxe_class,
+                         void *stream, std::string &err) {
+    using Fn = void (*)(const BatchInst *, const BatchTask *);
+    Fn fn = maxe_class <= 2 ? (Fn)settled_batch_kernel<2>
+            : maxe_class <= 4 ? (Fn)settled_batch_kernel<4> : (Fn)settled_batch_kernel<kMaxExpPoly>;
+    if (lds_bytes > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (e != hipSuccess) {
+            err = std::string("hipFuncSetAttribute: ") + hipGetErrorString(e);
+            return SA_EDEVICE;
+        }
+    }
+    hipLaunchKernelGGL(fn, dim3((unsigned)n_tasks), dim3(kWave), (size_t)lds_bytes, (hipStream_t)stream, insts, tasks);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        err = std::string("kernel launch: ") + hipGetErrorString(e);
+        return SA_EDEVICE;
+    }
+    return SA_OK;
+}
+
+void settle_batch(const std::vector<BatchInst> &insts, const std::vector<int> &lds, const std::vector<double> &cost,
+                  std::vector<BatchTask> &tasks, SettledGroup (&groups)[kSettledGroups]) {
+    const int limit[kSettledGroups] = {160 * 1024, 40 * 1024, 10 * 1024};
+    std::vector<int32_t> order;
+    for (size_t i = 0; i < insts.size(); ++i)
+        if (lds[i] > 0) order.push_back((int32_t)i);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[(size_t)x] > cost[(size_t)y]; });
+    tasks.clear();
+    for (int g = 0; g < kSettledGroups; ++g) {
+        groups[g] = SettledGroup();
+        groups[g].first = (int32_t)tasks.size();
+        for (int32_t i : order) {
+            const int b = lds[(size_t)i];
+            if (b > limit[g] || (g + 1 < kSettledGroups && b <= limit[g + 1])) continue;
+            groups[g].lds_bytes = std::max(groups[g].lds_bytes, b);
+            for (int32_t r = 0; r < insts[(size_t)i].n_reads; ++r) tasks.push_back(BatchTask{i, r});
+        }
+        groups[g].n = (int32_t)tasks.size() - groups[g].first;
+    }
+}
+
+int settle_inst(const Packed &p, bool coef32, const SchedRec *order, int32_t n_order, int32_t n_sweeps, int device,
+                BatchInst &d) {
+    d.next = nullptr;
+    const SettledChoice sc = choose_settled(p, coef32, 1, n_order, n_sweeps, device);
+    if (sc.lds_bytes == 0) return 0;
+    d.order = order;
+    d.n_order = n_order;
+    d.off_c = sc.off_c;
+    d.off_c2 = sc.off_c2;
+    d.off_m = sc.off_m;
+    d.z30 = p.z30 ? 1 : 0;
+    d.leave = 0;   // set with the team size
+    return sc.lds_bytes;
 }
 
 }  // namespace sa

@@ -54,10 +54,11 @@ struct Request {
     std::array<uint64_t, 3> cache_key{};
     std::vector<double> beta;
     // device state of an admitted request
-    void *mem = nullptr;  // beta | states | energies
+    void *mem = nullptr;  // beta | states | energies | next sweeps
     double *beta_dev = nullptr;
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
+    int32_t *next_dev = nullptr;
     size_t footprint = 0;
     bool accounted = false;  // footprint counted in the server's memory in use
     int32_t next_sweep = 0;
@@ -297,6 +298,11 @@ void prep_loop(sa_server *S) {
                     break;
                 }
             }
+            sa_plan::Sched *all = nullptr;
+            if (rc == SA_OK && sa::get_order(r->plan, &all) != SA_OK) {
+                rc = SA_ENOMEM;
+                err = sa_last_error();
+            }
         }
         if (rc == SA_OK) {
             const size_t zb = sizeof(int32_t) * (size_t)r->n_reads * (size_t)r->plan->dp.n;
@@ -327,7 +333,8 @@ int admit_device(Request *r) {
     const size_t bb = align256(sizeof(double) * r->beta.size());
     const size_t zb = align256(sizeof(int32_t) * (size_t)r->n_reads * (size_t)r->plan->dp.n);
     const size_t eb = align256(sizeof(int64_t) * (size_t)r->n_reads);
-    hipError_t e = hipMalloc(&r->mem, bb + zb + eb);
+    // (the next sweeps, four bytes per read, are not counted in the footprint)
+    hipError_t e = hipMalloc(&r->mem, bb + zb + eb + align256(sizeof(int32_t) * (size_t)r->n_reads));
     if (e != hipSuccess) {
         r->mem = nullptr;
         return SA_ENOMEM;
@@ -335,6 +342,7 @@ int admit_device(Request *r) {
     r->beta_dev = (double *)r->mem;
     r->z_dev = (int32_t *)((char *)r->mem + bb);
     r->e_dev = (int64_t *)((char *)r->mem + bb + zb);
+    r->next_dev = (int32_t *)((char *)r->mem + bb + zb + eb);
     e = hipMemcpy(r->beta_dev, r->beta.data(), sizeof(double) * r->beta.size(), hipMemcpyHostToDevice);
     return e == hipSuccess ? SA_OK : SA_EDEVICE;
 }
@@ -378,7 +386,7 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     }
     const double share = total / ((double)S->cus * groups_per_cu * sa::kBatchWaves);
     std::vector<sa::BatchInst> insts(n);
-    std::vector<int> team(n);
+    std::vector<int> team(n), settled_lds(n);
     int64_t lds_elems = 0;
     for (int i = 0; i < n; ++i) {
         Request *r = act[i];
@@ -418,6 +426,9 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         d.instance_id = r->instance_id;
         d.z_out = r->z_dev;
         d.e_out = r->e_dev;
+        settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
+        if (settled_lds[i]) d.next = r->next_dev;
+        d.leave = std::max<int32_t>(1, 3 * d.n_order / sa::settled_share(G));
     }
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
@@ -428,7 +439,11 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         for (int32_t rd = 0; rd < act[i]->n_reads; rd += sa::kBatchWaves / team[i])
             tasks.push_back(sa::BatchTask{i, rd});
     const size_t o_task = align256(sizeof(sa::BatchInst) * n);
-    const size_t o_ctr = o_task + align256(sizeof(sa::BatchTask) * tasks.size());
+    sa::BatchLaunch bl;
+    std::vector<sa::BatchTask> settled;
+    sa::settle_batch(insts, settled_lds, cost, settled, bl.settled);
+    const size_t o_settled = o_task + align256(sizeof(sa::BatchTask) * tasks.size());
+    const size_t o_ctr = o_settled + align256(sizeof(sa::BatchTask) * settled.size());
     const size_t need = o_ctr + 256;
     if (need > S->chunk_cap) {
         if (S->chunk_mem.base) (void)hipFree(S->chunk_mem.base);
@@ -446,6 +461,9 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     std::vector<char> staging(o_ctr, 0);
     std::memcpy(staging.data(), insts.data(), sizeof(sa::BatchInst) * n);
     std::memcpy(staging.data() + o_task, tasks.data(), sizeof(sa::BatchTask) * tasks.size());
+    if (!settled.empty())
+        std::memcpy(staging.data() + o_settled, settled.data(), sizeof(sa::BatchTask) * settled.size());
+    bl.settled_tasks = (const sa::BatchTask *)(base + o_settled);
     hipError_t e = hipMemcpyAsync(base, staging.data(), o_ctr, hipMemcpyHostToDevice, S->stream);
     if (e != hipSuccess) {
         err = std::string("hipMemcpyAsync(chunk): ") + hipGetErrorString(e);
@@ -460,7 +478,6 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     a.parts_words = state_words;
     a.lds_words = state_words + 2 * sa::kBatchWaves;
     a.sweep_limit = 0;
-    sa::BatchLaunch bl;
     bl.maxe_class = maxe;
     bl.narrow = narrow && maxe <= 2;
     bl.z16 = z16;

@@ -28,8 +28,8 @@
 // sweeps became 1.4 times slower.
 //
 // A variable whose terms hold it to the first or second power with at most three other factors
-// (SchedRec::pad[1], "cached") keeps a_k^(1) modulo 2^32 in ca, and a_k^(2) in cb when some term holds
-// its square (the true values fit: DevProblem::coef32); a change of another variable adds the change of
+// (SchedRec::pad[1], "cached") keeps a_k^(1) in ca, and a_k^(2) in cb when some term holds a square,
+// modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a change of another variable adds the change of
 // each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
 // also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
 // the upper half of a float; 0 when it is not known, or not positive.  A change of a variable sharing a
@@ -46,6 +46,10 @@ namespace {
 // cm of a variable without a cached coefficient known to be linear with a_k^(1) = 0: every value has
 // the same energy.  And of a fixed variable: frozen at every temperature.
 constexpr uint16_t kFlat = 0x8000, kFixed = 0x7FFF;
+template <int k>
+struct Int {
+    static constexpr int value = k;
+};
 // e^(-beta M) = 0 in the device's exponential (exp_nonpos clamps there)
 constexpr double kSettledArg = 746.0;
 
@@ -53,8 +57,10 @@ constexpr double kSettledArg = 746.0;
 struct SettleView {
     ReplicaCtx R;
     const SchedRec *order;   // every variable in index order (k = -1 for a fixed one)
+    bool closed;         // heat bath: the closed-form draw where dE is linear
     bool small;          // cached coefficients fit 32 bits, and every value 30
-    uint32_t *ca, *cb;   // nullptr where no variable is cached / cached with its square
+    bool wide;           // ca and cb hold 64-bit words
+    void *ca, *cb;       // nullptr where no variable is cached / none has a square
     uint16_t *cm;        // whole groups of four
 };
 
@@ -66,7 +72,13 @@ __device__ __forceinline__ uint16_t margin_bits(int64_t M) {
 }
 __device__ __forceinline__ double margin_value(uint16_t b) { return (double)__uint_as_float((uint32_t)b << 16); }
 
+// a cached coefficient of variable i
+__device__ __forceinline__ int64_t cache_read(const SettleView &S, const void *c, int32_t i) {
+    return S.wide ? ((const int64_t *)c)[i] : (int64_t)((const int32_t *)c)[i];
+}
+
 // The coefficients of every cached variable from the state, and no margins known: one variable per lane.
+// (Products and sums modulo 2^64; the low words are those modulo 2^32.)
 template <typename ZT>
 __device__ __forceinline__ void settled_init(const SettleView &S, const ZT *z, int lane) {
     const DevProblem &P = S.R.P;
@@ -76,17 +88,45 @@ __device__ __forceinline__ void settled_init(const SettleView &S, const ZT *z, i
         if (i < P.n) sl = S.order[i];
         S.cm[i] = sl.k >= 0 ? 0 : kFixed;
         if (sl.k >= 0 && S.ca && sl.pad[1]) {
-            uint32_t a1 = 0, a2 = 0;
+            uint64_t a1 = 0, a2 = 0;
             for (int32_t q = 0; q < sl.deg; ++q) {
                 int e;
-                const uint32_t p =
-                    record_product<uint32_t, ZT>(P, z, P.inc[sl.row + q], (uint64_t)P.inc_coef[sl.row + q], e);
+                const uint64_t p =
+                    record_product<uint64_t, ZT>(P, z, P.inc[sl.row + q], (uint64_t)P.inc_coef[sl.row + q], e);
                 a1 += e == 1 ? p : 0u;
                 a2 += e == 2 ? p : 0u;
             }
-            S.ca[i] = a1;
-            if (S.cb) S.cb[i] = a2;
+            if (S.wide) ((uint64_t *)S.ca)[i] = a1;
+            else ((uint32_t *)S.ca)[i] = (uint32_t)a1;
+            if (S.cb) {
+                if (S.wide) ((uint64_t *)S.cb)[i] = a2;
+                else ((uint32_t *)S.cb)[i] = (uint32_t)a2;
+            }
         }
+    }
+}
+
+// One record's other factors i0, i1, i2 (sorted; -1 where there are fewer): z_k^e moved from zk^e to v^e.
+// A factor that occurs once moves its variable's a^(1), one that occurs twice its a^(2) (three times:
+// not a cached variable).
+template <typename Part, typename Word, typename ZT>
+__device__ __forceinline__ void scatter_record(Word *ca, Word *cb, const ZT *z, uint64_t coef, int e, int64_t zk, int64_t v,
+                                               int32_t i0, int32_t i1, int32_t i2) {
+    const Part g = (Part)coef * (upow<Part>((Part)v, e) - upow<Part>((Part)zk, e));
+    const Part z0 = (Part)(int64_t)z[i0];
+    const Part z1 = i1 >= 0 ? (Part)(int64_t)z[i1] : (Part)1;
+    const Part z2 = i2 >= 0 ? (Part)(int64_t)z[i2] : (Part)1;
+    if (i0 != i1) {
+        atomicAdd(&ca[i0], (Word)(g * z1 * z2));
+        if (i1 >= 0 && i1 != i2) {
+            atomicAdd(&ca[i1], (Word)(g * z0 * z2));
+            if (i2 >= 0) atomicAdd(&ca[i2], (Word)(g * z0 * z1));
+        } else if (i2 >= 0 && cb) {
+            atomicAdd(&cb[i1], (Word)(g * z0));
+        }
+    } else if (i1 != i2) {
+        if (cb) atomicAdd(&cb[i0], (Word)(g * z2));
+        if (i2 >= 0) atomicAdd(&ca[i2], (Word)(g * z0 * z1));
     }
 }
 
@@ -109,24 +149,8 @@ __device__ __forceinline__ void settled_scatter(const SettleView &S, const ZT *z
         } else if (no > 0) {
             const int32_t i0 = r.o[0], i1 = no > 1 ? r.o[1] : -1, i2 = no > 2 ? r.o[2] : -1;
             if (S.ca) {
-                const uint32_t g = (uint32_t)coef * (upow<uint32_t>((uint32_t)v, e) - upow<uint32_t>((uint32_t)zk, e));
-                const uint32_t z0 = (uint32_t)(int32_t)z[i0];
-                const uint32_t z1 = no > 1 ? (uint32_t)(int32_t)z[i1] : 1u;
-                const uint32_t z2 = no > 2 ? (uint32_t)(int32_t)z[i2] : 1u;
-                // the others are sorted, so equal ones are neighbours: a factor that occurs once moves
-                // its variable's a^(1), one that occurs twice its a^(2) (three times: no cached variable)
-                if (i0 != i1) {
-                    atomicAdd(&S.ca[i0], g * z1 * z2);
-                    if (no > 1 && i1 != i2) {
-                        atomicAdd(&S.ca[i1], g * z0 * z2);
-                        if (no > 2) atomicAdd(&S.ca[i2], g * z0 * z1);
-                    } else if (no > 2 && S.cb) {
-                        atomicAdd(&S.cb[i1], g * z0);
-                    }
-                } else if (i1 != i2) {
-                    if (S.cb) atomicAdd(&S.cb[i0], g * z2);
-                    if (no > 2) atomicAdd(&S.ca[i2], g * z0 * z1);
-                }
+                if (S.wide) scatter_record<uint64_t>((unsigned long long *)S.ca, (unsigned long long *)S.cb, z, coef, e, zk, v, i0, i1, i2);
+                else scatter_record<uint32_t>((uint32_t *)S.ca, (uint32_t *)S.cb, z, coef, e, zk, v, i0, i1, i2);
             }
             S.cm[i0] = 0;
             if (no > 1) S.cm[i1] = 0;
@@ -189,9 +213,9 @@ __device__ __forceinline__ bool settled_visit(const SettleView &S, const ZT *z, 
     row_coeffs<kE, Acc, ZT>(P, z, k, row, deg, em, lane, rec, rc, C);
     const bool linear = kE == 1 || (em & ~2u) == 0;
     bool taken = true;
-    if (kRule == SA_HEAT_BATH || kRule == SA_HEAT_BATH_CLOSED) {
+    if (kRule == SA_HEAT_BATH) {
         if constexpr (kE == kMaxE) {
-            if (kRule == SA_HEAT_BATH_CLOSED && linear)
+            if (S.closed && linear)
                 v = heat_bath_closed(to_i64<Acc>(C.a[1]), lo, W, beta, U, r1);
             else
                 v = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, lo, W, zk, beta, U, lane, linear, cy);
@@ -256,12 +280,12 @@ __device__ __forceinline__ int64_t lane_argmin_quadratic(int64_t a1, int64_t a2,
 // One block of 64 variables (slots sl, one per lane) of a settled sweep.  Returns the number of changes.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT>
 __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, int lane, int32_t b, const SchedRec &sl,
-                                                  int32_t s, double beta, double r_opt, ScanCarry &cy, uint64_t &H) {
+                                                  int32_t s, double beta, double r_opt, ScanCarry &cy, uint64_t &H,
+                                                  int64_t &E) {
     const ReplicaCtx &R = S.R;
     const DevProblem &P = R.P;
-    constexpr bool kEnumerated = kRule == SA_HEAT_BATH;
-    constexpr bool kClosed = kRule == SA_HEAT_BATH_CLOSED;
-    constexpr bool kHeatBath = kEnumerated || kClosed;
+    constexpr bool kHeatBath = kRule == SA_HEAT_BATH;
+    const bool closed = kHeatBath && S.closed;
     uint32_t moves = 0;
     const bool valid = sl.k >= 0;
     const int32_t kk = valid ? sl.k : 0;
@@ -304,15 +328,15 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
         }
         M = (double)m;
         // (the closed-form draw at the top of the range depends on U = 0: never frozen)
-        mbits = kClosed && linear && zk != lo ? 0 : margin_bits(m);
+        mbits = closed && linear && zk != lo ? 0 : margin_bits(m);
     };
     // decisions that read M find it each time; the others only now and then, for cm (below)
-    constexpr bool kUsesMargin = kEnumerated || kRule == SA_OPT_METROPOLIS;
+    constexpr bool kUsesMargin = kRule != SA_METROPOLIS;
     auto read_caches = [&] {
         if (has) {
-            a1 = kDense ? R.c1[kk] : (int64_t)(int32_t)S.ca[kk];
-            if (!kDense && !linear) a2 = (int64_t)(int32_t)S.cb[kk];
-            if (kUsesMargin || (kClosed && !all_linear)) find_margin();
+            a1 = kDense ? R.c1[kk] : cache_read(S, S.ca, kk);
+            if (!kDense && !linear) a2 = cache_read(S, S.cb, kk);
+            if (kUsesMargin) find_margin();
         } else {
             mbits = S.cm[kk];
             M = margin_value(mbits);   // (-0.0 for a flat one)
@@ -328,10 +352,11 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
     for (;;) {
         // want: 0 stays, 1 changes to v (energy change d), 2 needs a visit
         int want = 0;
-        int64_t v = zk;
+        int64_t v = zk, d = 0;
         if (kHeatBath) {
-            if (kClosed && cached && linear) {
+            if (closed && cached && linear) {
                 v = heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1);
+                d = a1 * (v - zk);
                 want = v != zk ? 1 : 0;
             } else {
                 want = 2;
@@ -352,7 +377,8 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
                 v = lo + (int64_t)(((uint64_t)x1 * (uint64_t)(W32 - 1u)) >> 32);
                 if (v >= zk) v += 1;
             }
-            want = v != zk && metropolis_accept(de(v), beta, U) ? 1 : 0;
+            d = de(v);
+            want = v != zk && metropolis_accept(d, beta, U) ? 1 : 0;
         } else {
             // a positive margin: z_k is the optimal value, and a proposal's rise is at least M
             want = M > 0.0 && U > exp_nonpos(-(beta * M)) * (1.0 + 1e-9) ? 0 : 2;
@@ -370,6 +396,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
             int64_t vj, dj;
             if (lane_read32((uint32_t)want, j) == 1u) {
                 vj = (int64_t)(int32_t)lane_read32((uint32_t)(int32_t)v, j);
+                dj = (int64_t)lane_read64((uint64_t)d, j);
                 changed = true;
             } else {
                 const int64_t loj = (int32_t)lane_read32((uint32_t)sl.lo, j);
@@ -386,17 +413,20 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
                     C.a[1] = (Acc)lane_read64((uint64_t)a1, j);
                     if (kMaxE >= 2) C.a[kMaxE >= 2 ? 2 : 1] = (Acc)lane_read64((uint64_t)a2, j);
                     vj = heat_bath_pick<kRegChunk, kMaxE, Acc>(C, loj, Wj, zj, beta, Uj, lane, (em & ~2u) == 0, cy);
+                    dj = poly_delta(C, zj, vj);
                 } else if constexpr (!kDense) {
                     taken = settled_visit<kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, kj, loj, Wj, em, row, deg, r0, r1, Uj, zj,
                                                                             beta, r_opt, lane, cy, vj, dj);
                 } else {
                     vj = zj;   // (not reached: the dense form's other rules decide in the lane)
+                    dj = 0;
                 }
                 changed = taken && vj != zj;
             }
             if (changed) {
                 moves += 1;
                 z[kj] = (ZT)vj;   // every lane stores the same value
+                E += dj;
                 if (R.trace) H += hash_word(kj, vj) - hash_word(kj, zj);
                 if (kDense) {
                     dense_cache_update(P, R.c1, kj, vj - zj, lane, nullptr);
@@ -412,8 +442,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
     }
     // the margins found; a variable that changed here (its z_k no longer the lane's) has none.  (Where no
     // decision reads them they are found every fourth sweep.)
-    constexpr bool kAlways = kUsesMargin || kClosed;
-    if (kAlways || (s & 3) == 0) {
+    if (kUsesMargin || (s & 3) == 0) {
         if (!kUsesMargin && has) find_margin();
         if (valid ? has : b + lane < P.n) S.cm[b + lane] = !valid ? kFixed : (int64_t)z[kk] == zk ? mbits : 0;
         state_write_fence<true>();
@@ -423,10 +452,10 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
 
 // One settled sweep of one replica (one wave).  kDense: the dense form with its coefficient cache
 // (c1; the changes keep it exact), else the incidence form.  Adds to H the changes of the state hash
-// (tracing); the energy is formed from the state at the end of the run.  Returns the number of changes.
+// (tracing) and to E those of the energy.  Returns the number of changes.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT>
 __device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, int lane, int32_t s, double beta, double r_opt,
-                                                  ScanCarry &cy, uint64_t &H) {
+                                                  ScanCarry &cy, uint64_t &H, int64_t &E) {
     const int32_t n = S.R.P.n;
     // the least margin bits with beta M >= 746: above 746 / beta rounded up
     const float t = (float)(kSettledArg / beta) * 1.000001f;
@@ -472,7 +501,7 @@ __device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, in
             SchedRec sn = sl;
             if (qn < 4) sn = load(base + kWave * qn);   // under this block's work
             const uint32_t c = settled_block<kDense, kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, lane, base + kWave * q, sl, s, beta,
-                                                                                       r_opt, cy, H);
+                                                                                       r_opt, cy, H, E);
             moves += c;
             if (c != 0) {
                 am = active();
@@ -487,9 +516,39 @@ __device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, in
     return moves;
 }
 
-// The settled part of a run: read blockIdx.x from the state in z_out and the sweep in e_out to the end of
-// the schedule, or to where it has come unsettled (more than A.leave changes in each of three sweeps
-// on end); leaves the state and the next sweep there.
+// The settled part of a run of one replica from sweep s: to s_end, or to where it has come unsettled
+// (more than `leave` changes in each of three sweeps on end).  `z`: its state in LDS, `off_*` the byte
+// offsets of the caches after it.  Returns the next sweep; adds to E the energy changes.
+template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc>
+__device__ __forceinline__ int32_t settled_run(SettleView &S, int32_t *z, int lane, int32_t s, int32_t s_end, int32_t off_c,
+                                               int32_t off_c2, int32_t off_m, uint32_t leave, int64_t &E) {
+    ReplicaCtx &R = S.R;
+    R.c1 = kDense ? (int64_t *)((char *)z + off_c) : nullptr;
+    S.wide = !R.P.coef32;
+    S.ca = !kDense && off_c >= 0 ? (void *)((char *)z + off_c) : nullptr;
+    S.cb = !kDense && off_c2 >= 0 ? (void *)((char *)z + off_c2) : nullptr;
+    S.cm = (uint16_t *)((char *)z + off_m);
+    state_write_fence<true>();
+    settled_init(S, z, lane);
+    if (kDense) dense_cache_init(R.P, z, R.c1, lane, kWave);
+    state_write_fence<true>();
+    ScanCarry cy;
+    int busy = 0;   // sweeps on end past `leave`
+    for (; s < s_end; ++s) {
+        uint64_t H = 0;
+        const double beta = R.beta[s];
+        const double r_opt =
+            R.otm_r >= 0.0 ? R.otm_r : (R.n_sweeps > 1 ? (double)s / (double)(R.n_sweeps - 1) : 0.0);
+        const uint32_t moves = settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H, E);
+        if (R.trace && H != 0 && lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
+        busy = moves > leave ? busy + 1 : 0;
+        if (busy == 3) return s + 1;
+    }
+    return s;
+}
+
+// Plain runs: read blockIdx.x from the state in z_out and the sweep in e_out; leaves the state and the
+// next sweep there.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc>
 __global__ void __launch_bounds__(kWave) settled_kernel(AnnealArgs A) {
     extern __shared__ int32_t lds_state[];
@@ -516,32 +575,72 @@ __global__ void __launch_bounds__(kWave) settled_kernel(AnnealArgs A) {
     R.trace = A.trace ? A.trace + (size_t)read * (size_t)(A.s_end - A.s_begin) - A.s_begin : nullptr;
     S.order = A.order;
     S.small = A.P.coef32 && A.z30;
-    R.c1 = kDense ? (int64_t *)((char *)lds_state + A.off_c) : nullptr;
-    S.ca = !kDense && A.off_c >= 0 ? (uint32_t *)((char *)lds_state + A.off_c) : nullptr;
-    S.cb = !kDense && A.off_c2 >= 0 ? (uint32_t *)((char *)lds_state + A.off_c2) : nullptr;
-    S.cm = (uint16_t *)((char *)lds_state + A.off_m);
-    state_write_fence<true>();
-    settled_init(S, z, lane);
-    if (kDense) dense_cache_init(A.P, z, R.c1, lane, kWave);
-    state_write_fence<true>();
-    ScanCarry cy;
-    int busy = 0;   // sweeps on end past A.leave
-    for (; s < A.s_end; ++s) {
-        uint64_t H = 0;
-        const double beta = A.beta[s];
-        const double r_opt =
-            A.otm_r >= 0.0 ? A.otm_r : (A.n_sweeps > 1 ? (double)s / (double)(A.n_sweeps - 1) : 0.0);
-        const uint32_t moves =
-            settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H);
-        if (R.trace && H != 0 && lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
-        busy = moves > (uint32_t)A.leave ? busy + 1 : 0;
-        if (busy == 3) {
-            ++s;
-            break;
-        }
-    }
+    S.closed = A.closed != 0;
+    int64_t E = 0;   // (the last launch sums the energy of every state)
+    s = settled_run<kDense, kRule, kRegChunk, kMaxE, Acc>(S, z, lane, s, A.s_end, A.off_c, A.off_c2, A.off_m,
+                                                          (uint32_t)A.leave, E);
     for (int32_t k = lane; k < n; k += kWave) zo[k] = z[k];
     if (lane == 0) A.e_out[read] = s;
+}
+
+// Batches and server chunks: task blockIdx.x, a read whose D.next says it has settled.  Leaves its
+// state, energy and next sweep (as ~s_end while it stays settled, for the next chunk).
+template <int kMaxE>
+__global__ void __launch_bounds__(kWave) settled_batch_kernel(const BatchInst *insts, const BatchTask *tasks) {
+    extern __shared__ int32_t lds_state[];
+    using Acc = uint64_t;
+    constexpr int kOtmE = kMaxE < 4 ? kMaxE : 4;
+    const int lane = (int)threadIdx.x;
+    const BatchTask task = tasks[blockIdx.x];
+    const BatchInst &D = insts[task.inst];
+    const int32_t read = task.read;
+    int32_t s = uni_load(&D.next[read]);
+    if (s >= 0 || ~s >= D.s_end) return;   // uniform: not settled, or done
+    s = ~s;
+    SettleView S;
+    ReplicaCtx &R = S.R;
+    R.P = D.P;
+    const int32_t n = R.P.n;
+    int32_t *z = lds_state;
+    int32_t *zo = D.z_out + (size_t)read * n;
+    for (int32_t k = lane; k < n; k += kWave) z[k] = zo[k];
+    R.beta = D.beta;
+    R.n_sweeps = D.n_sweeps;
+    R.key0 = D.key0;
+    R.key1 = D.key1;
+    R.instance_id = D.instance_id;
+    R.read = (uint32_t)read;
+    R.otm_r = -1.0;
+    R.otm_enum_max = kOtmEnumMax;
+    R.trace = nullptr;
+    S.order = D.order;
+    S.small = R.P.coef32 && D.z30;
+    S.closed = D.rule == SA_HEAT_BATH_CLOSED;
+    int64_t E = 0;
+    auto go = [&](auto dense, auto rule, auto chunk, auto maxe) {
+        s = settled_run<decltype(dense)::value, decltype(rule)::value, decltype(chunk)::value, decltype(maxe)::value, Acc>(
+            S, z, lane, s, D.s_end, D.off_c, D.off_c2, D.off_m, (uint32_t)D.leave, E);
+    };
+    auto by_rule = [&](auto dense, auto maxe, auto otm_e) {
+        if (D.rule == SA_METROPOLIS) {
+            go(dense, Int<SA_METROPOLIS>(), Int<0>(), Int<1>());
+        } else if (D.rule == SA_OPT_METROPOLIS) {
+            go(dense, Int<SA_OPT_METROPOLIS>(), Int<0>(), otm_e);
+        } else if (D.chunk == 1 || D.chunk == 2) {
+            go(dense, Int<SA_HEAT_BATH>(), Int<2>(), maxe);
+        } else if (D.chunk == 8) {
+            go(dense, Int<SA_HEAT_BATH>(), Int<8>(), maxe);
+        } else {
+            go(dense, Int<SA_HEAT_BATH>(), Int<0>(), maxe);
+        }
+    };
+    if (R.P.dense) by_rule(Int<1>(), Int<2>(), Int<2>());
+    else by_rule(Int<0>(), Int<kMaxE>(), Int<kOtmE>());
+    for (int32_t k = lane; k < n; k += kWave) zo[k] = z[k];
+    if (lane == 0) {
+        D.e_out[read] += E;
+        D.next[read] = s < D.s_end ? s : ~s;
+    }
 }
 
 }  // namespace
