@@ -176,6 +176,7 @@ int build_plan(const sa_instance *inst, const sa_bounds *bounds, int32_t rule, s
     sa::Packed pk;
     rc = sa::pack(canon, pk, err);
     if (rc != SA_OK) return fail(rc, err);
+    pk.energy_bound = bound;
     rc = check_rule_support(rule, pk.max_exp);
     if (rc != SA_OK) return rc;
     std::unique_ptr<sa_plan> plan(new sa_plan());
@@ -563,6 +564,34 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.waves_per_replica = qw;
         plan->last.lanes_per_update = 4;
         plan->last.n_levels = lv->n_levels;
+    } else if (const sa::TeamChoice team = G == 0 ? sa::choose_team(plan->rule, plan->packed, plan->dp.coef32 != 0, n_reads,
+                                                                    plan->device)
+                                                  : sa::TeamChoice();
+               team.waves > 0) {
+        sa_plan::Sched *all = nullptr;
+        rc = sa::get_order(plan, &all);
+        if (rc != SA_OK) {
+            if (tmp) (void)hipFree(tmp);
+            return rc;
+        }
+        a.order = all->dev;
+        a.n_order = all->n_active;
+        std::string err;
+        rc = sa::launch_dense_team(plan->rule, a, team, stream, err);
+        if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
+        if (rc != SA_OK) {
+            if (tmp) (void)hipFree(tmp);
+            return fail(rc, err);
+        }
+        plan->last = sa_launch_info{};
+        plan->last.waves_per_group = team.waves;
+        plan->last.groups = n_reads;
+        plan->last.lds_bytes = team.lds_bytes;
+        plan->last.state_in_lds = 1;
+        plan->last.kernel_variant = 3000000 + plan->rule * 100000;
+        plan->last.waves_per_replica = team.waves;
+        plan->last.n_windows = all->n_active;
+        plan->last.lanes_per_update = 64;
     } else {
         if (G == 0) G = auto_waves_per_replica(plan, n_reads, plan->device);
         sa::LaunchChoice lc = sa::choose_launch(plan->rule, n, n_reads, plan->info.max_width,

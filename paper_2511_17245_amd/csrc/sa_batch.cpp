@@ -45,11 +45,17 @@ struct sa_batch {
     char *base = nullptr;
     size_t o_inst = 0, o_task = 0, o_settled = 0;
     std::vector<int> settled_lds;      // LDS bytes of a settled replica of each problem (0: none)
+    std::vector<sa::TeamChoice> dense_team;   // problems of the dense team kernel (waves > 0)
+    hipStream_t side = nullptr;        // its stream, and the events that tie it to the batch's
+    hipEvent_t fork = nullptr, join = nullptr;
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
     ~sa_batch() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
+        if (fork) (void)hipEventDestroy(fork);
+        if (join) (void)hipEventDestroy(join);
+        if (side) (void)hipStreamDestroy(side);
         if (own_stream && stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -93,6 +99,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
     const double share = total / waves;
     int64_t lds_elems_max = 0;
     for (int32_t i = 0; i < n; ++i) {
+        if (b.dense_team[i].waves > 0) continue;
         sa_plan &p = *b.plans[i];
         int G = 1;
         if (policy > 0.0)
@@ -125,17 +132,19 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
                      [&](int32_t x, int32_t y) { return b.replica_cost[x] / b.team[x] > b.replica_cost[y] / b.team[y]; });
     std::vector<sa::BatchTask> tasks;
     for (int32_t i : order) {
+        if (b.dense_team[i].waves > 0) continue;
         const int per = sa::kBatchWaves / b.team[i];
         for (int32_t r = 0; r < b.n_reads[i]; r += per) tasks.push_back(sa::BatchTask{i, r});
     }
     b.n_tasks = (int64_t)tasks.size();
     std::vector<sa::BatchTask> settled;
     sa::settle_batch(b.insts, b.settled_lds, b.replica_cost, settled, b.launch.settled);
+    sa::group_teams(b.insts, b.dense_team, settled, b.launch.teams);
     b.launch.settled_tasks = (const sa::BatchTask *)(b.base + b.o_settled);
     hipError_t e = hipMemcpy(b.base + b.o_inst, b.insts.data(), sizeof(sa::BatchInst) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess && !settled.empty())
         e = hipMemcpy(b.base + b.o_settled, settled.data(), sizeof(sa::BatchTask) * settled.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
+    if (e == hipSuccess && !tasks.empty())
         e = hipMemcpy(b.base + b.o_task, tasks.data(), sizeof(sa::BatchTask) * tasks.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(batch tasks)");
     const int32_t state_words = (int32_t)((lds_elems_max * zsize + 7) / 8 * 2);
@@ -287,8 +296,10 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         sa_plan::Sched *all = nullptr;
         int rc = sa::get_order(&p, &all);
         if (rc != SA_OK) return rc;
+        b->dense_team.push_back(sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, all->dev, d.n_reads, b->device, d));
         b->settled_lds.push_back(
-            sa::settle_inst(p.packed, p.dp.coef32 != 0, all->dev, all->n_active, d.n_sweeps, b->device, d));
+            d.team_waves > 0 ? 0
+                             : sa::settle_inst(p.packed, p.dp.coef32 != 0, all->dev, all->n_active, d.n_sweeps, b->device, d));
         if (b->settled_lds.back()) d.next = (int32_t *)(b->base + o_next) + b->e_off[i];
     }
     b->args.insts = (const sa::BatchInst *)(b->base + b->o_inst);
@@ -302,6 +313,18 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         e = hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");
         b->own_stream = true;
+    }
+
+    bool teams = false;
+    for (const auto &tc : b->dense_team) teams = teams || tc.waves > 0;
+    if (teams) {
+        e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "hipStreamCreate(batch)");
+        b->launch.side_stream = b->side;
+        b->launch.fork = b->fork;
+        b->launch.join = b->join;
     }
 
     // choose the team-size policy and the number of persistent workgroups
@@ -424,12 +447,14 @@ int32_t sa_batch_get_info(const sa_batch *b, sa_batch_info *info) {
     if (!b || !info) return fail(SA_EINVAL, "batch and info are required");
     info->n_problems = (int32_t)b->plans.size();
     info->n_tasks = b->n_tasks;
+    for (const auto &g : b->launch.teams) info->n_tasks += g.n;
     info->total_updates = b->total_updates;
     info->waves_per_group = b->launch.waves_per_group;
     info->groups = b->launch.groups;
     info->slot_bytes = b->args.lds_words * 4;
     int32_t tmax = 1;
     for (int32_t t : b->team) tmax = std::max(tmax, t);
+    for (const auto &tc : b->dense_team) tmax = std::max(tmax, tc.waves);
     info->max_team = tmax;
     info->policy = b->policy;
     info->kernel_maxe = b->launch.maxe_class;

@@ -102,6 +102,7 @@ struct Packed {
     std::vector<uint8_t> cached;
     bool any_cached = false, any_square = false;   // of one that is not fixed / and has a square
     bool z30 = false;               // every bound below 2^30 in magnitude
+    double energy_bound = 0.0;      // sum_t |J_t| prod zmax^e (check_int64_bound; set by the caller of pack)
 };
 int pack(const Canonical &c, Packed &out, std::string &err);
 int maxe_class_of(int32_t max_exp);
@@ -225,8 +226,10 @@ struct AnnealArgs {
     // the settled kernel (order also where phase is kPhaseFirst)
     const SchedRec *order;   // every variable in index order (build_order)
     int32_t n_order;         // those that are not fixed
-    int32_t off_c, off_c2, off_m;   // LDS byte offsets of the caches (dense: c1, else ca; cb; margins); -1: none
+    int32_t off_c, off_c2, off_m;   // LDS byte offsets of the caches (dense: c1, else ca; cb; margins; the
+                                    // dense team's: c1, -, the state); -1: none
     int32_t closed;          // heat bath: closed-form draws
+    int32_t exact53;         // energy differences are below 2^52 in magnitude
     int32_t z30;             // every bound of the problem is below 2^30 in magnitude
     int32_t leave;           // changes per sweep past which a replica leaves
 };
@@ -329,6 +332,23 @@ int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const Settled
 int launch_rounds(int rule, QuadArgs q, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp,
                   bool narrow, void *stream, std::string &err);
 
+// The dense team kernel (sa_dense_team.h) for a run, or none (waves = 0): several waves per replica where
+// the row or the range gives each thread two columns or values, with all waves resident at once.  The
+// fewest waves (4, 8 or 16) that hold four values and eight columns per thread: every wave repeats a
+// draw's scalar part, about a quarter of its instructions, so more of them are slower.
+constexpr int kTeamExchangeBytes = 272;
+struct TeamChoice {
+    int waves = 0;
+    bool small = false;    // c1 as int32
+    bool exact53 = false;  // energy differences below 2^52
+    int off_c = 0, off_z = 0;
+    int lds_bytes = 0;
+};
+struct BatchInst;
+struct BatchTask;
+TeamChoice choose_team(int rule, const Packed &p, bool coef32, int32_t n_reads, int device);
+int launch_dense_team(int rule, AnnealArgs a, const TeamChoice &tc, void *stream, std::string &err);
+
 // Byte layout of a packed instance in one device area, each part 256-byte aligned (the records
 // and their coefficients are followed by one zero record).
 struct PackedLayout {
@@ -374,6 +394,8 @@ struct BatchInst {
     int32_t *next;           // n_reads: the next sweep s, or ~s of a settled replica (device)
     const SchedRec *order;
     int32_t n_order, off_c, off_c2, off_m, z30, leave;
+    int32_t team_waves;      // > 0: run by the dense team kernel (off_c: c1, off_m: the state; exact53 as AnnealArgs)
+    int32_t exact53;
 };
 struct BatchTask {
     int32_t inst;
@@ -397,6 +419,12 @@ struct SettledGroup {
     int lds_bytes = 0;
 };
 constexpr int kSettledGroups = 3;
+// One launch of the dense team kernel over tasks of the same list: problems of one rule and team size.
+struct TeamGroup {
+    int32_t first = 0, n = 0;
+    int rule = 0, waves = 0, lds_bytes = 0;
+    bool small = false;
+};
 // The groups and their task list, for problems whose replicas take lds[i] bytes (0: not settled) and cost[i].
 void settle_batch(const std::vector<BatchInst> &insts, const std::vector<int> &lds, const std::vector<double> &cost,
                   std::vector<BatchTask> &tasks, SettledGroup (&groups)[kSettledGroups]);
@@ -405,9 +433,20 @@ int launch_settled_batch(const BatchInst *insts, const BatchTask *tasks, int32_t
 // Fills a problem's settled fields (next is the caller's) for teams of `team` waves; returns its LDS bytes, or 0.
 int settle_inst(const Packed &p, bool coef32, const SchedRec *order, int32_t n_order, int32_t n_sweeps, int device,
                 BatchInst &d);
+// Gives a dense problem of a batch to the team kernel if choose_team does; returns the choice.
+TeamChoice team_inst(int rule, const Packed &p, bool coef32, const SchedRec *order, int32_t n_reads, int device, BatchInst &d);
+// Appends the tasks of the problems run by the team kernel (choices[i].waves > 0) and returns their groups.
+void group_teams(const std::vector<BatchInst> &insts, const std::vector<TeamChoice> &choices, std::vector<BatchTask> &tasks,
+                 std::vector<TeamGroup> &groups);
+int launch_team_group(const BatchInst *insts, const BatchTask *tasks, const TeamGroup &g, void *stream, std::string &err);
 struct BatchLaunch {
     SettledGroup settled[kSettledGroups];
-    const BatchTask *settled_tasks = nullptr;   // device
+    std::vector<TeamGroup> teams;
+    const BatchTask *settled_tasks = nullptr;   // device: the groups' tasks
+    // the dense team kernels run beside the persistent kernel: a stream of their own, and the events that
+    // fork it from the batch's stream and join it again (nullptr: they run first on the batch's stream)
+    void *side_stream = nullptr, *fork = nullptr, *join = nullptr;
+    // problems run by the dense team kernel get no task of the persistent kernel
     int waves_per_group = kBatchWaves;
     int groups = 1;
     int maxe_class = 1;

@@ -33,6 +33,34 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
             return SA_EDEVICE;
         }
     }
+    // dense teams first, beside the persistent kernel where a side stream is given
+    const bool teams = !bl.teams.empty() && b.sweep_limit == 0;
+    if (teams) {
+        void *s = bl.side_stream ? bl.side_stream : stream;
+        hipError_t e = hipSuccess;
+        if (bl.side_stream) {
+            e = hipEventRecord((hipEvent_t)bl.fork, (hipStream_t)stream);
+            if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)s, (hipEvent_t)bl.fork, 0);
+        }
+        for (const TeamGroup &g : bl.teams) {
+            if (e != hipSuccess) break;
+            int rc = launch_team_group(b.insts, bl.settled_tasks, g, s, err);
+            if (rc != SA_OK) return rc;
+        }
+        if (bl.side_stream && e == hipSuccess) e = hipEventRecord((hipEvent_t)bl.join, (hipStream_t)s);
+        if (e != hipSuccess) {
+            err = std::string("batch launch: ") + hipGetErrorString(e);
+            return SA_EDEVICE;
+        }
+    }
+    auto join = [&]() -> int {
+        if (!teams || !bl.side_stream) return SA_OK;
+        hipError_t e = hipStreamWaitEvent((hipStream_t)stream, (hipEvent_t)bl.join, 0);
+        if (e == hipSuccess) return SA_OK;
+        err = std::string("batch launch: ") + hipGetErrorString(e);
+        return SA_EDEVICE;
+    };
+    if (b.n_tasks == 0) return join();
     int32_t n_settled = 0;
     for (const SettledGroup &g : bl.settled) n_settled += g.n;
     BatchArgs a = b;
@@ -58,7 +86,7 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
         err = std::string("batch launch: ") + hipGetErrorString(e);
         return SA_EDEVICE;
     }
-    return SA_OK;
+    return join();
 }
 
 }  // namespace sa

@@ -71,6 +71,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     sa::Packed pk;
     rc = sa::pack(canon, pk, err);
     if (rc != SA_OK) return sa::fail(rc, err);
+    pk.energy_bound = bound;
     rc = sa::check_rule_support(rule, pk.max_exp);
     if (rc != SA_OK) return rc;
     std::vector<double> beta((size_t)S);
@@ -135,12 +136,16 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
                                                   sa::dE_fits_32(canon), enum_max, pk.dense);
     std::vector<sa::SchedRec> sch;
     const int32_t n_win = lanes == 64 ? sa::build_schedule(pk, lc.win_waves, sch) : 0;
-    // the settled kernel's list of the variables
+    // the list of the variables for the settled kernel, or for the dense team's
+    const sa::TeamChoice team = lanes == 64 && opts.waves_per_replica == 0
+                                    ? sa::choose_team(rule, pk, sa::coefs_fit_32(canon), n_reads, device)
+                                    : sa::TeamChoice();
+    bool by_team = team.waves > 0;
     sa::SettledChoice set;
     std::vector<sa::SchedRec> order;
     if (lanes == 64 || mo) {
         set = sa::choose_settled(pk, sa::coefs_fit_32(canon), n_reads, active, s1 - s0, device);
-        if (set.lds_bytes) (void)sa::build_order(pk, order);
+        if (set.lds_bytes || by_team) (void)sa::build_order(pk, order);
     }
 
     // one image: packed instance | inverse temperatures | schedule (windows, or level offsets then
@@ -158,6 +163,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     if (!order.empty() && total > kScratchBytes) {
         // no room for the list: every sweep in the ordinary kernel (the same results)
         set = sa::SettledChoice();
+        by_team = false;
         order.clear();
         total = off_order;
     }
@@ -240,6 +246,8 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
         q.trace = a.trace;
         rc = mo ? sa::launch_rounds(rule, q, a, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err)
                 : sa::launch_quad(rule, q, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
+    } else if (by_team) {
+        rc = sa::launch_dense_team(rule, a, team, stream, err);
     } else {
         rc = sa::launch_windows(rule, a, lc, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
     }

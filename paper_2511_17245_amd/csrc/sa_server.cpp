@@ -69,7 +69,10 @@ struct Request {
     double t_submit = 0, t_admit = 0, t_done = 0;
 };
 
-double cost_of_update(const sa_plan &p) {
+double cost_of_update(const sa_plan &p, bool team = false) {
+    // a dense team's update (about 1.2 us while hot, N = 2048, W = 2001) against the others' scale, where
+    // a hot update of the N = 2000 HUIO requests (2.6) takes about 70 ns
+    if (team) return 40.0;
     const double chunks = 1.0 + (double)p.info.n_incidences / std::max(1, p.info.n_vars) / 64.0;
     const double per_lane = std::ceil(p.info.max_width / 64.0);
     if (p.rule == SA_HEAT_BATH_CLOSED && p.info.max_exponent <= 1) return chunks + 2.0;
@@ -83,7 +86,8 @@ double cost_of_update(const sa_plan &p) {
 struct sa_server {
     sa_server_opts opts{};
     int device = 0, cus = 256, max_lds = 65536;
-    hipStream_t stream = nullptr;
+    hipStream_t stream = nullptr, side = nullptr;   // side: dense teams, tied to stream by the events
+    hipEvent_t fork = nullptr, join = nullptr;
     std::chrono::steady_clock::time_point t0;
     std::mutex mu;
     std::condition_variable cv_prep, cv_sched, cv_done;
@@ -365,7 +369,11 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     // sweeps per request in this chunk: a chunk lasts as long as its slowest replica, so every
     // request gets about the same time (C sweeps of the median request), not the same sweeps
     std::vector<double> per_sweep(n);
-    for (int i = 0; i < n; ++i) per_sweep[i] = act[i]->plan->dp.n * cost_of_update(*act[i]->plan);
+    for (int i = 0; i < n; ++i) {
+        const sa_plan &p = *act[i]->plan;
+        const bool team = sa::choose_team(p.rule, p.packed, p.dp.coef32 != 0, act[i]->n_reads, S->device).waves > 0;
+        per_sweep[i] = p.dp.n * cost_of_update(p, team);
+    }
     std::vector<double> sorted(per_sweep);
     std::nth_element(sorted.begin(), sorted.begin() + n / 2, sorted.end());
     // capped, so that a chunk of heavy requests alone stays short: requests are admitted only
@@ -387,6 +395,7 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     const double share = total / ((double)S->cus * groups_per_cu * sa::kBatchWaves);
     std::vector<sa::BatchInst> insts(n);
     std::vector<int> team(n), settled_lds(n);
+    std::vector<sa::TeamChoice> choices(n);
     int64_t lds_elems = 0;
     for (int i = 0; i < n; ++i) {
         Request *r = act[i];
@@ -405,8 +414,9 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
             return SA_EUNSUPPORTED;
         }
         team[i] = G;
-        lds_elems = std::max<int64_t>(lds_elems, (int64_t)(sa::kBatchWaves / G) * stride);
         sa::BatchInst &d = insts[i];
+        choices[i] = sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, p.order.dev, r->n_reads, S->device, d);
+        if (choices[i].waves == 0) lds_elems = std::max<int64_t>(lds_elems, (int64_t)(sa::kBatchWaves / G) * stride);
         d.P = p.dp;
         d.beta = r->beta_dev;
         d.sched = p.sched[G].dev;
@@ -426,7 +436,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         d.instance_id = r->instance_id;
         d.z_out = r->z_dev;
         d.e_out = r->e_dev;
-        settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
+        if (choices[i].waves == 0)
+            settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
         if (settled_lds[i]) d.next = r->next_dev;
         d.leave = std::max<int32_t>(1, 3 * d.n_order / sa::settled_share(G));
     }
@@ -435,13 +446,19 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     std::stable_sort(order.begin(), order.end(),
                      [&](int x, int y) { return cost[x] / team[x] > cost[y] / team[y]; });
     std::vector<sa::BatchTask> tasks;
-    for (int i : order)
+    for (int i : order) {
+        if (choices[i].waves > 0) continue;   // the dense team kernel's
         for (int32_t rd = 0; rd < act[i]->n_reads; rd += sa::kBatchWaves / team[i])
             tasks.push_back(sa::BatchTask{i, rd});
+    }
     const size_t o_task = align256(sizeof(sa::BatchInst) * n);
     sa::BatchLaunch bl;
     std::vector<sa::BatchTask> settled;
     sa::settle_batch(insts, settled_lds, cost, settled, bl.settled);
+    sa::group_teams(insts, choices, settled, bl.teams);
+    bl.side_stream = S->side;
+    bl.fork = S->fork;
+    bl.join = S->join;
     const size_t o_settled = o_task + align256(sizeof(sa::BatchTask) * tasks.size());
     const size_t o_ctr = o_settled + align256(sizeof(sa::BatchTask) * settled.size());
     const size_t need = o_ctr + 256;
@@ -631,6 +648,9 @@ int32_t sa_server_create(const sa_server_opts *opts, sa_server **out) {
     (void)hipDeviceGetAttribute(&S->cus, hipDeviceAttributeMultiprocessorCount, S->device);
     (void)hipDeviceGetAttribute(&S->max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, S->device);
     e = hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&S->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&S->join, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");
     S->t0 = std::chrono::steady_clock::now();
     sa_server *raw = S.get();
@@ -785,6 +805,9 @@ void sa_server_destroy(sa_server *S) {
     }
     for (auto &kv : S->plan_cache) delete kv.second.plan;
     S->plan_cache.clear();
+    if (S->fork) (void)hipEventDestroy(S->fork);
+    if (S->join) (void)hipEventDestroy(S->join);
+    if (S->side) (void)hipStreamDestroy(S->side);
     if (S->stream) (void)hipStreamDestroy(S->stream);
     delete S;
 }
