@@ -193,8 +193,8 @@ typedef struct {
     int32_t kernel_variant;     /* internal id of the instantiated kernel */
     int32_t waves_per_replica;  /* G: wavefronts cooperating on one replica */
     int32_t n_windows;          /* windows per sweep in the schedule (N for G = 1 without fixed vars) */
-    int32_t lanes_per_update;   /* 64, or 4 for the quad kernel */
-    int32_t n_levels;           /* quad kernel: dependency levels per sweep (0 otherwise) */
+    int32_t lanes_per_update;   /* 64, 4 for the quad kernel, 1 for the lane kernel */
+    int32_t n_levels;           /* quad and lane kernels: dependency levels per sweep (0 otherwise) */
 } sa_launch_info;
 int32_t sa_plan_last_launch(const sa_plan *plan, sa_launch_info *info);
 

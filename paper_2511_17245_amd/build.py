@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsa.so")
 # the annealing kernels are compiled per rule so that the files build in parallel
 SOURCES = ["sa_kernels_heat_bath.hip", "sa_kernels_quad.hip", "sa_kernels_quad_mo.hip", "sa_kernels_batch.hip", "sa_kernels_batch16.hip", "sa_kernels_heat_bath_closed.hip",
-           "sa_kernels_otm.hip", "sa_kernels_metropolis.hip", "sa_kernels_settled.hip", "sa_kernels_dense_team.hip", "sa_kernels.hip", "sa_noalloc.hip", "sa_api.cpp",
+           "sa_kernels_otm.hip", "sa_kernels_metropolis.hip", "sa_kernels_settled.hip", "sa_kernels_dense_team.hip", "sa_kernels_lane.hip", "sa_kernels.hip", "sa_noalloc.hip", "sa_api.cpp",
            "sa_host.cpp", "sa_batch.cpp", "sa_server.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -290,6 +290,72 @@ int get_order(sa_plan *plan, sa_plan::Sched **out) {
     return SA_OK;
 }
 
+LaneLayout lane_layout(const LaneImage &im) {
+    LaneLayout L;
+    L.slots = align256(std::max<size_t>(im.chunks.size(), 1) * sizeof(LaneRows));
+    L.recs = L.slots + align256(std::max<size_t>(im.slots.size(), 1) * sizeof(LaneSlot));
+    L.total = L.recs + align256(std::max<size_t>(im.recs.size(), 1));
+    return L;
+}
+
+void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image) {
+    auto put = [&](size_t at, const void *from, size_t bytes) {
+        if (bytes) std::memcpy(image + at, from, bytes);
+    };
+    put(0, im.chunks.data(), im.chunks.size() * sizeof(LaneRows));
+    put(L.slots, im.slots.data(), im.slots.size() * sizeof(LaneSlot));
+    put(L.recs, im.recs.data(), im.recs.size());
+}
+
+int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out) {
+    std::lock_guard<std::mutex> lk(plan->sched_mu);
+    sa_plan::Lanes &ln = plan->lanes;
+    if (!ln.dev) {
+        build_lanes(plan->packed, compact, ln.im);
+        const LaneLayout L = lane_layout(ln.im);
+        std::vector<char> img(L.total, 0);
+        stage_lanes(ln.im, L, img.data());
+        void *dev = nullptr;
+        hipError_t e = hipMalloc(&dev, L.total);
+        if (e != hipSuccess) return fail(SA_ENOMEM, std::string("hipMalloc(lanes): ") + hipGetErrorString(e));
+        e = hipMemcpy(dev, img.data(), L.total, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(dev);
+            return hip_fail(e, "hipMemcpy(lanes)");
+        }
+        ln.dev = dev;
+        ln.chunks = (const LaneRows *)dev;
+        ln.slots = (const LaneSlot *)((char *)dev + L.slots);
+        ln.recs = (const void *)((char *)dev + L.recs);
+        ln.im.chunks = std::vector<LaneRows>();
+        ln.im.slots = std::vector<LaneSlot>();
+        ln.im.recs = std::vector<uint8_t>();
+    }
+    *out = &ln;
+    return SA_OK;
+}
+
+int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out) {
+    std::lock_guard<std::mutex> lk(plan->sched_mu);
+    sa_plan::Lanes::Rounds &r = plan->lanes.rounds[waves == 8 ? 3 : waves == 4 ? 2 : waves == 2 ? 1 : 0];
+    if (!r.dev) {
+        std::vector<LaneRows> host;
+        build_lane_rounds(plan->lanes.im, waves, host);
+        void *dev = nullptr;
+        hipError_t e = hipMalloc(&dev, std::max<size_t>(host.size(), 1) * sizeof(LaneRows));
+        if (e != hipSuccess) return fail(SA_ENOMEM, std::string("hipMalloc(lane rounds): ") + hipGetErrorString(e));
+        if (!host.empty()) e = hipMemcpy(dev, host.data(), host.size() * sizeof(LaneRows), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(dev);
+            return hip_fail(e, "hipMemcpy(lane rounds)");
+        }
+        r.dev = (LaneRows *)dev;
+        r.n = (int32_t)host.size();
+    }
+    *out = &r;
+    return SA_OK;
+}
+
 int get_levels(sa_plan *plan, sa_plan::Levels **out) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Levels &lv = plan->levels;
@@ -488,6 +554,65 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         if (tmp) (void)hipFree(tmp);
         return fail(SA_EINVAL, "waves_per_replica must be 0, 1, 2, 4, 8 or 16");
     }
+    // the automatic choice for the heat bath of pair problems: one update per lane, for runs that repay
+    // building and uploading its image (a few sweeps' time in the quad kernel)
+    int lane_wv = 0;
+    bool compact = false;
+    if (opts.lanes_per_update == 0 && G == 0 && s1 - s0 >= 16 &&
+        sa::lane_eligible(plan->rule, plan->packed, plan->dp.coef32 != 0, plan->device, compact)) {
+        sa_plan::Lanes *ln = nullptr;
+        rc = sa::get_lanes(plan, compact, &ln);
+        if (rc != SA_OK) {
+            if (tmp) (void)hipFree(tmp);
+            return rc;
+        }
+        lane_wv = sa::lane_waves(ln->im, n, n_reads, plan->device);
+        if (lane_wv > 0) {
+            sa_plan::Lanes::Rounds *rounds = nullptr;
+            rc = sa::get_lane_rounds(plan, lane_wv, &rounds);
+            if (rc != SA_OK) {
+                if (tmp) (void)hipFree(tmp);
+                return rc;
+            }
+            sa::LaneArgs q{};
+            q.P = plan->dp;
+            q.beta = plan->beta_dev;
+            q.n_sweeps = S;
+            q.s_begin = s0;
+            q.s_end = s1;
+            q.n_reads = n_reads;
+            q.key0 = a.key0;
+            q.key1 = a.key1;
+            q.instance_id = a.instance_id;
+            q.closed = plan->rule == SA_HEAT_BATH_CLOSED ? 1 : 0;
+            q.n_rounds = rounds->n;
+            q.rounds = rounds->dev;
+            q.chunks = ln->chunks;
+            q.slots = ln->slots;
+            q.recs = ln->recs;
+            q.z_init = zi_dev;
+            q.z_out = z_dev;
+            q.e_out = e_dev;
+            q.trace = t_dev;
+            std::string err;
+            rc = sa::launch_lane(q, compact, lane_wv, stream, err);
+            if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
+            if (rc != SA_OK) {
+                if (tmp) (void)hipFree(tmp);
+                return fail(rc, err);
+            }
+            plan->last = sa_launch_info{};
+            plan->last.waves_per_group = lane_wv;
+            plan->last.groups = n_reads;
+            plan->last.lds_bytes = (int32_t)sa::lane_lds_bytes(n, lane_wv, q.n_rounds);
+            plan->last.state_in_lds = 1;
+            plan->last.kernel_variant = 4000000 + plan->rule * 100000;
+            plan->last.waves_per_replica = lane_wv;
+            plan->last.lanes_per_update = 1;
+            plan->last.n_levels = ln->im.n_levels;
+        }
+    }
+    if (lane_wv == 0) {
     const bool eligible = sa::quad_eligible(plan->rule, plan->packed, plan->device);
     sa_plan::Levels *lv = nullptr;
     if (eligible && G == 0 && opts.lanes_per_update != 64) {
@@ -637,6 +762,7 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.n_windows = sc->n_win;
         plan->last.lanes_per_update = 64;
         plan->last.n_levels = 0;
+    }
     }
     if (!opts.device_buffers) {
         e = hipMemcpyAsync(out_states, z_dev, zbytes, hipMemcpyDeviceToHost, stream);

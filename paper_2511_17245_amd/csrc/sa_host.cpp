@@ -343,8 +343,11 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
     p.n_terms = (int32_t)nt;
     p.var.resize(n);
     p.emask.assign(n, 0u);
-    p.z30 = true;
-    for (int32_t k = 0; k < n; ++k) p.z30 = p.z30 && c.lo[k] > -(1 << 30) && c.hi[k] < (1 << 30);
+    p.z30 = p.z23 = true;
+    for (int32_t k = 0; k < n; ++k) {
+        p.z30 = p.z30 && c.lo[k] > -(1 << 30) && c.hi[k] < (1 << 30);
+        p.z23 = p.z23 && c.lo[k] > -(1 << 23) && c.hi[k] < (1 << 23);
+    }
     if (pack_dense(c, p)) {
         for (int32_t k = 0; k < n; ++k) {
             const int64_t w = (int64_t)c.hi[k] - c.lo[k] + 1;
@@ -688,6 +691,61 @@ int32_t build_rounds(const Packed &p, std::vector<SchedRec> &rounds, int32_t &n_
     while (rounds.size() % (size_t)(kRoundQuads * kRoundBatch)) rounds.push_back(idle);
     n_real = (int32_t)slots.size();
     return n_levels;
+}
+
+void build_lanes(const Packed &p, bool compact, LaneImage &im) {
+    im = LaneImage();
+    im.compact = compact;
+    std::vector<int32_t> start;
+    std::vector<SchedRec> slots;
+    im.n_levels = build_levels(p, 64, start, slots);
+    im.n_slots = (int32_t)slots.size();
+    const size_t rec_bytes = compact ? 4 : 8;
+    int32_t rows = 0;
+    for (int32_t l = 0; l < im.n_levels; ++l) {
+        im.level_chunk.push_back((int32_t)im.chunks.size());
+        // by falling degree, so that a chunk's rows hold few empty records
+        std::stable_sort(slots.begin() + start[(size_t)l], slots.begin() + start[(size_t)l + 1],
+                         [](const SchedRec &x, const SchedRec &y) { return x.deg > y.deg; });
+        for (int32_t b = start[(size_t)l]; b < start[(size_t)l + 1]; b += 64) {
+            const int32_t m = std::min<int32_t>(64, start[(size_t)l + 1] - b);
+            const int32_t r = (std::max<int32_t>(slots[(size_t)b].deg, 1) + 3) / 4 * 4;
+            im.chunks.push_back(LaneRows{rows, r});
+            im.recs.resize((size_t)(rows + r) * 64 * rec_bytes, 0);   // (an empty record: variable 0, coupling 0)
+            for (int32_t q = 0; q < 64; ++q) {
+                if (q >= m) {
+                    im.slots.push_back(LaneSlot{-1, 0, 1, 0});
+                    continue;
+                }
+                const SchedRec &s = slots[(size_t)(b + q)];
+                im.slots.push_back(LaneSlot{s.k, s.lo, s.width, s.pad[0]});
+                for (int32_t i = 0; i < s.deg; ++i) {
+                    const PairRec &pr = p.pair[(size_t)s.row + (size_t)i];
+                    uint8_t *to = im.recs.data() + ((size_t)(rows + i) * 64 + (size_t)q) * rec_bytes;
+                    if (compact) {
+                        const uint32_t w = ((uint32_t)pr.J << 16) | ((uint32_t)pr.j & 0xFFFFu);
+                        std::memcpy(to, &w, 4);
+                    } else {
+                        std::memcpy(to, &pr, 8);
+                    }
+                }
+            }
+            rows += r;
+        }
+        im.max_chunks = std::max(im.max_chunks, (int32_t)im.chunks.size() - im.level_chunk.back());
+    }
+    im.level_chunk.push_back((int32_t)im.chunks.size());
+    // the kernel reads kLaneReach rows from a chunk's first on, also of the last
+    im.recs.resize((size_t)(rows + kLaneReach) * 64 * rec_bytes, 0);
+}
+
+void build_lane_rounds(const LaneImage &im, int waves, std::vector<LaneRows> &rounds) {
+    rounds.clear();
+    for (int32_t l = 0; l < im.n_levels; ++l) {
+        const int32_t end = im.level_chunk[(size_t)l + 1];
+        for (int32_t c = im.level_chunk[(size_t)l]; c < end; c += waves)
+            rounds.push_back(LaneRows{c, c + waves >= end ? ~end : end});
+    }
 }
 
 }  // namespace sa

@@ -101,7 +101,7 @@ struct Packed {
     // holds it to the first or second power with at most three other factors)
     std::vector<uint8_t> cached;
     bool any_cached = false, any_square = false;   // of one that is not fixed / and has a square
-    bool z30 = false;               // every bound below 2^30 in magnitude
+    bool z30 = false, z23 = false;  // every bound below 2^30, 2^23 in magnitude
     double energy_bound = 0.0;      // sum_t |J_t| prod zmax^e (check_int64_bound; set by the caller of pack)
 };
 int pack(const Canonical &c, Packed &out, std::string &err);
@@ -301,6 +301,57 @@ int launch_quad(int rule, const QuadArgs &a, int32_t max_width, int32_t max_exp,
 // (defined in sa_kernels_quad_mo.hip).
 int launch_quad_mo(int rule, const QuadArgs &a, int32_t max_width, int32_t max_exp, bool narrow, void *stream,
                    std::string &err);
+
+// One lane's slot of a chunk of the lane kernel (k = -1: idle; h: the linear coefficient), and where a
+// chunk's records are: its first row of 64, and its rows (whole fours).
+struct LaneSlot {
+    int32_t k, lo, width, h;
+};
+struct LaneRows {
+    int32_t first, rows;
+};
+
+// Kernel arguments of one launch of the lane kernel (sa_lane.h: heat bath of multilinear pair problems,
+// one update per lane over dependency levels).
+struct LaneArgs {
+    DevProblem P;
+    const double *beta;
+    int32_t n_sweeps, s_begin, s_end, n_reads;
+    uint32_t key0, key1, instance_id;
+    int32_t closed;              // closed-form draws of SA_HEAT_BATH_CLOSED
+    int32_t n_rounds;
+    int32_t off_places;          // LDS byte offset of the waves' places in every round
+    const LaneRows *rounds;      // per round: its first chunk and its level's end (~end in a level's last round)
+    const LaneRows *chunks;
+    const LaneSlot *slots;       // per chunk and lane
+    const void *recs;            // rows of 64 records: 16-bit index and coupling, or 32-bit ones
+    const int32_t *z_init;
+    int32_t *z_out;
+    int64_t *e_out;
+    uint64_t *trace;             // as AnnealArgs::trace
+};
+// The same on the host.
+struct LaneImage {
+    std::vector<int32_t> level_chunk;
+    std::vector<LaneRows> chunks;
+    std::vector<LaneSlot> slots;
+    std::vector<uint8_t> recs;
+    int32_t n_levels = 0, n_slots = 0, max_chunks = 0;   // most chunks of a level
+    bool compact = false;
+};
+constexpr int kLaneMaxWaves = 8;
+constexpr int32_t kLaneReach = 12;   // rows loaded ahead (sa_lane.h, kLaneAhead)
+// The rounds of a sweep for `waves` waves per replica (LaneArgs::rounds).
+void build_lane_rounds(const LaneImage &im, int waves, std::vector<LaneRows> &rounds);
+// Levels, chunks and records of a problem with compact pair records; compact: 16-bit records.
+void build_lanes(const Packed &p, bool compact, LaneImage &out);
+// Whether the lane kernel can run `rule` on this packed problem, and whether with 16-bit records.
+bool lane_eligible(int rule, const Packed &p, bool coef32, int device, bool &compact);
+// Waves per replica (0: the automatic choice goes to another kernel).
+int lane_waves(const LaneImage &im, int32_t n, int32_t n_reads, int device);
+// LDS bytes of one replica: state, energy parts and the waves' places in n_rounds rounds.
+int64_t lane_lds_bytes(int32_t n, int waves, int32_t n_rounds);
+int launch_lane(LaneArgs a, bool compact, int waves, void *stream, std::string &err);
 
 struct LaunchChoice {
     int win_waves = 1;         // waves per replica (window width)

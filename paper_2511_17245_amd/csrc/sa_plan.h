@@ -66,11 +66,28 @@ struct sa_plan {
     };
     Levels levels;
     Sched order;                      // every variable in index order (the settled kernel), on first use
+    // the lane kernel's levels, chunks and records (heat bath of pair problems), on first use
+    struct Lanes {
+        void *dev = nullptr;
+        sa::LaneImage im;             // counts and level offsets (its large arrays are released)
+        const sa::LaneRows *chunks = nullptr;
+        const sa::LaneSlot *slots = nullptr;
+        const void *recs = nullptr;
+        struct Rounds {
+            sa::LaneRows *dev = nullptr;
+            int32_t n = 0;
+        };
+        Rounds rounds[4];             // for 1, 2, 4 and 8 waves per replica, on first use
+    };
+    Lanes lanes;
     std::mutex sched_mu;  // guards the lazy building of sched and levels (a server's preparers share plans)
     ~sa_plan() {
         if (beta_dev) (void)hipFree(beta_dev);
         for (auto &sc : sched)
             if (sc.dev) (void)hipFree(sc.dev);
+        if (lanes.dev) (void)hipFree(lanes.dev);
+        for (auto &r : lanes.rounds)
+            if (r.dev) (void)hipFree(r.dev);
         if (order.dev) (void)hipFree(order.dev);
         if (levels.dev) (void)hipFree(levels.dev);
     }
@@ -92,6 +109,15 @@ int resolve_schedule(sa_plan *plan, const sa_schedule *sched, std::vector<double
 int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out);
 // The plan's variables in index order (build_order; n_active of them not fixed).
 int get_order(sa_plan *plan, sa_plan::Sched **out);
+// The plan's lane image (16-bit records or not), built and uploaded on first use.
+int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out);
+int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out);
+// Byte layout of a lane image (chunks | slots | records), and its staging.
+struct LaneLayout {
+    size_t slots, recs, total;
+};
+LaneLayout lane_layout(const LaneImage &im);
+void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image);
 // Uploads the inverse temperatures unless the device already holds the same array.
 int stage_beta(sa_plan *plan, const std::vector<double> &beta, hipStream_t stream);
 // Heat-bath register chunk class of a plan's widest range (1, 2, 8, 32, or 0 = recompute).
