@@ -356,6 +356,33 @@ int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out) {
     return SA_OK;
 }
 
+int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &q) {
+    choice = LaneChoice();
+    bool compact = false;
+    if (n_sweeps < kLaneMinSweeps || !lane_eligible(plan->rule, plan->packed, plan->dp.coef32 != 0, plan->device, compact))
+        return SA_OK;
+    sa_plan::Lanes *ln = nullptr;
+    int rc = get_lanes(plan, compact, &ln);
+    if (rc != SA_OK) return rc;
+    const int waves = lane_waves(ln->im, plan->dp.n, n_reads, plan->device);
+    if (waves == 0) return SA_OK;
+    sa_plan::Lanes::Rounds *rounds = nullptr;
+    rc = get_lane_rounds(plan, waves, &rounds);
+    if (rc != SA_OK) return rc;
+    q.P = plan->dp;
+    q.closed = plan->rule == SA_HEAT_BATH_CLOSED ? 1 : 0;
+    q.n_rounds = rounds->n;
+    q.rounds = rounds->dev;
+    q.chunks = ln->chunks;
+    q.slots = ln->slots;
+    q.recs = ln->recs;
+    q.off_places = lane_off_places(plan->dp.n, waves);
+    choice.waves = waves;
+    choice.compact = compact;
+    choice.lds_bytes = (int)lane_lds_bytes(plan->dp.n, waves, q.n_rounds);
+    return SA_OK;
+}
+
 int get_levels(sa_plan *plan, sa_plan::Levels **out) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Levels &lv = plan->levels;
@@ -554,28 +581,13 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         if (tmp) (void)hipFree(tmp);
         return fail(SA_EINVAL, "waves_per_replica must be 0, 1, 2, 4, 8 or 16");
     }
-    // the automatic choice for the heat bath of pair problems: one update per lane, for runs that repay
-    // building and uploading its image (a few sweeps' time in the quad kernel)
-    int lane_wv = 0;
-    bool compact = false;
-    if (opts.lanes_per_update == 0 && G == 0 && s1 - s0 >= 16 &&
-        sa::lane_eligible(plan->rule, plan->packed, plan->dp.coef32 != 0, plan->device, compact)) {
-        sa_plan::Lanes *ln = nullptr;
-        rc = sa::get_lanes(plan, compact, &ln);
-        if (rc != SA_OK) {
-            if (tmp) (void)hipFree(tmp);
-            return rc;
-        }
-        lane_wv = sa::lane_waves(ln->im, n, n_reads, plan->device);
-        if (lane_wv > 0) {
-            sa_plan::Lanes::Rounds *rounds = nullptr;
-            rc = sa::get_lane_rounds(plan, lane_wv, &rounds);
-            if (rc != SA_OK) {
-                if (tmp) (void)hipFree(tmp);
-                return rc;
-            }
-            sa::LaneArgs q{};
-            q.P = plan->dp;
+    // the automatic choice for the heat bath of pair problems: one update per lane
+    sa::LaneChoice lane;
+    if (opts.lanes_per_update == 0 && G == 0) {
+        sa::LaneArgs q{};
+        rc = sa::choose_lane_run(plan, n_reads, s1 - s0, lane, q);
+        std::string err;
+        if (rc == SA_OK && lane.waves > 0) {
             q.beta = plan->beta_dev;
             q.n_sweeps = S;
             q.s_begin = s0;
@@ -584,35 +596,29 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
             q.key0 = a.key0;
             q.key1 = a.key1;
             q.instance_id = a.instance_id;
-            q.closed = plan->rule == SA_HEAT_BATH_CLOSED ? 1 : 0;
-            q.n_rounds = rounds->n;
-            q.rounds = rounds->dev;
-            q.chunks = ln->chunks;
-            q.slots = ln->slots;
-            q.recs = ln->recs;
             q.z_init = zi_dev;
             q.z_out = z_dev;
             q.e_out = e_dev;
             q.trace = t_dev;
-            std::string err;
-            rc = sa::launch_lane(q, compact, lane_wv, stream, err);
+            rc = sa::launch_lane(q, lane.compact, lane.waves, stream, err);
             if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
-            if (rc != SA_OK) {
-                if (tmp) (void)hipFree(tmp);
-                return fail(rc, err);
-            }
+            if (rc != SA_OK) (void)fail(rc, err);
             plan->last = sa_launch_info{};
-            plan->last.waves_per_group = lane_wv;
+            plan->last.waves_per_group = lane.waves;
             plan->last.groups = n_reads;
-            plan->last.lds_bytes = (int32_t)sa::lane_lds_bytes(n, lane_wv, q.n_rounds);
+            plan->last.lds_bytes = lane.lds_bytes;
             plan->last.state_in_lds = 1;
             plan->last.kernel_variant = 4000000 + plan->rule * 100000;
-            plan->last.waves_per_replica = lane_wv;
+            plan->last.waves_per_replica = lane.waves;
             plan->last.lanes_per_update = 1;
-            plan->last.n_levels = ln->im.n_levels;
+            plan->last.n_levels = plan->lanes.im.n_levels;
+        }
+        if (rc != SA_OK) {
+            if (tmp) (void)hipFree(tmp);
+            return rc;
         }
     }
-    if (lane_wv == 0) {
+    if (lane.waves == 0) {
     const bool eligible = sa::quad_eligible(plan->rule, plan->packed, plan->device);
     sa_plan::Levels *lv = nullptr;
     if (eligible && G == 0 && opts.lanes_per_update != 64) {

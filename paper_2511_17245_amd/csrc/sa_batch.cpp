@@ -46,7 +46,10 @@ struct sa_batch {
     size_t o_inst = 0, o_task = 0, o_settled = 0;
     std::vector<int> settled_lds;      // LDS bytes of a settled replica of each problem (0: none)
     std::vector<sa::TeamChoice> dense_team;   // problems of the dense team kernel (waves > 0)
-    hipStream_t side = nullptr;        // its stream, and the events that tie it to the batch's
+    std::vector<sa::LaneChoice> lane;  // problems of the lane kernel (waves > 0)
+    std::vector<sa::LaneArgs> lane_args;
+    size_t o_lane = 0;
+    hipStream_t side = nullptr;        // their stream, and the events that tie it to the batch's
     hipEvent_t fork = nullptr, join = nullptr;
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
@@ -99,7 +102,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
     const double share = total / waves;
     int64_t lds_elems_max = 0;
     for (int32_t i = 0; i < n; ++i) {
-        if (b.dense_team[i].waves > 0) continue;
+        if (b.dense_team[i].waves > 0 || b.lane[i].waves > 0) continue;
         sa_plan &p = *b.plans[i];
         int G = 1;
         if (policy > 0.0)
@@ -132,7 +135,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
                      [&](int32_t x, int32_t y) { return b.replica_cost[x] / b.team[x] > b.replica_cost[y] / b.team[y]; });
     std::vector<sa::BatchTask> tasks;
     for (int32_t i : order) {
-        if (b.dense_team[i].waves > 0) continue;
+        if (b.dense_team[i].waves > 0 || b.lane[i].waves > 0) continue;
         const int per = sa::kBatchWaves / b.team[i];
         for (int32_t r = 0; r < b.n_reads[i]; r += per) tasks.push_back(sa::BatchTask{i, r});
     }
@@ -140,6 +143,8 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
     std::vector<sa::BatchTask> settled;
     sa::settle_batch(b.insts, b.settled_lds, b.replica_cost, settled, b.launch.settled);
     sa::group_teams(b.insts, b.dense_team, settled, b.launch.teams);
+    sa::group_lanes(b.lane, b.n_reads, settled, b.launch.lanes);
+    b.launch.lane_args = (const sa::LaneArgs *)(b.base + b.o_lane);
     b.launch.settled_tasks = (const sa::BatchTask *)(b.base + b.o_settled);
     hipError_t e = hipMemcpy(b.base + b.o_inst, b.insts.data(), sizeof(sa::BatchInst) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess && !settled.empty())
@@ -259,7 +264,8 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
     const size_t o_z = o_beta + align256(sizeof(double) * beta_total);
     const size_t o_e = o_z + align256(sizeof(int32_t) * z_total);
     const size_t o_next = o_e + align256(sizeof(int64_t) * e_total);
-    const size_t total = o_next + align256(sizeof(int32_t) * e_total);
+    b->o_lane = o_next + align256(sizeof(int32_t) * e_total);
+    const size_t total = b->o_lane + align256(sizeof(sa::LaneArgs) * n);
     hipError_t e = hipMalloc(&b->arena.base, total);
     if (e != hipSuccess) {
         b->arena.base = nullptr;
@@ -297,8 +303,23 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         int rc = sa::get_order(&p, &all);
         if (rc != SA_OK) return rc;
         b->dense_team.push_back(sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, all->dev, d.n_reads, b->device, d));
+        b->lane.emplace_back();
+        b->lane_args.emplace_back();
+        sa::LaneArgs &q = b->lane_args.back();
+        q = sa::LaneArgs{};
+        if (d.team_waves == 0) rc = sa::choose_lane_run(&p, d.n_reads, d.n_sweeps, b->lane.back(), q);
+        if (rc != SA_OK) return rc;
+        q.beta = d.beta;
+        q.n_sweeps = q.s_end = d.n_sweeps;
+        q.n_reads = d.n_reads;
+        q.key0 = d.key0;
+        q.key1 = d.key1;
+        q.instance_id = d.instance_id;
+        q.z_out = d.z_out;
+        q.e_out = d.e_out;
         b->settled_lds.push_back(
-            d.team_waves > 0 ? 0
+            d.team_waves > 0 || b->lane.back().waves > 0
+                             ? 0
                              : sa::settle_inst(p.packed, p.dp.coef32 != 0, all->dev, all->n_active, d.n_sweeps, b->device, d));
         if (b->settled_lds.back()) d.next = (int32_t *)(b->base + o_next) + b->e_off[i];
     }
@@ -317,6 +338,9 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
 
     bool teams = false;
     for (const auto &tc : b->dense_team) teams = teams || tc.waves > 0;
+    for (const auto &lc : b->lane) teams = teams || lc.waves > 0;
+    e = hipMemcpy(b->base + b->o_lane, b->lane_args.data(), sizeof(sa::LaneArgs) * n, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(batch lanes)");
     if (teams) {
         e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
@@ -448,6 +472,7 @@ int32_t sa_batch_get_info(const sa_batch *b, sa_batch_info *info) {
     info->n_problems = (int32_t)b->plans.size();
     info->n_tasks = b->n_tasks;
     for (const auto &g : b->launch.teams) info->n_tasks += g.n;
+    for (const auto &g : b->launch.lanes) info->n_tasks += g.n;
     info->total_updates = b->total_updates;
     info->waves_per_group = b->launch.waves_per_group;
     info->groups = b->launch.groups;
@@ -455,6 +480,7 @@ int32_t sa_batch_get_info(const sa_batch *b, sa_batch_info *info) {
     int32_t tmax = 1;
     for (int32_t t : b->team) tmax = std::max(tmax, t);
     for (const auto &tc : b->dense_team) tmax = std::max(tmax, tc.waves);
+    for (const auto &lc : b->lane) tmax = std::max(tmax, lc.waves);
     info->max_team = tmax;
     info->policy = b->policy;
     info->kernel_maxe = b->launch.maxe_class;

@@ -351,6 +351,15 @@ bool lane_eligible(int rule, const Packed &p, bool coef32, int device, bool &com
 int lane_waves(const LaneImage &im, int32_t n, int32_t n_reads, int device);
 // LDS bytes of one replica: state, energy parts and the waves' places in n_rounds rounds.
 int64_t lane_lds_bytes(int32_t n, int waves, int32_t n_rounds);
+int32_t lane_off_places(int32_t n, int waves);
+// The lane kernel for a run, or none (waves = 0).
+struct LaneChoice {
+    int waves = 0;
+    bool compact = false;
+    int lds_bytes = 0;
+};
+// A run of fewer sweeps does not repay building and uploading the lane kernel's image.
+constexpr int32_t kLaneMinSweeps = 16;
 int launch_lane(LaneArgs a, bool compact, int waves, void *stream, std::string &err);
 
 struct LaunchChoice {
@@ -490,14 +499,25 @@ TeamChoice team_inst(int rule, const Packed &p, bool coef32, const SchedRec *ord
 void group_teams(const std::vector<BatchInst> &insts, const std::vector<TeamChoice> &choices, std::vector<BatchTask> &tasks,
                  std::vector<TeamGroup> &groups);
 int launch_team_group(const BatchInst *insts, const BatchTask *tasks, const TeamGroup &g, void *stream, std::string &err);
+// One launch of the lane kernel over tasks of the same list: problems of one width of records and team.
+struct LaneGroup {
+    int32_t first = 0, n = 0;
+    int waves = 0, lds_bytes = 0;
+    bool compact = false;
+};
+void group_lanes(const std::vector<LaneChoice> &choices, const std::vector<int32_t> &n_reads, std::vector<BatchTask> &tasks,
+                 std::vector<LaneGroup> &groups);
+int launch_lane_group(const LaneArgs *list, const BatchTask *tasks, const LaneGroup &g, void *stream, std::string &err);
 struct BatchLaunch {
+    std::vector<LaneGroup> lanes;
+    const LaneArgs *lane_args = nullptr;        // device: per problem
     SettledGroup settled[kSettledGroups];
     std::vector<TeamGroup> teams;
     const BatchTask *settled_tasks = nullptr;   // device: the groups' tasks
-    // the dense team kernels run beside the persistent kernel: a stream of their own, and the events that
-    // fork it from the batch's stream and join it again (nullptr: they run first on the batch's stream)
+    // the dense team and lane kernels run beside the persistent kernel: a stream of their own, and the
+    // events that fork it from the batch's stream and join it again (nullptr: they run first on the
+    // batch's stream); their problems get no task of the persistent kernel
     void *side_stream = nullptr, *fork = nullptr, *join = nullptr;
-    // problems run by the dense team kernel get no task of the persistent kernel
     int waves_per_group = kBatchWaves;
     int groups = 1;
     int maxe_class = 1;

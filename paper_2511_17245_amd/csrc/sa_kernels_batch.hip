@@ -33,8 +33,8 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
             return SA_EDEVICE;
         }
     }
-    // dense teams first, beside the persistent kernel where a side stream is given
-    const bool teams = !bl.teams.empty() && b.sweep_limit == 0;
+    // dense teams and lane kernels first, beside the persistent kernel where a side stream is given
+    const bool teams = (!bl.teams.empty() || !bl.lanes.empty()) && b.sweep_limit == 0;
     if (teams) {
         void *s = bl.side_stream ? bl.side_stream : stream;
         hipError_t e = hipSuccess;
@@ -45,6 +45,11 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
         for (const TeamGroup &g : bl.teams) {
             if (e != hipSuccess) break;
             int rc = launch_team_group(b.insts, bl.settled_tasks, g, s, err);
+            if (rc != SA_OK) return rc;
+        }
+        for (const LaneGroup &g : bl.lanes) {
+            if (e != hipSuccess) break;
+            int rc = launch_lane_group(bl.lane_args, bl.settled_tasks, g, s, err);
             if (rc != SA_OK) return rc;
         }
         if (bl.side_stream && e == hipSuccess) e = hipEventRecord((hipEvent_t)bl.join, (hipStream_t)s);

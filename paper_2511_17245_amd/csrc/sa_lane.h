@@ -110,14 +110,11 @@ struct LanePlace {
 // kCompact: records of 16-bit index and coupling, every value below 2^23 and every coefficient below 2^31 in
 // magnitude (24-bit products, 32-bit sums); else 32-bit index and coupling and 64-bit sums.
 template <bool kCompact>
-__global__ void __launch_bounds__(512) lane_kernel(LaneArgs A) {
-    extern __shared__ int32_t lds_state[];
+__device__ __forceinline__ void lane_run(const LaneArgs &A, int read, int32_t *lds_state) {
     using Rec = std::conditional_t<kCompact, uint32_t, uint2>;
     using Sum = std::conditional_t<kCompact, int32_t, int64_t>;
     const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave, nw = nthr / kWave;
-    const int read = (int)blockIdx.x;
-    if (read >= A.n_reads) return;
     const int32_t n = A.P.n;
     int32_t *z = lds_state;
     init_state(A.P, z, A.z_init ? A.z_init + (size_t)read * n : nullptr, (uint32_t)read, A.instance_id, A.key0, A.key1, tid,
@@ -275,6 +272,44 @@ __global__ void __launch_bounds__(512) lane_kernel(LaneArgs A) {
     }
     int32_t *zo = A.z_out + (size_t)read * n;
     for (int32_t k = tid; k < n; k += nthr) zo[k] = z[k];
+}
+
+// Plain runs: one workgroup per read.
+template <bool kCompact>
+__global__ void __launch_bounds__(512) lane_kernel(LaneArgs A) {
+    extern __shared__ int32_t lds_state[];
+    if ((int)blockIdx.x >= A.n_reads) return;
+    lane_run<kCompact>(A, (int)blockIdx.x, lds_state);
+}
+
+// A wave-uniform pointer read from memory, known to point into device memory (a load through a pointer of
+// unknown address space counts as an LDS access too, and every wait for LDS would wait for it).
+template <typename T>
+__device__ __forceinline__ T *in_device_memory(T *p) {
+    const uint64_t b = (uint64_t)(uintptr_t)p;
+    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)(((uint64_t)uni32((uint32_t)(b >> 32)) << 32) |
+                                                                  uni32((uint32_t)b));
+}
+
+// Batches and server chunks: task blockIdx.x, its problem's arguments in `list`.
+template <bool kCompact>
+__global__ void __launch_bounds__(512) lane_batch_kernel(const LaneArgs *list, const BatchTask *tasks) {
+    extern __shared__ int32_t lds_state[];
+    const BatchTask task = tasks[blockIdx.x];
+    LaneArgs A = list[task.inst];
+    A.P.var = in_device_memory(A.P.var);
+    A.P.t_off = in_device_memory(A.P.t_off);
+    A.P.t_var = in_device_memory(A.P.t_var);
+    A.P.t_coef = in_device_memory(A.P.t_coef);
+    A.beta = in_device_memory(A.beta);
+    A.rounds = in_device_memory(A.rounds);
+    A.chunks = in_device_memory(A.chunks);
+    A.slots = in_device_memory(A.slots);
+    A.recs = (const void *)in_device_memory((const char *)A.recs);
+    if (A.z_init) A.z_init = in_device_memory(A.z_init);
+    A.z_out = in_device_memory(A.z_out);
+    A.e_out = in_device_memory(A.e_out);
+    lane_run<kCompact>(A, task.read, lds_state);
 }
 
 }  // namespace

@@ -112,6 +112,8 @@ int get_order(sa_plan *plan, sa_plan::Sched **out);
 // The plan's lane image (16-bit records or not), built and uploaded on first use.
 int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out);
 int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out);
+// The lane kernel's choice for a run of n_sweeps sweeps, and its arguments that come from the plan.
+int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &args);
 // Byte layout of a lane image (chunks | slots | records), and its staging.
 struct LaneLayout {
     size_t slots, recs, total;

@@ -302,6 +302,12 @@ void prep_loop(sa_server *S) {
                     break;
                 }
             }
+            sa::LaneChoice lane;
+            sa::LaneArgs lane_args{};
+            if (rc == SA_OK && sa::choose_lane_run(r->plan, r->n_reads, r->n_sweeps, lane, lane_args) != SA_OK) {
+                rc = SA_ENOMEM;
+                err = sa_last_error();
+            }
             sa_plan::Sched *all = nullptr;
             if (rc == SA_OK && sa::get_order(r->plan, &all) != SA_OK) {
                 rc = SA_ENOMEM;
@@ -396,6 +402,9 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     std::vector<sa::BatchInst> insts(n);
     std::vector<int> team(n), settled_lds(n);
     std::vector<sa::TeamChoice> choices(n);
+    std::vector<sa::LaneChoice> lanes(n);
+    std::vector<sa::LaneArgs> lane_args(n);
+    std::vector<int32_t> n_reads(n);
     int64_t lds_elems = 0;
     for (int i = 0; i < n; ++i) {
         Request *r = act[i];
@@ -416,7 +425,15 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         team[i] = G;
         sa::BatchInst &d = insts[i];
         choices[i] = sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, p.order.dev, r->n_reads, S->device, d);
-        if (choices[i].waves == 0) lds_elems = std::max<int64_t>(lds_elems, (int64_t)(sa::kBatchWaves / G) * stride);
+        // (its image was built by the request's preparer)
+        lane_args[i] = sa::LaneArgs{};
+        n_reads[i] = r->n_reads;
+        if (choices[i].waves == 0 &&
+            sa::choose_lane_run(&p, r->n_reads, r->n_sweeps, lanes[i], lane_args[i]) != SA_OK) {
+            err = sa_last_error();
+            return SA_ENOMEM;
+        }
+        if (choices[i].waves == 0 && lanes[i].waves == 0) lds_elems = std::max<int64_t>(lds_elems, (int64_t)(sa::kBatchWaves / G) * stride);
         d.P = p.dp;
         d.beta = r->beta_dev;
         d.sched = p.sched[G].dev;
@@ -436,7 +453,19 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         d.instance_id = r->instance_id;
         d.z_out = r->z_dev;
         d.e_out = r->e_dev;
-        if (choices[i].waves == 0)
+        sa::LaneArgs &q = lane_args[i];
+        q.beta = d.beta;
+        q.n_sweeps = d.n_sweeps;
+        q.s_begin = d.s_begin;
+        q.s_end = d.s_end;
+        q.n_reads = d.n_reads;
+        q.key0 = d.key0;
+        q.key1 = d.key1;
+        q.instance_id = d.instance_id;
+        q.z_init = d.resume ? d.z_out : nullptr;
+        q.z_out = d.z_out;
+        q.e_out = d.e_out;
+        if (choices[i].waves == 0 && lanes[i].waves == 0)
             settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
         if (settled_lds[i]) d.next = r->next_dev;
         d.leave = std::max<int32_t>(1, 3 * d.n_order / sa::settled_share(G));
@@ -447,7 +476,7 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
                      [&](int x, int y) { return cost[x] / team[x] > cost[y] / team[y]; });
     std::vector<sa::BatchTask> tasks;
     for (int i : order) {
-        if (choices[i].waves > 0) continue;   // the dense team kernel's
+        if (choices[i].waves > 0 || lanes[i].waves > 0) continue;   // the dense team's, the lane kernel's
         for (int32_t rd = 0; rd < act[i]->n_reads; rd += sa::kBatchWaves / team[i])
             tasks.push_back(sa::BatchTask{i, rd});
     }
@@ -456,11 +485,13 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     std::vector<sa::BatchTask> settled;
     sa::settle_batch(insts, settled_lds, cost, settled, bl.settled);
     sa::group_teams(insts, choices, settled, bl.teams);
+    sa::group_lanes(lanes, n_reads, settled, bl.lanes);
     bl.side_stream = S->side;
     bl.fork = S->fork;
     bl.join = S->join;
     const size_t o_settled = o_task + align256(sizeof(sa::BatchTask) * tasks.size());
-    const size_t o_ctr = o_settled + align256(sizeof(sa::BatchTask) * settled.size());
+    const size_t o_lane = o_settled + align256(sizeof(sa::BatchTask) * settled.size());
+    const size_t o_ctr = o_lane + align256(sizeof(sa::LaneArgs) * n);
     const size_t need = o_ctr + 256;
     if (need > S->chunk_cap) {
         if (S->chunk_mem.base) (void)hipFree(S->chunk_mem.base);
@@ -481,6 +512,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     if (!settled.empty())
         std::memcpy(staging.data() + o_settled, settled.data(), sizeof(sa::BatchTask) * settled.size());
     bl.settled_tasks = (const sa::BatchTask *)(base + o_settled);
+    std::memcpy(staging.data() + o_lane, lane_args.data(), sizeof(sa::LaneArgs) * n);
+    bl.lane_args = (const sa::LaneArgs *)(base + o_lane);
     hipError_t e = hipMemcpyAsync(base, staging.data(), o_ctr, hipMemcpyHostToDevice, S->stream);
     if (e != hipSuccess) {
         err = std::string("hipMemcpyAsync(chunk): ") + hipGetErrorString(e);
