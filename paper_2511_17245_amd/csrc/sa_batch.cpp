@@ -49,16 +49,13 @@ struct sa_batch {
     std::vector<sa::LaneChoice> lane;  // problems of the lane kernel (waves > 0)
     std::vector<sa::LaneArgs> lane_args;
     size_t o_lane = 0;
-    hipStream_t side = nullptr;        // their stream, and the events that tie it to the batch's
-    hipEvent_t fork = nullptr, join = nullptr;
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
     ~sa_batch() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        if (fork) (void)hipEventDestroy(fork);
-        if (join) (void)hipEventDestroy(join);
-        if (side) (void)hipStreamDestroy(side);
+        launch.beside.destroy();
+        launch.settled_side.destroy();
         if (own_stream && stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -339,17 +336,13 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
     bool teams = false;
     for (const auto &tc : b->dense_team) teams = teams || tc.waves > 0;
     for (const auto &lc : b->lane) teams = teams || lc.waves > 0;
+    bool settled = false;
+    for (int bytes : b->settled_lds) settled = settled || bytes > 0;
     e = hipMemcpy(b->base + b->o_lane, b->lane_args.data(), sizeof(sa::LaneArgs) * n, hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(batch lanes)");
-    if (teams) {
-        e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
-        if (e != hipSuccess) return hip_fail(e, "hipStreamCreate(batch)");
-        b->launch.side_stream = b->side;
-        b->launch.fork = b->fork;
-        b->launch.join = b->join;
-    }
+    if (teams) e = (hipError_t)b->launch.beside.create();
+    if (e == hipSuccess && settled) e = (hipError_t)b->launch.settled_side.create();
+    if (e != hipSuccess) return hip_fail(e, "hipStreamCreate(batch)");
 
     // choose the team-size policy and the number of persistent workgroups
     Tuned choice{0.5, 2};

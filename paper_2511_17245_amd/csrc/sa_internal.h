@@ -508,16 +508,27 @@ struct LaneGroup {
 void group_lanes(const std::vector<LaneChoice> &choices, const std::vector<int32_t> &n_reads, std::vector<BatchTask> &tasks,
                  std::vector<LaneGroup> &groups);
 int launch_lane_group(const LaneArgs *list, const BatchTask *tasks, const LaneGroup &g, void *stream, std::string &err);
+// A stream beside a batch's, with the events that fork it from there and join it again (hipStream_t,
+// hipEvent_t; nullptr: none, its work runs on the batch's stream).
+struct SideStream {
+    void *stream = nullptr, *fork = nullptr, *join = nullptr;
+    int create();                       // hipError_t
+    void destroy();
+    int fork_from(void *main) const;    // the side stream's next work waits for main's so far
+    int mark() const;                   // the end of the side stream's work so far ...
+    int join_to(void *main) const;      // ... which main's next work waits for
+};
 struct BatchLaunch {
     std::vector<LaneGroup> lanes;
     const LaneArgs *lane_args = nullptr;        // device: per problem
     SettledGroup settled[kSettledGroups];
     std::vector<TeamGroup> teams;
     const BatchTask *settled_tasks = nullptr;   // device: the groups' tasks
-    // the dense team and lane kernels run beside the persistent kernel: a stream of their own, and the
-    // events that fork it from the batch's stream and join it again (nullptr: they run first on the
-    // batch's stream); their problems get no task of the persistent kernel
-    void *side_stream = nullptr, *fork = nullptr, *join = nullptr;
+    // the dense team and lane kernels run beside the persistent kernel (without a side stream: first);
+    // their problems get no task of the persistent kernel
+    SideStream beside;
+    // the settled groups run beside each other: the first on the batch's stream, the others here
+    SideStream settled_side;
     int waves_per_group = kBatchWaves;
     int groups = 1;
     int maxe_class = 1;

@@ -86,8 +86,8 @@ double cost_of_update(const sa_plan &p, bool team = false) {
 struct sa_server {
     sa_server_opts opts{};
     int device = 0, cus = 256, max_lds = 65536;
-    hipStream_t stream = nullptr, side = nullptr;   // side: dense teams, tied to stream by the events
-    hipEvent_t fork = nullptr, join = nullptr;
+    hipStream_t stream = nullptr;
+    sa::SideStream beside, settled_side;   // of the chunks' launches
     std::chrono::steady_clock::time_point t0;
     std::mutex mu;
     std::condition_variable cv_prep, cv_sched, cv_done;
@@ -486,9 +486,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     sa::settle_batch(insts, settled_lds, cost, settled, bl.settled);
     sa::group_teams(insts, choices, settled, bl.teams);
     sa::group_lanes(lanes, n_reads, settled, bl.lanes);
-    bl.side_stream = S->side;
-    bl.fork = S->fork;
-    bl.join = S->join;
+    bl.beside = S->beside;
+    bl.settled_side = S->settled_side;
     const size_t o_settled = o_task + align256(sizeof(sa::BatchTask) * tasks.size());
     const size_t o_lane = o_settled + align256(sizeof(sa::BatchTask) * settled.size());
     const size_t o_ctr = o_lane + align256(sizeof(sa::LaneArgs) * n);
@@ -681,9 +680,8 @@ int32_t sa_server_create(const sa_server_opts *opts, sa_server **out) {
     (void)hipDeviceGetAttribute(&S->cus, hipDeviceAttributeMultiprocessorCount, S->device);
     (void)hipDeviceGetAttribute(&S->max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, S->device);
     e = hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&S->side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&S->fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&S->join, hipEventDisableTiming);
+    if (e == hipSuccess) e = (hipError_t)S->beside.create();
+    if (e == hipSuccess) e = (hipError_t)S->settled_side.create();
     if (e != hipSuccess) return hip_fail(e, "hipStreamCreate");
     S->t0 = std::chrono::steady_clock::now();
     sa_server *raw = S.get();
@@ -838,9 +836,8 @@ void sa_server_destroy(sa_server *S) {
     }
     for (auto &kv : S->plan_cache) delete kv.second.plan;
     S->plan_cache.clear();
-    if (S->fork) (void)hipEventDestroy(S->fork);
-    if (S->join) (void)hipEventDestroy(S->join);
-    if (S->side) (void)hipStreamDestroy(S->side);
+    S->beside.destroy();
+    S->settled_side.destroy();
     if (S->stream) (void)hipStreamDestroy(S->stream);
     delete S;
 }

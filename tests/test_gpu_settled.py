@@ -97,3 +97,23 @@ def test_resumed_and_without_allocations(rule):
                          stream=torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert np.array_equal(z, zt.cpu().numpy()) and np.array_equal(e, et.cpu().numpy())
+
+
+@pytest.mark.parametrize("sizes", [(100, 90), (100, 1500), (1500, 100, 4500, 120, 1600)])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_groups_beside_each_other(sizes, graph):
+    """One, two and three groups of settled replicas in one batch (by the LDS a replica takes): each
+    problem ends as in a run of its own, in each of three runs of the batch."""
+    items = [I.Workload(I.erdos_renyi_quio(n, 4.0, -3, 4, 10, 10, rng(n)), sa.METROPOLIS, 40, 3, 5 + i, i)
+             for i, n in enumerate(sizes)]
+    want = []
+    for w in items:
+        plan = sa.Plan(w.problem, w.rule)
+        want.append(plan.run(w.n_sweeps, w.n_reads, w.seed, instance_id=w.instance_id)[:2])
+        plan.close()
+    b = sa.Batch(items, use_graph=graph)
+    for _ in range(3):
+        b.run()
+        for (z, e), (zp, ep) in zip(b.results(), want):
+            assert np.array_equal(z, zp) and np.array_equal(e, ep)
+    b.close()
