@@ -518,6 +518,136 @@ __device__ __forceinline__ bool metropolis_accept(int64_t d, double beta, double
     return U < exp_nonpos(-(beta * (double)d));
 }
 
+// expm1(x) for x <= 0 (the closed-form heat bath's expm1(-c W)).  Below -40, e^x is under half an
+// ulp of 1 and the value is -1 exactly.  On [-0.35, 0] the Taylor series of e^x - 1 to x^14 (error
+// below 2^-60 relative); otherwise e^x - 1, which cancels nothing because e^x <= 0.71.
+__device__ __forceinline__ double expm1_nonpos(double x) {
+    if (x < -40.0) return -1.0;
+    if (x < -0.35) return exp_nonpos(x) - 1.0;
+    // Horner on 1/k!, k = 14 .. 2, then x + x^2 (...)
+    double p = 1.0 / 87178291200.0;            // 1/14!
+    p = fma(p, x, 1.0 / 6227020800.0);         // 1/13!
+    p = fma(p, x, 1.0 / 479001600.0);          // 1/12!
+    p = fma(p, x, 1.0 / 39916800.0);           // 1/11!
+    p = fma(p, x, 1.0 / 3628800.0);            // 1/10!
+    p = fma(p, x, 1.0 / 362880.0);             // 1/9!
+    p = fma(p, x, 1.0 / 40320.0);              // 1/8!
+    p = fma(p, x, 1.0 / 5040.0);               // 1/7!
+    p = fma(p, x, 1.0 / 720.0);                // 1/6!
+    p = fma(p, x, 1.0 / 120.0);                // 1/5!
+    p = fma(p, x, 1.0 / 24.0);                 // 1/4!
+    p = fma(p, x, 1.0 / 6.0);                  // 1/3!
+    p = fma(p, x, 0.5);                        // 1/2!
+    return fma(p * x, x, x);
+}
+
+// log1p(y) for -1 < y <= 0 (the closed-form heat bath's log1p(U m)).  u = 1 + y rounded; log(u)
+// from u = f 2^e with f in [sqrt(1/2), sqrt(2)) and log f = 2 atanh(s), s = (f - 1)/(f + 1),
+// |s| <= 0.1716, by its odd series to s^21 (error below 2^-62 relative); the rounding of u is
+// put back to first order, log1p(y) = log(u) + (y - (u - 1)) / u (Kahan's correction).
+__device__ __forceinline__ double log1p_nonpos(double y) {
+    if (y == 0.0) return 0.0;
+    if (y <= -1.0) return -__builtin_huge_val();
+    const double u = 1.0 + y;
+    const double corr = (y - (u - 1.0)) * __builtin_amdgcn_rcp(u);
+    int e = __builtin_amdgcn_frexp_exp(u);
+    double f = __builtin_amdgcn_frexp_mant(u);  // [0.5, 1)
+    if (f < 0.70710678118654752) {
+        f = f + f;
+        e -= 1;
+    }
+    const double s = (f - 1.0) / (f + 1.0);
+    const double s2 = s * s;
+    double r = 1.0 / 21.0;
+    r = fma(r, s2, 1.0 / 19.0);
+    r = fma(r, s2, 1.0 / 17.0);
+    r = fma(r, s2, 1.0 / 15.0);
+    r = fma(r, s2, 1.0 / 13.0);
+    r = fma(r, s2, 1.0 / 11.0);
+    r = fma(r, s2, 1.0 / 9.0);
+    r = fma(r, s2, 1.0 / 7.0);
+    r = fma(r, s2, 1.0 / 5.0);
+    r = fma(r, s2, 1.0 / 3.0);
+    const double ln2_hi = 0.6931471803691238;    // ln 2 rounded to 32 bits: e * ln2_hi is exact
+    const double ln2_lo = 1.9082149292705877e-10;  // ln 2 - ln2_hi
+    const double ed = (double)e;
+    const double two_s = s + s;
+    // log u = e ln2_hi + (2 s + (2 s s^2 r + e ln2_lo)) + corr
+    return fma(ed, ln2_hi, two_s + (fma(two_s * s2, r, ed * ln2_lo) + corr));
+}
+
+// Cumulative weights in value order, by one lane: the value drawn where the closed form cannot tell.
+__device__ __forceinline__ uint32_t linear_draw_by_sums(bool from_top, double slope, uint32_t W, double beta, double U) {
+    double total = 0.0;
+    for (uint32_t j = 0; j < W; ++j) total += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
+    const double thr = U * total;
+    double run = 0.0;
+    for (uint32_t j = 0; j < W; ++j) {
+        run += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
+        if (run > thr) return j;
+    }
+    return W - 1u;
+}
+
+// The closed form in double precision; it errs by some ulp of W, so a step nearer than 1e-10 + 1e-14 W is
+// left to the sums (above 65536 values, whose sums round as much as that, it is taken as it is).
+__device__ __forceinline__ uint32_t linear_draw_double(bool from_top, double slope, uint32_t W, double beta, double U) {
+    const double c = beta * slope, Wd = (double)W;
+    const double m = expm1_nonpos(-(c * Wd));
+    const double L = log1p_nonpos((from_top ? 1.0 - U : U) * m) / c;
+    const double x = from_top ? Wd + L : -L;
+    const double near = rint(x);
+    if (W <= 65536u && !(__builtin_fabs(x - near) > 1e-10 + 1e-14 * Wd) && near > 0.5 && near < Wd - 0.5)
+        return linear_draw_by_sums(from_top, slope, W, beta, U);
+    return !(x > 0.0) ? 0u : x >= Wd ? W - 1u : (uint32_t)ceil(x) - 1u;
+}
+
+// Heat-bath draw of a variable with dE(v) = a (v - z_k): the first value whose cumulative weight exceeds
+// U times the total.  Index i = ceil(x) - 1 with x = -log1p(P m) / c from the lower end for a > 0, W + the
+// same for a < 0; c = beta |a|, m = expm1(-c W), P = U or 1 - U.
+//
+// It replaced the enumeration in every kernel: 32 random-interaction problems (N = 100, W = 201, most
+// variables linear; 100 sweeps x 100 reads) 24.6 to 20.1 ms, 64 mixed problems 103 to 95 ms.
+//
+// In single precision: m from the series of expm1 (c W < 1/2; relative error below 1e-6 with the
+// rounding of c W) or e^-cW - 1 (below 1e-6 as |m| > 0.39); y = P m to 2e-6; log1p(y) from the series of
+// 2 atanh(y / (2 + y)) (|y| < 0.3, where log1p passes on at most 1.2 of y's relative error: 4e-6 in all) or
+// log(1 + y), off by 2e-6 |y| / (1 + y) and by 1e-6 of itself.  `err` is at least twice that.
+__device__ __forceinline__ int64_t linear_draw(int64_t a, int64_t lo, uint32_t W, double beta, double U) {
+    const bool from_top = a < 0;
+    const double slope = (double)(from_top ? -a : a);
+    const double c = beta * slope;
+    const float cf = (float)c, Wf = (float)W;
+    const float t = cf * Wf;
+    const float series = -t * (1.0f - t * (0.5f - t * (0.16666667f - t * (0.041666667f - t * (0.0083333333f - t * 0.0013888889f)))));
+    const float m = t < 0.5f ? series : __builtin_amdgcn_exp2f(t * -1.4426950f) - 1.0f;
+    const float y = (float)(from_top ? 1.0 - U : U) * m;
+    const float s = y * __builtin_amdgcn_rcpf(2.0f + y), s2 = s * s;
+    const float near0 = 2.0f * s * (1.0f + s2 * (0.33333333f + s2 * (0.2f + s2 * (0.14285714f + s2 * 0.11111111f))));
+    const float u = 1.0f + y;
+    const bool small = y > -0.3f;
+    const float L = small ? near0 : __builtin_amdgcn_logf(u) * 0.69314718f;
+    const float ic = __builtin_amdgcn_rcpf(cf);
+    const float aL = -L;
+    const float err = (small ? 1e-5f * aL : 5e-6f * __builtin_amdgcn_rcpf(u) + 4e-6f * aL) * ic + 1e-6f * Wf;
+    const float x = from_top ? Wf - aL * ic : aL * ic;
+    const float step = __builtin_rintf(x);
+    // a NaN or an infinity anywhere (c = 0, 1 + y = 0) fails the comparison; steps 0 and W decide nothing
+    const bool sure = W < (1u << 20) && err < 0.25f &&
+                      (__builtin_fabsf(x - step) > err || step < 0.5f || step > Wf - 0.5f) && c > 1e-30;
+    uint32_t i = x <= 0.0f ? 0u : (uint32_t)__builtin_ceilf(x) - 1u;
+    i = i < W ? i : W - 1u;
+    if (!sure) {
+        if (!(c * (double)W > 1e-17)) {   // every weight is 1: the count of v - l + 1 <= U W
+            i = (uint32_t)(U * (double)W);
+            i = i < W ? i : W - 1u;
+        } else {
+            i = linear_draw_double(from_top, slope, W, beta, U);
+        }
+    }
+    return lo + (int64_t)i;
+}
+
 // DPP destinations that keep zeros where their move does not write: each is written only by the
 // one masked move it serves, so the rows (or the lane) that the move skips hold the zero they
 // started with, and no zeroing instruction is needed per scan.  Kept by the caller across scans.
@@ -555,22 +685,16 @@ __device__ __forceinline__ double wave_shift_up1_zero(double x, ScanCarry &cy) {
 // <= W + 63.
 template <int kRegChunk, int kMaxE, typename Acc>
 __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, int64_t lo, int64_t W,
-                                                  int64_t zk, double beta, double U, int lane, bool linear_in,
+                                                  int64_t zk, double beta, double U, int lane, bool linear,
                                                   ScanCarry &cy) {
     const uint32_t W32 = (uint32_t)W;
     const uint32_t c = (W32 + kWave - 1) / kWave;
     const uint32_t j0 = (uint32_t)lane * c;
-    const bool linear = kMaxE == 1 || linear_in;   // no term holds z_k to a power above one
-    // Weights are taken relative to the minimum energy difference.  Linear dE(v) = a1 (v - z_k)
-    // has it at an end of the range, and dE(v) - dE_min = |a1| times the distance of v from that
-    // end, the same integer as the difference of the two energy differences.
+    // no term holds z_k to a power above one: the inverse of the distribution, whatever the width
+    if (kMaxE == 1 || linear) return linear_draw(to_i64<Acc>(C.a[1]), lo, W32, beta, U);
+    // Weights are taken relative to the minimum energy difference.
     int64_t dmin = 0, dlane = INT64_MAX;   // dlane: the smallest dE of this lane's values
-    Acc slope = 0;
-    bool from_top = false;
-    if (linear) {
-        from_top = to_i64<Acc>(C.a[1]) < 0;
-        slope = from_top ? (Acc)0 - C.a[1] : C.a[1];
-    } else if (kMaxE == 2 && c > 8) {
+    if (kMaxE == 2 && c > 8) {
         // dE(v) = a2 v^2 + a1 v + const: over the lane's values its minimum is at an end or at an
         // integer next to the vertex v = -a1 / (2 a2) (a2 > 0).  The vertex's index, computed in
         // double, is within one of the exact one, so the integers floor(t) - 1 .. floor(t) + 2 hold
@@ -611,14 +735,8 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     constexpr uint32_t kGroup = 4;
     // exp(-beta * (dE - dmin)); in 32-bit mode the difference is formed in 32 bits (it fits)
     auto weight = [&](uint32_t j) -> double {
-        double x;
-        if (linear) {
-            const Acc g = slope * (Acc)(from_top ? W32 - 1u - j : j);
-            x = sizeof(Acc) == 4 ? (double)(uint32_t)g : (double)(int64_t)g;
-        } else {
-            const int64_t d = poly_delta(C, zk, lo + (int64_t)j);
-            x = sizeof(Acc) == 4 ? (double)(int32_t)((uint32_t)d - (uint32_t)dmin) : (double)(d - dmin);
-        }
+        const int64_t d = poly_delta(C, zk, lo + (int64_t)j);
+        const double x = sizeof(Acc) == 4 ? (double)(int32_t)((uint32_t)d - (uint32_t)dmin) : (double)(d - dmin);
         return exp_nonpos(-(beta * x));
     };
 
@@ -633,15 +751,8 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     auto cold_draw = [&](int64_t &v) -> bool {
         bool live = false;
         if (j0 < W32) {
-            double xl;
-            if (linear) {
-                // the lane's value nearest the minimising end
-                const uint32_t jn = from_top ? (j0 + c - 1u < W32 ? j0 + c - 1u : W32 - 1u) : j0;
-                const Acc g = slope * (Acc)(from_top ? W32 - 1u - jn : jn);
-                xl = sizeof(Acc) == 4 ? (double)(uint32_t)g : (double)(int64_t)g;
-            } else {
-                xl = sizeof(Acc) == 4 ? (double)(int32_t)((uint32_t)dlane - (uint32_t)dmin) : (double)(dlane - dmin);
-            }
+            const double xl =
+                sizeof(Acc) == 4 ? (double)(int32_t)((uint32_t)dlane - (uint32_t)dmin) : (double)(dlane - dmin);
             live = !(beta * xl >= 746.0);   // a NaN product counts as live
         }
         const uint64_t lmask = __ballot(live);
@@ -688,31 +799,7 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     constexpr int kR = kRegChunk > 0 ? kRegChunk : 1;
     double w[kR];
     double lane_sum = 0.0;
-    // Linear dE, eight or more values per lane: once beta |a1| 64 >= 745.2, every value at
-    // distance 64 or more from the minimising end weighs exactly 0 (exp_nonpos of an argument at
-    // or below -745.2 is 0, and the rounded products beta |a1| d grow with d).  Lane d then
-    // evaluates the weight of the value at distance d, and each slot takes its weight from that
-    // lane: one exponential per lane instead of kRegChunk, the same numbers.  (With two values
-    // per lane the exchange costs more than the exponential it saves: measured slower.)
-    constexpr bool kGather = kRegChunk >= 8;
-    const bool gather = kGather && linear && beta * ((double)slope * 64.0) >= 745.2;
-    if (kGather && gather) {
-        const uint32_t dl = (uint32_t)lane < W32 ? (uint32_t)lane : W32 - 1u;
-        const double wl = weight(from_top ? W32 - 1u - dl : dl);
-        const uint32_t lo32 = (uint32_t)__double_as_longlong(wl);
-        const uint32_t hi32 = (uint32_t)((uint64_t)__double_as_longlong(wl) >> 32);
-#pragma unroll
-        for (int i = 0; i < kR; ++i) {
-            const uint32_t j = j0 + (uint32_t)i;
-            const bool valid = (uint32_t)i < c && j < W32;
-            const uint32_t d = from_top ? W32 - 1u - j : j;
-            const int src = (int)((valid && d < (uint32_t)kWave ? d : 0u) << 2);
-            const uint64_t bits = ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)hi32) << 32) |
-                                  (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)lo32);
-            w[i] = (valid && d < (uint32_t)kWave) ? __longlong_as_double((long long)bits) : 0.0;
-            lane_sum = i == 0 ? w[0] : lane_sum + w[i];
-        }
-    } else if (kRegChunk > 0) {
+    if (kRegChunk > 0) {
         if constexpr (kRegChunk >= 8) {
             int64_t vc;
             if (cold_draw(vc)) return vc;
@@ -912,64 +999,6 @@ __device__ __forceinline__ int64_t argmin_wide(const Coeffs<kMaxE, Acc> &C, int6
     }
     dbest = wave_min_i64(best);
     return wave_min_i32(best == dbest ? bv : INT32_MAX);
-}
-
-// expm1(x) for x <= 0 (the closed-form heat bath's expm1(-c W)).  Below -40, e^x is under half an
-// ulp of 1 and the value is -1 exactly.  On [-0.35, 0] the Taylor series of e^x - 1 to x^14 (error
-// below 2^-60 relative); otherwise e^x - 1, which cancels nothing because e^x <= 0.71.
-__device__ __forceinline__ double expm1_nonpos(double x) {
-    if (x < -40.0) return -1.0;
-    if (x < -0.35) return exp_nonpos(x) - 1.0;
-    // Horner on 1/k!, k = 14 .. 2, then x + x^2 (...)
-    double p = 1.0 / 87178291200.0;            // 1/14!
-    p = fma(p, x, 1.0 / 6227020800.0);         // 1/13!
-    p = fma(p, x, 1.0 / 479001600.0);          // 1/12!
-    p = fma(p, x, 1.0 / 39916800.0);           // 1/11!
-    p = fma(p, x, 1.0 / 3628800.0);            // 1/10!
-    p = fma(p, x, 1.0 / 362880.0);             // 1/9!
-    p = fma(p, x, 1.0 / 40320.0);              // 1/8!
-    p = fma(p, x, 1.0 / 5040.0);               // 1/7!
-    p = fma(p, x, 1.0 / 720.0);                // 1/6!
-    p = fma(p, x, 1.0 / 120.0);                // 1/5!
-    p = fma(p, x, 1.0 / 24.0);                 // 1/4!
-    p = fma(p, x, 1.0 / 6.0);                  // 1/3!
-    p = fma(p, x, 0.5);                        // 1/2!
-    return fma(p * x, x, x);
-}
-
-// log1p(y) for -1 < y <= 0 (the closed-form heat bath's log1p(U m)).  u = 1 + y rounded; log(u)
-// from u = f 2^e with f in [sqrt(1/2), sqrt(2)) and log f = 2 atanh(s), s = (f - 1)/(f + 1),
-// |s| <= 0.1716, by its odd series to s^21 (error below 2^-62 relative); the rounding of u is
-// put back to first order, log1p(y) = log(u) + (y - (u - 1)) / u (Kahan's correction).
-__device__ __forceinline__ double log1p_nonpos(double y) {
-    if (y == 0.0) return 0.0;
-    if (y <= -1.0) return -__builtin_huge_val();
-    const double u = 1.0 + y;
-    const double corr = (y - (u - 1.0)) * __builtin_amdgcn_rcp(u);
-    int e = __builtin_amdgcn_frexp_exp(u);
-    double f = __builtin_amdgcn_frexp_mant(u);  // [0.5, 1)
-    if (f < 0.70710678118654752) {
-        f = f + f;
-        e -= 1;
-    }
-    const double s = (f - 1.0) / (f + 1.0);
-    const double s2 = s * s;
-    double r = 1.0 / 21.0;
-    r = fma(r, s2, 1.0 / 19.0);
-    r = fma(r, s2, 1.0 / 17.0);
-    r = fma(r, s2, 1.0 / 15.0);
-    r = fma(r, s2, 1.0 / 13.0);
-    r = fma(r, s2, 1.0 / 11.0);
-    r = fma(r, s2, 1.0 / 9.0);
-    r = fma(r, s2, 1.0 / 7.0);
-    r = fma(r, s2, 1.0 / 5.0);
-    r = fma(r, s2, 1.0 / 3.0);
-    const double ln2_hi = 0.6931471803691238;    // ln 2 rounded to 32 bits: e * ln2_hi is exact
-    const double ln2_lo = 1.9082149292705877e-10;  // ln 2 - ln2_hi
-    const double ed = (double)e;
-    const double two_s = s + s;
-    // log u = e ln2_hi + (2 s + (2 s s^2 r + e ln2_lo)) + corr
-    return fma(ed, ln2_hi, two_s + (fma(two_s * s2, r, ed * ln2_lo) + corr));
 }
 
 // Heat bath for a variable whose energy difference is linear, dE(v) = a (v - z_k) (Sec. 3.3.2,
@@ -1289,12 +1318,14 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
 // ------------------------------------------------------------------------------------------------
 // kThreads: 512 (up to 8 waves per replica) or 1024 (16 waves; fewer registers per lane, so only
 // the variants that need no more than 128 VGPRs are built that way).
-// The generic-record Metropolis and OTM variants (the HUIO workloads) are held to 128 VGPRs, four
-// waves per SIMD: their cold paths (long terms, the wide-range argmin) would otherwise raise the
-// register count past 128 and cost a wave per SIMD on every problem.
+// The generic-record Metropolis and OTM variants (the HUIO workloads) and the heat bath of linear
+// variables are held to 128 VGPRs, four waves per SIMD: their cold paths (long terms, the wide-range
+// argmin, the draw in double precision) would otherwise raise the register count past 128 and cost a
+// wave per SIMD on every problem.
 template <int kRule, bool kStateInLds, int kRegChunk, int kMaxE, typename Acc, int kThreads>
-__global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 && kRule != SA_HEAT_BATH &&
-                                             kRule != SA_HEAT_BATH_CLOSED) ? 4 : 1)
+__global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &&
+                                             ((kRule != SA_HEAT_BATH && kRule != SA_HEAT_BATH_CLOSED) ||
+                                              (kRule == SA_HEAT_BATH && kMaxE == 1))) ? 4 : 1)
     anneal_kernel(AnnealArgs A) {
     extern __shared__ int32_t lds_state[];
     const int lane = (int)(threadIdx.x & (kWave - 1));

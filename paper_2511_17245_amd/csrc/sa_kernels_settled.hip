@@ -8,9 +8,11 @@ namespace {
 
 using SettledFn = void (*)(AnnealArgs);
 
-// Heat-bath visits: weights per lane in registers up to 8 (kRegChunk), recomputed above.
+// Heat-bath visits: linear variables need no weights; with powers, weights per lane in registers up to 8
+// (kRegChunk), recomputed above.
 template <bool kDense, int kRule, int kMaxE, typename Acc>
 SettledFn pick_chunk(int32_t max_width) {
+    if constexpr (kMaxE == 1) return settled_kernel<kDense, kRule, 0, kMaxE, Acc>;
     if (max_width <= 2 * kWave) return settled_kernel<kDense, kRule, 2, kMaxE, Acc>;
     if (max_width <= 8 * kWave) return settled_kernel<kDense, kRule, 8, kMaxE, Acc>;
     return settled_kernel<kDense, kRule, 0, kMaxE, Acc>;

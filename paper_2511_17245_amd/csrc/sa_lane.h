@@ -30,75 +30,6 @@
 namespace sa {
 namespace {
 
-// Cumulative weights in value order, by one lane: the value drawn where the closed form cannot tell.
-__device__ __forceinline__ uint32_t linear_draw_by_sums(bool from_top, double slope, uint32_t W, double beta, double U) {
-    double total = 0.0;
-    for (uint32_t j = 0; j < W; ++j) total += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
-    const double thr = U * total;
-    double run = 0.0;
-    for (uint32_t j = 0; j < W; ++j) {
-        run += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
-        if (run > thr) return j;
-    }
-    return W - 1u;
-}
-
-// The closed form in double precision; it errs by some ulp of W, so a step nearer than 1e-10 + 1e-14 W is
-// left to the sums (above 65536 values, whose sums round as much as that, it is taken as it is).
-__device__ __forceinline__ uint32_t linear_draw_double(bool from_top, double slope, uint32_t W, double beta, double U) {
-    const double c = beta * slope, Wd = (double)W;
-    const double m = expm1_nonpos(-(c * Wd));
-    const double L = log1p_nonpos((from_top ? 1.0 - U : U) * m) / c;
-    const double x = from_top ? Wd + L : -L;
-    const double near = rint(x);
-    if (W <= 65536u && !(__builtin_fabs(x - near) > 1e-10 + 1e-14 * Wd) && near > 0.5 && near < Wd - 0.5)
-        return linear_draw_by_sums(from_top, slope, W, beta, U);
-    return !(x > 0.0) ? 0u : x >= Wd ? W - 1u : (uint32_t)ceil(x) - 1u;
-}
-
-// Heat-bath draw of a variable with dE(v) = a (v - z_k): the first value whose cumulative weight exceeds
-// U times the total.  Index i = ceil(x) - 1 with x = -log1p(P m) / c from the lower end for a > 0, W + the
-// same for a < 0; c = beta |a|, m = expm1(-c W), P = U or 1 - U.
-//
-// In single precision: m from the series of expm1 (c W < 1/2; relative error below 1e-6 with the
-// rounding of c W) or e^-cW - 1 (below 1e-6 as |m| > 0.39); y = P m to 2e-6; log1p(y) from the series of
-// 2 atanh(y / (2 + y)) (|y| < 0.3, where log1p passes on at most 1.2 of y's relative error: 4e-6 in all) or
-// log(1 + y), off by 2e-6 |y| / (1 + y) and by 1e-6 of itself.  `err` is at least twice that.
-__device__ __forceinline__ int64_t linear_draw(int64_t a, int64_t lo, uint32_t W, double beta, double U) {
-    const bool from_top = a < 0;
-    const double slope = (double)(from_top ? -a : a);
-    const double c = beta * slope;
-    const float cf = (float)c, Wf = (float)W;
-    const float t = cf * Wf;
-    const float series = -t * (1.0f - t * (0.5f - t * (0.16666667f - t * (0.041666667f - t * (0.0083333333f - t * 0.0013888889f)))));
-    const float m = t < 0.5f ? series : __builtin_amdgcn_exp2f(t * -1.4426950f) - 1.0f;
-    const float y = (float)(from_top ? 1.0 - U : U) * m;
-    const float s = y * __builtin_amdgcn_rcpf(2.0f + y), s2 = s * s;
-    const float near0 = 2.0f * s * (1.0f + s2 * (0.33333333f + s2 * (0.2f + s2 * (0.14285714f + s2 * 0.11111111f))));
-    const float u = 1.0f + y;
-    const bool small = y > -0.3f;
-    const float L = small ? near0 : __builtin_amdgcn_logf(u) * 0.69314718f;
-    const float ic = __builtin_amdgcn_rcpf(cf);
-    const float aL = -L;
-    const float err = (small ? 1e-5f * aL : 5e-6f * __builtin_amdgcn_rcpf(u) + 4e-6f * aL) * ic + 1e-6f * Wf;
-    const float x = from_top ? Wf - aL * ic : aL * ic;
-    const float step = __builtin_rintf(x);
-    // a NaN or an infinity anywhere (c = 0, 1 + y = 0) fails the comparison; steps 0 and W decide nothing
-    const bool sure = W < (1u << 20) && err < 0.25f &&
-                      (__builtin_fabsf(x - step) > err || step < 0.5f || step > Wf - 0.5f) && c > 1e-30;
-    uint32_t i = x <= 0.0f ? 0u : (uint32_t)__builtin_ceilf(x) - 1u;
-    i = i < W ? i : W - 1u;
-    if (!sure) {
-        if (!(c > 0.0)) {   // every weight is 1: the count of v - l + 1 <= U W
-            i = (uint32_t)(U * (double)W);
-            i = i < W ? i : W - 1u;
-        } else {
-            i = linear_draw_double(from_top, slope, W, beta, U);
-        }
-    }
-    return lo + (int64_t)i;
-}
-
 constexpr int kLaneAhead = kLaneReach;   // records of the next chunk loaded one round ahead
 
 // A wave's chunk in one round: the chunk (-1: none; the wave's lanes idle), its first row of records and its
