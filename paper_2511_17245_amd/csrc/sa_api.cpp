@@ -464,11 +464,6 @@ int choose_lanes(int32_t quads, int requested, int waves_per_replica, bool eligi
     return (int64_t)n_slots * 2 >= (int64_t)quads * (int64_t)n_levels ? 4 : 64;
 }
 
-int reg_chunk_class(int32_t max_width) {
-    const int64_t chunk = ((int64_t)max_width + 63) / 64;
-    return chunk <= 1 ? 1 : chunk <= 2 ? 2 : chunk <= 8 ? 8 : chunk <= kHeatBathRegChunk ? 32 : 0;
-}
-
 }  // namespace sa
 
 namespace {

@@ -289,8 +289,6 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         d.s_end = d.n_sweeps;
         d.resume = 0;
         d.rule = p.rule;
-        const int rc_class = sa::reg_chunk_class(p.info.max_width);
-        d.chunk = rc_class == 32 ? 0 : rc_class;
         d.key0 = (uint32_t)problems[i].seed;
         d.key1 = (uint32_t)(problems[i].seed >> 32);
         d.instance_id = problems[i].instance_id;

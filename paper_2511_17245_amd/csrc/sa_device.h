@@ -678,6 +678,69 @@ __device__ __forceinline__ double wave_shift_up1_zero(double x, ScanCarry &cy) {
     return __longlong_as_double((long long)cy.sh);
 }
 
+// Inclusive scan of one float per lane, in the same network's order.
+__device__ __forceinline__ float wave_scan_f32(float x) {
+    auto step = [](float v, uint32_t shifted) { return v + __uint_as_float(shifted); };
+    x = step(x, dpp32<0x111, 0xf, 0xf>(__float_as_uint(x), 0));
+    x = step(x, dpp32<0x112, 0xf, 0xf>(__float_as_uint(x), 0));
+    x = step(x, dpp32<0x114, 0xf, 0xf>(__float_as_uint(x), 0));
+    x = step(x, dpp32<0x118, 0xf, 0xf>(__float_as_uint(x), 0));
+    x = step(x, dpp32<0x142, 0xa, 0xf>(__float_as_uint(x), 0));
+    x = step(x, dpp32<0x143, 0xc, 0xf>(__float_as_uint(x), 0));
+    return x;
+}
+
+// Heat-bath draw among at most 8 * 64 values in single precision, value j in lane j / c as in
+// heat_bath_pick; x(j) >= 0 is the energy above the range's minimum.  Returns the index drawn, or -1 where a
+// cumulative weight lies so near the threshold that the precision could decide.
+//
+// The bound: x and beta / ln 2 are rounded and multiplied, 1.8e-7 of the exponent in all, so a weight errs by
+// 1.8e-7 t w + 1.2e-7 w (t = beta x; exp2 to an ulp).  Over a sum of weights this is 1.8e-7 <t> + 1.2e-7 of the
+// total, and <t> <= ln W <= 6.3 (the entropy of W states bounds it, the total being at least 1): 1.3e-6.
+// The additions (8 in the lane, 6 in the scan, one each for the lanes before and the threshold) err by 6e-8
+// of the total each: 1e-6.  The threshold carries the total's error again: below 5e-6 in all; the margin
+// is 1e-5.  A NaN or an infinity fails the comparison.
+//
+// A double-precision exponential takes some 35 instructions, a single-precision one takes one: N = 100
+// fully connected, W = 201 (squares; four values per lane), 300 sweeps x 1000 reads 32.2 to 19.4 ms; 32
+// random-interaction problems of W = 201 20.1 to 17.8 ms.  With one or two values per lane the energies are
+// evaluated once and the minimum taken over the wave (the vertex cost more: N = 30, W = 17 +10 %).
+constexpr uint32_t kSingleMost = 8;
+template <uint32_t kMost, typename XF>
+__device__ __forceinline__ int32_t draw_single(uint32_t W, uint32_t c, uint32_t j0, double beta, double U, XF &&x) {
+    const float kf = (float)(beta * -1.4426950408889634);
+    float w[kMost], sum = 0.0f;
+#pragma unroll
+    for (uint32_t i = 0; i < kMost; ++i) {
+        w[i] = 0.0f;
+        if (i < c) {   // uniform
+            const uint32_t j = j0 + i;
+            const float e = __builtin_amdgcn_exp2f(kf * (float)x(i, j < W ? j : W - 1u));
+            w[i] = j < W ? e : 0.0f;
+            sum += w[i];
+        }
+    }
+    const float incl = wave_scan_f32(sum);
+    const float total = __uint_as_float(lane_read32(__float_as_uint(incl), kWave - 1));
+    const float before = __uint_as_float(dpp32<0x138, 0xf, 0xf>(__float_as_uint(incl), 0));
+    const float thr = (float)U * total, tol = 1e-5f * total;
+    float run = before;
+    int32_t hit = -1;
+    bool near = false;
+#pragma unroll
+    for (uint32_t i = 0; i < kMost; ++i) {
+        if (i < c) {
+            run += w[i];
+            const bool valid = j0 + i < W;
+            near = near || (valid && !(__builtin_fabsf(run - thr) > tol));
+            hit = hit < 0 && valid && run > thr ? (int32_t)(j0 + i) : hit;
+        }
+    }
+    const uint64_t found = __ballot(hit >= 0);
+    if (__ballot(near) != 0 || found == 0) return -1;
+    return (int32_t)lane_read32((uint32_t)hit, __ffsll((unsigned long long)found) - 1);
+}
+
 // Heat-bath choice (Sec. 3.3.2) among all W values, with the fixed summation order: value j of the
 // range belongs to lane j / c (c = ceil(W/64)); lane sums are left to right; the lanes' sums are
 // combined by wave_scan_rows; the first value whose cumulative weight exceeds U * total is drawn
@@ -693,33 +756,53 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     // no term holds z_k to a power above one: the inverse of the distribution, whatever the width
     if (kMaxE == 1 || linear) return linear_draw(to_i64<Acc>(C.a[1]), lo, W32, beta, U);
     // Weights are taken relative to the minimum energy difference.
-    int64_t dmin = 0, dlane = INT64_MAX;   // dlane: the smallest dE of this lane's values
-    if (kMaxE == 2 && c > 8) {
-        // dE(v) = a2 v^2 + a1 v + const: over the lane's values its minimum is at an end or at an
-        // integer next to the vertex v = -a1 / (2 a2) (a2 > 0).  The vertex's index, computed in
-        // double, is within one of the exact one, so the integers floor(t) - 1 .. floor(t) + 2 hold
-        // the minimisers; every candidate is evaluated exactly.
-        if (j0 < W32) {
-            const uint32_t jh = j0 + c - 1u < W32 ? j0 + c - 1u : W32 - 1u;
-            const int64_t dl = poly_delta(C, zk, lo + (int64_t)j0), dh = poly_delta(C, zk, lo + (int64_t)jh);
-            dlane = dl < dh ? dl : dh;
-            const int64_t a1 = to_i64<Acc>(C.a[1]), a2 = to_i64<Acc>(C.a[kMaxE >= 2 ? 2 : 1]);
+    int64_t dmin = 0, dlane = INT64_MAX;   // dlane: the smallest dE of this lane's values (c > 8)
+    if (c <= 2) {   // uniform: each value's difference once, the minimum over the wave
+        int64_t d[2];
+        d[0] = poly_delta(C, zk, lo + (int64_t)(j0 < W32 ? j0 : W32 - 1u));
+        d[1] = c > 1 ? poly_delta(C, zk, lo + (int64_t)(j0 + 1u < W32 ? j0 + 1u : W32 - 1u)) : d[0];
+        const int64_t least = d[0] < d[1] ? d[0] : d[1];
+        dmin = sizeof(Acc) == 4 ? (int64_t)wave_min_i32((int32_t)least) : wave_min_i64(least);
+        const int32_t j = draw_single<2>(W32, c, j0, beta, U, [&](uint32_t i, uint32_t) -> double {
+            return sizeof(Acc) == 4 ? (double)((int32_t)d[i] - (int32_t)dmin) : (double)(d[i] - dmin);
+        });
+        if (j >= 0) return lo + j;
+    } else if constexpr (kMaxE == 2) {
+        // dE(v) = a2 v^2 + a1 v + const has its minimum at an end or, a2 > 0, at one of the two integers
+        // around -a1 / (2 a2): the computed vertex errs by less than would move it past an integer that
+        // is not a minimum itself.  dE(v) - dE(vm) = (v - vm) (a1 + a2 (v + vm)), an exact integer.
+        const int64_t hi = lo + W - 1, a1 = to_i64<Acc>(C.a[1]), a2 = to_i64<Acc>(C.a[2]);
+        const double a1d = (double)a1, a2d = (double)a2;
+        auto vertex_side = [&](int64_t first, int64_t last) -> int64_t {   // a minimiser within first .. last
             if (a2 > 0) {
-                const double t = -(double)a1 / (2.0 * (double)a2) - (double)lo;
-                if (t > (double)j0 - 2.0 && t < (double)jh + 2.0) {
-                    const int64_t f = (int64_t)__builtin_floor(t);
-#pragma unroll
-                    for (int e = -1; e <= 2; ++e) {
-                        const int64_t j = f + e;
-                        if (j >= (int64_t)j0 && j <= (int64_t)jh) {
-                            const int64_t d = poly_delta(C, zk, lo + j);
-                            dlane = d < dlane ? d : dlane;
-                        }
-                    }
-                }
+                double r = __builtin_amdgcn_rcp(a2d);
+                r = fma(r, fma(-a2d, r, 1.0), r);
+                const double t = -0.5 * a1d * r;
+                first = t < (double)first ? first : t > (double)last ? last : (int64_t)__builtin_floor(t);
+                last = first < last ? first + 1 : last;
             }
+            return poly_delta(C, zk, last) < poly_delta(C, zk, first) ? last : first;
+        };
+        const int64_t vm = vertex_side(lo, hi);   // uniform
+        dmin = poly_delta(C, zk, vm);
+        if (c <= kSingleMost) {   // uniform
+            const double vmd = (double)vm, lod = (double)lo;
+            const bool exact53 = sizeof(Acc) == 4 || (__builtin_fabs(a1d) < 0x1p53 && __builtin_fabs(a2d) < 0x1p53);
+            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
+                if (exact53) {   // the factors are exact, their sum and product rounded once
+                    const double vd = lod + (double)j;
+                    return (vd - vmd) * fma(a2d, vd + vmd, a1d);
+                }
+                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
+            });
+            if (j >= 0) return lo + j;
+        } else if (j0 < W32) {
+            const int64_t jl = lo + (int64_t)j0, jh = lo + (int64_t)(j0 + c - 1u < W32 ? j0 + c - 1u : W32 - 1u);
+            // the ends of the lane's values, and the vertex where it lies among them
+            const int64_t dl = poly_delta(C, zk, jl), dh = poly_delta(C, zk, jh);
+            dlane = dl < dh ? dl : dh;
+            if (vm >= jl && vm <= jh) dlane = dmin;
         }
-        dmin = wave_min_i64(dlane);
     } else {
         for (uint32_t i = 0; i < c; ++i) {
             const uint32_t j = j0 + i;
@@ -729,6 +812,12 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
             }
         }
         dmin = wave_min_i64(dlane);
+        if (c <= kSingleMost) {   // uniform
+            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
+                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
+            });
+            if (j >= 0) return lo + j;
+        }
     }
     // kRegChunk = 0 evaluates the weights in groups of kGroup independent exponentials (their
     // latencies overlap); they are still added one by one in value order
@@ -800,10 +889,8 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     double w[kR];
     double lane_sum = 0.0;
     if (kRegChunk > 0) {
-        if constexpr (kRegChunk >= 8) {
-            int64_t vc;
-            if (cold_draw(vc)) return vc;
-        }
+        int64_t vc;
+        if (c > kSingleMost && cold_draw(vc)) return vc;
 #pragma unroll
         for (int i = 0; i < kR; ++i) {
             // evaluated for every slot (at a clamped index past the range) so that the exps of a
@@ -815,7 +902,7 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
         }
     } else {
         int64_t vc;
-        if (cold_draw(vc)) return vc;
+        if (c > kSingleMost && cold_draw(vc)) return vc;
         for (uint32_t i = 0; i < c; i += kGroup) {
             double wv[kGroup];
 #pragma unroll
@@ -1416,8 +1503,8 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
 // repeatedly takes the next task from a global counter (tasks are ordered longest first).  A task
 // is kBatchWaves / G_p consecutive reads of one problem p: each read is annealed by a team of G_p
 // waves (G_p = 1: independent waves; G_p > 1: cooperating waves over the problem's window schedule,
-// as in the plain kernel).  Rule and heat-bath chunk class are dispatched per task; the exponent
-// class, integer width and state width are those of the whole batch.
+// as in the plain kernel).  The rule is dispatched per task; the exponent class, integer width and
+// state width are those of the whole batch.
 // ------------------------------------------------------------------------------------------------
 template <int kMaxE, typename Acc, typename ZT>
 __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B) {
@@ -1504,19 +1591,9 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         if (D.rule == SA_METROPOLIS) {
             E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane, s_next);
         } else if (D.rule == SA_HEAT_BATH) {
-            switch (D.chunk) {
-                case 1: E += sweep_replica<SA_HEAT_BATH, true, 1, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                case 2: E += sweep_replica<SA_HEAT_BATH, true, 2, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                case 8: E += sweep_replica<SA_HEAT_BATH, true, 8, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                default: E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-            }
+            E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next);
         } else if (D.rule == SA_HEAT_BATH_CLOSED) {
-            switch (D.chunk) {
-                case 1: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 1, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                case 2: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 2, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                case 8: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 8, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-                default: E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next); break;
-            }
+            E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next);
         } else {
             E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane, s_next);
         }
@@ -1539,25 +1616,13 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
 // Kernel entry of the plain launch.
 using AnnealKernel = void (*)(AnnealArgs);
 
-// Heat bath: the weights of ceil(W/64) <= kRegChunk values per lane stay in registers (the
-// unrolled loops then cost kRegChunk steps); wider ranges recompute them (kRegChunk = 0).
+// Heat bath of powers: with 9 to 32 values per lane the weights stay in registers (the unrolled loops
+// cost 32 steps); fewer are drawn in single precision, and recomputed where that cannot decide, as wider
+// ranges are (kRegChunk = 0).
 template <int kRule, int kMaxE, typename Acc>
 AnnealKernel pick_heat_bath_lds(int reg_chunk) {
-    switch (reg_chunk) {
-        case 1: return anneal_kernel<kRule, true, 1, kMaxE, Acc, 512>;
-        case 2: return anneal_kernel<kRule, true, 2, kMaxE, Acc, 512>;
-        case 8: return anneal_kernel<kRule, true, 8, kMaxE, Acc, 512>;
-        case 32: return anneal_kernel<kRule, true, 32, kMaxE, Acc, 512>;
-        default: return anneal_kernel<kRule, true, 0, kMaxE, Acc, 512>;
-    }
-}
-template <int kRule, int kMaxE, typename Acc>
-AnnealKernel pick_heat_bath_lds_16(int reg_chunk) {
-    switch (reg_chunk) {
-        case 1: return anneal_kernel<kRule, true, 1, kMaxE, Acc, 1024>;
-        case 2: return anneal_kernel<kRule, true, 2, kMaxE, Acc, 1024>;
-        default: return anneal_kernel<kRule, true, 8, kMaxE, Acc, 1024>;
-    }
+    if (reg_chunk == kHeatBathRegChunk) return anneal_kernel<kRule, true, kHeatBathRegChunk, kMaxE, Acc, 512>;
+    return anneal_kernel<kRule, true, 0, kMaxE, Acc, 512>;
 }
 
 }  // namespace

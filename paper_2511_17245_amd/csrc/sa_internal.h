@@ -446,7 +446,6 @@ struct BatchInst {
     int32_t s_begin, s_end;  // sweeps of this launch (a server chunk, or the whole schedule)
     int32_t resume;          // 1: start from the states in z_out and energies in e_out (an earlier chunk's)
     int32_t rule;
-    int32_t chunk;           // heat bath: register chunk class (1, 2, 8; 0 = recompute)
     uint32_t key0, key1, instance_id;
     int32_t *z_out;          // n_reads x n (device)
     int64_t *e_out;          // n_reads (device)

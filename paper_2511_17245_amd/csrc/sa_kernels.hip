@@ -43,7 +43,7 @@ using KernelFn = AnnealKernelFn;
 // when every variable takes the closed form.
 bool sixteen_waves_ok(int rule, bool in_lds, int reg_chunk, int maxe_class) {
     if (!in_lds || maxe_class > 2) return false;
-    if (rule == SA_HEAT_BATH) return maxe_class == 1 || (reg_chunk >= 1 && reg_chunk <= 8);
+    if (rule == SA_HEAT_BATH) return reg_chunk == 0;
     if (rule == SA_HEAT_BATH_CLOSED) return maxe_class == 1;
     if (rule == SA_OPT_METROPOLIS || rule == SA_METROPOLIS) return reg_chunk == 0;
     return true;
@@ -86,8 +86,7 @@ LaunchChoice choose_launch(int rule, int32_t n, int32_t n_reads, int32_t max_wid
     const bool otm_wide = rule == SA_OPT_METROPOLIS && max_width > otm_enum_max;
     const int reg_in_lds =
         heat_bath
-            ? max_exp <= 1 ? 0   // (every draw by the inverse of the distribution: no weights)
-            : (chunk <= 1 ? 1 : chunk <= 2 ? 2 : chunk <= 8 ? 8 : chunk <= kHeatBathRegChunk ? 32 : 0)
+            ? (max_exp > 1 && chunk > 8 && chunk <= kHeatBathRegChunk ? kHeatBathRegChunk : 0)
             : (otm_wide || (rule == SA_METROPOLIS && dense) ? 1 : 0);
     if (win_waves == 16 && !(shared_state_bytes(n, 16) <= max_lds &&
                              sixteen_waves_ok(rule, true, reg_in_lds, maxe_class_of(max_exp))))

@@ -10,8 +10,8 @@ AnnealKernelFn heat_bath_kernel(bool in_lds, int reg_chunk, int maxe_class, bool
         if (maxe_class == 1)
             return narrow ? anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint32_t, 1024>
                           : anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint64_t, 1024>;
-        return narrow ? pick_heat_bath_lds_16<SA_HEAT_BATH, 2, uint32_t>(reg_chunk)
-                      : pick_heat_bath_lds_16<SA_HEAT_BATH, 2, uint64_t>(reg_chunk);
+        return narrow ? anneal_kernel<SA_HEAT_BATH, true, 0, 2, uint32_t, 1024>
+                      : anneal_kernel<SA_HEAT_BATH, true, 0, 2, uint64_t, 1024>;
     }
     if (!in_lds) return anneal_kernel<SA_HEAT_BATH, false, 0, kMaxExpPoly, uint64_t, 512>;
     switch (maxe_class) {

@@ -8,22 +8,12 @@ namespace {
 
 using SettledFn = void (*)(AnnealArgs);
 
-// Heat-bath visits: linear variables need no weights; with powers, weights per lane in registers up to 8
-// (kRegChunk), recomputed above.
-template <bool kDense, int kRule, int kMaxE, typename Acc>
-SettledFn pick_chunk(int32_t max_width) {
-    if constexpr (kMaxE == 1) return settled_kernel<kDense, kRule, 0, kMaxE, Acc>;
-    if (max_width <= 2 * kWave) return settled_kernel<kDense, kRule, 2, kMaxE, Acc>;
-    if (max_width <= 8 * kWave) return settled_kernel<kDense, kRule, 8, kMaxE, Acc>;
-    return settled_kernel<kDense, kRule, 0, kMaxE, Acc>;
-}
-
 template <bool kDense, int kMaxE, typename Acc>
 SettledFn pick_rule(int rule, int32_t max_width, int32_t otm_enum_max) {
     switch (rule) {
         case SA_METROPOLIS: return settled_kernel<kDense, SA_METROPOLIS, 0, 1, Acc>;
         case SA_HEAT_BATH:
-        case SA_HEAT_BATH_CLOSED: return pick_chunk<kDense, SA_HEAT_BATH, kMaxE, Acc>(max_width);
+        case SA_HEAT_BATH_CLOSED: return settled_kernel<kDense, SA_HEAT_BATH, 0, kMaxE, Acc>;
         default:
             return max_width > otm_enum_max ? settled_kernel<kDense, SA_OPT_METROPOLIS, 1, kMaxE < 4 ? kMaxE : 4, Acc>
                                             : settled_kernel<kDense, SA_OPT_METROPOLIS, 0, kMaxE < 4 ? kMaxE : 4, Acc>;

@@ -446,8 +446,6 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         d.s_end = r->next_sweep + sweeps[i];
         d.resume = r->next_sweep > 0 ? 1 : 0;
         d.rule = p.rule;
-        const int cls = sa::reg_chunk_class(p.info.max_width);
-        d.chunk = cls == 32 ? 0 : cls;
         d.key0 = (uint32_t)r->seed;
         d.key1 = (uint32_t)(r->seed >> 32);
         d.instance_id = r->instance_id;

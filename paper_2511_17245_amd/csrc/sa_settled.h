@@ -617,21 +617,17 @@ __global__ void __launch_bounds__(kWave) settled_batch_kernel(const BatchInst *i
     S.small = R.P.coef32 && D.z30;
     S.closed = D.rule == SA_HEAT_BATH_CLOSED;
     int64_t E = 0;
-    auto go = [&](auto dense, auto rule, auto chunk, auto maxe) {
-        s = settled_run<decltype(dense)::value, decltype(rule)::value, decltype(chunk)::value, decltype(maxe)::value, Acc>(
+    auto go = [&](auto dense, auto rule, auto maxe) {
+        s = settled_run<decltype(dense)::value, decltype(rule)::value, 0, decltype(maxe)::value, Acc>(
             S, z, lane, s, D.s_end, D.off_c, D.off_c2, D.off_m, (uint32_t)D.leave, E);
     };
     auto by_rule = [&](auto dense, auto maxe, auto otm_e) {
         if (D.rule == SA_METROPOLIS) {
-            go(dense, Int<SA_METROPOLIS>(), Int<0>(), Int<1>());
+            go(dense, Int<SA_METROPOLIS>(), Int<1>());
         } else if (D.rule == SA_OPT_METROPOLIS) {
-            go(dense, Int<SA_OPT_METROPOLIS>(), Int<0>(), otm_e);
-        } else if (D.chunk == 1 || D.chunk == 2) {
-            go(dense, Int<SA_HEAT_BATH>(), Int<2>(), maxe);
-        } else if (D.chunk == 8) {
-            go(dense, Int<SA_HEAT_BATH>(), Int<8>(), maxe);
+            go(dense, Int<SA_OPT_METROPOLIS>(), otm_e);
         } else {
-            go(dense, Int<SA_HEAT_BATH>(), Int<0>(), maxe);
+            go(dense, Int<SA_HEAT_BATH>(), maxe);
         }
     };
     if (R.P.dense) by_rule(Int<1>(), Int<2>(), Int<2>());

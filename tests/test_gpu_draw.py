@@ -48,3 +48,33 @@ def test_linear(width):
     prob.upper[:] = lo + width - 1
     for G in (1, 2):
         check(f"linear W {width} G {G}", prob, betas(float(width) ** 3), 2 if width > 4096 else 8, 91 + width, G)
+
+
+@pytest.mark.parametrize("width", [2, 63, 64, 65, 511, 512, 513, 2048, 2049])
+@pytest.mark.parametrize("kind", ["squares", "dense", "powers"])
+def test_powers(width, kind):
+    """Powers above one: single precision up to 512 values, double beyond; minima inside the range, at an
+    end and (negative squares) at both."""
+    g = np.random.Generator(np.random.PCG64(width))
+    lo = -(width // 3)
+    scale = float(width) ** 2 * 10
+    if kind == "squares":
+        prob = I.erdos_renyi_quio(12, 3.0, lo, lo + width - 1, 10, 20, g)
+        terms = [(int(c), [i, i]) for i, c in enumerate(g.integers(-6, 7, 12))]
+        prob = I.from_terms(12, terms + [(3, [0, 1]), (-2, [1, 2]), (5, [3]), (-7, [4])], prob.lower, prob.upper)
+    elif kind == "dense":
+        prob = I.dense_quio(12, lo, lo + width - 1, 10, 10, g)
+    else:
+        prob = I.random_huio(12, 40, [1, 2, 3], lo, lo + width - 1, 5, g)
+        scale *= width
+    for G in (1, 2):
+        if kind == "dense" and G == 2:
+            continue
+        check(f"{kind} W {width} G {G}", prob, betas(scale), 8, 17 + width, G)
+
+
+def test_single_precision_over_many_draws():
+    """Enough draws that thousands of them pass near a step of the distribution."""
+    g = np.random.Generator(np.random.PCG64(5))
+    prob = I.dense_quio(30, -100, 100, 10, 10, g)
+    check("many draws", prob, np.geomspace(1e-5, 1e-1, 120), 400, 3, 1)
