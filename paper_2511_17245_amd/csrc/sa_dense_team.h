@@ -15,8 +15,8 @@
 //
 // What bounds it: the chain of one draw (LDS reads, minimum, exponentials, scan, three barriers): 50 %
 // of the wave time waits, 330 VALU instructions per wave and hot draw.  Measured: dense N = 4096,
-// W = 2001 heat bath, 20 sweeps x 16 reads 467 to 109 ms (hot sweeps 33 to 9.5 ms, settled ones 12 to
-// 0.4 ms); a served burst of 18 HUIO and two dense N = 2048 requests 321 to 115 ms.
+// W = 2001 heat bath, 20 sweeps x 16 reads 467 to 100 ms (109 before the draws in single precision) (hot sweeps 33 to 9.5 ms, settled ones 12 to
+// 0.4 ms); a served burst of 18 HUIO and two dense N = 2048 requests 321 to 112 ms.
 #pragma once
 
 #include "sa_settled.h"
@@ -95,7 +95,8 @@ __device__ __forceinline__ void team_update(const DevProblem &P, C *c1, int32_t 
 }
 
 // A heat-bath draw by enumeration, by the whole team: value j of the range belongs to thread j / c,
-// c = ceil(W / nthr) <= 4.  inv = -1 / (2 a2) (a2 > 0).  Two barriers; every thread returns the drawn value.
+// c = ceil(W / nthr) <= 4.  inv = -1 / (2 a2) (a2 > 0).  Two barriers (four where single precision cannot
+// decide); every thread returns the drawn value.
 // Weights are relative to the smallest dE, that of vm: an end of the range, or (a2 > 0) one of the two
 // integers around the vertex -a1 / (2 a2), whose computed value errs by less than would move it past an
 // integer that is not the minimum itself; dE(v) - dE(vm) = (v - vm) (a1 + a2 (v + vm)), an exact integer.
@@ -123,21 +124,68 @@ __device__ __forceinline__ int64_t team_draw(int64_t a1, int64_t a2, double inv,
     const uint32_t c = (W32 + (uint32_t)nthr - 1u) / (uint32_t)nthr;
     const uint32_t j0 = (uint32_t)tid * c;
     const double a1d = (double)a1, a2d = (double)a2, vmd = (double)vm;
+    auto above = [&](uint32_t j) -> double {   // value j's energy above the minimum
+        const int64_t v = lo + (int64_t)j;
+        if (exact53) {   // every product and sum below 2^53
+            const double vd = (double)(int32_t)v;
+            return (vd - vmd) * fma(a2d, vd + vmd, a1d);
+        }
+        return (double)rise(v, vm);
+    };
+    const int nw = nthr / kWave;
+    {
+        // In single precision first, as draw_single: at most four additions per lane, six in the scan and
+        // four in the waves' scan, <t> <= ln 4096 = 8.4, so below 5.5e-6 of the total; the margin is 1.2e-5.
+        // Only the wave that holds the threshold decides: cumulative weights never decrease, so where its
+        // first and last are clear of the threshold the other waves' are too.
+        const float kf = (float)(beta * -1.4426950408889634);
+        float f[kMost], sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kMost; ++i) {
+            f[i] = 0.0f;
+            if ((uint32_t)i < c) {   // uniform
+                const uint32_t j = j0 + (uint32_t)i;
+                const float e = __builtin_amdgcn_exp2f(kf * (float)above(j < W32 ? j : W32 - 1u));
+                f[i] = j < W32 ? e : 0.0f;
+                sum += f[i];
+            }
+        }
+        const float incl = wave_scan_f32(sum);
+        if (lane == kWave - 1) X->sum[turn][wave] = (double)incl;
+        window_barrier();
+        const float ws = wave_scan_f32(lane < nw ? (float)X->sum[turn][lane] : 0.0f);
+        auto of = [&](float x, int l) { return __uint_as_float(lane_read32(__float_as_uint(x), l)); };
+        const float total = of(ws, nw - 1), thr = (float)U * total, tol = 1.2e-5f * total;
+        const uint64_t past = __ballot(lane < nw && ws > thr);
+        const int holder = past ? __ffsll((unsigned long long)past) - 1 : nw - 1;
+        if (wave == holder) {
+            const float first = wave > 0 ? of(ws, wave - 1) : 0.0f;
+            float run = first + __uint_as_float(dpp32<0x138, 0xf, 0xf>(__float_as_uint(incl), 0));
+            int32_t hit = -1;
+            bool near = wave > 0 && !(__builtin_fabsf(first - thr) > tol);
+#pragma unroll
+            for (int i = 0; i < kMost; ++i) {
+                run += f[i];
+                const bool in = (uint32_t)i < c && j0 + (uint32_t)i < W32;
+                near = near || (in && !(__builtin_fabsf(run - thr) > tol));
+                hit = hit < 0 && in && run > thr ? (int32_t)(j0 + (uint32_t)i) : hit;
+            }
+            const uint64_t m = __ballot(hit >= 0);
+            const bool sure = m != 0 && __ballot(near) == 0;
+            const int32_t j = m ? (int32_t)lane_read32((uint32_t)hit, __ffsll((unsigned long long)m) - 1) : 0;
+            if (lane == 0) X->drawn[turn] = sure ? j : -1;
+        }
+        window_barrier();
+        const int32_t j = X->drawn[turn];
+        if (j >= 0) return lo + (int64_t)j;   // uniform over the team
+    }
     double w[kMost], lane_sum = 0.0;
 #pragma unroll
     for (int i = 0; i < kMost; ++i) {
         w[i] = 0.0;
         if ((uint32_t)i < c) {   // uniform
             const uint32_t j = j0 + (uint32_t)i;
-            const int64_t v = lo + (int64_t)(j < W32 ? j : W32 - 1u);
-            double x;
-            if (exact53) {   // every product and sum below 2^53
-                const double vd = (double)(int32_t)v;
-                x = (vd - vmd) * fma(a2d, vd + vmd, a1d);
-            } else {
-                x = (double)rise(v, vm);
-            }
-            const double e = exp_nonpos(-(beta * x));
+            const double e = exp_nonpos(-(beta * above(j < W32 ? j : W32 - 1u)));
             w[i] = j < W32 ? e : 0.0;
             lane_sum += w[i];
         }
@@ -146,7 +194,6 @@ __device__ __forceinline__ int64_t team_draw(int64_t a1, int64_t a2, double inv,
     if (lane == kWave - 1) X->sum[turn][wave] = incl;
     window_barrier();
     // every wave: the running sums of the waves' sums, in lanes 0 .. 15
-    const int nw = nthr / kWave;
     const double ws = wave_scan_rows(lane < nw ? X->sum[turn][lane] : 0.0, cy);
     const double thr = U * lane_double(ws, nw - 1);
     const uint64_t past = __ballot(lane < nw && ws > thr);
@@ -169,10 +216,10 @@ __device__ __forceinline__ int64_t team_draw(int64_t a1, int64_t a2, double inv,
         } else {
             j = ((uint32_t)wave + 1u) * kWave * c - 1u;
         }
-        if (lane == 0) X->drawn[turn] = (int32_t)(lo + (int64_t)(j < W32 ? j : W32 - 1u));
+        if (lane == 0) X->drawn[turn] = (int32_t)(j < W32 ? j : W32 - 1u);
     }
     window_barrier();
-    return (int64_t)X->drawn[turn];
+    return lo + (int64_t)X->drawn[turn];
 }
 
 // The sweeps of one replica by its team.  Returns in E the energy changes (the same in every thread).
@@ -272,16 +319,15 @@ __device__ __forceinline__ void team_sweeps(const TeamCtx &T, ZT *z, C *c1, Team
                     d = de(v);
                     want = v != zk && metropolis_accept(d, beta, U) ? 1 : 0;
                 } else if (!hot) {
-                    if (closed && linear) {
-                        v = heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1);
+                    if (linear) {
+                        v = closed ? heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1) : linear_draw(a1, lo, W32, beta, U);
                         d = de(v);
                         want = v != zk ? 1 : 0;
                     } else {
                         const double M = margin();
                         if (M > 0.0) {
                             const double ex = exp_nonpos(-(beta * M));
-                            const double rho = linear     ? geometric_tail(ex)
-                                               : a2 >= 0 ? 2.0 * geometric_tail(ex) : (double)(W32 - 1u) * ex;
+                            const double rho = a2 >= 0 ? 2.0 * geometric_tail(ex) : (double)(W32 - 1u) * ex;
                             want = heat_bath_stays(rho, U) ? 0 : 2;
                         }
                     }
@@ -314,8 +360,9 @@ __device__ __forceinline__ void team_sweeps(const TeamCtx &T, ZT *z, C *c1, Team
                         const double Uj = lane_double(U, j);
                         const int64_t a1j = (int64_t)lane_read64((uint64_t)a1, j);
                         const int64_t a2j = (int64_t)lane_read64((uint64_t)a2, j);
-                        if (closed && a2j == 0) {
-                            vj = heat_bath_closed(a1j, loj, Wj, beta, Uj, lane_read32(x1, j));
+                        if (a2j == 0) {
+                            vj = closed ? heat_bath_closed(a1j, loj, Wj, beta, Uj, lane_read32(x1, j))
+                                        : linear_draw(a1j, loj, (uint32_t)Wj, beta, Uj);
                             apart = false;
                         } else {
                             vj = team_draw<kSmallC>(a1j, a2j, lane_double(inv, j), loj, Wj, beta, Uj, T.exact53, lane, wave, T.tid,

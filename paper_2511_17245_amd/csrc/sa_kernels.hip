@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(256) trace_prefix_kernel(uint64_t *trace, int3
 using KernelFn = AnnealKernelFn;
 
 // Variants built for 16 waves per replica (their register needs fit 128 VGPRs): states in LDS,
-// every exponent <= 2, at most 8 heat-bath weights per lane, and the closed-form heat bath only
+// every exponent <= 2, at most 8 or over 32 heat-bath values per lane, and the closed-form heat bath only
 // when every variable takes the closed form.
 bool sixteen_waves_ok(int rule, bool in_lds, int reg_chunk, int maxe_class) {
     if (!in_lds || maxe_class > 2) return false;

@@ -122,7 +122,6 @@ LaneLayout lane_layout(const LaneImage &im);
 void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image);
 // Uploads the inverse temperatures unless the device already holds the same array.
 int stage_beta(sa_plan *plan, const std::vector<double> &beta, hipStream_t stream);
-// Heat-bath register chunk class of a plan's widest range (1, 2, 8, 32, or 0 = recompute).
 // The plan's dependency levels (built and uploaded on first use).
 int get_levels(sa_plan *plan, sa_plan::Levels **out);
 // The common width of the level slots, or 0 when widths differ.
