@@ -119,15 +119,18 @@ typedef struct {
                                    with mix the 64-bit finaliser of SplitMix64.  Two runs of a chain
                                    part at the first sweep whose hashes differ.  Plain launches only
                                    (batches and the server do not trace). */
-    int32_t lanes_per_update;   /* heat bath: lanes that carry one update.  0: automatic.  64: one
+    int32_t lanes_per_update;   /* heat bath: lanes that carry one update.  0: automatic (for sparse
+                                   problems of pairs one lane per update, the lane kernel, from 16
+                                   sweeps on; else 4 or 64, dense problems by a team of waves).  64: one
                                    wavefront per update (the candidate values split over its lanes,
                                    the waves of a replica over schedule windows, as waves_per_replica
                                    says).  4: one quad of lanes per update, the 16 quads of each of a
                                    workgroup's 8 waves over the dependency levels of the sweep
                                    (sparse problems, exponents <= 2, ranges of at most 128 values,
                                    waves_per_replica 0; SA_EINVAL otherwise).  Both follow the
-                                   sequential sweep; they differ only in the order in which heat-bath
-                                   weights are added (a quad adds them in value order). */
+                                   sequential sweep; they differ only in how a heat-bath value is found
+                                   (a quad adds the weights in value order; a variable without powers
+                                   is drawn by the inverse of its distribution elsewhere). */
 } sa_opts;
 
 void sa_opts_default(sa_opts *opts);

@@ -19,9 +19,10 @@
 // What bounds it: in a settled sweep, the latency of one block's chain (slots, caches, decision: about
 // 250 cycles per 64 variables while all are frozen, 700 with their random words); before that, the
 // visits.  Measured, ordinary sweeps only against this: dense N = 100 Metropolis, 1000 sweeps x 16
-// reads 49.4 to 2.25 ms; FC p = 2, u = 100 heat bath, 300 sweeps x 1000 reads 56.4 to 34.3 ms; ML
-// p = 10 optimal transition, 300 sweeps x 100 reads 42.5 to 18.9 ms; one-shot HUIO N = 30 heat bath,
-// 100 sweeps x 8 reads 2.6 to 1.7 ms.
+// reads 49.4 to 2.5 ms; FC p = 2, u = 100 heat bath, 300 sweeps x 1000 reads 56.4 to 34.5 ms (19.4 with
+// the draws in single precision); ML p = 10 optimal transition, 300 sweeps x 100 reads 42.5 to 17.9 ms; HUIO
+// N = 2000, 300 sweeps x 1024 reads 48.0 to 24.0 ms (optimal transition) and 42.6 to 28.0 ms (Metropolis);
+// one-shot HUIO N = 30 heat bath, 100 sweeps x 8 reads 2.3 to 1.5 ms.
 //
 // It is a kernel of its own (a second launch) because inlined into the ordinary kernels it cost their
 // sweeps registers: 460 spilled scalars instead of 114 in the wide heat-bath variant, whose ordinary
@@ -29,8 +30,8 @@
 //
 // A variable whose terms hold it to the first or second power with at most three other factors
 // (SchedRec::pad[1], "cached") keeps a_k^(1) in ca, and a_k^(2) in cb when some term holds a square,
-// modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a change of another variable adds the change of
-// each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
+// modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a change of another
+// variable adds the change of each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
 // also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
 // the upper half of a float; 0 when it is not known, or not positive.  A change of a variable sharing a
 // term sets it to 0, the next decision of a cached variable and the next visit of another finds it
