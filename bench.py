@@ -25,9 +25,10 @@ PEAK_FP64_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
 # The heat bath's algorithmic FP64 work per weight w = exp(-beta * dE), as the method states it:
 # one multiply, one exponential evaluated directly (the FP64 operations of the gfx950 exp sequence,
-# FMA = 2 flops) and the additions of the cumulative sum.  The kernel's factored weights for
-# linear variables execute far fewer (two exponentials per lane and one fused multiply-add per
-# weight); the counter record gives the executed instructions.
+# FMA = 2 flops) and the additions of the cumulative sum.  The quad kernel's factored weights execute
+# far fewer (two exponentials per lane and one fused multiply-add per weight), and the lane kernel
+# evaluates no weights at all (the inverse of the distribution): for it the bound reported is VALU
+# issue.
 FP64_FLOPS_PER_WEIGHT = 30.0
 # VALU issue: a wave64 VALU instruction occupies one of the 4 SIMDs of a compute unit for 4 cycles
 VALU_ISSUE_PEAK_G = 256 * 4 * 2.4 / 4   # 10^9 wave instructions/s
@@ -97,8 +98,9 @@ def workload(args):
 
 # the sources that define the device program and the data it reads: kernels, their argument
 # layout, the instance packing and the launch choice (geometry and waves per replica)
-KERNEL_SOURCES = ("sa_device.h", "sa_quad.h", "sa_quad_mo.h", "sa_kernels_quad.hip", "sa_kernels_quad_mo.hip",
-                  "sa_kernels.hip", "sa_kernels_heat_bath.hip", "sa_kernels_heat_bath_closed.hip",
+KERNEL_SOURCES = ("sa_device.h", "sa_lane.h", "sa_settled.h", "sa_dense_team.h", "sa_quad.h", "sa_quad_mo.h",
+                  "sa_kernels_lane.hip", "sa_kernels_settled.hip", "sa_kernels_dense_team.hip",
+                  "sa_kernels_quad.hip", "sa_kernels_quad_mo.hip", "sa_kernels.hip", "sa_kernels_heat_bath.hip", "sa_kernels_heat_bath_closed.hip",
                   "sa_kernels_metropolis.hip", "sa_kernels_otm.hip", "sa_kernels_batch.hip",
                   "sa_kernels_batch16.hip", "sa_kernel_table.h", "sa_internal.h", "sa_host.cpp",
                   "sa_api.cpp")
@@ -1037,7 +1039,7 @@ def main():
     e_host = e.cpu().numpy()
     W_mean = float(np.mean(prob.upper.astype(np.int64) - prob.lower + 1))
     traffic = measured_traffic(f"{args.config}:{S}:{R}")
-    if w.rule == sa.HEAT_BATH:
+    if w.rule == sa.HEAT_BATH and launch["lanes_per_update"] != 1:
         # the method's work: W weights per update, one direct exponential each (the kernel's
         # factored weights execute fewer instructions; the executed VALU issue is reported in
         # valu_issue below)
@@ -1048,8 +1050,8 @@ def main():
                 "basis": "algorithmic: W weights x 30 FP64 flops per update (one direct exponential each); "
                          "executed instructions in valu_issue"}
     else:
-        # Metropolis / OTM: the incidence records come from the caches (measured HBM traffic is a
-        # small fraction of them), and the counters show VALU issue as the busy resource: the
+        # Metropolis / OTM, and the heat bath of the lane kernel: the records come from the caches
+        # (measured HBM traffic is a small fraction of them), and the counters show VALU issue as the busy resource: the
         # bound reported is VALU issue, from the counted instructions per update (committed
         # counter record of the same kernel sources) at this run's rate; null without a record
         crec = counter_record(f"{args.config}:{S}:{R}")
