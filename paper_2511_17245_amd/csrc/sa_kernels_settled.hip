@@ -27,6 +27,10 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
     // a run too short to gain what two more launches cost (about 10 us; a sweep that changes nothing
     // costs about 0.5 us per variable in the ordinary kernels)
     if (n_sweeps < 16 || (int64_t)n_sweeps * n_order < 2000) return sc;
+    // nor one whose whole sweep costs less than two of the settled kernel's changes (about 8 us each in a
+    // problem where every variable meets every other): N = 21 binary variables that keep changing, 300 sweeps
+    // x 19 reads, 5.5 ms with the settled kernel and 4.3 without; N = 30 of 17 values 1.4 and 2.2 ms
+    if (n_order < 24) return sc;
     int cus = 256, max_lds = 65536;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
