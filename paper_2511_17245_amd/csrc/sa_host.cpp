@@ -427,7 +427,13 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
         const VarRec &vr = p.var[k];
         for (int32_t q = vr.row; q < vr.row + vr.deg; ++q)
             if ((p.inc[q].meta & 0xFFu) > 2 || (p.inc[q].meta >> 8) > 3) p.cached[k] = 0;
-        if (vr.width > 1 && p.cached[k]) {
+    }
+    // nor a variable of another's longer record, whose changes would not reach it: in x^2 y z w the
+    // record of x names three others, that of y four
+    for (int32_t j : p.overflow)
+        if (j >= 0) p.cached[j] = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        if (p.var[k].width > 1 && p.cached[k]) {
             p.any_cached = true;
             p.any_square = p.any_square || (p.emask[k] & 4u) != 0;
         }

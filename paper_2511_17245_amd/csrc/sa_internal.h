@@ -97,8 +97,8 @@ struct Packed {
     // {0, 0} up to a multiple of kPairBlock) and its linear coefficient
     std::vector<PairRec> pair;
     std::vector<int32_t> pair_row, pair_deg, pair_h;
-    // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficients cached (every term
-    // holds it to the first or second power with at most three other factors)
+    // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficients cached (every term holds
+    // it to the first or second power, and no variable of the term has more than three other factors there)
     std::vector<uint8_t> cached;
     bool any_cached = false, any_square = false;   // of one that is not fixed / and has a square
     bool z30 = false, z23 = false;  // every bound below 2^30, 2^23 in magnitude

@@ -28,10 +28,10 @@
 // sweeps registers: 460 spilled scalars instead of 114 in the wide heat-bath variant, whose ordinary
 // sweeps became 1.4 times slower.
 //
-// A variable whose terms hold it to the first or second power with at most three other factors
-// (SchedRec::pad[1], "cached") keeps a_k^(1) in ca, and a_k^(2) in cb when some term holds a square,
-// modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a change of another
-// variable adds the change of each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
+// A variable whose terms hold it to the first or second power, and in whose terms no variable has more
+// than three other factors (SchedRec::pad[1], "cached"), keeps a_k^(1) in ca, and a_k^(2) in cb when some term
+// holds a square, modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a
+// change of another variable adds the change of each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
 // also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
 // the upper half of a float; 0 when it is not known, or not positive.  A change of a variable sharing a
 // term sets it to 0, the next decision of a cached variable and the next visit of another finds it
