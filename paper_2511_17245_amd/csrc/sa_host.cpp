@@ -525,8 +525,9 @@ int32_t build_order(const Packed &p, std::vector<SchedRec> &out) {
         const VarRec &vr = p.var[k];
         const bool fixed = vr.width == 1;
         n_order += fixed ? 0 : 1;
-        out[(size_t)k] = SchedRec{fixed ? -1 : k, vr.lo, vr.width, vr.row, vr.deg, p.emask[k],
-                                  {0, p.cached.empty() ? 1 : p.cached[k]}};
+        // (a fixed variable's slot is read like the others: it asks for no cache)
+        out[(size_t)k] = SchedRec{fixed ? -1 : k, vr.lo, vr.width, vr.row, vr.deg, fixed ? 0u : p.emask[k],
+                                  {0, fixed ? 0 : p.cached.empty() ? 1 : p.cached[k]}};
     }
     return n_order;
 }

@@ -51,6 +51,16 @@ std::vector<Raw> problems() {
     }
     out.push_back(a);
     out.push_back(b);
+    // a chain whose only squares are on fixed variables; all variables fixed
+    Raw c(40, -2, 3), d(33, 1, 1);
+    for (int32_t i = 0; i + 1 < 40; ++i) c.term(1 + i % 3, {i, i + 1});
+    c.term(2, {0, 0, 1});
+    c.term(2, {7, 7});
+    c.lo[0] = c.hi[0] = 2;
+    c.lo[7] = c.hi[7] = -1;
+    for (int32_t i = 0; i < 33; ++i) d.term(3, {i, i});
+    out.push_back(c);
+    out.push_back(d);
     std::mt19937_64 g(11);
     for (int rep = 0; rep < 200; ++rep) {
         Raw r(2 + (int32_t)(g() % 40), -2, 3);
@@ -87,6 +97,25 @@ void cached(const sa::Packed &pk, int rep) {
     expect(any == pk.any_cached && square == pk.any_square, "flags of the cached variables", rep);
 }
 
+// The settled kernel reads a^(2) of every slot that is marked cached and has a power above one, also where no
+// update follows: there must be a cache to read. A fixed variable's slot asks for nothing.
+void slots(const sa::Packed &pk, int rep) {
+    std::vector<sa::SchedRec> order;
+    const int32_t n_order = sa::build_order(pk, order);
+    int32_t movable = 0;
+    for (int32_t k = 0; k < pk.n; ++k) {
+        const sa::SchedRec &s = order[(size_t)k];
+        const bool fixed = pk.var[(size_t)k].width == 1;
+        movable += fixed ? 0 : 1;
+        expect(s.k == (fixed ? -1 : k), "slot in index order", rep);
+        expect(!fixed || (s.emask == 0 && s.pad[1] == 0), "a fixed variable's slot asks for nothing", rep);
+        if (pk.dense || !s.pad[1]) continue;
+        expect(pk.any_cached, "a cached slot has a cache", rep);
+        expect((s.emask & ~2u) == 0 || pk.any_square, "a cached slot with a square has its cache", rep);
+    }
+    expect((int32_t)order.size() == pk.n && n_order == movable, "slots of every variable", rep);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -98,6 +127,8 @@ int main(int argc, char **argv) {
             expect(false, "packs", rep);
         } else if (which == "cached") {
             cached(pk, rep);
+        } else if (which == "slots") {
+            slots(pk, rep);
         } else {
             std::fprintf(stderr, "no check named %s\n", which.c_str());
             return 2;

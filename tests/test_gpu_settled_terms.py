@@ -59,6 +59,23 @@ def test_every_sweep_against_the_oracle(kind, rule):
                      lambda i: np.array_equal(z[i], zo[i]) and e[i] == eo[i] and np.array_equal(h[i], ho[i]), explain)
 
 
+@pytest.mark.parametrize("rule", RULES)
+def test_squares_on_fixed_variables_only(rule):
+    """Cached coefficients without one of a square, and fixed variables that have a square."""
+    g = np.random.Generator(np.random.PCG64(8))
+    terms = [(int(g.integers(1, 9)) * (1 if i % 2 else -1), [i, i + 1]) for i in range(39)]
+    terms += [(int(g.integers(-9, 10)) or 1, [i]) for i in range(40)] + [(2, [0, 0, 1]), (3, [7, 7]), (-2, [21, 21, 20])]
+    prob = I.from_terms(40, terms, -2, 3)
+    for k, v in ((0, 2), (7, -1), (21, 3)):
+        prob.lower[k] = prob.upper[k] = v
+    P = oracle.Poly(prob)
+    beta = schedule(prob)
+    for G in (1, 2):
+        z, e, h = run(prob, rule, beta, 4, 0xF1 + rule, G)
+        zo, eo, ho = P.anneal(rule, beta, 4, 0xF1 + rule, trace=True)
+        assert np.array_equal(z, zo) and np.array_equal(e, eo) and np.array_equal(h, ho)
+
+
 def items():
     out = []
     for i, (kind, rule) in enumerate((k, r) for k in ("one_square", "two_squares", "mixed") for r in RULES):

@@ -17,7 +17,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("which", ["cached"])
+@pytest.mark.parametrize("which", ["cached", "slots"])
 def test_pack(checker, which):
     out = subprocess.run([checker, which], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stderr[-4000:]
