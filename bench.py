@@ -98,7 +98,7 @@ def workload(args):
 
 # the sources that define the device program and the data it reads: kernels, their argument
 # layout, the instance packing and the launch choice (geometry and waves per replica)
-KERNEL_SOURCES = ("sa_device.h", "sa_lane.h", "sa_settled.h", "sa_dense_team.h", "sa_quad.h", "sa_quad_mo.h",
+KERNEL_SOURCES = ("sa_device.h", "sa_draw.h", "sa_lane.h", "sa_settled.h", "sa_dense_team.h", "sa_quad.h", "sa_quad_mo.h",
                   "sa_kernels_lane.hip", "sa_kernels_settled.hip", "sa_kernels_dense_team.hip",
                   "sa_kernels_quad.hip", "sa_kernels_quad_mo.hip", "sa_kernels.hip", "sa_kernels_heat_bath.hip", "sa_kernels_heat_bath_closed.hip",
                   "sa_kernels_metropolis.hip", "sa_kernels_otm.hip", "sa_kernels_batch.hip",

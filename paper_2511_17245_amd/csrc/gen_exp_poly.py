@@ -1,4 +1,4 @@
-"""Coefficients of the device exponential's polynomial (exp_nonpos in sa_device.h).
+"""Coefficients of the device exponential's polynomial (exp_nonpos in sa_draw.h).
 
 e^r on [-ln2/2, ln2/2] is approximated by the degree-11 polynomial that interpolates it at the 12
 Chebyshev nodes of the interval (a near-minimax fit), solved in 200-bit arithmetic and rounded to

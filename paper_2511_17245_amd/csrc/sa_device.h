@@ -21,6 +21,7 @@
 #include <climits>
 #include <cstdint>
 
+#include "sa_draw.h"
 #include "sa_internal.h"
 
 namespace sa {
@@ -484,168 +485,10 @@ __device__ __forceinline__ int64_t direct_delta(const DevProblem &P, const ZT *z
     return to_i64<Acc>(wave_sum<Acc>(acc));
 }
 
-// e^x for x <= 0 (every exponential of the annealer has a non-positive argument): x = n ln 2 + r
-// with |r| <= ln(2)/2, e^r by the degree-11 polynomial that interpolates it at the 12 Chebyshev
-// nodes of that interval (relative error below 2^-55.7; gen_exp_poly.py derives the coefficients
-// and checks the routine: at most about 0.83 ulp), then scaled by 2^n.  The scaling rounds once,
-// so below -745.2, where e^x is under half the smallest subnormal, the result is 0 (arguments
-// under -746 are clamped there first).  Within about an ulp, like the host library the oracle
-// uses; a last-bit difference moves a draw only when a uniform number falls within that ulp of a
-// threshold.
-__device__ __forceinline__ double exp_nonpos(double x) {
-    const double xc = x > -746.0 ? x : -746.0;
-    const double n = rint(xc * 1.4426950408889634);     // 1 / ln 2
-    double r = fma(-n, 0.6931471803691238, xc);          // ln 2 rounded to 32 bits (n * it exact)
-    r = fma(-n, 1.9082149292705877e-10, r);              // the rest of ln 2
-    double p = 2.5110037605963777e-08;
-    p = fma(p, r, 2.763263963904103e-07);
-    p = fma(p, r, 2.755724091857897e-06);
-    p = fma(p, r, 2.4801485482328494e-05);
-    p = fma(p, r, 0.00019841269890047113);
-    p = fma(p, r, 0.0013888888952314775);
-    p = fma(p, r, 0.008333333333319601);
-    p = fma(p, r, 0.0416666666664881);
-    p = fma(p, r, 0.1666666666666668);
-    p = fma(p, r, 0.5000000000000019);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    return __builtin_amdgcn_ldexp(p, (int)n);
-}
-
 // Metropolis acceptance min[1, exp(-dE/T)] (Sec. 3.3.1), T = 1/beta; U in [0,1).
 __device__ __forceinline__ bool metropolis_accept(int64_t d, double beta, double U) {
     if (d <= 0) return true;
     return U < exp_nonpos(-(beta * (double)d));
-}
-
-// expm1(x) for x <= 0 (the closed-form heat bath's expm1(-c W)).  Below -40, e^x is under half an
-// ulp of 1 and the value is -1 exactly.  On [-0.35, 0] the Taylor series of e^x - 1 to x^14 (error
-// below 2^-60 relative); otherwise e^x - 1, which cancels nothing because e^x <= 0.71.
-__device__ __forceinline__ double expm1_nonpos(double x) {
-    if (x < -40.0) return -1.0;
-    if (x < -0.35) return exp_nonpos(x) - 1.0;
-    // Horner on 1/k!, k = 14 .. 2, then x + x^2 (...)
-    double p = 1.0 / 87178291200.0;            // 1/14!
-    p = fma(p, x, 1.0 / 6227020800.0);         // 1/13!
-    p = fma(p, x, 1.0 / 479001600.0);          // 1/12!
-    p = fma(p, x, 1.0 / 39916800.0);           // 1/11!
-    p = fma(p, x, 1.0 / 3628800.0);            // 1/10!
-    p = fma(p, x, 1.0 / 362880.0);             // 1/9!
-    p = fma(p, x, 1.0 / 40320.0);              // 1/8!
-    p = fma(p, x, 1.0 / 5040.0);               // 1/7!
-    p = fma(p, x, 1.0 / 720.0);                // 1/6!
-    p = fma(p, x, 1.0 / 120.0);                // 1/5!
-    p = fma(p, x, 1.0 / 24.0);                 // 1/4!
-    p = fma(p, x, 1.0 / 6.0);                  // 1/3!
-    p = fma(p, x, 0.5);                        // 1/2!
-    return fma(p * x, x, x);
-}
-
-// log1p(y) for -1 < y <= 0 (the closed-form heat bath's log1p(U m)).  u = 1 + y rounded; log(u)
-// from u = f 2^e with f in [sqrt(1/2), sqrt(2)) and log f = 2 atanh(s), s = (f - 1)/(f + 1),
-// |s| <= 0.1716, by its odd series to s^21 (error below 2^-62 relative); the rounding of u is
-// put back to first order, log1p(y) = log(u) + (y - (u - 1)) / u (Kahan's correction).
-__device__ __forceinline__ double log1p_nonpos(double y) {
-    if (y == 0.0) return 0.0;
-    if (y <= -1.0) return -__builtin_huge_val();
-    const double u = 1.0 + y;
-    const double corr = (y - (u - 1.0)) * __builtin_amdgcn_rcp(u);
-    int e = __builtin_amdgcn_frexp_exp(u);
-    double f = __builtin_amdgcn_frexp_mant(u);  // [0.5, 1)
-    if (f < 0.70710678118654752) {
-        f = f + f;
-        e -= 1;
-    }
-    const double s = (f - 1.0) / (f + 1.0);
-    const double s2 = s * s;
-    double r = 1.0 / 21.0;
-    r = fma(r, s2, 1.0 / 19.0);
-    r = fma(r, s2, 1.0 / 17.0);
-    r = fma(r, s2, 1.0 / 15.0);
-    r = fma(r, s2, 1.0 / 13.0);
-    r = fma(r, s2, 1.0 / 11.0);
-    r = fma(r, s2, 1.0 / 9.0);
-    r = fma(r, s2, 1.0 / 7.0);
-    r = fma(r, s2, 1.0 / 5.0);
-    r = fma(r, s2, 1.0 / 3.0);
-    const double ln2_hi = 0.6931471803691238;    // ln 2 rounded to 32 bits: e * ln2_hi is exact
-    const double ln2_lo = 1.9082149292705877e-10;  // ln 2 - ln2_hi
-    const double ed = (double)e;
-    const double two_s = s + s;
-    // log u = e ln2_hi + (2 s + (2 s s^2 r + e ln2_lo)) + corr
-    return fma(ed, ln2_hi, two_s + (fma(two_s * s2, r, ed * ln2_lo) + corr));
-}
-
-// Cumulative weights in value order, by one lane: the value drawn where the closed form cannot tell.
-__device__ __forceinline__ uint32_t linear_draw_by_sums(bool from_top, double slope, uint32_t W, double beta, double U) {
-    double total = 0.0;
-    for (uint32_t j = 0; j < W; ++j) total += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
-    const double thr = U * total;
-    double run = 0.0;
-    for (uint32_t j = 0; j < W; ++j) {
-        run += exp_nonpos(-(beta * (slope * (double)(from_top ? W - 1u - j : j))));
-        if (run > thr) return j;
-    }
-    return W - 1u;
-}
-
-// The closed form in double precision; it errs by some ulp of W, so a step nearer than 1e-10 + 1e-14 W is
-// left to the sums (above 65536 values, whose sums round as much as that, it is taken as it is).
-__device__ __forceinline__ uint32_t linear_draw_double(bool from_top, double slope, uint32_t W, double beta, double U) {
-    const double c = beta * slope, Wd = (double)W;
-    const double m = expm1_nonpos(-(c * Wd));
-    const double L = log1p_nonpos((from_top ? 1.0 - U : U) * m) / c;
-    const double x = from_top ? Wd + L : -L;
-    const double near = rint(x);
-    if (W <= 65536u && !(__builtin_fabs(x - near) > 1e-10 + 1e-14 * Wd) && near > 0.5 && near < Wd - 0.5)
-        return linear_draw_by_sums(from_top, slope, W, beta, U);
-    return !(x > 0.0) ? 0u : x >= Wd ? W - 1u : (uint32_t)ceil(x) - 1u;
-}
-
-// Heat-bath draw of a variable with dE(v) = a (v - z_k): the first value whose cumulative weight exceeds
-// U times the total.  Index i = ceil(x) - 1 with x = -log1p(P m) / c from the lower end for a > 0, W + the
-// same for a < 0; c = beta |a|, m = expm1(-c W), P = U or 1 - U.
-//
-// It replaced the enumeration in every kernel: 32 random-interaction problems (N = 100, W = 201, most
-// variables linear; 100 sweeps x 100 reads) 24.6 to 20.1 ms, 64 mixed problems 103 to 95 ms.
-//
-// In single precision: m from the series of expm1 (c W < 1/2; relative error below 1e-6 with the
-// rounding of c W) or e^-cW - 1 (below 1e-6 as |m| > 0.39); y = P m to 2e-6; log1p(y) from the series of
-// 2 atanh(y / (2 + y)) (|y| < 0.3, where log1p passes on at most 1.2 of y's relative error: 4e-6 in all) or
-// log(1 + y), off by 2e-6 |y| / (1 + y) and by 1e-6 of itself.  `err` is at least twice that.
-__device__ __forceinline__ int64_t linear_draw(int64_t a, int64_t lo, uint32_t W, double beta, double U) {
-    const bool from_top = a < 0;
-    const double slope = (double)(from_top ? -a : a);
-    const double c = beta * slope;
-    const float cf = (float)c, Wf = (float)W;
-    const float t = cf * Wf;
-    const float series = -t * (1.0f - t * (0.5f - t * (0.16666667f - t * (0.041666667f - t * (0.0083333333f - t * 0.0013888889f)))));
-    const float m = t < 0.5f ? series : __builtin_amdgcn_exp2f(t * -1.4426950f) - 1.0f;
-    const float y = (float)(from_top ? 1.0 - U : U) * m;
-    const float s = y * __builtin_amdgcn_rcpf(2.0f + y), s2 = s * s;
-    const float near0 = 2.0f * s * (1.0f + s2 * (0.33333333f + s2 * (0.2f + s2 * (0.14285714f + s2 * 0.11111111f))));
-    const float u = 1.0f + y;
-    const bool small = y > -0.3f;
-    const float L = small ? near0 : __builtin_amdgcn_logf(u) * 0.69314718f;
-    const float ic = __builtin_amdgcn_rcpf(cf);
-    const float aL = -L;
-    const float err = (small ? 1e-5f * aL : 5e-6f * __builtin_amdgcn_rcpf(u) + 4e-6f * aL) * ic + 1e-6f * Wf;
-    const float x = from_top ? Wf - aL * ic : aL * ic;
-    const float step = __builtin_rintf(x);
-    // a NaN or an infinity anywhere (c = 0, 1 + y = 0) fails the comparison; steps 0 and W decide nothing
-    const bool sure = W < (1u << 20) && err < 0.25f &&
-                      (__builtin_fabsf(x - step) > err || step < 0.5f || step > Wf - 0.5f) && c > 1e-30;
-    uint32_t i = x <= 0.0f ? 0u : (uint32_t)__builtin_ceilf(x) - 1u;
-    i = i < W ? i : W - 1u;
-    if (!sure) {
-        if (!(c > 1e-280)) {   // every weight is 1: the count of v - l + 1 <= U W
-            i = (uint32_t)(U * (double)W);
-            i = i < W ? i : W - 1u;
-        } else {
-            i = linear_draw_double(from_top, slope, W, beta, U);
-        }
-    }
-    return lo + (int64_t)i;
 }
 
 // DPP destinations that keep zeros where their move does not write: each is written only by the
@@ -1088,30 +931,6 @@ __device__ __forceinline__ int64_t argmin_wide(const Coeffs<kMaxE, Acc> &C, int6
     }
     dbest = wave_min_i64(best);
     return wave_min_i32(best == dbest ? bv : INT32_MAX);
-}
-
-// Heat bath for a variable whose energy difference is linear, dE(v) = a (v - z_k) (Sec. 3.3.2,
-// multilinear case): the inverse of the cumulative distribution in O(1).  Index i = v - lo has
-// probability proportional to exp(-beta a i); with c = beta |a| and g(q) = -log1p(q expm1(-c W)) / c
-// the paper's x = -(T/a) ln[1 - U (1 - exp(-a W / T))] is g(U) for a > 0 and W - g(1 - U) for a < 0
-// (the same value without overflowing exp(c W)); v = lo + ceil(x) - 1, clamped to the box.  a = 0
-// or beta = 0 is the uniform distribution, drawn from x1 by a multiply-high.  Wave-uniform.
-// expm1 and log1p are the functions above (about an ulp, like the host library); a last-bit
-// difference moves a draw only when x lies within a few ulps of an integer.
-__device__ __forceinline__ int64_t heat_bath_closed(int64_t a, int64_t lo, int64_t W, double beta, double U,
-                                                    uint32_t x1) {
-    const double c = beta * (double)(a < 0 ? -a : a);
-    if (a == 0 || !(c > 0.0)) return lo + (int64_t)(((uint64_t)x1 * (uint64_t)W) >> 32);
-    const double Wd = (double)W;
-    const double m = expm1_nonpos(-(c * Wd));
-    double x;
-    if (a > 0)
-        x = -log1p_nonpos(U * m) / c;
-    else
-        x = Wd + log1p_nonpos((1.0 - U) * m) / c;
-    if (!(x > 0.0)) return lo;
-    if (x >= Wd) return lo + W - 1;
-    return lo + (int64_t)ceil(x) - 1;
 }
 
 // ------------------------------------------------------------------------------------------------
