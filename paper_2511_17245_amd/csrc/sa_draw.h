@@ -207,5 +207,29 @@ __device__ __forceinline__ int64_t heat_bath_closed(int64_t a, int64_t lo, int64
     return lo + (int64_t)ceil(x) - 1;
 }
 
+// The margin of a settled sweep (sa_settled.h) as it is kept: M rounded down to the upper half of a float; 0
+// where M <= 0.
+__device__ __forceinline__ uint16_t margin_bits(int64_t M) {
+    if (M <= 0) return 0;
+    // below M after the conversion's rounding, then cut to 16 bits (toward zero)
+    const float f = (float)M * 0.9999998f;
+    uint32_t b;
+    __builtin_memcpy(&b, &f, 4);
+    return (uint16_t)(b >> 16);
+}
+
+// Whether a linear variable may be passed over without its random number once every other value's weight is
+// 0. Not at the top of its range with the closed-form draw, which gives the lowest value at U = 0.
+__device__ __forceinline__ bool may_freeze(bool closed, int64_t lo, int64_t zk) { return !closed || zk == lo; }
+
+// Every value of the variable has the same energy.
+constexpr uint16_t kFlat = 0x8000;
+// The kept margin of a linear variable at z_k with coefficient a1; with the sign bit set where it may not freeze.
+__device__ __forceinline__ uint16_t linear_margin(bool closed, int64_t a1, int64_t lo, int64_t hi, int64_t zk) {
+    if (a1 == 0) return kFlat;
+    const uint16_t b = margin_bits(zk == lo ? a1 : zk == hi ? -a1 : 0);
+    return b != 0 && !may_freeze(closed, lo, zk) ? (uint16_t)(b | 0x8000u) : b;
+}
+
 }  // namespace
 }  // namespace sa

@@ -33,7 +33,8 @@
 // holds a square, modulo 2^32 where every coefficient fits (DevProblem::coef32), else modulo 2^64; a
 // change of another variable adds the change of each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
 // also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
-// the upper half of a float; 0 when it is not known, or not positive.  A change of a variable sharing a
+// the upper half of a float; 0 when it is not known, or not positive; with the sign set where it may not
+// freeze the variable (linear_margin).  A change of a variable sharing a
 // term sets it to 0, the next decision of a cached variable and the next visit of another finds it
 // again.  A sweep first reads cm alone, four variables per lane, and skips the blocks of 64 whose
 // variables are all frozen: beta M >= 746, where every other value's acceptance or weight is exactly 0.
@@ -45,8 +46,8 @@ namespace sa {
 namespace {
 
 // cm of a variable without a cached coefficient known to be linear with a_k^(1) = 0: every value has
-// the same energy.  And of a fixed variable: frozen at every temperature.
-constexpr uint16_t kFlat = 0x8000, kFixed = 0x7FFF;
+// the same energy (kFlat, sa_draw.h).  And of a fixed variable: frozen at every temperature.
+constexpr uint16_t kFixed = 0x7FFF;
 template <int k>
 struct Int {
     static constexpr int value = k;
@@ -65,13 +66,8 @@ struct SettleView {
     uint16_t *cm;        // whole groups of four
 };
 
-__device__ __forceinline__ uint16_t margin_bits(int64_t M) {
-    if (M <= 0) return 0;
-    // below M after the conversion's rounding, then cut to 16 bits (toward zero)
-    const float f = (float)M * 0.9999998f;
-    return (uint16_t)(__float_as_uint(f) >> 16);
-}
-__device__ __forceinline__ double margin_value(uint16_t b) { return (double)__uint_as_float((uint32_t)b << 16); }
+// (without the sign: 0 for a flat variable)
+__device__ __forceinline__ double margin_value(uint16_t b) { return (double)__uint_as_float((uint32_t)(b & 0x7FFFu) << 16); }
 
 // a cached coefficient of variable i
 __device__ __forceinline__ int64_t cache_read(const SettleView &S, const void *c, int32_t i) {
@@ -181,9 +177,9 @@ __device__ __forceinline__ int64_t quadratic_margin(int64_t a1, int64_t a2, int6
 // Margin of a variable that a visit left at z_k, from its coefficients (wave-uniform).
 template <int kE, typename Acc>
 __device__ __forceinline__ uint16_t settled_margin(const Coeffs<kE, Acc> &C, uint32_t em, int64_t lo, int64_t W,
-                                                   int64_t zk, int lane) {
+                                                   int64_t zk, bool closed, int lane) {
     const int64_t a1 = to_i64<Acc>(C.a[1]), hi = lo + W - 1;
-    if (kE == 1 || (em & ~2u) == 0) return a1 == 0 ? kFlat : margin_bits(zk == lo ? a1 : zk == hi ? -a1 : 0);
+    if (kE == 1 || (em & ~2u) == 0) return linear_margin(closed, a1, lo, hi, zk);
     if (kE == 2 || (em & ~6u) == 0)
         return margin_bits(quadratic_margin(a1, to_i64<Acc>(C.a[kE >= 2 ? 2 : 1]), lo, hi, zk));
     if (W > 16 * kWave) return 0;   // not worth the enumeration
@@ -240,7 +236,7 @@ __device__ __forceinline__ bool settled_visit(const SettleView &S, const ZT *z, 
         taken = metropolis_accept(d, beta, U);
     }
     if (!taken || v == zk) {
-        const uint16_t m = settled_margin(C, em, lo, W, zk, lane);
+        const uint16_t m = settled_margin(C, em, lo, W, zk, kRule == SA_HEAT_BATH && S.closed, lane);
         if (lane == 0) S.cm[k] = m;   // (k: its place in index order)
     }
     return taken;
@@ -328,8 +324,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
             }
         }
         M = (double)m;
-        // (the closed-form draw at the top of the range depends on U = 0: never frozen)
-        mbits = closed && linear && zk != lo ? 0 : margin_bits(m);
+        mbits = linear && !may_freeze(closed, lo, zk) ? 0 : margin_bits(m);
     };
     // decisions that read M find it each time; the others only now and then, for cm (below)
     constexpr bool kUsesMargin = kRule != SA_METROPOLIS;
@@ -340,7 +335,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
             if (kUsesMargin) find_margin();
         } else {
             mbits = S.cm[kk];
-            M = margin_value(mbits);   // (-0.0 for a flat one)
+            M = margin_value(mbits);
             cached = mbits == kFlat;
         }
     };

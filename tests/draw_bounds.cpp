@@ -151,6 +151,30 @@ void sums() {
     }
 }
 
+// A margin that freezes a variable in the settled sweeps (the kept bits, as a signed number, at or above
+// those of 746 / beta) leaves it where it is for every U, the extremes among them
+void margins() {
+    int64_t frozen = 0;
+    for (int i = 0; i < 400000; ++i) {
+        const int64_t lo = -(int64_t)(g() % 50), hi = lo + 1 + (int64_t)(g() % 60);
+        const int64_t zk = g() % 2 ? lo : hi, a = (int64_t)(log_uniform(1.0, 1e9)) * (g() % 2 ? 1 : -1);
+        const double beta = log_uniform(1e-6, 1e4);
+        const bool closed = g() % 2;
+        const float t = (float)(746.0 / beta) * 1.000001f;
+        uint32_t tb;
+        std::memcpy(&tb, &t, 4);
+        if ((int16_t)sa::linear_margin(closed, a, lo, hi, zk) < (int16_t)((tb >> 16) + 1u)) continue;
+        ++frozen;
+        for (double U : {0.0, 0x1p-53, 0.5, 1.0 - 0x1p-52, 1.0 - 0x1p-53}) {
+            const uint32_t W = (uint32_t)(hi - lo + 1);
+            const int64_t v = closed ? sa::heat_bath_closed(a, lo, W, beta, U, 12345u) : sa::linear_draw(a, lo, W, beta, U);
+            if (v != zk) fail(closed ? "frozen, closed form" : "frozen", beta * (double)std::abs(a), W, a < 0, U);
+        }
+    }
+    std::printf("frozen %lld\n", (long long)frozen);
+    if (frozen < 1000) fail("some freeze", 0, 0, false, 0);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -158,6 +182,7 @@ int main(int argc, char **argv) {
     if (which == "single") single();
     else if (which == "decided") decided();
     else if (which == "sums") sums();
+    else if (which == "margins") margins();
     else return 2;
     if (failures) {
         std::fprintf(stderr, "%d failures\n", failures);

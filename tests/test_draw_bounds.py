@@ -1,6 +1,6 @@
 """The heat bath's draws by the inverse of the distribution (csrc/sa_draw.h, compiled for the host) against
 113-bit arithmetic and against the weights added one by one: the stated error bounds, the tails, ranges past
-65536 values, U = 0 (no GPU)."""
+65536 values, U = 0, and the margins that pass over a draw (no GPU)."""
 import os
 import subprocess
 
@@ -17,7 +17,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("which", ["single", "decided", "sums"])
+@pytest.mark.parametrize("which", ["single", "decided", "sums", "margins"])
 def test_draws(checker, which):
     out = subprocess.run([checker, which], capture_output=True, text=True, timeout=300)
     print(out.stdout)
