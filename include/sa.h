@@ -124,7 +124,8 @@ typedef struct {
                                    sweeps on; else 4 or 64, dense problems by a team of waves).  64: one
                                    wavefront per update (the candidate values split over its lanes,
                                    the waves of a replica over schedule windows, as waves_per_replica
-                                   says).  4: one quad of lanes per update, the 16 quads of each of a
+                                   says; a replica whose sweeps change little is finished by one
+                                   wavefront, as with 0).  4: one quad of lanes per update, the 16 quads of each of a
                                    workgroup's 8 waves over the dependency levels of the sweep
                                    (sparse problems, exponents <= 2, ranges of at most 128 values,
                                    waves_per_replica 0; SA_EINVAL otherwise).  Both follow the

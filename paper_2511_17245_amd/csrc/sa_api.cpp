@@ -690,9 +690,10 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.waves_per_replica = qw;
         plan->last.lanes_per_update = 4;
         plan->last.n_levels = lv->n_levels;
-    } else if (const sa::TeamChoice team = G == 0 ? sa::choose_team(plan->rule, plan->packed, plan->dp.coef32 != 0, n_reads,
-                                                                    plan->device)
-                                                  : sa::TeamChoice();
+    } else if (const sa::TeamChoice team =
+                   G == 0 && opts.lanes_per_update == 0
+                       ? sa::choose_team(plan->rule, plan->packed, plan->dp.coef32 != 0, n_reads, plan->device)
+                       : sa::TeamChoice();
                team.waves > 0) {
         sa_plan::Sched *all = nullptr;
         rc = sa::get_order(plan, &all);

@@ -137,7 +137,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     std::vector<sa::SchedRec> sch;
     const int32_t n_win = lanes == 64 ? sa::build_schedule(pk, lc.win_waves, sch) : 0;
     // the list of the variables for the settled kernel, or for the dense team's
-    const sa::TeamChoice team = lanes == 64 && opts.waves_per_replica == 0
+    const sa::TeamChoice team = opts.lanes_per_update == 0 && lanes == 64 && opts.waves_per_replica == 0
                                     ? sa::choose_team(rule, pk, sa::coefs_fit_32(canon), n_reads, device)
                                     : sa::TeamChoice();
     bool by_team = team.waves > 0;
