@@ -307,14 +307,25 @@ void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image) {
     put(L.recs, im.recs.data(), im.recs.size());
 }
 
+const LaneImage &get_lane_chunks(sa_plan *plan) {
+    std::lock_guard<std::mutex> lk(plan->sched_mu);
+    sa_plan::Lanes &ln = plan->lanes;
+    if (!ln.chunked) {
+        build_lane_chunks(plan->packed, ln.im);
+        ln.chunked = true;
+    }
+    return ln.im;
+}
+
 int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Lanes &ln = plan->lanes;
     if (!ln.dev) {
-        build_lanes(plan->packed, compact, ln.im);
+        build_lane_records(plan->packed, compact, ln.im);
         const LaneLayout L = lane_layout(ln.im);
         std::vector<char> img(L.total, 0);
         stage_lanes(ln.im, L, img.data());
+        ln.im.recs = std::vector<uint8_t>();
         void *dev = nullptr;
         hipError_t e = hipMalloc(&dev, L.total);
         if (e != hipSuccess) return fail(SA_ENOMEM, std::string("hipMalloc(lanes): ") + hipGetErrorString(e));
@@ -327,9 +338,7 @@ int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out) {
         ln.chunks = (const LaneRows *)dev;
         ln.slots = (const LaneSlot *)((char *)dev + L.slots);
         ln.recs = (const void *)((char *)dev + L.recs);
-        ln.im.chunks = std::vector<LaneRows>();
         ln.im.slots = std::vector<LaneSlot>();
-        ln.im.recs = std::vector<uint8_t>();
     }
     *out = &ln;
     return SA_OK;
@@ -359,13 +368,19 @@ int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out) {
 int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &q) {
     choice = LaneChoice();
     bool compact = false;
-    if (n_sweeps < kLaneMinSweeps || !lane_eligible(plan->rule, plan->packed, plan->dp.coef32 != 0, plan->device, compact))
-        return SA_OK;
+    int cus = 256, max_lds = 65536;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, plan->device);
+    (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, plan->device);
+    const Packed &p = plan->packed;
+    if (n_sweeps < kLaneMinSweeps || !lane_eligible(plan->rule, p, plan->dp.coef32 != 0, max_lds, compact)) return SA_OK;
+    const int32_t quads = quad_eligible(plan->rule, p, plan->device)
+                              ? 16 * quad_waves(plan->rule, p.max_width, p.max_exp, quad_uniform_width(p))
+                              : 0;
+    const int waves = lane_waves(get_lane_chunks(plan), p, compact, n_reads, quads, cus, max_lds);
+    if (waves == 0) return SA_OK;
     sa_plan::Lanes *ln = nullptr;
     int rc = get_lanes(plan, compact, &ln);
     if (rc != SA_OK) return rc;
-    const int waves = lane_waves(ln->im, plan->dp.n, n_reads, plan->device);
-    if (waves == 0) return SA_OK;
     sa_plan::Lanes::Rounds *rounds = nullptr;
     rc = get_lane_rounds(plan, waves, &rounds);
     if (rc != SA_OK) return rc;

@@ -448,6 +448,7 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
     for (size_t q = 0; compact && q < p.inc.size(); ++q)
         compact = p.inc_coef[q] >= INT32_MIN && p.inc_coef[q] <= INT32_MAX;
     if (compact) {
+        p.pair16 = n <= 65536;
         p.pair_row.assign(n, 0);
         p.pair_deg.assign(n, 0);
         p.pair_h.assign(n, 0);
@@ -458,8 +459,10 @@ int pack(const Canonical &c, Packed &p, std::string &err) {
             for (int32_t q = vr.row; q < vr.row + vr.deg; ++q) {
                 if ((p.inc[q].meta >> 8) == 0)
                     h += p.inc_coef[q];
-                else
+                else {
                     p.pair.push_back(PairRec{p.inc[q].o[0], (int32_t)p.inc_coef[q]});
+                    p.pair16 = p.pair16 && p.inc_coef[q] >= INT16_MIN && p.inc_coef[q] <= INT16_MAX;
+                }
             }
             p.pair_deg[k] = (int32_t)p.pair.size() - p.pair_row[k];
             while ((p.pair.size() - (size_t)p.pair_row[k]) % kPairBlock) p.pair.push_back(PairRec{0, 0});
@@ -700,25 +703,22 @@ int32_t build_rounds(const Packed &p, std::vector<SchedRec> &rounds, int32_t &n_
     return n_levels;
 }
 
-void build_lanes(const Packed &p, bool compact, LaneImage &im) {
+void build_lane_chunks(const Packed &p, LaneImage &im) {
     im = LaneImage();
-    im.compact = compact;
     std::vector<int32_t> start;
     std::vector<SchedRec> slots;
     im.n_levels = build_levels(p, 64, start, slots);
     im.n_slots = (int32_t)slots.size();
-    const size_t rec_bytes = compact ? 4 : 8;
-    int32_t rows = 0;
     for (int32_t l = 0; l < im.n_levels; ++l) {
         im.level_chunk.push_back((int32_t)im.chunks.size());
+        im.level_slots.push_back(start[(size_t)l + 1] - start[(size_t)l]);
         // by falling degree, so that a chunk's rows hold few empty records
         std::stable_sort(slots.begin() + start[(size_t)l], slots.begin() + start[(size_t)l + 1],
                          [](const SchedRec &x, const SchedRec &y) { return x.deg > y.deg; });
         for (int32_t b = start[(size_t)l]; b < start[(size_t)l + 1]; b += 64) {
             const int32_t m = std::min<int32_t>(64, start[(size_t)l + 1] - b);
             const int32_t r = (std::max<int32_t>(slots[(size_t)b].deg, 1) + 3) / 4 * 4;
-            im.chunks.push_back(LaneRows{rows, r});
-            im.recs.resize((size_t)(rows + r) * 64 * rec_bytes, 0);   // (an empty record: variable 0, coupling 0)
+            im.chunks.push_back(LaneRows{(int32_t)im.n_rows, r});
             for (int32_t q = 0; q < 64; ++q) {
                 if (q >= m) {
                     im.slots.push_back(LaneSlot{-1, 0, 1, 0});
@@ -726,24 +726,88 @@ void build_lanes(const Packed &p, bool compact, LaneImage &im) {
                 }
                 const SchedRec &s = slots[(size_t)(b + q)];
                 im.slots.push_back(LaneSlot{s.k, s.lo, s.width, s.pad[0]});
-                for (int32_t i = 0; i < s.deg; ++i) {
-                    const PairRec &pr = p.pair[(size_t)s.row + (size_t)i];
-                    uint8_t *to = im.recs.data() + ((size_t)(rows + i) * 64 + (size_t)q) * rec_bytes;
-                    if (compact) {
-                        const uint32_t w = ((uint32_t)pr.J << 16) | ((uint32_t)pr.j & 0xFFFFu);
-                        std::memcpy(to, &w, 4);
-                    } else {
-                        std::memcpy(to, &pr, 8);
-                    }
-                }
             }
-            rows += r;
+            im.n_rows += r;
+            if (im.n_rows > INT32_MAX - kLaneReach) {   // (row numbers are 32-bit: not for this kernel)
+                im.n_levels = 0;
+                return;
+            }
         }
-        im.max_chunks = std::max(im.max_chunks, (int32_t)im.chunks.size() - im.level_chunk.back());
     }
     im.level_chunk.push_back((int32_t)im.chunks.size());
-    // the kernel reads kLaneReach rows from a chunk's first on, also of the last
-    im.recs.resize((size_t)(rows + kLaneReach) * 64 * rec_bytes, 0);
+    std::vector<SchedRec> windows;
+    im.n_win8 = build_schedule(p, 8, windows);
+}
+
+void build_lane_records(const Packed &p, bool compact, LaneImage &im) {
+    const size_t rec_bytes = compact ? 4 : 8;
+    im.compact = compact;
+    // (an empty record: variable 0, coupling 0; the kernel reads kLaneReach rows from a chunk's first on,
+    // also of the last)
+    im.recs.assign((size_t)(im.n_rows + kLaneReach) * 64 * rec_bytes, 0);
+    for (size_t c = 0; c < im.chunks.size(); ++c) {
+        for (size_t q = 0; q < 64; ++q) {
+            const int32_t k = im.slots[c * 64 + q].k;
+            if (k < 0) continue;
+            for (int32_t i = 0; i < p.pair_deg[(size_t)k]; ++i) {
+                const PairRec &pr = p.pair[(size_t)p.pair_row[(size_t)k] + (size_t)i];
+                uint8_t *to = im.recs.data() + ((size_t)(im.chunks[c].first + i) * 64 + q) * rec_bytes;
+                if (compact) {
+                    const uint32_t w = ((uint32_t)pr.J << 16) | ((uint32_t)pr.j & 0xFFFFu);
+                    std::memcpy(to, &w, 4);
+                } else {
+                    std::memcpy(to, &pr, 8);
+                }
+            }
+        }
+    }
+}
+
+int32_t lane_off_places(int32_t n, int waves) {
+    const int64_t state = (((int64_t)n + 1) & ~(int64_t)1) * 4 + 8 * (int64_t)waves;   // as shared_state_bytes
+    return (int32_t)((state + 15) & ~(int64_t)15);
+}
+
+int64_t lane_lds_bytes(int32_t n, int waves, int32_t n_rounds) {
+    return lane_off_places(n, waves) + 16 * (int64_t)n_rounds * waves;
+}
+
+int lane_waves(const LaneImage &im, const Packed &p, bool compact, int32_t n_reads, int32_t quads, int cus, int max_lds) {
+    // a level of fewer than eight variables leaves a wave's lanes idle that the windows would use
+    if (im.n_levels <= 0 || (int64_t)im.n_slots < 8 * (int64_t)im.n_levels) return 0;
+    // a wave for every chunk of an average level, as far as all replicas' waves are resident (two per SIMD)
+    // and the places fit
+    const int32_t chunks = im.level_chunk.back();
+    const int32_t mean = (chunks + im.n_levels - 1) / im.n_levels;
+    auto fits = [&](int w) { return lane_lds_bytes(p.n, w, im.n_levels + chunks / w) <= max_lds; };
+    if (!fits(1)) return 0;
+    int alone = 1, waves = 1;   // of one replica by itself, and of this run's
+    while (alone < kLaneMaxWaves && alone < mean && fits(2 * alone)) alone *= 2;
+    while (waves < alone && (int64_t)n_reads * waves * 2 <= (int64_t)cus * 8) waves *= 2;
+    // A lane adds its variable's records one after another, so the rows past those loaded ahead decide
+    // whether one update per lane pays.  Microseconds per sweep of one replica by itself (with many, the other
+    // kernels' wider teams lose more): here a round 1.15 and a row past kLaneReach 0.042, or 0.075 where the
+    // records leave the L2; the quad kernel a round 1.3 + 0.028 W and a quarter of the rows; the windows 0.65
+    // each, 1.45 with over 64 records per variable.  Fitted over 100 .. 12000 variables of mean degree 3 .. 250
+    // and hubs of 500 .. 30000 neighbours, where it is within 15 % but for images about the size of an L2.
+    // Measured here, by windows (before their settled sweeps) and in the quad kernel: N = 4000, degree 40
+    // 247, 314 and 234 us, degree 80 1313, 910 and 526, degree 250 9533, 1192 and 3805; N = 1000, degree 16 51, 100
+    // and 78, degree 40 225, 118 and 221; a hub of 9999 in N = 10^4 453 and in the quad kernel 215.
+    const double row_us = (double)im.n_rows * 64 * (compact ? 4 : 8) <= 3.5e6 ? 0.042 : 0.075;
+    double rounds = 0.0, past = 0.0, records = 0.0;
+    for (int32_t l = 0; l < im.n_levels; ++l)
+        for (int32_t c = im.level_chunk[(size_t)l]; c < im.level_chunk[(size_t)l + 1]; c += alone) {
+            rounds += 1.0;
+            past += std::max<int32_t>(0, im.chunks[(size_t)c].rows - kLaneReach);
+        }
+    for (int32_t d : p.pair_deg) records += d;
+    double other = (double)im.n_win8 * (records > 64.0 * im.n_slots ? 1.45 : 0.65);
+    if (quads > 0 && (int64_t)im.n_slots * 2 >= (int64_t)quads * im.n_levels) {   // as choose_lanes
+        double q = 0.0;
+        for (int32_t m : im.level_slots) q += (m + quads - 1) / quads;
+        other = q * (1.3 + 0.028 * p.max_width) + 0.25 * row_us * past;
+    }
+    return 1.15 * rounds + row_us * past < other ? waves : 0;
 }
 
 void build_lane_rounds(const LaneImage &im, int waves, std::vector<LaneRows> &rounds) {

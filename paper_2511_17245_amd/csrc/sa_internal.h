@@ -97,6 +97,7 @@ struct Packed {
     // {0, 0} up to a multiple of kPairBlock) and its linear coefficient
     std::vector<PairRec> pair;
     std::vector<int32_t> pair_row, pair_deg, pair_h;
+    bool pair16 = false;   // they have 16-bit indices and couplings
     // settled sweeps (sa_settled.h): 1 for a variable that keeps its coefficients cached (every term holds
     // it to the first or second power, and no variable of the term has more than three other factors there)
     std::vector<uint8_t> cached;
@@ -332,23 +333,27 @@ struct LaneArgs {
 };
 // The same on the host.
 struct LaneImage {
-    std::vector<int32_t> level_chunk;
+    std::vector<int32_t> level_chunk, level_slots;   // per level: its first chunk; its variables
     std::vector<LaneRows> chunks;
     std::vector<LaneSlot> slots;
     std::vector<uint8_t> recs;
-    int32_t n_levels = 0, n_slots = 0, max_chunks = 0;   // most chunks of a level
+    int64_t n_rows = 0;
+    int32_t n_levels = 0, n_slots = 0;   // (n_levels 0: none)
+    int32_t n_win8 = 0;                  // windows of eight waves (build_schedule)
     bool compact = false;
 };
 constexpr int kLaneMaxWaves = 8;
 constexpr int32_t kLaneReach = 12;   // rows loaded ahead (sa_lane.h, kLaneAhead)
 // The rounds of a sweep for `waves` waves per replica (LaneArgs::rounds).
 void build_lane_rounds(const LaneImage &im, int waves, std::vector<LaneRows> &rounds);
-// Levels, chunks and records of a problem with compact pair records; compact: 16-bit records.
-void build_lanes(const Packed &p, bool compact, LaneImage &out);
+// Levels and chunks of a problem with compact pair records, and then their records; compact: 16-bit ones.
+void build_lane_chunks(const Packed &p, LaneImage &out);
+void build_lane_records(const Packed &p, bool compact, LaneImage &im);
 // Whether the lane kernel can run `rule` on this packed problem, and whether with 16-bit records.
-bool lane_eligible(int rule, const Packed &p, bool coef32, int device, bool &compact);
-// Waves per replica (0: the automatic choice goes to another kernel).
-int lane_waves(const LaneImage &im, int32_t n, int32_t n_reads, int device);
+bool lane_eligible(int rule, const Packed &p, bool coef32, int max_lds, bool &compact);
+// Waves per replica from a problem's chunks (0: the automatic choice goes to another kernel); quads: those of
+// the quad kernel's workgroup, 0 where it cannot run the problem.
+int lane_waves(const LaneImage &im, const Packed &p, bool compact, int32_t n_reads, int32_t quads, int cus, int max_lds);
 // LDS bytes of one replica: state, energy parts and the waves' places in n_rounds rounds.
 int64_t lane_lds_bytes(int32_t n, int waves, int32_t n_rounds);
 int32_t lane_off_places(int32_t n, int waves);

@@ -6,39 +6,12 @@
 
 namespace sa {
 
-bool lane_eligible(int rule, const Packed &p, bool coef32, int device, bool &compact) {
+bool lane_eligible(int rule, const Packed &p, bool coef32, int max_lds, bool &compact) {
     compact = false;
     if ((rule != SA_HEAT_BATH && rule != SA_HEAT_BATH_CLOSED) || p.dense || p.pair_row.empty()) return false;
-    int max_lds = 65536;
-    (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
-    if (shared_state_bytes(p.n, kLaneMaxWaves) > max_lds) return false;
-    compact = coef32 && p.z23 && p.n <= 65536;
-    for (size_t i = 0; compact && i < p.pair.size(); ++i) compact = p.pair[i].J >= INT16_MIN && p.pair[i].J <= INT16_MAX;
+    if (lane_off_places(p.n, kLaneMaxWaves) > max_lds) return false;
+    compact = coef32 && p.z23 && p.pair16;
     return true;
-}
-
-int32_t lane_off_places(int32_t n, int waves) { return (int32_t)((shared_state_bytes(n, waves) + 15) & ~(int64_t)15); }
-
-int64_t lane_lds_bytes(int32_t n, int waves, int32_t n_rounds) {
-    return lane_off_places(n, waves) + 16 * (int64_t)n_rounds * waves;
-}
-
-int lane_waves(const LaneImage &im, int32_t n, int32_t n_reads, int device) {
-    // a level of fewer than eight variables leaves a wave's lanes idle that the windows would use
-    if (im.n_levels <= 0 || (int64_t)im.n_slots < 8 * (int64_t)im.n_levels) return 0;
-    int cus = 256, max_lds = 65536;
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
-    (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
-    // a wave for every chunk of an average level, as far as all replicas' waves are resident (two per SIMD)
-    // and the places fit
-    const int32_t chunks = im.level_chunk.back();
-    const int32_t mean = (chunks + im.n_levels - 1) / im.n_levels;
-    auto fits = [&](int w) { return lane_lds_bytes(n, w, im.n_levels + chunks / w) <= max_lds; };
-    if (!fits(1)) return 0;
-    int waves = 1;
-    while (waves < kLaneMaxWaves && waves < mean && fits(2 * waves) && (int64_t)n_reads * waves * 2 <= (int64_t)cus * 8)
-        waves *= 2;
-    return waves;
 }
 
 int launch_lane(LaneArgs a, bool compact, int waves, void *stream, std::string &err) {

@@ -66,10 +66,12 @@ struct sa_plan {
     };
     Levels levels;
     Sched order;                      // every variable in index order (the settled kernel), on first use
-    // the lane kernel's levels, chunks and records (heat bath of pair problems), on first use
+    // the lane kernel's levels and chunks (heat bath of pair problems), on first use; its records and
+    // their device image once a run is given to it
     struct Lanes {
+        bool chunked = false;
         void *dev = nullptr;
-        sa::LaneImage im;             // counts and level offsets (its large arrays are released)
+        sa::LaneImage im;             // (its slots and records are released after the upload)
         const sa::LaneRows *chunks = nullptr;
         const sa::LaneSlot *slots = nullptr;
         const void *recs = nullptr;
@@ -109,7 +111,9 @@ int resolve_schedule(sa_plan *plan, const sa_schedule *sched, std::vector<double
 int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out);
 // The plan's variables in index order (build_order; n_active of them not fixed).
 int get_order(sa_plan *plan, sa_plan::Sched **out);
-// The plan's lane image (16-bit records or not), built and uploaded on first use.
+// The plan's lane chunks, built on first use, and its lane image (16-bit records or not), built and uploaded
+// on first use.
+const LaneImage &get_lane_chunks(sa_plan *plan);
 int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out);
 int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out);
 // The lane kernel's choice for a run of n_sweeps sweeps, and its arguments that come from the plan.
