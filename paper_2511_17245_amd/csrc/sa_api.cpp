@@ -276,10 +276,14 @@ int get_order(sa_plan *plan, sa_plan::Sched **out) {
         std::vector<sa::SchedRec> host;
         sc.n_active = sa::build_order(plan->packed, host);
         sc.n_win = (int32_t)host.size();
+        // the counters of AnnealArgs::all follow the list
+        const size_t list = align256(host.size() * sizeof(sa::SchedRec));
+        std::vector<char> img(list + 256, 0);
+        std::memcpy(img.data(), host.data(), host.size() * sizeof(sa::SchedRec));
         void *dev = nullptr;
-        hipError_t e = hipMalloc(&dev, host.size() * sizeof(sa::SchedRec));
+        hipError_t e = hipMalloc(&dev, img.size());
         if (e != hipSuccess) return fail(SA_ENOMEM, std::string("hipMalloc(order): ") + hipGetErrorString(e));
-        e = hipMemcpy(dev, host.data(), host.size() * sizeof(sa::SchedRec), hipMemcpyHostToDevice);
+        e = hipMemcpy(dev, img.data(), img.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(dev);
             return hip_fail(e, "hipMemcpy(order)");
@@ -681,6 +685,7 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
             }
             a.order = one->dev;
             a.n_order = one->n_active;
+            a.all = sa::settled_counters(one->dev, n);
             a.z30 = plan->packed.z30 ? 1 : 0;
             const sa::SettledChoice set =
                 sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
@@ -759,11 +764,12 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         }
         a.order = one->dev;
         a.n_order = one->n_active;
+        a.all = sa::settled_counters(one->dev, n);
         a.z30 = plan->packed.z30 ? 1 : 0;
         const sa::SettledChoice set =
             sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
         std::string err;
-        rc = sa::launch_windows(plan->rule, a, lc, set, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
+        rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_visits(plan->rule, plan->packed), plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
                                 stream, err);
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
         if (rc != SA_OK) {

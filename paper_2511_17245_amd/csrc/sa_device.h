@@ -950,6 +950,15 @@ __device__ __forceinline__ void window_barrier() {
 // A word of device memory, the same for the whole wave.
 __device__ __forceinline__ int32_t uni_load(const int32_t *p) { return (int32_t)uni32((uint32_t)*p); }
 
+// The kernel's one argument, loaded anew from its segment: what only the code around the sweeps needs is not
+// held in scalar registers through them (16 to 20 spilled ones fewer in the anneal kernels).
+template <typename Args>
+__device__ __forceinline__ const Args __attribute__((address_space(4))) *arguments() {
+    auto p = (const Args __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // What one replica's sweeps need (shared by the plain and the batched kernels).
 struct ReplicaCtx {
     DevProblem P;
@@ -964,11 +973,7 @@ struct ReplicaCtx {
     bool active;            // false: an idle team that only keeps the workgroup's barriers
     uint64_t *trace;        // this read's hash word of sweep 0 (indexed by the sweep), or nullptr
     int64_t *c1;            // dense form: this replica's coefficient cache in LDS, or nullptr
-    int32_t stop;           // 0, or: end after a sweep with at most n_order / stop changes (the settled
-    int32_t n_order;        // kernel takes the rest); the variables of a sweep, over the replicas that share
-                            // the workgroup's barriers
     int32_t s_first;        // this replica's first sweep (s_begin: the workgroup's)
-    uint32_t *ctr;          // shared replicas that may end so: three change counters (LDS)
 };
 
 // Initial state (given, or uniform on each box, Sec. 3.1) written by threads tid, tid+nthr, ...
@@ -1081,39 +1086,62 @@ __device__ __forceinline__ bool update_rule(const ReplicaCtx &R, const ZT *z, in
     }
 }
 
+// Whether every replica of the launch that has started is settled now, this one (quiet; counted: it is counted
+// as settled so far) among them.  One wave; the counters only ever part by the replicas that run unsettled.
+__device__ __forceinline__ bool all_settled(uint32_t *all, bool quiet, bool &counted, int lane) {
+    uint32_t ahead = 1u;
+    if (lane == 0) {
+        if (quiet != counted) atomicAdd(&all[1], quiet ? 1u : ~0u);
+        if (quiet) ahead = atomicAdd(&all[0], 0u) - atomicAdd(&all[1], 0u);
+    }
+    counted = quiet;
+    return quiet && uni32(ahead) == 0u;
+}
+
+// After the sweeps since the last check, in which this wave made `moves` changes: whether the run ends here
+// (uniform over the waves that share barriers; they decide together, from their sum).  limit: changes up to which
+// a replica becomes settled; past twice as many it is no longer.  ctr: three change counters and the decision, in
+// LDS; all: the launch's counters, or nullptr (each replica, or workgroup, for itself).
+__device__ __forceinline__ bool settled_check(uint32_t moves, uint32_t limit, bool shared, uint32_t *ctr, uint32_t *all,
+                                              uint32_t &check_no, bool &counted, int lane) {
+    if (shared) {
+        // the next check's counter is cleared before this barrier, a check after its last reads
+        if (lane == 0 && moves != 0) atomicAdd(&ctr[check_no % 3], moves);
+        if (threadIdx.x == 0) ctr[(check_no + 1) % 3] = 0;
+        window_barrier();
+        moves = uni32(ctr[check_no % 3]);
+        ++check_no;
+    }
+    const bool quiet = moves <= (counted ? 2u * limit : limit);
+    if (!all) return quiet;
+    bool leave = false;
+    const bool speaks = !shared || threadIdx.x < (unsigned)kWave;
+    if (speaks) leave = all_settled(all, quiet, counted, lane);
+    counted = quiet;
+    if (shared && quiet) {   // uniform
+        if (threadIdx.x == 0) ctr[3] = leave ? 1u : 0u;
+        window_barrier();
+        leave = uni32(ctr[3]) != 0u;
+    }
+    return leave;
+}
+
 // Sweeps [s_begin, s_end) of one replica (index order, Sec. 3.1): this wave's slots of the
-// schedule.  Returns the sum of the energy changes this wave applied, and in s_next the first sweep
-// not made.
+// schedule.  Returns the sum of the energy changes this wave applied and adds their number to moves.
 template <int kRule, bool kStateInLds, int kRegChunk, int kMaxE, typename Acc, typename ZT>
-__device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int lane, int32_t &s_next) {
+__device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int lane, uint32_t &moves) {
     const DevProblem &P = R.P;
     const int32_t n_win = R.n_win;
     const SchedRec *mine = R.sched;
     int64_t E = 0;
     uint64_t H = 0;   // change of the state hash in this sweep by this wave's moves (tracing)
     ScanCarry cy;
-    s_next = R.s_end;
     if (!R.active && !R.shared) return 0;
-    uint32_t sweep_no = 0;
-    // after a sweep with `moves` changes by this wave: whether the run ends here (uniform over the waves
-    // that share barriers; they decide together, from their sum)
-    auto settled = [&](uint32_t moves) -> bool {
-        if (R.shared) {
-            // the next sweep's counter is cleared before this barrier, a sweep after its last reads
-            if (lane == 0 && moves != 0) atomicAdd(&R.ctr[sweep_no % 3], moves);
-            if (threadIdx.x == 0) R.ctr[(sweep_no + 1) % 3] = 0;
-            window_barrier();
-            moves = uni32(R.ctr[sweep_no % 3]);
-        }
-        return moves * (uint32_t)R.stop <= (uint32_t)R.n_order;
-    };
-    for (int32_t s = R.s_begin; s < R.s_end; ++s, ++sweep_no) {
+    for (int32_t s = R.s_begin; s < R.s_end; ++s) {
         if (!R.active || s < R.s_first) {   // an idle team only keeps the workgroup's barriers
             for (int32_t w = 0; w < n_win; ++w) window_barrier();
-            if (R.stop != 0 && settled(0)) return 0;
             continue;
         }
-        uint32_t moves = 0;   // changes by this wave
         const double beta = R.beta[s];
         const double r_opt =
             R.otm_r >= 0.0 ? R.otm_r : (R.n_sweeps > 1 ? (double)s / (double)(R.n_sweeps - 1) : 0.0);
@@ -1213,10 +1241,6 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
             if (lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
             H = 0;
         }
-        if (R.stop != 0 && settled(moves)) {
-            s_next = s + 1;
-            break;
-        }
     }
     return E;
 }
@@ -1248,8 +1272,14 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     int32_t *z = kStateInLds ? lds_state + (shared ? 0 : (size_t)wave * n) : A.z_out + (size_t)read * n;
     const int tid = g * kWave + lane, nthr = G * kWave;  // threads of this replica
 
-    // the last of a run's three launches starts where the others ended (e_out holds the next sweep)
-    const int32_t s_begin = A.phase == kPhaseLast ? (int32_t)A.e_out[read] : A.s_begin;
+    // the last of a run's three launches starts where the others ended, if they did not end the run
+    int32_t s = A.s_begin;
+    if (A.phase == kPhaseLast) {   // uniform over the replica's waves
+        // (in a scalar register, as everything that follows from the sweep's index)
+        const int64_t at = (int64_t)lane_read64((uint64_t)A.e_out[read], 0);
+        if (!handed_over(at)) return;
+        s = handed_sweep(at);
+    }
     init_state(P, z, A.z_init ? A.z_init + (size_t)read * n : nullptr, (uint32_t)read, A.instance_id,
                A.key0, A.key1, tid, nthr);
     if (shared) window_barrier();
@@ -1275,9 +1305,7 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     R.P = P;
     R.beta = A.beta;
     R.n_sweeps = A.n_sweeps;
-    R.s_begin = s_begin;
-    R.s_first = s_begin;
-    R.s_end = A.s_end;
+    R.s_first = INT32_MIN;
     R.key0 = A.key0;
     R.key1 = A.key1;
     R.instance_id = A.instance_id;
@@ -1290,18 +1318,37 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
     R.active = true;
     R.trace = trace ? trace - A.s_begin : nullptr;
     R.c1 = c1;
-    R.stop = A.phase == kPhaseFirst ? settled_share(G) : 0;
-    R.n_order = A.n_order;
     // the waves' energy parts follow the state (shared replicas); the change counters use their place
     int64_t *parts = (int64_t *)(lds_state + (((size_t)n + 1) & ~(size_t)1));
-    R.ctr = (uint32_t *)parts;
-    if (shared && R.stop != 0) {
-        if (tid < 3) R.ctr[tid] = 0;   // (a sweep's barriers come before their first use)
-        if (A.n_win == 0) window_barrier();
+    uint32_t *ctr = (uint32_t *)parts;
+    const bool first = A.phase == kPhaseFirst;
+    if (first) {
+        if (lane == 0 && g == 0) atomicAdd(&A.all[0], 1u);
+        if (shared) {
+            if (tid < 3) ctr[tid] = 0;
+            window_barrier();
+        }
     }
-    int32_t s_next;
-    E += sweep_replica<kRule, kStateInLds, kRegChunk, kMaxE, Acc, int32_t>(R, z, lane, s_next);
-    if (shared && R.stop != 0) window_barrier();   // the counters' last reads
+    uint32_t check_no = 0;
+    bool counted = false;
+    for (;;) {   // once, or in the first launch a stretch of sweeps at a time
+        R.s_begin = s;
+        {
+            const auto K = arguments<AnnealArgs>();
+            const bool more = first && K->s_end - s >= K->every + kSettledRest;   // (with enough left to hand over)
+            R.s_end = more ? s + K->every : K->s_end;
+        }
+        uint32_t moves = 0;
+        E += sweep_replica<kRule, kStateInLds, kRegChunk, kMaxE, Acc, int32_t>(R, z, lane, moves);
+        s = R.s_end;
+        const auto K = arguments<AnnealArgs>();
+        if (s >= K->s_end || settled_check(moves, K->limit, shared, ctr, K->all, check_no, counted, lane)) break;
+    }
+    const auto K = arguments<AnnealArgs>();
+    if (first) {
+        if (!counted && lane == 0 && g == 0) atomicAdd(&K->all[1], 1u);
+        if (shared) window_barrier();   // the counters' last reads
+    }
 
     if (shared) {
         // combine the waves' energy parts
@@ -1313,10 +1360,10 @@ __global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &
         }
     }
     if (kStateInLds) {
-        int32_t *zo = A.z_out + (size_t)read * n;
+        int32_t *zo = K->z_out + (size_t)read * n;
         for (int32_t k = tid; k < n; k += nthr) zo[k] = z[k];
     }
-    if (g == 0 && lane == 0) A.e_out[read] = A.phase == kPhaseFirst ? (int64_t)s_next : E;
+    if (g == 0 && lane == 0) K->e_out[read] = s < K->s_end ? hand_over(s) : E;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1405,18 +1452,27 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
         R.active = active;
         R.trace = nullptr;
         R.c1 = nullptr;
-        R.stop = may_stop ? settled_share(G) : 0;
-        R.n_order = G > 1 ? D.n_order * n_active : D.n_order;
-        R.ctr = (uint32_t *)parts;
-        int32_t s_next;
-        if (D.rule == SA_METROPOLIS) {
-            E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane, s_next);
-        } else if (D.rule == SA_HEAT_BATH) {
-            E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next);
-        } else if (D.rule == SA_HEAT_BATH_CLOSED) {
-            E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane, s_next);
-        } else {
-            E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane, s_next);
+        const int32_t run_end = R.s_end;
+        uint32_t check_no = 0;
+        bool counted = false;
+        int32_t s = R.s_begin;
+        for (;;) {   // once, or where replicas may end settled a stretch of sweeps at a time
+            R.s_begin = s;
+            R.s_end = may_stop && run_end - s >= D.every ? s + D.every : run_end;
+            uint32_t moves = 0;
+            if (D.rule == SA_METROPOLIS) {
+                E += sweep_replica<SA_METROPOLIS, true, 0, 1, Acc, ZT>(R, z, lane, moves);
+            } else if (D.rule == SA_HEAT_BATH) {
+                E += sweep_replica<SA_HEAT_BATH, true, 0, kMaxE, Acc, ZT>(R, z, lane, moves);
+            } else if (D.rule == SA_HEAT_BATH_CLOSED) {
+                E += sweep_replica<SA_HEAT_BATH_CLOSED, true, 0, kMaxE, Acc, ZT>(R, z, lane, moves);
+            } else {
+                E += sweep_replica<SA_OPT_METROPOLIS, true, 0, kOtmE, Acc, ZT>(R, z, lane, moves);
+            }
+            s = R.s_end;
+            if (s >= run_end || settled_check(moves, (uint32_t)(D.limit * (G > 1 ? n_active : 1)), G > 1, (uint32_t *)parts,
+                                              nullptr, check_no, counted, lane))
+                break;
         }
         if (may_stop && G > 1) window_barrier();   // the counters' last reads
         if (lane == 0) parts[wave] = E;
@@ -1426,7 +1482,7 @@ __global__ void __launch_bounds__(kBatchWaves * 64, 4) batch_kernel(BatchArgs B)
                 int64_t tot = 0;
                 for (int q = 0; q < G; ++q) tot += parts[team * G + q];
                 D.e_out[read] = tot;
-                if (chain) D.next[read] = may_stop && s_next < R.s_end ? ~s_next : s_next;
+                if (chain) D.next[read] = s < run_end ? ~s : s;
             }
             for (int32_t k = tid; k < P.n; k += nthr) zo[k] = (int32_t)z[k];
         }

@@ -184,20 +184,48 @@ struct DevProblem {
     const PairRec *pair;     // compact pair records (nullptr when the problem has none)
 };
 
-// A run is one launch, or three: the first ends each replica at its first sweep that changes few
-// variables (at most 1 / settled_share of them) and leaves the next sweep's
-// index in e_out; the settled kernel (sa_settled.h) takes it from there, and the last finishes the
-// replicas that came unsettled (a schedule that warms up) and writes every energy.  States pass
-// through z_out.
+// A run is one launch, or three: the first runs each replica to its end, or hands it over once the replicas
+// change few variables, the next sweep's index in e_out (hand_over); the settled kernel (sa_settled.h) takes it
+// from there, and the last writes its energy and finishes it where it came unsettled (a schedule that warms up).
+// States pass through z_out.
+//
+// The launches follow one another, so a replica that left the first while another stays there gains nothing
+// and may cost its settled sweeps on top: at a constant temperature, where each settles by chance at a sweep of
+// its own, runs took up to 2.4 times as long.  So a replica of a plain run leaves only when all that have
+// started are settled (two counters in device memory: started, settled; a replica that ends counts in both).
 constexpr int32_t kPhaseWhole = 0, kPhaseFirst = 1, kPhaseLast = 2;
-// A settled sweep serves its changes and visits one after another by one wave, where the ordinary
-// kernel's G waves share them: a quarter of the variables for G = 1 (a visit costs about the same in
-// both), and for G > 1 the share at which the serial visits (about 1 us each) cost less than the
-// sweep they replace.
-constexpr int32_t settled_share(int32_t G) { return G == 1 ? 4 : 8 * G; }
-// The same for the Metropolis / OTM quad kernel, whose ordinary update costs about 170 cycles (16 per
-// round): a settled sweep's change costs some ten times that.
-constexpr int32_t kSettledShareQuad = 16;
+// A replica becomes settled when at most one update in settled_share changed its variable, over settled_every
+// sweeps on end, and is no longer with over twice as many; it leaves the settled kernel after three such stretches.
+// A settled sweep serves its changes and visits one after another (about 1.1 us each), where the ordinary
+// kernel's G waves share the updates.  Share of changes at which the two take the same time, one replica at a
+// constant temperature (dense, HUIO, multilinear and pair problems of 26 to 4000 variables): G = 1 0.35 to 0.9,
+// but 0.16 to 0.3 where most ask for a visit (the heat bath's draws about two per change, variables without
+// cached coefficients); G = 2 0.2 to 0.34; G = 4 0.08 to 0.15; G = 8 0.03 to 0.05.
+constexpr int32_t settled_share(int32_t G, bool visits) { return G > 2 ? 6 * G : visits ? 14 : G == 2 ? 10 : 4; }
+// The Metropolis / OTM quad kernel (16 updates per round): 0.02 to 0.055, 0.01 for pair problems. (N = 2000 HUIO,
+// 300 sweeps x 1024 reads, one in 96, 48 and 40: optimal transition 27.4, 26.5 and 26.0 ms, Metropolis 31.7,
+// 29.3 and 28.7.)
+constexpr int32_t settled_share_quad(bool pairs) { return pairs ? 112 : 40; }
+// Sweeps left that repay forming the caches (N = 2000 HUIO: 1 ms, 7 sweeps of the quad kernel, of whose time a
+// settled one saves a third).
+constexpr int32_t kSettledRest = 16, kSettledRestQuad = 48;
+// Sweeps of some 30 us together: a check takes about 0.5 us, and over few updates the count of changes is
+// mostly chance.
+constexpr int32_t settled_every(int32_t n_order, int32_t G) {
+    int32_t every = 1;
+    while (every < 16 && (int64_t)every * n_order < 48 * G) every *= 2;
+    return every;
+}
+constexpr int32_t kSettledEveryQuad = 4;
+// Changes in settled_every sweeps up to which a replica becomes settled.
+constexpr int32_t settled_limit(int32_t n_order, int32_t every, int32_t share) {
+    const int64_t m = (int64_t)n_order * every / share;
+    return m > 1 ? (int32_t)m : 1;
+}
+// A sweep's index as it stands in e_out: energies lie within 2^62 of 0 (check_int64_bound).
+constexpr int64_t hand_over(int32_t s) { return INT64_MIN + s; }
+constexpr bool handed_over(int64_t e) { return e < -((int64_t)1 << 62); }
+constexpr int32_t handed_sweep(int64_t e) { return (int32_t)(e - INT64_MIN); }
 
 // Kernel arguments of one annealing launch.
 struct AnnealArgs {
@@ -232,7 +260,9 @@ struct AnnealArgs {
     int32_t closed;          // heat bath: closed-form draws
     int32_t exact53;         // energy differences are below 2^52 in magnitude
     int32_t z30;             // every bound of the problem is below 2^30 in magnitude
-    int32_t leave;           // changes per sweep past which a replica leaves
+    int32_t every;           // sweeps between the checks whether a replica has settled, or is no longer
+    int32_t limit;           // changes in as many sweeps up to which it becomes settled; past twice as many it is not
+    uint32_t *all;           // replicas started and settled (two counters)
 };
 
 // Kernel arguments of one launch of the quad kernel (one update per four lanes, dependency levels).
@@ -257,7 +287,8 @@ struct QuadArgs {
     int64_t *e_out;
     uint64_t *trace;             // as AnnealArgs::trace
     int32_t phase;               // as AnnealArgs::phase
-    int32_t n_order;
+    int32_t limit;               // (over kSettledEveryQuad sweeps)
+    uint32_t *all;
 };
 // Waves of the quad kernel's workgroup (one replica): heat bath, 8 or 16 (below), and Metropolis /
 // optimal transition, one (a HUIO level holds about 16 variables, and a single wave needs no
@@ -380,6 +411,10 @@ struct LaunchChoice {
     int variant = 0;
 };
 
+// The counters of AnnealArgs::all: in the 256 bytes after the order list's, rounded up to 256.
+inline uint32_t *settled_counters(const SchedRec *order, int32_t n) {
+    return (uint32_t *)((char *)const_cast<SchedRec *>(order) + (((size_t)n * sizeof(SchedRec) + 255) & ~(size_t)255));
+}
 // The settled kernel's launch for a problem and a run, or none (lds_bytes = 0).
 struct SettledChoice {
     int lds_bytes = 0;     // state and caches of one replica
@@ -389,8 +424,12 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
 // Launches it: `a` as for launch_anneal, with order, n_order and leave set.
 int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp, bool narrow,
                    void *stream, std::string &err);
-// A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order and n_order set).
-int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t max_width,
+// Whether settled sweeps visit most of what may change (settled_share).
+inline bool settled_visits(int rule, const Packed &p) {
+    return rule == SA_HEAT_BATH || rule == SA_HEAT_BATH_CLOSED || (!p.dense && !p.any_cached);
+}
+// A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order, n_order and all set).
+int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, bool visits, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err);
 
 // The same for the Metropolis / OTM quad kernel: q as for launch_quad_mo, a as for launch_settled.
@@ -457,7 +496,7 @@ struct BatchInst {
     // settled sweeps (as AnnealArgs); next == nullptr: none
     int32_t *next;           // n_reads: the next sweep s, or ~s of a settled replica (device)
     const SchedRec *order;
-    int32_t n_order, off_c, off_c2, off_m, z30, leave;
+    int32_t n_order, off_c, off_c2, off_m, z30, every, limit;
     int32_t team_waves;      // > 0: run by the dense team kernel (off_c: c1, off_m: the state; exact53 as AnnealArgs)
     int32_t exact53;
 };

@@ -94,12 +94,15 @@ int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_
     return SA_OK;
 }
 
-int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t max_width,
+int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, bool visits, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err) {
     a.phase = kPhaseWhole;
-    if (sc.lds_bytes == 0) return launch_anneal(rule, a, lc, stream, err);
+    // (two more launches cost a run of 0.5 ms a tenth: N = 24 pairs, G = 4, 90 sweeps 0.47 to 0.52 ms)
+    if (sc.lds_bytes == 0 || (int64_t)(a.s_end - a.s_begin) * a.n_order < 1200 * (int64_t)lc.win_waves)
+        return launch_anneal(rule, a, lc, stream, err);
     a.phase = kPhaseFirst;
-    a.leave = std::max<int32_t>(1, (int32_t)(3 * (int64_t)a.n_order / settled_share(lc.win_waves)));
+    a.every = settled_every(a.n_order, lc.win_waves);
+    a.limit = settled_limit(a.n_order, a.every, settled_share(lc.win_waves, visits));
     int rc = launch_anneal(rule, a, lc, stream, err);
     if (rc == SA_OK) rc = launch_settled(rule, a, sc, max_width, max_exp, narrow, stream, err);
     if (rc != SA_OK) return rc;
@@ -113,8 +116,9 @@ int launch_rounds(int rule, QuadArgs q, AnnealArgs a, const SettledChoice &sc, i
     q.phase = kPhaseWhole;
     if (sc.lds_bytes == 0) return launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
     q.phase = kPhaseFirst;
-    q.n_order = a.n_order;
-    a.leave = std::max<int32_t>(1, (int32_t)(3 * (int64_t)a.n_order / kSettledShareQuad));
+    a.every = kSettledEveryQuad;
+    q.limit = a.limit = settled_limit(a.n_order, a.every, settled_share_quad(q.P.pair != nullptr));
+    q.all = a.all;
     int rc = launch_quad_mo(rule, q, max_width, max_exp, narrow, stream, err);
     if (rc == SA_OK) rc = launch_settled(rule, a, sc, max_width, max_exp, narrow, stream, err);
     if (rc != SA_OK) return rc;
@@ -176,7 +180,7 @@ int settle_inst(const Packed &p, bool coef32, const SchedRec *order, int32_t n_o
     d.off_c2 = sc.off_c2;
     d.off_m = sc.off_m;
     d.z30 = p.z30 ? 1 : 0;
-    d.leave = 0;   // set with the team size
+    d.every = d.limit = 0;   // set with the team size
     return sc.lds_bytes;
 }
 

@@ -159,7 +159,8 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     const size_t off_order =
         lanes == 64 ? off_sched + sa::align256(std::max<size_t>(sch.size(), 1) * sizeof(sa::SchedRec))
                     : off_mcoef + sa::align256(std::max<size_t>(mcoef.size(), 1));
-    size_t total = off_order + sa::align256(order.size() * sizeof(sa::SchedRec));
+    // (the counters of AnnealArgs::all follow the list)
+    size_t total = off_order + (order.empty() ? 0 : sa::align256(order.size() * sizeof(sa::SchedRec)) + 256);
     if (!order.empty() && total > kScratchBytes) {
         // no room for the list: every sweep in the ordinary kernel (the same results)
         set = sa::SettledChoice();
@@ -216,6 +217,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     a.dense_cache = lc.dense_cache ? 1 : 0;
     a.order = order.empty() ? nullptr : (const sa::SchedRec *)((char *)area + off_order);
     a.n_order = active;
+    a.all = order.empty() ? nullptr : sa::settled_counters(a.order, (int32_t)order.size());
     a.z30 = pk.z30 ? 1 : 0;
     if (a.trace) {
         rc = sa::launch_zero_u64(a.trace, (int64_t)n_reads * (s1 - s0), stream, err);
@@ -249,7 +251,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
     } else if (by_team) {
         rc = sa::launch_dense_team(rule, a, team, stream, err);
     } else {
-        rc = sa::launch_windows(rule, a, lc, set, pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
+        rc = sa::launch_windows(rule, a, lc, set, sa::settled_visits(rule, pk), pk.max_width, pk.max_exp, sa::dE_fits_32(canon), stream, err);
     }
     if (rc == SA_OK && a.trace) rc = sa::launch_trace_prefix(a.trace, n_reads, s1 - s0, stream, err);
     if (rc != SA_OK) return sa::fail(rc, err);

@@ -128,9 +128,17 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
     int32_t *z = lds_state;
     using Part = std::conditional_t<kNarrow, uint32_t, uint64_t>;
 
-    // the last of a run's three launches starts where the others ended (e_out holds the next sweep)
-    const int32_t s_begin = A.phase == kPhaseLast ? (int32_t)A.e_out[read] : A.s_begin;
+    // the last of a run's three launches starts where the others ended, if they did not end the run
+    int32_t s_begin = A.s_begin;
+    if (A.phase == kPhaseLast) {
+        const int64_t at = (int64_t)lane_read64((uint64_t)A.e_out[read], 0);   // (in scalar registers)
+        if (!handed_over(at)) return;
+        s_begin = handed_sweep(at);
+    }
     int32_t s_next = A.s_end;
+    uint32_t recent = 0, sweep_no = 0;   // changes since the last check whether the replica has settled
+    bool counted = false;
+    if (A.phase == kPhaseFirst && lane == 0) atomicAdd(&A.all[0], 1u);
     init_state(P, z, A.z_init ? A.z_init + (size_t)read * n : nullptr, (uint32_t)read, A.instance_id, A.key0,
                A.key1, lane, kWave);
     if (lane == 0) z[n] = 1;   // the value of an unused factor place in the records' copy
@@ -157,7 +165,6 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
         uint32_t y0 = 0, y1 = 0, y2 = 0, y3 = 0;
 
         for (int32_t s = s_begin; s < A.s_end; ++s) {
-            uint32_t moves = 0;   // the sweep's changes
             const double beta = __ldg(&A.beta[s]);
             const double r_opt =
                 A.otm_r >= 0.0 ? A.otm_r : (A.n_sweeps > 1 ? (double)s / (double)(A.n_sweeps - 1) : 0.0);
@@ -229,7 +236,7 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
                     dE += d;
                     if (trace) H += hash_word(k, v) - hash_word(k, zk);
                 }
-                moves += (uint32_t)__popcll(__ballot(taken)) / 4u;
+                recent += (uint32_t)__popcll(__ballot(taken)) / 4u;
             };
 
             for (int32_t t = 0; t < R; t += 2) {
@@ -258,15 +265,23 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
                 if (lane == 0) atomicAdd((unsigned long long *)&trace[s - A.s_begin], (unsigned long long)hw);
                 H = 0;
             }
-            if (A.phase == kPhaseFirst && moves * (uint32_t)kSettledShareQuad <= (uint32_t)A.n_order) {
-                s_next = s + 1;
-                break;
+            if ((++sweep_no & (uint32_t)(kSettledEveryQuad - 1)) != 0) continue;
+            const auto K = arguments<QuadArgs>();
+            if (K->phase == kPhaseFirst && K->s_end - s > kSettledRestQuad) {   // as settled_check
+                const bool quiet = recent <= (uint32_t)(counted ? 2 * K->limit : K->limit);
+                recent = 0;
+                if (all_settled(K->all, quiet, counted, lane)) {
+                    s_next = s + 1;
+                    break;
+                }
             }
         }
     }
+    const auto K = arguments<QuadArgs>();
+    if (K->phase == kPhaseFirst && !counted && lane == 0) atomicAdd(&K->all[1], 1u);
     E += (int64_t)wave_sum_u64(ql == 0 ? (uint64_t)dE : 0ull);
-    if (lane == 0) A.e_out[read] = A.phase == kPhaseFirst ? (int64_t)s_next : E;
-    int32_t *zo = A.z_out + (size_t)read * n;
+    if (lane == 0) K->e_out[read] = s_next < K->s_end ? hand_over(s_next) : E;
+    int32_t *zo = K->z_out + (size_t)read * n;
     for (int32_t k = lane; k < n; k += kWave) zo[k] = z[k];
 }
 

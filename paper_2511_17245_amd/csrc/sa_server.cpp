@@ -466,7 +466,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         if (choices[i].waves == 0 && lanes[i].waves == 0)
             settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
         if (settled_lds[i]) d.next = r->next_dev;
-        d.leave = std::max<int32_t>(1, 3 * d.n_order / sa::settled_share(G));
+        d.every = sa::settled_every(d.n_order, G);
+        d.limit = sa::settled_limit(d.n_order, d.every, sa::settled_share(G, sa::settled_visits(p.rule, p.packed)));
     }
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);

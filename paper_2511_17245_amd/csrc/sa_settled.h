@@ -3,8 +3,8 @@
 //
 // Under geometric cooling more than half of a run's sweeps change next to nothing (of the N = 2000
 // HUIO problem's sweeps, 60 % change fewer than 1 % of the variables each), and a visit that changes
-// nothing costs as much as one that does.  Once a sweep has changed few variables (settled_share),
-// the replica comes here, with the coefficients cached in LDS (the paper's caches, Sec. 3.2):
+// nothing costs as much as one that does.  Once their sweeps change few variables (settled_share), the
+// replicas come here, with the coefficients cached in LDS (the paper's caches, Sec. 3.2):
 //  - each lane decides from its variable's cache and random words whether the update changes it:
 //    exactly for Metropolis, the closed-form draw and the ends taken by the optimal transition, and
 //    from a bound on the other values' weight for the heat bath; lanes that cannot tell ask for a
@@ -513,11 +513,11 @@ __device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, in
 }
 
 // The settled part of a run of one replica from sweep s: to s_end, or to where it has come unsettled
-// (more than `leave` changes in each of three sweeps on end).  `z`: its state in LDS, `off_*` the byte
-// offsets of the caches after it.  Returns the next sweep; adds to E the energy changes.
+// (more than twice `limit` changes in each of three stretches of `every` sweeps on end).  `z`: its state in LDS,
+// `off_*` the byte offsets of the caches after it.  Returns the next sweep; adds to E the energy changes.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc>
 __device__ __forceinline__ int32_t settled_run(SettleView &S, int32_t *z, int lane, int32_t s, int32_t s_end, int32_t off_c,
-                                               int32_t off_c2, int32_t off_m, uint32_t leave, int64_t &E) {
+                                               int32_t off_c2, int32_t off_m, int32_t every, uint32_t limit, int64_t &E) {
     ReplicaCtx &R = S.R;
     R.c1 = kDense ? (int64_t *)((char *)z + off_c) : nullptr;
     S.wide = !R.P.coef32;
@@ -529,30 +529,37 @@ __device__ __forceinline__ int32_t settled_run(SettleView &S, int32_t *z, int la
     if (kDense) dense_cache_init(R.P, z, R.c1, lane, kWave);
     state_write_fence<true>();
     ScanCarry cy;
-    int busy = 0;   // sweeps on end past `leave`
+    int busy = 0;   // stretches on end past twice `limit`
+    uint32_t moves = 0;
+    int32_t left = every;
     for (; s < s_end; ++s) {
         uint64_t H = 0;
         const double beta = R.beta[s];
         const double r_opt =
             R.otm_r >= 0.0 ? R.otm_r : (R.n_sweeps > 1 ? (double)s / (double)(R.n_sweeps - 1) : 0.0);
-        const uint32_t moves = settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H, E);
+        moves += settled_sweep<kDense, kRule, kRegChunk, kMaxE, Acc, int32_t>(S, z, lane, s, beta, r_opt, cy, H, E);
         if (R.trace && H != 0 && lane == 0) atomicAdd((unsigned long long *)&R.trace[s], (unsigned long long)H);
-        busy = moves > leave ? busy + 1 : 0;
-        if (busy == 3) return s + 1;
+        if (--left == 0) {
+            busy = moves > 2u * limit ? busy + 1 : 0;
+            if (busy == 3) return s + 1;
+            moves = 0;
+            left = every;
+        }
     }
     return s;
 }
 
-// Plain runs: read blockIdx.x from the state in z_out and the sweep in e_out; leaves the state and the
-// next sweep there.
+// Plain runs: read blockIdx.x, if it was handed over, from the state in z_out and the sweep in e_out; leaves
+// the state and the next sweep there.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc>
 __global__ void __launch_bounds__(kWave) settled_kernel(AnnealArgs A) {
     extern __shared__ int32_t lds_state[];
     const int lane = (int)threadIdx.x;
     const int read = (int)blockIdx.x;
     if (read >= A.n_reads) return;
-    int32_t s = (int32_t)A.e_out[read];
-    if (s >= A.s_end) return;   // uniform
+    const int64_t at = (int64_t)lane_read64((uint64_t)A.e_out[read], 0);   // (in scalar registers)
+    if (!handed_over(at)) return;   // uniform
+    int32_t s = handed_sweep(at);
     const int32_t n = A.P.n;
     int32_t *z = lds_state;
     int32_t *zo = A.z_out + (size_t)read * n;
@@ -574,9 +581,9 @@ __global__ void __launch_bounds__(kWave) settled_kernel(AnnealArgs A) {
     S.closed = A.closed != 0;
     int64_t E = 0;   // (the last launch sums the energy of every state)
     s = settled_run<kDense, kRule, kRegChunk, kMaxE, Acc>(S, z, lane, s, A.s_end, A.off_c, A.off_c2, A.off_m,
-                                                          (uint32_t)A.leave, E);
+                                                          A.every, (uint32_t)A.limit, E);
     for (int32_t k = lane; k < n; k += kWave) zo[k] = z[k];
-    if (lane == 0) A.e_out[read] = s;
+    if (lane == 0) A.e_out[read] = hand_over(s);
 }
 
 // Batches and server chunks: task blockIdx.x, a read whose D.next says it has settled.  Leaves its
@@ -615,7 +622,7 @@ __global__ void __launch_bounds__(kWave) settled_batch_kernel(const BatchInst *i
     int64_t E = 0;
     auto go = [&](auto dense, auto rule, auto maxe) {
         s = settled_run<decltype(dense)::value, decltype(rule)::value, 0, decltype(maxe)::value, Acc>(
-            S, z, lane, s, D.s_end, D.off_c, D.off_c2, D.off_m, (uint32_t)D.leave, E);
+            S, z, lane, s, D.s_end, D.off_c, D.off_c2, D.off_m, D.every, (uint32_t)D.limit, E);
     };
     auto by_rule = [&](auto dense, auto maxe, auto otm_e) {
         if (D.rule == SA_METROPOLIS) {
