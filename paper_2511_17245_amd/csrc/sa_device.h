@@ -586,84 +586,14 @@ __device__ __forceinline__ int32_t draw_single(uint32_t W, uint32_t c, uint32_t 
     return (int32_t)lane_read32((uint32_t)hit, __ffsll((unsigned long long)found) - 1);
 }
 
-// Heat-bath choice (Sec. 3.3.2) among all W values, with the fixed summation order: value j of the
-// range belongs to lane j / c (c = ceil(W/64)); lane sums are left to right; the lanes' sums are
-// combined by wave_scan_rows; the first value whose cumulative weight exceeds U * total is drawn
-// (the last value if rounding leaves none).  W < 2^31, so value indexes are 32-bit: j0 + i < 64 c
-// <= W + 63.
+// The weights in double precision: dmin is the smallest dE, dlane (c > 8) that of this lane's values.
 template <int kRegChunk, int kMaxE, typename Acc>
-__device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, int64_t lo, int64_t W,
-                                                  int64_t zk, double beta, double U, int lane, bool linear,
+__device__ __forceinline__ int64_t heat_bath_sums(const Coeffs<kMaxE, Acc> &C, int64_t lo, int64_t W, int64_t zk,
+                                                  double beta, double U, int64_t dmin, int64_t dlane, int lane,
                                                   ScanCarry &cy) {
     const uint32_t W32 = (uint32_t)W;
     const uint32_t c = (W32 + kWave - 1) / kWave;
     const uint32_t j0 = (uint32_t)lane * c;
-    // no term holds z_k to a power above one: the inverse of the distribution, whatever the width
-    if (kMaxE == 1 || linear) return linear_draw(to_i64<Acc>(C.a[1]), lo, W32, beta, U);
-    // Weights are taken relative to the minimum energy difference.
-    int64_t dmin = 0, dlane = INT64_MAX;   // dlane: the smallest dE of this lane's values (c > 8)
-    if (c <= 2) {   // uniform: each value's difference once, the minimum over the wave
-        int64_t d[2];
-        d[0] = poly_delta(C, zk, lo + (int64_t)(j0 < W32 ? j0 : W32 - 1u));
-        d[1] = c > 1 ? poly_delta(C, zk, lo + (int64_t)(j0 + 1u < W32 ? j0 + 1u : W32 - 1u)) : d[0];
-        const int64_t least = d[0] < d[1] ? d[0] : d[1];
-        dmin = sizeof(Acc) == 4 ? (int64_t)wave_min_i32((int32_t)least) : wave_min_i64(least);
-        const int32_t j = draw_single<2>(W32, c, j0, beta, U, [&](uint32_t i, uint32_t) -> double {
-            return sizeof(Acc) == 4 ? (double)((int32_t)d[i] - (int32_t)dmin) : (double)(d[i] - dmin);
-        });
-        if (j >= 0) return lo + j;
-    } else if constexpr (kMaxE == 2) {
-        // dE(v) = a2 v^2 + a1 v + const has its minimum at an end or, a2 > 0, at one of the two integers
-        // around -a1 / (2 a2): the computed vertex errs by less than would move it past an integer that
-        // is not a minimum itself.  dE(v) - dE(vm) = (v - vm) (a1 + a2 (v + vm)), an exact integer.
-        const int64_t hi = lo + W - 1, a1 = to_i64<Acc>(C.a[1]), a2 = to_i64<Acc>(C.a[2]);
-        const double a1d = (double)a1, a2d = (double)a2;
-        auto vertex_side = [&](int64_t first, int64_t last) -> int64_t {   // a minimiser within first .. last
-            if (a2 > 0) {
-                double r = __builtin_amdgcn_rcp(a2d);
-                r = fma(r, fma(-a2d, r, 1.0), r);
-                const double t = -0.5 * a1d * r;
-                first = t < (double)first ? first : t > (double)last ? last : (int64_t)__builtin_floor(t);
-                last = first < last ? first + 1 : last;
-            }
-            return poly_delta(C, zk, last) < poly_delta(C, zk, first) ? last : first;
-        };
-        const int64_t vm = vertex_side(lo, hi);   // uniform
-        dmin = poly_delta(C, zk, vm);
-        if (c <= kSingleMost) {   // uniform
-            const double vmd = (double)vm, lod = (double)lo;
-            const bool exact53 = sizeof(Acc) == 4 || (__builtin_fabs(a1d) < 0x1p53 && __builtin_fabs(a2d) < 0x1p53);
-            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
-                if (exact53) {   // the factors are exact, their sum and product rounded once
-                    const double vd = lod + (double)j;
-                    return (vd - vmd) * fma(a2d, vd + vmd, a1d);
-                }
-                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
-            });
-            if (j >= 0) return lo + j;
-        } else if (j0 < W32) {
-            const int64_t jl = lo + (int64_t)j0, jh = lo + (int64_t)(j0 + c - 1u < W32 ? j0 + c - 1u : W32 - 1u);
-            // the ends of the lane's values, and the vertex where it lies among them
-            const int64_t dl = poly_delta(C, zk, jl), dh = poly_delta(C, zk, jh);
-            dlane = dl < dh ? dl : dh;
-            if (vm >= jl && vm <= jh) dlane = dmin;
-        }
-    } else {
-        for (uint32_t i = 0; i < c; ++i) {
-            const uint32_t j = j0 + i;
-            if (j < W32) {
-                const int64_t d = poly_delta(C, zk, lo + (int64_t)j);
-                dlane = d < dlane ? d : dlane;
-            }
-        }
-        dmin = wave_min_i64(dlane);
-        if (c <= kSingleMost) {   // uniform
-            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
-                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
-            });
-            if (j >= 0) return lo + j;
-        }
-    }
     // kRegChunk = 0 evaluates the weights in groups of kGroup independent exponentials (their
     // latencies overlap); they are still added one by one in value order
     constexpr uint32_t kGroup = 4;
@@ -807,6 +737,116 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     if (mask == 0) return lo + W - 1;
     const int src = __ffsll((unsigned long long)mask) - 1;
     return lo + (int64_t)src * (int64_t)c + (int64_t)(int32_t)lane_read32((uint32_t)hit, src);
+}
+// The same out of line.
+template <int kMaxE, typename Acc>
+__device__ __attribute__((noinline)) int64_t heat_bath_sums_apart(Coeffs<kMaxE, Acc> C, int64_t lo, int64_t W, int64_t zk,
+                                                                  double beta, double U, int64_t dmin, int64_t dlane,
+                                                                  int lane) {
+    ScanCarry cy;
+    return heat_bath_sums<0, kMaxE, Acc>(C, lo, W, zk, beta, U, dmin, dlane, lane, cy);
+}
+
+// Heat-bath choice (Sec. 3.3.2) among all W values, with the fixed summation order: value j of the
+// range belongs to lane j / c (c = ceil(W/64)); lane sums are left to right; the lanes' sums are
+// combined by wave_scan_rows; the first value whose cumulative weight exceeds U * total is drawn
+// (the last value if rounding leaves none).  W < 2^31, so value indexes are 32-bit: j0 + i < 64 c
+// <= W + 63.
+//
+// kRegChunk = kApart: as 0, but what single precision leaves undecided, and ranges past 512 values, out of line.
+// Inline, the double-precision forms set the registers of the whole kernel: 168 VGPRs, three waves per SIMD,
+// where 122 allow four (powers, 64-bit sums), 128 with spills where 100 do (linear variables).
+constexpr int kApart = -1;
+template <int kRegChunk, int kMaxE, typename Acc>
+__device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, int64_t lo, int64_t W,
+                                                  int64_t zk, double beta, double U, int lane, bool linear,
+                                                  ScanCarry &cy) {
+    const uint32_t W32 = (uint32_t)W;
+    const uint32_t c = (W32 + kWave - 1) / kWave;
+    const uint32_t j0 = (uint32_t)lane * c;
+    // no term holds z_k to a power above one: with a value per lane the weights in single precision (a chain of
+    // some 250 cycles, the inverse's is 400: N = 100 multilinear, W = 3, hot sweeps 126 to 112 us), else, and where
+    // they cannot decide, the inverse of the distribution
+    if (kMaxE == 1 || linear) {
+        const int64_t a1 = to_i64<Acc>(C.a[1]);
+        if (c == 1) {   // uniform
+            const double slope = (double)(a1 < 0 ? -a1 : a1);
+            const int32_t j = draw_single<1>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
+                return slope * (double)(a1 < 0 ? W32 - 1u - j : j);
+            });
+            if (j >= 0) return lo + j;
+        }
+        return linear_draw<kRegChunk != 0>(a1, lo, W32, beta, U);
+    }
+    // Weights are taken relative to the minimum energy difference.
+    int64_t dmin = 0, dlane = INT64_MAX;   // dlane: the smallest dE of this lane's values (c > 8)
+    if (c <= 2) {   // uniform: each value's difference once, the minimum over the wave
+        int64_t d[2];
+        d[0] = poly_delta(C, zk, lo + (int64_t)(j0 < W32 ? j0 : W32 - 1u));
+        d[1] = c > 1 ? poly_delta(C, zk, lo + (int64_t)(j0 + 1u < W32 ? j0 + 1u : W32 - 1u)) : d[0];
+        const int64_t least = d[0] < d[1] ? d[0] : d[1];
+        dmin = sizeof(Acc) == 4 ? (int64_t)wave_min_i32((int32_t)least) : wave_min_i64(least);
+        const int32_t j = draw_single<2>(W32, c, j0, beta, U, [&](uint32_t i, uint32_t) -> double {
+            return sizeof(Acc) == 4 ? (double)((int32_t)d[i] - (int32_t)dmin) : (double)(d[i] - dmin);
+        });
+        if (j >= 0) return lo + j;
+    } else if constexpr (kMaxE == 2) {
+        // dE(v) = a2 v^2 + a1 v + const has its minimum at an end or, a2 > 0, at one of the two integers
+        // around -a1 / (2 a2): the computed vertex errs by less than would move it past an integer that
+        // is not a minimum itself.  dE(v) - dE(vm) = (v - vm) (a1 + a2 (v + vm)), an exact integer.
+        const int64_t hi = lo + W - 1, a1 = to_i64<Acc>(C.a[1]), a2 = to_i64<Acc>(C.a[2]);
+        const double a1d = (double)a1, a2d = (double)a2;
+        auto vertex_side = [&](int64_t first, int64_t last) -> int64_t {   // a minimiser within first .. last
+            if (a2 > 0) {
+                double r = __builtin_amdgcn_rcp(a2d);
+                r = fma(r, fma(-a2d, r, 1.0), r);
+                const double t = -0.5 * a1d * r;
+                first = t < (double)first ? first : t > (double)last ? last : (int64_t)__builtin_floor(t);
+                last = first < last ? first + 1 : last;
+            }
+            return poly_delta(C, zk, last) < poly_delta(C, zk, first) ? last : first;
+        };
+        const int64_t vm = vertex_side(lo, hi);   // uniform
+        dmin = poly_delta(C, zk, vm);
+        if (c <= kSingleMost) {   // uniform
+            const double vmd = (double)vm, lod = (double)lo;
+            const bool exact53 = sizeof(Acc) == 4 || (__builtin_fabs(a1d) < 0x1p53 && __builtin_fabs(a2d) < 0x1p53);
+            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
+                if (exact53) {   // the factors are exact, their sum and product rounded once
+                    const double vd = lod + (double)j;
+                    return (vd - vmd) * fma(a2d, vd + vmd, a1d);
+                }
+                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
+            });
+            if (j >= 0) return lo + j;
+        } else if (j0 < W32) {
+            const int64_t jl = lo + (int64_t)j0, jh = lo + (int64_t)(j0 + c - 1u < W32 ? j0 + c - 1u : W32 - 1u);
+            // the ends of the lane's values, and the vertex where it lies among them
+            const int64_t dl = poly_delta(C, zk, jl), dh = poly_delta(C, zk, jh);
+            dlane = dl < dh ? dl : dh;
+            if (vm >= jl && vm <= jh) dlane = dmin;
+        }
+    } else {
+        for (uint32_t i = 0; i < c; ++i) {
+            const uint32_t j = j0 + i;
+            if (j < W32) {
+                const int64_t d = poly_delta(C, zk, lo + (int64_t)j);
+                dlane = d < dlane ? d : dlane;
+            }
+        }
+        dmin = wave_min_i64(dlane);
+        if (c <= kSingleMost) {   // uniform
+            const int32_t j = draw_single<kSingleMost>(W32, c, j0, beta, U, [&](uint32_t, uint32_t j) -> double {
+                return (double)(poly_delta(C, zk, lo + (int64_t)j) - dmin);
+            });
+            if (j >= 0) return lo + j;
+        }
+    }
+    if constexpr (kRegChunk != 0) {
+        if (kRegChunk == kApart || c <= kSingleMost)   // uniform
+            return heat_bath_sums_apart<kMaxE, Acc>(C, lo, W, zk, beta, U, dmin, dlane, lane);
+    }
+    return heat_bath_sums<kRegChunk == kApart ? 0 : kRegChunk, kMaxE, Acc>(C, lo, W, zk, beta, U, dmin, dlane, lane, cy);
 }
 
 // Optimal transition (Sec. 3.3.3): the value of smallest dE over the whole range (z_k itself, with
@@ -1250,14 +1290,16 @@ __device__ __forceinline__ int64_t sweep_replica(const ReplicaCtx &R, ZT *z, int
 // ------------------------------------------------------------------------------------------------
 // kThreads: 512 (up to 8 waves per replica) or 1024 (16 waves; fewer registers per lane, so only
 // the variants that need no more than 128 VGPRs are built that way).
-// The generic-record Metropolis and OTM variants (the HUIO workloads) and the heat bath of linear
-// variables are held to 128 VGPRs, four waves per SIMD: their cold paths (long terms, the wide-range
-// argmin, the draw in double precision) would otherwise raise the register count past 128 and cost a
-// wave per SIMD on every problem.
+// Waves per SIMD that a variant's registers must allow: without it its cold paths (long terms, the wide-range
+// argmin, the closed form's functions) raise the register count past 128 or 168 and cost a wave per SIMD on
+// every problem.
+constexpr int anneal_waves(int rule, int reg_chunk, int max_e, int acc_bytes, int threads) {
+    if (threads != 512 || reg_chunk > 0) return 1;
+    if (rule == SA_HEAT_BATH_CLOSED) return max_e > 4 ? 1 : max_e == 1 && acc_bytes == 4 ? 4 : 3;
+    return rule == SA_HEAT_BATH && max_e > 4 ? 1 : 4;
+}
 template <int kRule, bool kStateInLds, int kRegChunk, int kMaxE, typename Acc, int kThreads>
-__global__ void __launch_bounds__(kThreads, (kThreads == 512 && kRegChunk == 0 &&
-                                             ((kRule != SA_HEAT_BATH && kRule != SA_HEAT_BATH_CLOSED) ||
-                                              (kRule == SA_HEAT_BATH && kMaxE == 1))) ? 4 : 1)
+__global__ void __launch_bounds__(kThreads, anneal_waves(kRule, kRegChunk, kMaxE, (int)sizeof(Acc), kThreads))
     anneal_kernel(AnnealArgs A) {
     extern __shared__ int32_t lds_state[];
     const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -1495,11 +1537,11 @@ using AnnealKernel = void (*)(AnnealArgs);
 
 // Heat bath of powers: with 9 to 32 values per lane the weights stay in registers (the unrolled loops
 // cost 32 steps); fewer are drawn in single precision, and recomputed where that cannot decide, as wider
-// ranges are (kRegChunk = 0).
+// ranges are (kApart).
 template <int kRule, int kMaxE, typename Acc>
 AnnealKernel pick_heat_bath_lds(int reg_chunk) {
     if (reg_chunk == kHeatBathRegChunk) return anneal_kernel<kRule, true, kHeatBathRegChunk, kMaxE, Acc, 512>;
-    return anneal_kernel<kRule, true, 0, kMaxE, Acc, 512>;
+    return anneal_kernel<kRule, true, kApart, kMaxE, Acc, 512>;
 }
 
 }  // namespace

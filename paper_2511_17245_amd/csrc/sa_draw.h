@@ -154,12 +154,29 @@ __device__ __forceinline__ void linear_draw_single(bool from_top, double c, uint
     x = from_top ? Wf - aL * ic : aL * ic;
 }
 
+// The index drawn where single precision cannot tell.
+__device__ __forceinline__ uint32_t linear_draw_rest(bool from_top, double slope, uint32_t W, double beta, double U) {
+    uint32_t i;
+    if (!(beta * slope > 1e-280)) {   // every weight is 1: the count of v - l + 1 <= U W
+        i = (uint32_t)(U * (double)W);
+        return i < W ? i : W - 1u;
+    }
+    if (!linear_draw_double(from_top, slope, W, beta, U, i)) i = linear_draw_by_sums(from_top, slope, W, beta, U);
+    return i;
+}
+// The same out of line (kApart below): its registers are then not the caller's.
+__device__ __attribute__((noinline, unused)) uint32_t linear_draw_rest_apart(bool from_top, double slope, uint32_t W,
+                                                                             double beta, double U) {
+    return linear_draw_rest(from_top, slope, W, beta, U);
+}
+
 // Heat-bath draw of a variable with dE(v) = a (v - z_k): the first value whose cumulative weight exceeds
 // U times the total.  Index i = ceil(x) - 1 with x = -log1p(P m) / c from the lower end for a > 0, W + the
 // same for a < 0; c = beta |a|, m = expm1(-c W), P = U or 1 - U.
 //
 // It replaced the enumeration in every kernel: 32 random-interaction problems (N = 100, W = 201, most
 // variables linear; 100 sweeps x 100 reads) 24.6 to 20.1 ms, 64 mixed problems 103 to 95 ms.
+template <bool kApart = false>
 __device__ __forceinline__ int64_t linear_draw(int64_t a, int64_t lo, uint32_t W, double beta, double U) {
     const bool from_top = a < 0;
     const double slope = (double)(from_top ? -a : a);
@@ -172,14 +189,8 @@ __device__ __forceinline__ int64_t linear_draw(int64_t a, int64_t lo, uint32_t W
                       (__builtin_fabsf(x - step) > err || step < 0.5f || step > Wf - 0.5f) && c > 1e-30;
     uint32_t i = x <= 0.0f ? 0u : (uint32_t)__builtin_ceilf(x) - 1u;
     i = i < W ? i : W - 1u;
-    if (!sure) {
-        if (!(c > 1e-280)) {   // every weight is 1: the count of v - l + 1 <= U W
-            i = (uint32_t)(U * (double)W);
-            i = i < W ? i : W - 1u;
-        } else if (!linear_draw_double(from_top, slope, W, beta, U, i)) {
-            i = linear_draw_by_sums(from_top, slope, W, beta, U);
-        }
-    }
+    if (!sure)
+        i = kApart ? linear_draw_rest_apart(from_top, slope, W, beta, U) : linear_draw_rest(from_top, slope, W, beta, U);
     return lo + (int64_t)i;
 }
 

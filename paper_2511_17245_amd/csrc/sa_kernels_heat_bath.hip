@@ -8,16 +8,16 @@ namespace sa {
 AnnealKernelFn heat_bath_kernel(bool in_lds, int reg_chunk, int maxe_class, bool narrow, bool sixteen) {
     if (sixteen) {
         if (maxe_class == 1)
-            return narrow ? anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint32_t, 1024>
-                          : anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint64_t, 1024>;
-        return narrow ? anneal_kernel<SA_HEAT_BATH, true, 0, 2, uint32_t, 1024>
-                      : anneal_kernel<SA_HEAT_BATH, true, 0, 2, uint64_t, 1024>;
+            return narrow ? anneal_kernel<SA_HEAT_BATH, true, kApart, 1, uint32_t, 1024>
+                          : anneal_kernel<SA_HEAT_BATH, true, kApart, 1, uint64_t, 1024>;
+        return narrow ? anneal_kernel<SA_HEAT_BATH, true, kApart, 2, uint32_t, 1024>
+                      : anneal_kernel<SA_HEAT_BATH, true, kApart, 2, uint64_t, 1024>;
     }
-    if (!in_lds) return anneal_kernel<SA_HEAT_BATH, false, 0, kMaxExpPoly, uint64_t, 512>;
+    if (!in_lds) return anneal_kernel<SA_HEAT_BATH, false, kApart, kMaxExpPoly, uint64_t, 512>;
     switch (maxe_class) {
         // every variable linear (class 1): no enumeration code at all
-        case 1: return narrow ? anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint32_t, 512>
-                              : anneal_kernel<SA_HEAT_BATH, true, 0, 1, uint64_t, 512>;
+        case 1: return narrow ? anneal_kernel<SA_HEAT_BATH, true, kApart, 1, uint32_t, 512>
+                              : anneal_kernel<SA_HEAT_BATH, true, kApart, 1, uint64_t, 512>;
         case 2: return narrow ? pick_heat_bath_lds<SA_HEAT_BATH, 2, uint32_t>(reg_chunk)
                               : pick_heat_bath_lds<SA_HEAT_BATH, 2, uint64_t>(reg_chunk);
         case 4: return pick_heat_bath_lds<SA_HEAT_BATH, 4, uint64_t>(reg_chunk);
