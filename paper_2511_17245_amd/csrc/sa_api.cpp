@@ -294,6 +294,14 @@ int get_order(sa_plan *plan, sa_plan::Sched **out) {
     return SA_OK;
 }
 
+int get_order_if_room(sa_plan *plan, sa_plan::Sched **out) {
+    const int rc = get_order(plan, out);
+    if (rc != SA_ENOMEM) return rc;
+    (void)hipGetLastError();   // (a launch would report it)
+    *out = nullptr;
+    return SA_OK;
+}
+
 LaneLayout lane_layout(const LaneImage &im) {
     LaneLayout L;
     L.slots = align256(std::max<size_t>(im.chunks.size(), 1) * sizeof(LaneRows));
@@ -383,10 +391,18 @@ int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice
     const int waves = lane_waves(get_lane_chunks(plan), p, compact, n_reads, quads, cus, max_lds);
     if (waves == 0) return SA_OK;
     sa_plan::Lanes *ln = nullptr;
-    int rc = get_lanes(plan, compact, &ln);
-    if (rc != SA_OK) return rc;
     sa_plan::Lanes::Rounds *rounds = nullptr;
-    rc = get_lane_rounds(plan, waves, &rounds);
+    int rc = SA_OK;
+    try {
+        rc = get_lanes(plan, compact, &ln);
+        if (rc == SA_OK) rc = get_lane_rounds(plan, waves, &rounds);
+    } catch (const std::bad_alloc &) {
+        rc = SA_ENOMEM;
+    }
+    if (rc == SA_ENOMEM) {   // no room for the image: the other kernels need none
+        (void)hipGetLastError();
+        return SA_OK;
+    }
     if (rc != SA_OK) return rc;
     q.P = plan->dp;
     q.closed = plan->rule == SA_HEAT_BATH_CLOSED ? 1 : 0;
@@ -633,6 +649,21 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         }
     }
     if (lane.waves == 0) {
+    // the list of the variables, for the dense team and the settled kernel
+    sa_plan::Sched *all = nullptr;
+    rc = sa::get_order_if_room(plan, &all);
+    if (rc != SA_OK) {
+        if (tmp) (void)hipFree(tmp);
+        return rc;
+    }
+    sa::SettledChoice set;
+    if (all) {
+        a.order = all->dev;
+        a.n_order = all->n_active;
+        a.all = sa::settled_counters(all->dev, n);
+        a.z30 = plan->packed.z30 ? 1 : 0;
+        set = sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
+    }
     const bool eligible = sa::quad_eligible(plan->rule, plan->packed, plan->device);
     sa_plan::Levels *lv = nullptr;
     if (eligible && G == 0 && opts.lanes_per_update != 64) {
@@ -677,18 +708,6 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         const bool mo = plan->rule == SA_METROPOLIS || plan->rule == SA_OPT_METROPOLIS;
         if (mo) {
             // the sweeps after the replicas have settled go to the settled kernel
-            sa_plan::Sched *one = nullptr;
-            rc = sa::get_order(plan, &one);
-            if (rc != SA_OK) {
-                if (tmp) (void)hipFree(tmp);
-                return rc;
-            }
-            a.order = one->dev;
-            a.n_order = one->n_active;
-            a.all = sa::settled_counters(one->dev, n);
-            a.z30 = plan->packed.z30 ? 1 : 0;
-            const sa::SettledChoice set =
-                sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
             rc = sa::launch_rounds(plan->rule, q, a, set, plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
                                    stream, err);
         } else {
@@ -711,18 +730,10 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.lanes_per_update = 4;
         plan->last.n_levels = lv->n_levels;
     } else if (const sa::TeamChoice team =
-                   G == 0 && opts.lanes_per_update == 0
+                   all && G == 0 && opts.lanes_per_update == 0
                        ? sa::choose_team(plan->rule, plan->packed, plan->dp.coef32 != 0, n_reads, plan->device)
                        : sa::TeamChoice();
                team.waves > 0) {
-        sa_plan::Sched *all = nullptr;
-        rc = sa::get_order(plan, &all);
-        if (rc != SA_OK) {
-            if (tmp) (void)hipFree(tmp);
-            return rc;
-        }
-        a.order = all->dev;
-        a.n_order = all->n_active;
         std::string err;
         rc = sa::launch_dense_team(plan->rule, a, team, stream, err);
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
@@ -756,18 +767,6 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         a.waves_per_group = lc.waves_per_group;
         a.dense_cache = lc.dense_cache ? 1 : 0;
         // the sweeps after the replicas have settled go to the settled kernel
-        sa_plan::Sched *one = nullptr;
-        rc = sa::get_order(plan, &one);
-        if (rc != SA_OK) {
-            if (tmp) (void)hipFree(tmp);
-            return rc;
-        }
-        a.order = one->dev;
-        a.n_order = one->n_active;
-        a.all = sa::settled_counters(one->dev, n);
-        a.z30 = plan->packed.z30 ? 1 : 0;
-        const sa::SettledChoice set =
-            sa::choose_settled(plan->packed, plan->dp.coef32 != 0, n_reads, a.n_order, s1 - s0, plan->device);
         std::string err;
         rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_visits(plan->rule, plan->packed), plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
                                 stream, err);

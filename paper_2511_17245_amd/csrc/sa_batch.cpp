@@ -297,9 +297,10 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         d.z_out = b->z_dev + b->z_off[i];
         d.e_out = b->e_dev + b->e_off[i];
         sa_plan::Sched *all = nullptr;
-        int rc = sa::get_order(&p, &all);
+        int rc = sa::get_order_if_room(&p, &all);
         if (rc != SA_OK) return rc;
-        b->dense_team.push_back(sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, all->dev, d.n_reads, b->device, d));
+        b->dense_team.push_back(
+            all ? sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, all->dev, d.n_reads, b->device, d) : sa::TeamChoice());
         b->lane.emplace_back();
         b->lane_args.emplace_back();
         sa::LaneArgs &q = b->lane_args.back();
@@ -315,7 +316,7 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
         q.z_out = d.z_out;
         q.e_out = d.e_out;
         b->settled_lds.push_back(
-            d.team_waves > 0 || b->lane.back().waves > 0
+            !all || d.team_waves > 0 || b->lane.back().waves > 0
                              ? 0
                              : sa::settle_inst(p.packed, p.dp.coef32 != 0, all->dev, all->n_active, d.n_sweeps, b->device, d));
         if (b->settled_lds.back()) d.next = (int32_t *)(b->base + o_next) + b->e_off[i];

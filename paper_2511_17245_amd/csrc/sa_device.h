@@ -765,7 +765,7 @@ __device__ __forceinline__ int64_t heat_bath_pick(const Coeffs<kMaxE, Acc> &C, i
     const uint32_t c = (W32 + kWave - 1) / kWave;
     const uint32_t j0 = (uint32_t)lane * c;
     // no term holds z_k to a power above one: with a value per lane the weights in single precision (a chain of
-    // some 250 cycles, the inverse's is 400: N = 100 multilinear, W = 3, hot sweeps 126 to 112 us), else, and where
+    // some 250 cycles, the inverse's is 400: N = 100 multilinear, W = 3, hot sweeps 126 to 110 us), else, and where
     // they cannot decide, the inverse of the distribution
     if (kMaxE == 1 || linear) {
         const int64_t a1 = to_i64<Acc>(C.a[1]);

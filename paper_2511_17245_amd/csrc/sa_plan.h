@@ -111,12 +111,16 @@ int resolve_schedule(sa_plan *plan, const sa_schedule *sched, std::vector<double
 int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out);
 // The plan's variables in index order (build_order; n_active of them not fixed).
 int get_order(sa_plan *plan, sa_plan::Sched **out);
+// The same where the device has room for the list, else nullptr (the dense team and the settled kernel then
+// take no part).
+int get_order_if_room(sa_plan *plan, sa_plan::Sched **out);
 // The plan's lane chunks, built on first use, and its lane image (16-bit records or not), built and uploaded
 // on first use.
 const LaneImage &get_lane_chunks(sa_plan *plan);
 int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out);
 int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out);
-// The lane kernel's choice for a run of n_sweeps sweeps, and its arguments that come from the plan.
+// The lane kernel's choice for a run of n_sweeps sweeps (none where its image finds no room), and its arguments
+// that come from the plan.
 int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &args);
 // Byte layout of a lane image (chunks | slots | records), and its staging.
 struct LaneLayout {

@@ -59,6 +59,10 @@ struct Request {
     int32_t *z_dev = nullptr;
     int64_t *e_dev = nullptr;
     int32_t *next_dev = nullptr;
+    // chosen once, by the preparer, so that every chunk of the request takes the same kernels
+    sa_plan::Sched *order = nullptr;   // nullptr: no room for it
+    sa::LaneChoice lane;
+    sa::LaneArgs lane_args{};
     size_t footprint = 0;
     bool accounted = false;  // footprint counted in the server's memory in use
     int32_t next_sweep = 0;
@@ -302,17 +306,9 @@ void prep_loop(sa_server *S) {
                     break;
                 }
             }
-            sa::LaneChoice lane;
-            sa::LaneArgs lane_args{};
-            if (rc == SA_OK && sa::choose_lane_run(r->plan, r->n_reads, r->n_sweeps, lane, lane_args) != SA_OK) {
-                rc = SA_ENOMEM;
-                err = sa_last_error();
-            }
-            sa_plan::Sched *all = nullptr;
-            if (rc == SA_OK && sa::get_order(r->plan, &all) != SA_OK) {
-                rc = SA_ENOMEM;
-                err = sa_last_error();
-            }
+            if (rc == SA_OK) rc = sa::choose_lane_run(r->plan, r->n_reads, r->n_sweeps, r->lane, r->lane_args);
+            if (rc == SA_OK) rc = sa::get_order_if_room(r->plan, &r->order);
+            if (rc != SA_OK && err.empty()) err = sa_last_error();
         }
         if (rc == SA_OK) {
             const size_t zb = sizeof(int32_t) * (size_t)r->n_reads * (size_t)r->plan->dp.n;
@@ -377,7 +373,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     std::vector<double> per_sweep(n);
     for (int i = 0; i < n; ++i) {
         const sa_plan &p = *act[i]->plan;
-        const bool team = sa::choose_team(p.rule, p.packed, p.dp.coef32 != 0, act[i]->n_reads, S->device).waves > 0;
+        const bool team =
+            act[i]->order && sa::choose_team(p.rule, p.packed, p.dp.coef32 != 0, act[i]->n_reads, S->device).waves > 0;
         per_sweep[i] = p.dp.n * cost_of_update(p, team);
     }
     std::vector<double> sorted(per_sweep);
@@ -424,15 +421,11 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         }
         team[i] = G;
         sa::BatchInst &d = insts[i];
-        choices[i] = sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, p.order.dev, r->n_reads, S->device, d);
-        // (its image was built by the request's preparer)
-        lane_args[i] = sa::LaneArgs{};
+        if (r->order)
+            choices[i] = sa::team_inst(p.rule, p.packed, p.dp.coef32 != 0, r->order->dev, r->n_reads, S->device, d);
+        lane_args[i] = r->lane_args;
         n_reads[i] = r->n_reads;
-        if (choices[i].waves == 0 &&
-            sa::choose_lane_run(&p, r->n_reads, r->n_sweeps, lanes[i], lane_args[i]) != SA_OK) {
-            err = sa_last_error();
-            return SA_ENOMEM;
-        }
+        if (choices[i].waves == 0) lanes[i] = r->lane;
         if (choices[i].waves == 0 && lanes[i].waves == 0) lds_elems = std::max<int64_t>(lds_elems, (int64_t)(sa::kBatchWaves / G) * stride);
         d.P = p.dp;
         d.beta = r->beta_dev;
@@ -463,8 +456,9 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
         q.z_init = d.resume ? d.z_out : nullptr;
         q.z_out = d.z_out;
         q.e_out = d.e_out;
-        if (choices[i].waves == 0 && lanes[i].waves == 0)
-            settled_lds[i] = sa::settle_inst(p.packed, p.dp.coef32 != 0, p.order.dev, p.order.n_active, r->n_sweeps, S->device, d);
+        if (r->order && choices[i].waves == 0 && lanes[i].waves == 0)
+            settled_lds[i] =
+                sa::settle_inst(p.packed, p.dp.coef32 != 0, r->order->dev, r->order->n_active, r->n_sweeps, S->device, d);
         if (settled_lds[i]) d.next = r->next_dev;
         d.every = sa::settled_every(d.n_order, G);
         d.limit = sa::settled_limit(d.n_order, d.every, sa::settled_share(G, sa::settled_visits(p.rule, p.packed)));
