@@ -79,10 +79,23 @@ double update_cost(const sa_plan &p) {
     return chunks + 1.0;
 }
 
+// Whether problem i is run by the persistent kernel, which alone the tuned choice concerns (the others have
+// the dense team or the lane kernel).
+bool persistent(const sa_batch &b, size_t i) { return b.dense_team[i].waves == 0 && b.lane[i].waves == 0; }
+
+// What the tuned choice depends on; empty where the persistent kernel has nothing to run.
 std::string shape_key(const sa_batch &b) {
-    return std::to_string(b.plans.size()) + ":" + std::to_string(b.max_tasks) + ":" +
-           std::to_string(b.total_updates) + ":" + std::to_string(b.launch.maxe_class) + ":" +
-           std::to_string(b.launch.narrow) + ":" + std::to_string(b.z16);
+    int64_t n[4] = {0, 0, 0, 0}, reads = 0, updates = 0;
+    for (size_t i = 0; i < b.plans.size(); ++i) {
+        if (!persistent(b, i)) continue;
+        n[b.plans[i]->rule]++;
+        reads += b.n_reads[i];
+        updates += (int64_t)b.n_reads[i] * b.n_sweeps[i] * b.plans[i]->dp.n;
+    }
+    if (reads == 0) return "";
+    std::string key;
+    for (int64_t m : {n[0], n[1], n[2], n[3], reads, updates}) key += std::to_string(m) + ":";
+    return key + std::to_string(b.launch.maxe_class) + ":" + std::to_string(b.launch.narrow) + ":" + std::to_string(b.z16);
 }
 
 // Team sizes, tasks and LDS layout for a policy strength and a workgroup count, uploaded to the
@@ -95,11 +108,12 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
     const int64_t budget = std::min<int64_t>(b.max_lds, 160 * 1024 / groups_per_cu) - 64;
     const double waves = (double)b.cus * groups_per_cu * sa::kBatchWaves;
     double total = 0.0;
-    for (int32_t i = 0; i < n; ++i) total += b.n_reads[i] * b.replica_cost[i];
+    for (int32_t i = 0; i < n; ++i)
+        if (persistent(b, (size_t)i)) total += b.n_reads[i] * b.replica_cost[i];
     const double share = total / waves;
     int64_t lds_elems_max = 0;
     for (int32_t i = 0; i < n; ++i) {
-        if (b.dense_team[i].waves > 0 || b.lane[i].waves > 0) continue;
+        if (!persistent(b, (size_t)i)) continue;
         sa_plan &p = *b.plans[i];
         int G = 1;
         if (policy > 0.0)
@@ -134,7 +148,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
                      [&](int32_t x, int32_t y) { return b.replica_cost[x] / b.team[x] > b.replica_cost[y] / b.team[y]; });
     std::vector<sa::BatchTask> tasks;
     for (int32_t i : order) {
-        if (b.dense_team[i].waves > 0 || b.lane[i].waves > 0) continue;
+        if (!persistent(b, (size_t)i)) continue;
         const int per = sa::kBatchWaves / b.team[i];
         for (int32_t r = 0; r < b.n_reads[i]; r += per) tasks.push_back(sa::BatchTask{i, r});
     }
@@ -348,8 +362,9 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
     // choose the team-size policy and the number of persistent workgroups
     Tuned choice{0.5, 2};
     const std::string key = shape_key(*b);
+    const bool tune = opts.autotune && !key.empty();
     bool cached = false;
-    if (opts.autotune) {
+    if (tune) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(key);
         if (it != g_tune_cache.end()) {
@@ -357,7 +372,7 @@ int create(const sa_problem *problems, int32_t n, const sa_batch_opts *opts_in, 
             cached = true;
         }
     }
-    if (opts.autotune && !cached) {
+    if (tune && !cached) {
         int32_t max_s = 1;
         for (int32_t i = 0; i < n; ++i) max_s = std::max(max_s, problems[i].sched.n_sweeps);
         const int32_t trial_sweeps = std::max<int32_t>(1, std::min<int32_t>(max_s, std::max(10, max_s / 20)));
