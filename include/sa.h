@@ -297,7 +297,8 @@ typedef struct {
 int32_t sa_server_create(const sa_server_opts *opts, sa_server **out);
 /* Copies the problem and queues it.  result's buffers (host, caller-owned) must stay valid until
  * the request is done; they are written at completion.  SA_ENOMEM at once if the states alone
- * exceed the budget; a request whose full footprint exceeds it completes with SA_ENOMEM. */
+ * exceed the budget; a request whose instance, schedule and states exceed it completes with SA_ENOMEM (one
+ * that exceeds it only with the lists its kernels run faster with is served by itself). */
 int32_t sa_server_submit(sa_server *server, const sa_problem *problem, sa_result *result,
                          uint64_t *ticket);
 /* Queues a run of an existing plan (shared, not copied: keep it alive until the request is done). */

@@ -262,6 +262,7 @@ int get_schedule(sa_plan *plan, int G, sa_plan::Sched **out) {
             e = hipMemcpy(sc.dev, host.data(), host.size() * sizeof(sa::SchedRec), hipMemcpyHostToDevice);
             if (e != hipSuccess) return hip_fail(e, "hipMemcpy(schedule)");
         }
+        plan->list_bytes += bytes;
         sc.n_win = n_win;
         sc.n_active = active;
     }
@@ -288,6 +289,7 @@ int get_order(sa_plan *plan, sa_plan::Sched **out) {
             (void)hipFree(dev);
             return hip_fail(e, "hipMemcpy(order)");
         }
+        plan->list_bytes += img.size();
         sc.dev = (sa::SchedRec *)dev;
     }
     *out = &sc;
@@ -346,6 +348,7 @@ int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out) {
             (void)hipFree(dev);
             return hip_fail(e, "hipMemcpy(lanes)");
         }
+        plan->list_bytes += L.total;
         ln.dev = dev;
         ln.chunks = (const LaneRows *)dev;
         ln.slots = (const LaneSlot *)((char *)dev + L.slots);
@@ -370,6 +373,7 @@ int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out) {
             (void)hipFree(dev);
             return hip_fail(e, "hipMemcpy(lane rounds)");
         }
+        plan->list_bytes += host.size() * sizeof(LaneRows);
         r.dev = (LaneRows *)dev;
         r.n = (int32_t)host.size();
     }
@@ -451,6 +455,7 @@ int get_levels(sa_plan *plan, sa_plan::Levels **out) {
         if (!mcoef.empty()) std::memcpy(img.data() + cb, mcoef.data(), mcoef.size());
         e = hipMemcpy(lv.dev, img.data(), bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hip_fail(e, "hipMemcpy(levels)");
+        plan->list_bytes += bytes;
         lv.start = (const int32_t *)lv.dev;
         lv.slots = (const SchedRec *)((char *)lv.dev + sb);
         lv.mrec = mo ? (const MoRec *)((char *)lv.dev + rb) : nullptr;

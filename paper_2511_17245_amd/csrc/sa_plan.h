@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <functional>
 #include <mutex>
 #include <string>
@@ -82,6 +83,7 @@ struct sa_plan {
         Rounds rounds[4];             // for 1, 2, 4 and 8 waves per replica, on first use
     };
     Lanes lanes;
+    std::atomic<size_t> list_bytes{0};   // device bytes of what is built on first use, above
     std::mutex sched_mu;  // guards the lazy building of sched and levels (a server's preparers share plans)
     ~sa_plan() {
         if (beta_dev) (void)hipFree(beta_dev);

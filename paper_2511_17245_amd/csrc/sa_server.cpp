@@ -63,7 +63,8 @@ struct Request {
     sa_plan::Sched *order = nullptr;   // nullptr: no room for it
     sa::LaneChoice lane;
     sa::LaneArgs lane_args{};
-    size_t footprint = 0;
+    size_t footprint = 0;    // device bytes of its own
+    size_t required = 0;     // of them, those without which it cannot run
     bool accounted = false;  // footprint counted in the server's memory in use
     int32_t next_sweep = 0;
     Phase phase = Phase::Queued;
@@ -312,13 +313,24 @@ void prep_loop(sa_server *S) {
         }
         if (rc == SA_OK) {
             const size_t zb = sizeof(int32_t) * (size_t)r->n_reads * (size_t)r->plan->dp.n;
-            // a cached plan's arena is counted once, while admitted requests use it (admission)
-            r->footprint = align256(sizeof(double) * r->beta.size()) + align256(zb) +
-                           align256(sizeof(int64_t) * (size_t)r->n_reads) +
-                           (r->own_plan ? r->plan->arena.bytes : 0);
+            // a cached plan's bytes are counted once, while admitted requests use it (admission)
+            r->required = align256(sizeof(double) * r->beta.size()) + align256(zb) +
+                          align256(sizeof(int64_t) * (size_t)r->n_reads) +
+                          (r->own_plan ? r->plan->arena.bytes : 0);
+            r->footprint = r->required + align256(sizeof(int32_t) * (size_t)r->n_reads) +
+                           (r->own_plan ? r->plan->list_bytes.load() : 0);
         }
         std::lock_guard<std::mutex> lk(S->mu);
         S->in_prep--;
+        if (r->cached) {
+            // with the lists that this request's preparation built
+            auto it = S->plan_cache.find(r->cache_key);
+            if (it != S->plan_cache.end()) {
+                const size_t bytes = r->plan->arena.bytes + r->plan->list_bytes;
+                if (it->second.active > 0) S->mem_used += bytes - it->second.bytes;
+                it->second.bytes = bytes;
+            }
+        }
         if (rc != SA_OK) {
             r->error = err;
             drop_plan_locked(S, r);
@@ -339,7 +351,6 @@ int admit_device(Request *r) {
     const size_t bb = align256(sizeof(double) * r->beta.size());
     const size_t zb = align256(sizeof(int32_t) * (size_t)r->n_reads * (size_t)r->plan->dp.n);
     const size_t eb = align256(sizeof(int64_t) * (size_t)r->n_reads);
-    // (the next sweeps, four bytes per read, are not counted in the footprint)
     hipError_t e = hipMalloc(&r->mem, bb + zb + eb + align256(sizeof(int32_t) * (size_t)r->n_reads));
     if (e != hipSuccess) {
         r->mem = nullptr;
@@ -560,18 +571,21 @@ void scheduler_loop(sa_server *S) {
                     if (r->cached) {
                         auto it = S->plan_cache.find(r->cache_key);
                         if (it != S->plan_cache.end()) {
-                            plan_bytes = it->second.bytes;
-                            plan_need = it->second.active == 0 ? plan_bytes : 0;
+                            plan_bytes = it->second.plan->arena.bytes;
+                            plan_need = it->second.active == 0 ? it->second.bytes : 0;
                         }
                     }
-                    if (r->footprint + plan_bytes > S->opts.mem_budget_bytes) {
+                    if (r->required + plan_bytes > S->opts.mem_budget_bytes) {
                         S->ready.erase(S->ready.begin());
                         r->error = "request footprint exceeds the server's memory budget";
                         release_device(S, r);
                         finish_locked(S, r, SA_ENOMEM);
                         continue;
                     }
-                    if (S->mem_used + r->footprint + plan_need > S->opts.mem_budget_bytes) break;
+                    // (one that fits only without the lists its sweeps are faster with runs by itself)
+                    if (S->mem_used + r->footprint + plan_need > S->opts.mem_budget_bytes &&
+                        !(S->active.empty() && admit.empty()))
+                        break;
                     S->ready.erase(S->ready.begin());
                     S->mem_used += r->footprint + plan_need;
                     if (r->cached) {
