@@ -194,7 +194,8 @@ typedef struct {
     int32_t groups;             /* workgroups launched */
     int32_t lds_bytes;          /* dynamic LDS per workgroup */
     int32_t state_in_lds;       /* 1: replica states live in LDS, 0: in device memory */
-    int32_t kernel_variant;     /* internal id of the instantiated kernel */
+    int32_t kernel_variant;     /* internal id of the instantiated kernel; 10000000 more where replicas that settle
+                                   are handed over to the settled kernel */
     int32_t waves_per_replica;  /* G: wavefronts cooperating on one replica */
     int32_t n_windows;          /* windows per sweep in the schedule (N for G = 1 without fixed vars) */
     int32_t lanes_per_update;   /* 64, 4 for the quad kernel, 1 for the lane kernel */

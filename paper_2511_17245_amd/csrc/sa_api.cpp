@@ -522,6 +522,8 @@ int auto_waves_per_replica(sa_plan *plan, int32_t n_reads, int device) {
     });
 }
 
+constexpr int32_t kSettledVariant = 10000000;   // sa_launch_info::kernel_variant of a run with settled launches
+
 int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t seed,
              int32_t *out_states, int64_t *out_energies, const sa_opts *opts_in) {
     if (!plan) return fail(SA_EINVAL, "plan is NULL");
@@ -730,7 +732,7 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.groups = n_reads;
         plan->last.lds_bytes = (int32_t)sa::shared_state_bytes(n, qw);
         plan->last.state_in_lds = 1;
-        plan->last.kernel_variant = 2000000 + plan->rule * 100000;
+        plan->last.kernel_variant = 2000000 + plan->rule * 100000 + (mo && set.lds_bytes ? kSettledVariant : 0);
         plan->last.waves_per_replica = qw;
         plan->last.lanes_per_update = 4;
         plan->last.n_levels = lv->n_levels;
@@ -773,8 +775,9 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         a.dense_cache = lc.dense_cache ? 1 : 0;
         // the sweeps after the replicas have settled go to the settled kernel
         std::string err;
-        rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_visits(plan->rule, plan->packed), plan->info.max_width, plan->info.max_exponent, plan->narrow_ok,
-                                stream, err);
+        if (!sa::settled_pays(s1 - s0, a.n_order, lc.win_waves)) set = sa::SettledChoice();
+        rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_visits(plan->rule, plan->packed), plan->info.max_width,
+                                plan->info.max_exponent, plan->narrow_ok, stream, err);
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);
@@ -784,7 +787,7 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         plan->last.groups = lc.groups;
         plan->last.lds_bytes = lc.lds_bytes;
         plan->last.state_in_lds = lc.state_in_lds ? 1 : 0;
-        plan->last.kernel_variant = lc.variant;
+        plan->last.kernel_variant = lc.variant + (set.lds_bytes ? kSettledVariant : 0);
         plan->last.waves_per_replica = lc.win_waves;
         plan->last.n_windows = sc->n_win;
         plan->last.lanes_per_update = 64;

@@ -424,6 +424,11 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
 // Launches it: `a` as for launch_anneal, with order, n_order and leave set.
 int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_width, int32_t max_exp, bool narrow,
                    void *stream, std::string &err);
+// Whether a run of the windows with G waves per replica is long enough for two more launches, which cost one of
+// 0.5 ms a tenth (N = 24 pairs, G = 4, 90 sweeps 0.47 to 0.52 ms).
+constexpr bool settled_pays(int32_t n_sweeps, int32_t n_order, int32_t G) {
+    return (int64_t)n_sweeps * n_order >= 1200 * (int64_t)G;
+}
 // Whether settled sweeps visit most of what may change (settled_share).
 inline bool settled_visits(int rule, const Packed &p) {
     return rule == SA_HEAT_BATH || rule == SA_HEAT_BATH_CLOSED || (!p.dense && !p.any_cached);

@@ -97,9 +97,7 @@ int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_
 int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, bool visits, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err) {
     a.phase = kPhaseWhole;
-    // (two more launches cost a run of 0.5 ms a tenth: N = 24 pairs, G = 4, 90 sweeps 0.47 to 0.52 ms)
-    if (sc.lds_bytes == 0 || (int64_t)(a.s_end - a.s_begin) * a.n_order < 1200 * (int64_t)lc.win_waves)
-        return launch_anneal(rule, a, lc, stream, err);
+    if (sc.lds_bytes == 0) return launch_anneal(rule, a, lc, stream, err);
     a.phase = kPhaseFirst;
     a.every = settled_every(a.n_order, lc.win_waves);
     a.limit = settled_limit(a.n_order, a.every, settled_share(lc.win_waves, visits));
