@@ -242,5 +242,13 @@ __device__ __forceinline__ uint16_t linear_margin(bool closed, int64_t a1, int64
     return b != 0 && !may_freeze(closed, lo, zk) ? (uint16_t)(b | 0x8000u) : b;
 }
 
+// And of a variable that never moves.
+constexpr uint16_t kFixed = 0x7FFF;
+// The margins i .. i + 3 of n after a change that may have moved all of them: not known, but those past n, which
+// are read with the others, stay those of variables that never move.
+__device__ __forceinline__ uint64_t cleared_margins(int32_t i, int32_t n) {
+    return i + 4 <= n ? 0ull : (~0ull << (16 * (n - i))) & 0x7FFF7FFF7FFF7FFFull;
+}
+
 }  // namespace
 }  // namespace sa

@@ -34,7 +34,8 @@
 // change of another variable adds the change of each shared term's product.  The dense form keeps c1 (int64) for every variable.  Every variable
 // also has in cm, when it is known, the smallest energy rise M of a move away from z_k, rounded down to
 // the upper half of a float; 0 when it is not known, or not positive; with the sign set where it may not
-// freeze the variable (linear_margin).  A change of a variable sharing a
+// freeze the variable (linear_margin); kFlat and kFixed for variables whose values all have the same energy and
+// that are fixed (sa_draw.h).  A change of a variable sharing a
 // term sets it to 0, the next decision of a cached variable and the next visit of another finds it
 // again.  A sweep first reads cm alone, four variables per lane, and skips the blocks of 64 whose
 // variables are all frozen: beta M >= 746, where every other value's acceptance or weight is exactly 0.
@@ -45,9 +46,6 @@
 namespace sa {
 namespace {
 
-// cm of a variable without a cached coefficient known to be linear with a_k^(1) = 0: every value has
-// the same energy (kFlat, sa_draw.h).  And of a fixed variable: frozen at every temperature.
-constexpr uint16_t kFixed = 0x7FFF;
 template <int k>
 struct Int {
     static constexpr int value = k;
@@ -426,7 +424,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
                 if (R.trace) H += hash_word(kj, vj) - hash_word(kj, zj);
                 if (kDense) {
                     dense_cache_update(P, R.c1, kj, vj - zj, lane, nullptr);
-                    for (int32_t i = 4 * lane; i < P.n; i += 4 * kWave) *(uint64_t *)&S.cm[i] = 0;
+                    for (int32_t i = 4 * lane; i < P.n; i += 4 * kWave) *(uint64_t *)&S.cm[i] = cleared_margins(i, P.n);
                 } else {
                     settled_scatter(S, z, kj, row, deg, zj, vj, lane);
                 }

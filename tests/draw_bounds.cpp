@@ -171,6 +171,13 @@ void margins() {
             if (v != zk) fail(closed ? "frozen, closed form" : "frozen", beta * (double)std::abs(a), W, a < 0, U);
         }
     }
+    // after a change of a dense problem: not known, but for the places past the last variable
+    for (int32_t n = 1; n <= 70; ++n)
+        for (int32_t i = 0; i < n; i += 4) {
+            const uint64_t w = sa::cleared_margins(i, n);
+            for (int32_t q = 0; q < 4; ++q)
+                if ((uint16_t)(w >> (16 * q)) != (i + q < n ? 0 : sa::kFixed)) fail("cleared margins", (double)i, (uint32_t)n, false, q);
+        }
     std::printf("frozen %lld\n", (long long)frozen);
     if (frozen < 1000) fail("some freeze", 0, 0, false, 0);
 }
