@@ -275,8 +275,8 @@ __device__ __forceinline__ int64_t lane_argmin_quadratic(int64_t a1, int64_t a2,
 // One block of 64 variables (slots sl, one per lane) of a settled sweep.  Returns the number of changes.
 template <bool kDense, int kRule, int kRegChunk, int kMaxE, typename Acc, typename ZT>
 __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, int lane, int32_t b, const SchedRec &sl,
-                                                  int32_t s, double beta, double r_opt, ScanCarry &cy, uint64_t &H,
-                                                  int64_t &E) {
+                                                  int32_t s, double beta, double r_opt, int16_t thr, ScanCarry &cy,
+                                                  uint64_t &H, int64_t &E) {
     const ReplicaCtx &R = S.R;
     const DevProblem &P = R.P;
     constexpr bool kHeatBath = kRule == SA_HEAT_BATH;
@@ -338,6 +338,17 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
         }
     };
     read_caches();
+    auto keep_margins = [&] {
+        if (valid ? has : b + lane < P.n) S.cm[b + lane] = !valid ? kFixed : (int64_t)z[kk] == zk ? mbits : 0;
+        state_write_fence<true>();
+    };
+    // Margins that a neighbour's change cleared and that hold all the same: nothing can change here.  (In a warm
+    // settled sweep most blocks are of this kind; HUIO of 2000 variables, optimal transition, 1024 reads x 300
+    // sweeps: 25.4 -> 24.9 ms.  Metropolis would have to find the margins for it each time: 28.7 -> 31.1 ms.)
+    if (kUsesMargin && __ballot(valid && (int16_t)mbits < thr) == 0) {
+        keep_margins();
+        return 0;
+    }
     uint32_t x0 = (uint32_t)sl.k, x1 = (uint32_t)s, x2 = R.read, x3 = R.instance_id;
     philox4x32_10(x0, x1, x2, x3, R.key0, R.key1);
     const double U = (double)((((uint64_t)x2 << 32) | x3) >> 11) * 0x1p-53;
@@ -438,8 +449,7 @@ __device__ __forceinline__ uint32_t settled_block(const SettleView &S, ZT *z, in
     // decision reads them they are found every fourth sweep.)
     if (kUsesMargin || (s & 3) == 0) {
         if (!kUsesMargin && has) find_margin();
-        if (valid ? has : b + lane < P.n) S.cm[b + lane] = !valid ? kFixed : (int64_t)z[kk] == zk ? mbits : 0;
-        state_write_fence<true>();
+        keep_margins();
     }
     return moves;
 }
@@ -495,7 +505,7 @@ __device__ __forceinline__ uint32_t settled_sweep(const SettleView &S, ZT *z, in
             SchedRec sn = sl;
             if (qn < 4) sn = load(base + kWave * qn);   // under this block's work
             const uint32_t c = settled_block<kDense, kRule, kRegChunk, kMaxE, Acc, ZT>(S, z, lane, base + kWave * q, sl, s, beta,
-                                                                                       r_opt, cy, H, E);
+                                                                                       r_opt, thr, cy, H, E);
             moves += c;
             if (c != 0) {
                 am = active();
