@@ -74,10 +74,17 @@ struct Request {
     double t_submit = 0, t_admit = 0, t_done = 0;
 };
 
+// What a hot update costs, in units of about 52 ns (of 18 HUIO requests, N = 2000, 16 reads each, in one chunk: 156 ns,
+// about 3 units).  A dense team's grows with the rule's barriers per update, the row and a draw's range: measured
+// with 16 reads, W = 2001, at N = 512, 2048 and 8192 Metropolis 0.71, 0.88 and 1.31 us, optimal transition
+// 1.69, 1.70 and 2.65, heat bath 2.03, 2.12 and 2.80 (W = 201: 1.66 and 1.85 at 512 and 2048).
 double cost_of_update(const sa_plan &p, bool team = false) {
-    // a dense team's update (about 1.2 us while hot, N = 2048, W = 2001) against the others' scale, where
-    // a hot update of the N = 2000 HUIO requests (2.6) takes about 70 ns
-    if (team) return 40.0;
+    if (team) {
+        const double n = (double)p.dp.n, w = (double)p.info.max_width;
+        if (p.rule == SA_METROPOLIS) return 14.0 + n / 700.0;
+        if (p.rule == SA_OPT_METROPOLIS) return 31.0 + n / 450.0;
+        return 30.0 + n / 450.0 + w / 330.0;
+    }
     const double chunks = 1.0 + (double)p.info.n_incidences / std::max(1, p.info.n_vars) / 64.0;
     const double per_lane = std::ceil(p.info.max_width / 64.0);
     if (p.rule == SA_HEAT_BATH_CLOSED && p.info.max_exponent <= 1) return chunks + 2.0;
