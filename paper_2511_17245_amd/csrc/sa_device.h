@@ -1138,6 +1138,13 @@ __device__ __forceinline__ bool all_settled(uint32_t *all, bool quiet, bool &cou
     return quiet && uni32(ahead) == 0u;
 }
 
+// A replica that may not leave any more, so near its end: not settled until it ends, so that none leaves whose
+// settled sweeps would only start when this one is through.
+__device__ __forceinline__ void stays(uint32_t *all, bool &counted, int lane) {
+    if (counted && lane == 0) atomicAdd(&all[1], ~0u);
+    counted = false;
+}
+
 // After the sweeps since the last check, in which this wave made `moves` changes: whether the run ends here
 // (uniform over the waves that share barriers; they decide together, from their sum).  limit: changes up to which
 // a replica becomes settled; past twice as many it is no longer.  ctr: three change counters and the decision, in
@@ -1385,6 +1392,7 @@ __global__ void __launch_bounds__(kThreads, anneal_waves(kRule, kRegChunk, kMaxE
         s = R.s_end;
         const auto K = arguments<AnnealArgs>();
         if (s >= K->s_end || settled_check(moves, K->limit, shared, ctr, K->all, check_no, counted, lane)) break;
+        if (K->s_end - s < K->every + kSettledRest) stays(K->all, counted, g == 0 ? lane : 1);   // that was its last check
     }
     const auto K = arguments<AnnealArgs>();
     if (first) {

@@ -267,13 +267,14 @@ __global__ void __launch_bounds__(kWave) quad_mo_kernel(QuadArgs A) {
             }
             if ((++sweep_no & (uint32_t)(kSettledEveryQuad - 1)) != 0) continue;
             const auto K = arguments<QuadArgs>();
-            if (K->phase == kPhaseFirst && K->s_end - s > kSettledRestQuad) {   // as settled_check
+            if (K->phase == kPhaseFirst && K->s_end - s > kSettledRestQuad - kSettledEveryQuad) {   // as settled_check
                 const bool quiet = recent <= (uint32_t)(counted ? 2 * K->limit : K->limit);
                 recent = 0;
                 if (all_settled(K->all, quiet, counted, lane)) {
                     s_next = s + 1;
                     break;
                 }
+                if (K->s_end - s <= kSettledRestQuad) stays(K->all, counted, lane);   // its last check
             }
         }
     }

@@ -67,3 +67,39 @@ def test_one_plan_on_two_streams():
     for a, b in zip(bufs[:2], bufs[2:]):
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     plan.close()
+
+
+def test_replicas_that_settle_near_the_end():
+    """Some settle while they may still leave, others after: none leaves, or the settled kernel's sweeps come on top
+    of the run (a seventh of it).  Against the same run in pieces of 40 sweeps, which leave too little to hand over;
+    two runs of one kind differ by less than 0.01."""
+    import time
+
+    import torch
+    n, S, reads = 3000, 200, 512
+    prob = I.erdos_renyi_quio(n, 8, 0, 3, 10, 10, np.random.Generator(np.random.PCG64(3)))
+    plan = sa.Plan(prob, sa.OPT_METROPOLIS)
+    bufs = [(torch.empty((reads, n), dtype=torch.int32, device="cuda"), torch.empty(reads, dtype=torch.int64, device="cuda"))
+            for _ in range(3)]
+
+    def timed(pieces):
+        best = 1e9
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            zi = None
+            for i, (s0, s1) in enumerate(pieces):
+                z, e = bufs[i % 3]
+                plan.run_device(S, reads, 5, z, e, sweep_begin=s0, sweep_end=s1, init_states=zi,
+                                stream=torch.cuda.current_stream().cuda_stream)
+                zi = z
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        return best, z.clone(), e.clone()
+
+    whole, z, e = timed([(0, S)])
+    parts, zp, ep = timed([(s, s + 40) for s in range(0, S, 40)])
+    plan.close()
+    print(f"whole {1e3 * whole:.2f} ms, in pieces {1e3 * parts:.2f} ms")
+    assert torch.equal(z, zp) and torch.equal(e, ep)
+    assert whole < 1.06 * parts
