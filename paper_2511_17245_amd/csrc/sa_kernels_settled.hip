@@ -27,9 +27,10 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
     // a run too short to gain what two more launches cost (about 10 us; a sweep that changes nothing
     // costs about 0.5 us per variable in the ordinary kernels)
     if (n_sweeps < 16 || (int64_t)n_sweeps * n_order < 2000) return sc;
-    // nor one whose whole sweep costs less than two of the settled kernel's changes (about 8 us each in a
-    // problem where every variable meets every other): N = 21 binary variables that keep changing, 300 sweeps
-    // x 19 reads, 5.5 ms with the settled kernel and 4.3 without; N = 30 of 17 values 1.4 and 2.2 ms
+    // nor one of very few variables.  (The line was drawn when each replica left by itself and N = 21 binary
+    // variables that keep changing lost, 4.3 to 5.5 ms.  They leave together now, and from 8 variables on no run
+    // of any rule was slower than 0.98 times with the line at 1: 360 runs of 8 to 23 variables of 2 to 101
+    // values, 300 to 3000 sweeps, the best seven times as fast.)
     if (n_order < 24) return sc;
     int cus = 256, max_lds = 65536;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
@@ -42,8 +43,13 @@ SettledChoice choose_settled(const Packed &p, bool coef32, int32_t n_reads, int3
     const int64_t words = coef32 ? state : 8 * n;
     const int64_t c = p.dense ? 8 * n : sparse_cache ? words : 0, c2 = sparse_cache && p.any_square ? words : 0;
     const int64_t bytes = state + c + c2 + 2 * ((n + 3) & ~(int64_t)3);
-    // every replica at once, or in two goes
-    if (bytes > max_lds || (max_lds / bytes) * cus * 2 < n_reads) return sc;
+    // Every replica at once, or in two goes, for pair problems in 1.8, as the quad kernel's sweep of them is no
+    // dearer than two settled ones: with against without, 200 sweeps, HUIO N = 4000 at 1.9 goes 48.7 and 53.4 ms
+    // (Metropolis), 51.6 and 57.0 (optimal transition), at 2.2 71.1 and 65.7, 95.7 and 109.1; pairs, 500 sweeps, W = 17,
+    // N = 6000 at 1.76 goes 163.8 and 169.9, 159.6 and 165.9, N = 10000 at 2 196.7 and 188.7, 211.6 and 196.2.
+    // (The windows gain at up to 4.5 goes: dense N = 1000, Metropolis 1222 and 1426, N = 200 401 and 412.)
+    const int64_t tenths = p.pair_row.empty() ? 20 : 18;
+    if (bytes > max_lds || (max_lds / bytes) * cus * tenths / 10 < n_reads) return sc;
     sc.lds_bytes = (int)bytes;
     sc.off_c = c ? (int)state : -1;
     sc.off_c2 = c2 ? (int)(state + c) : -1;

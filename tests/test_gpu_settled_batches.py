@@ -33,6 +33,18 @@ def test_the_settled_kernel_takes_part(kind, rule):
     plan.close()
 
 
+def test_pairs_in_two_goes_stay():
+    """Pair problems of 10000 variables, one settled replica per CU: in 1.8 goes, not in two."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    prob = I.erdos_renyi_quio(10000, 4, 0, 3, 10, 10, rng(3))
+    plan = sa.Plan(prob, sa.METROPOLIS)
+    for reads, settled in ((cus * 9 // 5, True), (2 * cus, False)):
+        plan.run(60, reads, 1)
+        assert (plan.last_launch()["kernel_variant"] >= 10_000_000) == settled
+    plan.close()
+
+
 def warming(prob, sweeps):
     """Cooled, warmed past the start, cooled again."""
     b = oracle.Poly(prob).schedule(sweeps)[0]
