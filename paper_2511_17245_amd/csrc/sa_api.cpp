@@ -321,11 +321,11 @@ void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image) {
     put(L.recs, im.recs.data(), im.recs.size());
 }
 
-const LaneImage &get_lane_chunks(sa_plan *plan) {
+const LaneImage &get_lane_chunks(sa_plan *plan, LevelGraph *graph) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Lanes &ln = plan->lanes;
     if (!ln.chunked) {
-        build_lane_chunks(plan->packed, ln.im);
+        build_lane_chunks(plan->packed, ln.im, graph);
         ln.chunked = true;
     }
     return ln.im;
@@ -381,7 +381,8 @@ int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out) {
     return SA_OK;
 }
 
-int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &q) {
+int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &q,
+                    LevelGraph *graph) {
     choice = LaneChoice();
     bool compact = false;
     int cus = 256, max_lds = 65536;
@@ -392,7 +393,7 @@ int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice
     const int32_t quads = quad_eligible(plan->rule, p, plan->device)
                               ? 16 * quad_waves(plan->rule, p.max_width, p.max_exp, quad_uniform_width(p))
                               : 0;
-    const int waves = lane_waves(get_lane_chunks(plan), p, compact, n_reads, quads, cus, max_lds);
+    const int waves = lane_waves(get_lane_chunks(plan, graph), p, compact, n_reads, quads, cus, max_lds);
     if (waves == 0) return SA_OK;
     sa_plan::Lanes *ln = nullptr;
     sa_plan::Lanes::Rounds *rounds = nullptr;
@@ -422,7 +423,7 @@ int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice
     return SA_OK;
 }
 
-int get_levels(sa_plan *plan, sa_plan::Levels **out) {
+int get_levels(sa_plan *plan, sa_plan::Levels **out, LevelGraph *graph) {
     std::lock_guard<std::mutex> lk(plan->sched_mu);
     sa_plan::Levels &lv = plan->levels;
     if (lv.n_levels < 0) {
@@ -434,7 +435,7 @@ int get_levels(sa_plan *plan, sa_plan::Levels **out) {
                               : build_levels(plan->packed,
                                              quad_waves(plan->rule, plan->packed.max_width, plan->packed.max_exp,
                                                         quad_uniform_width(plan->packed)) * 16,
-                                             start, slots);
+                                             start, slots, graph);
         if (!mo) n_real = (int32_t)slots.size();
         std::vector<MoRec> mrec;
         std::vector<uint8_t> mcoef;
@@ -620,9 +621,10 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
     }
     // the automatic choice for the heat bath of pair problems: one update per lane
     sa::LaneChoice lane;
+    sa::LevelGraph graph;   // (of the levels of either kernel)
     if (opts.lanes_per_update == 0 && G == 0) {
         sa::LaneArgs q{};
-        rc = sa::choose_lane_run(plan, n_reads, s1 - s0, lane, q);
+        rc = sa::choose_lane_run(plan, n_reads, s1 - s0, lane, q, &graph);
         std::string err;
         if (rc == SA_OK && lane.waves > 0) {
             q.beta = plan->beta_dev;
@@ -674,7 +676,7 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
     const bool eligible = sa::quad_eligible(plan->rule, plan->packed, plan->device);
     sa_plan::Levels *lv = nullptr;
     if (eligible && G == 0 && opts.lanes_per_update != 64) {
-        rc = sa::get_levels(plan, &lv);
+        rc = sa::get_levels(plan, &lv, &graph);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);
             return rc;

@@ -539,25 +539,36 @@ int32_t build_order(const Packed &p, std::vector<SchedRec> &out) {
 
 namespace sa {
 
-int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level_start,
-                     std::vector<SchedRec> &slots) {
+void build_level_graph(const Packed &p, LevelGraph &g) {
     const int32_t n = p.n;
-    // lower-index neighbours of every variable that is not fixed (a fixed variable never changes:
-    // it orders nothing)
-    std::vector<std::vector<int32_t>> lower((size_t)n), upper((size_t)n);
+    g = LevelGraph();
+    g.lower_at.assign((size_t)n + 1, 0);
+    g.upper_at.assign((size_t)n + 1, 0);
+    g.lower.reserve(p.inc.size());
+    g.upper.reserve(p.inc.size());
+    std::vector<int32_t> near;
+    // (the pairs of one variable come in order and once)
+    auto append = [&](std::vector<int32_t> &to) {
+        bool rising = true;
+        for (size_t i = 1; i < near.size(); ++i) rising = rising && near[i - 1] < near[i];
+        if (!rising) {
+            std::sort(near.begin(), near.end());
+            near.erase(std::unique(near.begin(), near.end()), near.end());
+        }
+        to.insert(to.end(), near.begin(), near.end());
+    };
+    std::vector<int32_t> above;
     for (int32_t k = 0; k < n; ++k) {
         const VarRec &vr = p.var[k];
-        if (vr.width == 1) continue;
+        near.clear();
+        above.clear();
         auto see = [&](int32_t j) {
-            if (j != k && p.var[j].width > 1) {
-                if (j < k) lower[(size_t)k].push_back(j);
-                else upper[(size_t)k].push_back(j);
-            }
+            if (j != k && p.var[j].width > 1) (j < k ? near : above).push_back(j);
         };
-        if (p.dense) {
+        if (vr.width > 1 && p.dense) {
             // every pair is coupled: each variable waits for all earlier ones
             for (int32_t j = 0; j < n; ++j) see(j);
-        } else {
+        } else if (vr.width > 1) {
             for (int32_t q = vr.row; q < vr.row + vr.deg; ++q) {
                 const IncRec &r = p.inc[q];
                 const uint32_t no = r.meta >> 8;
@@ -568,13 +579,27 @@ int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level
                 }
             }
         }
-        auto &lo = lower[(size_t)k];
-        std::sort(lo.begin(), lo.end());
-        lo.erase(std::unique(lo.begin(), lo.end()), lo.end());
-        auto &up = upper[(size_t)k];
-        std::sort(up.begin(), up.end());
-        up.erase(std::unique(up.begin(), up.end()), up.end());
+        append(g.lower);
+        near.swap(above);
+        append(g.upper);
+        g.lower_at[(size_t)k + 1] = (int64_t)g.lower.size();
+        g.upper_at[(size_t)k + 1] = (int64_t)g.upper.size();
     }
+}
+
+int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level_start, std::vector<SchedRec> &slots,
+                     LevelGraph *shared) {
+    const int32_t n = p.n;
+    LevelGraph own;
+    LevelGraph &g = shared ? *shared : own;
+    if (g.lower_at.empty()) build_level_graph(p, g);
+    struct Span {
+        const int32_t *b, *e;
+        const int32_t *begin() const { return b; }
+        const int32_t *end() const { return e; }
+    };
+    auto lower = [&](int32_t k) { return Span{g.lower.data() + g.lower_at[(size_t)k], g.lower.data() + g.lower_at[(size_t)k + 1]}; };
+    auto upper = [&](int32_t k) { return Span{g.upper.data() + g.upper_at[(size_t)k], g.upper.data() + g.upper_at[(size_t)k + 1]}; };
     // earliest level (longest chain of lower-index neighbours below k) and latest level (the
     // number of levels minus the longest chain above k)
     std::vector<int32_t> asap((size_t)n, -1), down((size_t)n, 0);
@@ -582,14 +607,14 @@ int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level
     for (int32_t k = 0; k < n; ++k) {
         if (p.var[k].width == 1) continue;
         int32_t lv = 0;
-        for (int32_t j : lower[(size_t)k]) lv = std::max(lv, asap[(size_t)j] + 1);
+        for (int32_t j : lower(k)) lv = std::max(lv, asap[(size_t)j] + 1);
         asap[(size_t)k] = lv;
         n_levels = std::max(n_levels, lv + 1);
     }
     for (int32_t k = n - 1; k >= 0; --k) {
         if (p.var[k].width == 1) continue;
         int32_t d = 0;
-        for (int32_t j : upper[(size_t)k]) d = std::max(d, down[(size_t)j] + 1);
+        for (int32_t j : upper(k)) d = std::max(d, down[(size_t)j] + 1);
         down[(size_t)k] = d;
     }
     // level by level: every variable that must go now (its latest level) goes, and the level is
@@ -599,7 +624,7 @@ int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level
     std::set<std::pair<int32_t, int32_t>> ready;   // (latest level, index)
     for (int32_t k = 0; k < n; ++k) {
         if (p.var[k].width == 1) continue;
-        waiting[(size_t)k] = (int32_t)lower[(size_t)k].size();
+        waiting[(size_t)k] = (int32_t)(g.lower_at[(size_t)k + 1] - g.lower_at[(size_t)k]);
         if (waiting[(size_t)k] == 0) ready.insert({n_levels - 1 - down[(size_t)k], k});
     }
     const int32_t Q = std::max<int32_t>(quads, 1);
@@ -612,7 +637,7 @@ int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level
         ready.erase(ready.begin(), it);
         for (int32_t k : take) level[(size_t)k] = l;
         for (int32_t k : take)
-            for (int32_t j : upper[(size_t)k])
+            for (int32_t j : upper(k))
                 if (--waiting[(size_t)j] == 0) ready.insert({n_levels - 1 - down[(size_t)j], j});
     }
     // counting sort by level; index order inside a level
@@ -703,11 +728,11 @@ int32_t build_rounds(const Packed &p, std::vector<SchedRec> &rounds, int32_t &n_
     return n_levels;
 }
 
-void build_lane_chunks(const Packed &p, LaneImage &im) {
+void build_lane_chunks(const Packed &p, LaneImage &im, LevelGraph *graph) {
     im = LaneImage();
     std::vector<int32_t> start;
     std::vector<SchedRec> slots;
-    im.n_levels = build_levels(p, 64, start, slots);
+    im.n_levels = build_levels(p, 64, start, slots, graph);
     im.n_slots = (int32_t)slots.size();
     for (int32_t l = 0; l < im.n_levels; ++l) {
         im.level_chunk.push_back((int32_t)im.chunks.size());

@@ -133,8 +133,13 @@ int32_t build_order(const Packed &p, std::vector<SchedRec> &out);
 // longest chain of neighbours in index order; each variable goes to a level between its earliest
 // and its latest, and levels are filled up to whole rounds of `quads` updates where the slack
 // allows.  Returns the number of levels; slots are level-major, level_start has one more entry.
+// graph: the neighbours, made here if it is empty; for a caller that builds levels for more than one kernel.
+struct LevelGraph {
+    std::vector<int64_t> lower_at, upper_at;   // n + 1 each: where a variable's neighbours start
+    std::vector<int32_t> lower, upper;         // neighbours of lower and of higher index that are not fixed, rising
+};
 int32_t build_levels(const Packed &p, int32_t quads, std::vector<int32_t> &level_start,
-                     std::vector<SchedRec> &slots);
+                     std::vector<SchedRec> &slots, LevelGraph *graph = nullptr);
 // Rounds of the one-wave quad kernel: the levels of 16 (one wavefront of quads), each cut into
 // rounds of 16 slots and padded to whole rounds with idle slots (k = -1, no records), and the sweep
 // padded with idle rounds to a multiple of kRoundBatch rounds.  Every slot points at its
@@ -380,7 +385,7 @@ constexpr int32_t kLaneReach = 12;   // rows loaded ahead (sa_lane.h, kLaneAhead
 // The rounds of a sweep for `waves` waves per replica (LaneArgs::rounds).
 void build_lane_rounds(const LaneImage &im, int waves, std::vector<LaneRows> &rounds);
 // Levels and chunks of a problem with compact pair records, and then their records; compact: 16-bit ones.
-void build_lane_chunks(const Packed &p, LaneImage &out);
+void build_lane_chunks(const Packed &p, LaneImage &out, LevelGraph *graph = nullptr);
 void build_lane_records(const Packed &p, bool compact, LaneImage &im);
 // Whether the lane kernel can run `rule` on this packed problem, and whether with 16-bit records.
 bool lane_eligible(int rule, const Packed &p, bool coef32, int max_lds, bool &compact);

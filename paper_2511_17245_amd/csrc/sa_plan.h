@@ -118,12 +118,13 @@ int get_order(sa_plan *plan, sa_plan::Sched **out);
 int get_order_if_room(sa_plan *plan, sa_plan::Sched **out);
 // The plan's lane chunks, built on first use, and its lane image (16-bit records or not), built and uploaded
 // on first use.
-const LaneImage &get_lane_chunks(sa_plan *plan);
+const LaneImage &get_lane_chunks(sa_plan *plan, LevelGraph *graph);
 int get_lanes(sa_plan *plan, bool compact, sa_plan::Lanes **out);
 int get_lane_rounds(sa_plan *plan, int waves, sa_plan::Lanes::Rounds **out);
 // The lane kernel's choice for a run of n_sweeps sweeps (none where its image finds no room), and its arguments
 // that come from the plan.
-int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &args);
+int choose_lane_run(sa_plan *plan, int32_t n_reads, int32_t n_sweeps, LaneChoice &choice, LaneArgs &args,
+                    LevelGraph *graph = nullptr);
 // Byte layout of a lane image (chunks | slots | records), and its staging.
 struct LaneLayout {
     size_t slots, recs, total;
@@ -133,7 +134,7 @@ void stage_lanes(const LaneImage &im, const LaneLayout &L, char *image);
 // Uploads the inverse temperatures unless the device already holds the same array.
 int stage_beta(sa_plan *plan, const std::vector<double> &beta, hipStream_t stream);
 // The plan's dependency levels (built and uploaded on first use).
-int get_levels(sa_plan *plan, sa_plan::Levels **out);
+int get_levels(sa_plan *plan, sa_plan::Levels **out, LevelGraph *graph = nullptr);
 // The common width of the level slots, or 0 when widths differ.
 int32_t uniform_width(const std::vector<SchedRec> &slots);
 // Whether the quad kernel can run `rule` on this packed problem with n replicas' state in LDS.

@@ -129,10 +129,67 @@ void image() {
 
 }  // namespace
 
+// Levels from neighbours that two kernels share, and by definition: after all lower neighbours, as many as
+// the longest chain.  With long terms, repeated factors and fixed variables.
+void levels() {
+    std::mt19937_64 g(11);
+    for (int rep = 0; rep < 60; ++rep) {
+        const int n = 2 + (int)(g() % 90), m = 1 + (int)(g() % (unsigned)(3 * n)), most = rep % 3 == 0 ? 2 : 6;
+        std::vector<int64_t> ptr{0}, coef;
+        std::vector<int32_t> fac, lo((size_t)n, 0), hi((size_t)n, 3);
+        for (int k = 0; k < n; k += 5) hi[(size_t)k] = (int32_t)(g() % 2) * 3;
+        for (int t = 0; t < m; ++t) {
+            const int d = 1 + (int)(g() % (unsigned)most);
+            for (int i = 0; i < d; ++i) fac.push_back((int32_t)(g() % (unsigned)n));
+            ptr.push_back((int64_t)fac.size());
+            coef.push_back(1 + (int64_t)(g() % 9));
+        }
+        sa_instance in{n, (int64_t)coef.size(), ptr.data(), fac.data(), coef.data()};
+        sa_bounds bd{lo.data(), hi.data()};
+        sa::Canonical c;
+        std::string err;
+        sa::Packed p;
+        if (sa::canonicalize(&in, &bd, c, err) != SA_OK || sa::pack(c, p, err) != SA_OK) {
+            expect(false, err.c_str(), n, m, rep);
+            continue;
+        }
+        sa::LevelGraph graph;
+        for (int32_t quads : {64, 16, 64, 1}) {
+            std::vector<int32_t> s0, s1;
+            std::vector<sa::SchedRec> a, b;
+            const int32_t n0 = sa::build_levels(p, quads, s0, a), n1 = sa::build_levels(p, quads, s1, b, &graph);
+            expect(n0 == n1 && s0 == s1 && a.size() == b.size() &&
+                       (a.empty() || std::memcmp(a.data(), b.data(), a.size() * sizeof(a[0])) == 0), "shared neighbours", n, m, quads);
+            std::vector<int> at((size_t)n, -1), first((size_t)n, 0);
+            for (int32_t l = 0; l < n0; ++l)
+                for (int32_t i = s0[(size_t)l]; i < s0[(size_t)l + 1]; ++i) at[(size_t)a[(size_t)i].k] = l;
+            int longest = 0;
+            for (int k = 0; k < n; ++k) {
+                expect((at[(size_t)k] >= 0) == (hi[(size_t)k] > 0), "every variable that is not fixed", n, m, k);
+                if (at[(size_t)k] < 0) continue;
+                // (of the packed problem: pairs whose coefficients cancel are no neighbours)
+                for (int64_t t = 0; t < (int64_t)c.t_coef.size(); ++t) {
+                    bool has = false;
+                    for (int64_t q = c.t_off[(size_t)t]; q < c.t_off[(size_t)t + 1]; ++q) has = has || c.t_var[(size_t)q] == k;
+                    for (int64_t q = c.t_off[(size_t)t]; has && q < c.t_off[(size_t)t + 1]; ++q) {
+                        const int j = c.t_var[(size_t)q];
+                        if (j >= k || at[(size_t)j] < 0) continue;
+                        expect(at[(size_t)j] < at[(size_t)k], "after its lower neighbours", n, m, k);
+                        first[(size_t)k] = std::max(first[(size_t)k], first[(size_t)j] + 1);
+                    }
+                }
+                longest = std::max(longest, first[(size_t)k] + 1);
+            }
+            if (!p.dense) expect(n0 == longest, "as many levels as the longest chain", n, m, n0);
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "choice") choice();
     else if (which == "image") image();
+    else if (which == "levels") levels();
     else return 2;
     if (failures) return 1;
     std::printf("ok\n");

@@ -17,7 +17,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("which", ["choice", "image"])
+@pytest.mark.parametrize("which", ["choice", "image", "levels"])
 def test_lane(checker, which):
     out = subprocess.run([checker, which], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stderr[-4000:]
