@@ -57,8 +57,23 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
             return SA_EDEVICE;
         }
     }
+    // `stream` waits for every side stream that was forked from it, also where a launch fails: the caller, who
+    // knows of `stream` alone, gives the buffers back after it.
+    const SideStream *open[2] = {nullptr, nullptr};
+    auto join = [&]() -> int {
+        int first = 0;
+        for (const SideStream *&side : open) {
+            if (!side) continue;
+            int e = side->mark();
+            if (!e) e = side->join_to(stream);
+            if (!first) first = e;
+            side = nullptr;
+        }
+        return first;
+    };
     auto failed = [&](int e) {
         err = std::string("batch launch: ") + hipGetErrorString((hipError_t)e);
+        (void)join();
         return SA_EDEVICE;
     };
     // dense teams and lane kernels first, beside the persistent kernel where a side stream is given
@@ -66,24 +81,24 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
     const bool beside = teams && bl.beside.stream;
     if (teams) {
         void *s = beside ? bl.beside.stream : stream;
-        if (beside)
+        if (beside) {
+            open[0] = &bl.beside;
             if (int e = bl.beside.fork_from(stream)) return failed(e);
-        for (const TeamGroup &g : bl.teams) {
-            int rc = launch_team_group(b.insts, bl.settled_tasks, g, s, err);
-            if (rc != SA_OK) return rc;
         }
-        for (const LaneGroup &g : bl.lanes) {
-            int rc = launch_lane_group(bl.lane_args, bl.settled_tasks, g, s, err);
-            if (rc != SA_OK) return rc;
+        int rc = SA_OK;
+        for (size_t i = 0; rc == SA_OK && i < bl.teams.size(); ++i)
+            rc = launch_team_group(b.insts, bl.settled_tasks, bl.teams[i], s, err);
+        for (size_t i = 0; rc == SA_OK && i < bl.lanes.size(); ++i)
+            rc = launch_lane_group(bl.lane_args, bl.settled_tasks, bl.lanes[i], s, err);
+        if (rc != SA_OK) {
+            (void)join();
+            return rc;
         }
-        if (beside)
-            if (int e = bl.beside.mark()) return failed(e);
     }
-    auto join = [&]() -> int {
-        const int e = beside ? bl.beside.join_to(stream) : 0;
+    if (b.n_tasks == 0) {
+        const int e = join();
         return e ? failed(e) : SA_OK;
-    };
-    if (b.n_tasks == 0) return join();
+    }
     int32_t n_settled = 0;
     for (const SettledGroup &g : bl.settled) n_settled += g.n;
     BatchArgs a = b;
@@ -107,23 +122,29 @@ int launch_batch(const BatchArgs &b, const BatchLaunch &bl, void *stream, std::s
         for (const SettledGroup &g : bl.settled) {
             if (g.n == 0) continue;
             if (s == stream && --left > 0 && bl.settled_side.stream) {
+                open[1] = &bl.settled_side;
                 if (int e = bl.settled_side.fork_from(stream)) return failed(e);
                 forked = true;
             }
             int rc = launch_settled_batch(b.insts, bl.settled_tasks + g.first, g.n, g.lds_bytes, bl.maxe_class, s, err);
-            if (rc != SA_OK) return rc;
+            if (rc != SA_OK) {
+                (void)join();
+                return rc;
+            }
             if (forked) s = bl.settled_side.stream;
         }
         if (forked) {
             int e = bl.settled_side.mark();
             if (!e) e = bl.settled_side.join_to(stream);
             if (e) return failed(e);
+            open[1] = nullptr;
         }
         persistent(kPhaseLast);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return failed(e);
-    return join();
+    const int je = join();
+    return je ? failed(je) : SA_OK;
 }
 
 }  // namespace sa

@@ -543,8 +543,8 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
     bl.z16 = z16;
     bl.groups = S->cus * groups_per_cu;
     int rc = sa::launch_batch(a, bl, S->stream, err);
+    e = hipStreamSynchronize(S->stream);   // also of what was launched before a failure: the requests' buffers go back
     if (rc != SA_OK) return rc;
-    e = hipStreamSynchronize(S->stream);
     if (e != hipSuccess) {
         err = std::string("chunk: ") + hipGetErrorString(e);
         return SA_EDEVICE;
