@@ -27,8 +27,8 @@ PEAK_HBM_GBS = 8000.0
 # one multiply, one exponential evaluated directly (the FP64 operations of the gfx950 exp sequence,
 # FMA = 2 flops) and the additions of the cumulative sum.  The quad kernel's factored weights execute
 # far fewer (two exponentials per lane and one fused multiply-add per weight), and the lane kernel
-# evaluates no weights at all (the inverse of the distribution): for it the bound reported is VALU
-# issue.
+# evaluates no weights at all (the inverse of the distribution): for it the share of VALU issue is
+# reported.
 FP64_FLOPS_PER_WEIGHT = 30.0
 # VALU issue: a wave64 VALU instruction occupies one of the 4 SIMDs of a compute unit for 4 cycles
 VALU_ISSUE_PEAK_G = 256 * 4 * 2.4 / 4   # 10^9 wave instructions/s
@@ -1050,15 +1050,17 @@ def main():
                 "basis": "algorithmic: W weights x 30 FP64 flops per update (one direct exponential each); "
                          "executed instructions in valu_issue"}
     else:
-        # Metropolis / OTM, and the heat bath of the lane kernel: the records come from the caches
-        # (measured HBM traffic is a small fraction of them), and the counters show VALU issue as the busy resource: the
-        # bound reported is VALU issue, from the counted instructions per update (committed
-        # counter record of the same kernel sources) at this run's rate; null without a record
+        # Metropolis / OTM, and the heat bath of the lane kernel: the records come from the caches (measured
+        # HBM traffic is a small fraction of them) and half of the wave cycles wait, for the levels' barriers
+        # and the gathers behind them: what bounds the run is the latency of one replica's chain.  What is
+        # reported is how much of VALU issue, the busiest resource, the run takes, from the counted
+        # instructions per update (committed counter record of the same kernel sources) at this run's
+        # rate; null without a record
         crec = counter_record(f"{args.config}:{S}:{R}")
         vi = crec["valu_insts_per_update"] * value / 1e9 if crec and crec.get("valu_insts_per_update") else None
-        roof = {"bound": "alu", "achieved": vi, "peak": VALU_ISSUE_PEAK_G, "unit": "G wave-instructions/s",
+        roof = {"bound": "latency", "achieved": vi, "peak": VALU_ISSUE_PEAK_G, "unit": "G wave-instructions/s",
                 "frac": vi / VALU_ISSUE_PEAK_G if vi is not None else None, "traffic": traffic,
-                "basis": "counted VALU instructions per update x update rate (issue-bound)"}
+                "basis": "counted VALU instructions per update x update rate, against VALU issue"}
 
     out = {
         "metric": "single-variable updates/sec at 1 GPU",
