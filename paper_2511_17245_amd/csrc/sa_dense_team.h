@@ -15,8 +15,9 @@
 //
 // What bounds it: the chain of one draw (LDS reads, minimum, exponentials, scan, three barriers): 50 %
 // of the wave time waits, 330 VALU instructions per wave and hot draw.  Measured: dense N = 4096,
-// W = 2001 heat bath, 20 sweeps x 16 reads 467 to 100 ms (109 before the draws in single precision) (hot sweeps 33 to 9.5 ms, settled ones 12 to
-// 0.4 ms); a served burst of 18 HUIO and two dense N = 2048 requests 321 to 112 ms.
+// W = 2001 heat bath, 20 sweeps x 16 reads 467 to 100 ms (109 before the draws in single precision; hot sweeps
+// 33 to 9.5 ms, settled ones 12 to 0.4 ms); a served burst of 18 HUIO and two dense N = 2048 requests 321 to
+// 108 ms.
 #pragma once
 
 #include "sa_settled.h"
@@ -320,7 +321,10 @@ __device__ __forceinline__ void team_sweeps(const TeamCtx &T, ZT *z, C *c1, Team
                     want = v != zk && metropolis_accept(d, beta, U) ? 1 : 0;
                 } else if (!hot) {
                     if (linear) {
-                        v = closed ? heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1) : linear_draw(a1, lo, W32, beta, U);
+                        // (its rare double-precision rest out of line: inlined, it spilled registers of the hot
+                        // draws, N = 4096, W = 2001, 20 sweeps x 16 reads 100.4 to 102.1 ms)
+                        v = closed ? heat_bath_closed(a1, lo, (int64_t)W32, beta, U, x1)
+                                   : linear_draw<true>(a1, lo, W32, beta, U);
                         d = de(v);
                         want = v != zk ? 1 : 0;
                     } else {
