@@ -778,8 +778,8 @@ int plan_run(sa_plan *plan, const sa_schedule *sched, int32_t n_reads, uint64_t 
         // the sweeps after the replicas have settled go to the settled kernel
         std::string err;
         if (!sa::settled_pays(s1 - s0, a.n_order, lc.win_waves)) set = sa::SettledChoice();
-        rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_visits(plan->rule, plan->packed), plan->info.max_width,
-                                plan->info.max_exponent, plan->narrow_ok, stream, err);
+        rc = sa::launch_windows(plan->rule, a, lc, set, sa::settled_share(lc.win_waves, plan->rule, plan->packed),
+                                plan->info.max_width, plan->info.max_exponent, plan->narrow_ok, stream, err);
         if (rc == SA_OK && t_dev) rc = sa::launch_trace_prefix(t_dev, n_reads, n_traced, stream, err);
         if (rc != SA_OK) {
             if (tmp) (void)hipFree(tmp);

@@ -137,8 +137,7 @@ int configure(sa_batch &b, double policy, int groups_per_cu) {
         b.insts[i].n_win = sc->n_win;
         b.insts[i].slot_stride = (int32_t)stride;
         b.insts[i].every = sa::settled_every(b.insts[i].n_order, G);
-        b.insts[i].limit = sa::settled_limit(b.insts[i].n_order, b.insts[i].every,
-                                             sa::settled_share(G, sa::settled_visits(p.rule, p.packed)));
+        b.insts[i].limit = sa::settled_limit(b.insts[i].n_order, b.insts[i].every, sa::settled_share(G, p.rule, p.packed));
         lds_elems_max = std::max<int64_t>(lds_elems_max, (int64_t)(sa::kBatchWaves / G) * stride);
     }
     // tasks: problems by decreasing cost of one replica, kBatchWaves / G_p reads per task

@@ -207,8 +207,12 @@ constexpr int32_t kPhaseWhole = 0, kPhaseFirst = 1, kPhaseLast = 2;
 // kernel's G waves share the updates.  Share of changes at which the two take the same time, one replica at a
 // constant temperature (dense, HUIO, multilinear and pair problems of 26 to 4000 variables): G = 1 0.35 to 0.9,
 // but 0.16 to 0.3 where most ask for a visit (the heat bath's draws about two per change, variables without
-// cached coefficients); G = 2 0.2 to 0.34; G = 4 0.08 to 0.15; G = 8 0.03 to 0.05.
-constexpr int32_t settled_share(int32_t G, bool visits) { return G > 2 ? 6 * G : visits ? 14 : G == 2 ? 10 : 4; }
+// cached coefficients); G = 2 0.2 to 0.34; G = 4 0.08 to 0.15; G = 8 0.03 to 0.05.  In the
+// dense form (G = 1, no visits), whose ordinary kernel adds every change to the cached sums as well, a settled sweep
+// takes at most 1.24 times an ordinary one however much changes, and less up to 0.65 to 0.95: one in two, and no
+// replica comes unsettled, as runs some of whose replicas did took both launches' time.  (64 reads at one temperature,
+// one in four against one in two: N = 60 binary, 0.37 changes per update, 13.0 and 7.8 ms; N = 100, W = 16, 0.34, 15.0 and
+// 10.6.  Cold, then warmer: N = 60, optimal transition, 20.1 and 7.1 ms.)
 // The Metropolis / OTM quad kernel (16 updates per round): 0.02 to 0.055, 0.01 for pair problems. (N = 2000 HUIO,
 // 300 sweeps x 1024 reads, one in 96, 48 and 40: optimal transition 27.4, 26.5 and 26.0 ms, Metropolis 31.7,
 // 29.3 and 28.7.)
@@ -226,7 +230,7 @@ constexpr int32_t settled_every(int32_t n_order, int32_t G) {
 constexpr int32_t kSettledEveryQuad = 4;
 // Changes in settled_every sweeps up to which a replica becomes settled.
 constexpr int32_t settled_limit(int32_t n_order, int32_t every, int32_t share) {
-    const int64_t m = (int64_t)n_order * every / share;
+    const int64_t m = ((int64_t)n_order * every + 1) / share;   // (one in two: up, so that twice as many are all)
     return m > 1 ? (int32_t)m : 1;
 }
 // A sweep's index as it stands in e_out: energies lie within 2^62 of 0 (check_int64_bound).
@@ -436,12 +440,14 @@ int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_
 constexpr bool settled_pays(int32_t n_sweeps, int32_t n_order, int32_t G) {
     return (int64_t)n_sweeps * n_order >= 1200 * (int64_t)G;
 }
-// Whether settled sweeps visit most of what may change (settled_share).
-inline bool settled_visits(int rule, const Packed &p) {
-    return rule == SA_HEAT_BATH || rule == SA_HEAT_BATH_CLOSED || (!p.dense && !p.any_cached);
+inline int32_t settled_share(int32_t G, int rule, const Packed &p) {
+    // whether settled sweeps visit most of what may change
+    const bool visits = rule == SA_HEAT_BATH || rule == SA_HEAT_BATH_CLOSED || (!p.dense && !p.any_cached);
+    return G > 2 ? 6 * G : visits ? 14 : G == 2 ? 10 : p.dense ? 2 : 4;
 }
-// A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order, n_order and all set).
-int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, bool visits, int32_t max_width,
+// A run of the one-wavefront-per-update kernels: one launch, or with sc three (a: order, n_order and all set;
+// share: settled_share).
+int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t share, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err);
 
 // The same for the Metropolis / OTM quad kernel: q as for launch_quad_mo, a as for launch_settled.

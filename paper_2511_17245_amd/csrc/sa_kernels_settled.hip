@@ -100,13 +100,13 @@ int launch_settled(int rule, AnnealArgs a, const SettledChoice &sc, int32_t max_
     return SA_OK;
 }
 
-int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, bool visits, int32_t max_width,
+int launch_windows(int rule, AnnealArgs a, const LaunchChoice &lc, const SettledChoice &sc, int32_t share, int32_t max_width,
                    int32_t max_exp, bool narrow, void *stream, std::string &err) {
     a.phase = kPhaseWhole;
     if (sc.lds_bytes == 0) return launch_anneal(rule, a, lc, stream, err);
     a.phase = kPhaseFirst;
     a.every = settled_every(a.n_order, lc.win_waves);
-    a.limit = settled_limit(a.n_order, a.every, settled_share(lc.win_waves, visits));
+    a.limit = settled_limit(a.n_order, a.every, share);
     int rc = launch_anneal(rule, a, lc, stream, err);
     if (rc == SA_OK) rc = launch_settled(rule, a, sc, max_width, max_exp, narrow, stream, err);
     if (rc != SA_OK) return rc;

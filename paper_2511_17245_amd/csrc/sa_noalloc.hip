@@ -252,7 +252,7 @@ int run_noalloc(const sa_instance *inst, const sa_bounds *bounds, const sa_sched
         rc = sa::launch_dense_team(rule, a, team, stream, err);
     } else {
         if (!sa::settled_pays(s1 - s0, active, lc.win_waves)) set = sa::SettledChoice();
-        rc = sa::launch_windows(rule, a, lc, set, sa::settled_visits(rule, pk), pk.max_width, pk.max_exp,
+        rc = sa::launch_windows(rule, a, lc, set, sa::settled_share(lc.win_waves, rule, pk), pk.max_width, pk.max_exp,
                                 sa::dE_fits_32(canon), stream, err);
     }
     if (rc == SA_OK && a.trace) rc = sa::launch_trace_prefix(a.trace, n_reads, s1 - s0, stream, err);

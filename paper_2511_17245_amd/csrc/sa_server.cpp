@@ -479,7 +479,7 @@ int run_chunk(sa_server *S, const std::vector<Request *> &act, std::string &err)
                 sa::settle_inst(p.packed, p.dp.coef32 != 0, r->order->dev, r->order->n_active, r->n_sweeps, S->device, d);
         if (settled_lds[i]) d.next = r->next_dev;
         d.every = sa::settled_every(d.n_order, G);
-        d.limit = sa::settled_limit(d.n_order, d.every, sa::settled_share(G, sa::settled_visits(p.rule, p.packed)));
+        d.limit = sa::settled_limit(d.n_order, d.every, sa::settled_share(G, p.rule, p.packed));
     }
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);

@@ -19,7 +19,7 @@
 // What bounds it: in a settled sweep, the latency of one block's chain (slots, caches, decision: about
 // 250 cycles per 64 variables while all are frozen, 700 with their random words); before that, the
 // visits.  Measured, ordinary sweeps only against this: dense N = 100 Metropolis, 1000 sweeps x 16
-// reads 49.4 to 2.7 ms; FC p = 2, u = 100 heat bath, 300 sweeps x 1000 reads 56.4 to 34.5 ms (18.9 with
+// reads 49.4 to 2.6 ms; FC p = 2, u = 100 heat bath, 300 sweeps x 1000 reads 56.4 to 34.5 ms (18.9 with
 // the draws in single precision); ML p = 10 optimal transition, 300 sweeps x 100 reads 42.5 to 18.6 ms; HUIO
 // N = 2000, 300 sweeps x 1024 reads 48.0 to 24.9 ms (optimal transition) and 42.6 to 28.6 ms (Metropolis);
 // one-shot HUIO N = 30 heat bath, 100 sweeps x 8 reads 2.3 to 1.5 ms.
